@@ -55,6 +55,14 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_sched);
     (void)hipFree(h->d_ws_slot);
     (void)hipFree(h->d_ws);
+    (void)hipFree(h->d_row_tasks);
+    (void)hipFree(h->d_chunks);
+    (void)hipFree(h->d_split_rows);
+    (void)hipFree(h->d_tile_tasks);
+    (void)hipFree(h->d_tile_split);
+    (void)hipFree(h->d_e_row_ptr);
+    (void)hipFree(h->d_e_col);
+    (void)hipFree(h->d_e_val);
     (void)hipFree(h->d_c_rank_info);
     (void)hipFree(h->d_c_slice_rows);
     (void)hipFree(h->d_c_piece_rows);
@@ -67,6 +75,28 @@ static asp_status_t upload(T **dst, const void *src, size_t bytes, hipStream_t s
     *dst = nullptr;
     ASP_HIP_TRY(hipMalloc((void **)dst, bytes > 0 ? bytes : 16));
     if (bytes > 0) ASP_HIP_TRY(hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, stream));
+    return ASP_OK;
+}
+
+// the entries of rows.runs, one after the other; the kernels read whole batches of 8 entries
+static asp_status_t upload_runs(void **dst, const void *src, size_t esize, const HostRows &rows, std::vector<uint8_t> &host,
+                                hipStream_t stream) {
+    *dst = nullptr;
+    ASP_HIP_TRY(hipMalloc(dst, ((size_t)rows.n_entries + 16) * esize));
+    if (rows.n_entries == 0) return ASP_OK;
+    const uint8_t *from = (const uint8_t *)src + (size_t)rows.runs[0].first * esize;
+    if (rows.runs.size() > 1) {
+        ASP_HIP_TRY(hipStreamSynchronize(stream));  // `host` may still be read by the previous upload
+        host.resize((size_t)rows.n_entries * esize);
+        uint8_t *to = host.data();
+        for (auto &r : rows.runs) {
+            const size_t bytes = (size_t)(r.second - r.first) * esize;
+            if (bytes > 0) std::memcpy(to, (const uint8_t *)src + (size_t)r.first * esize, bytes);
+            to += bytes;
+        }
+        from = host.data();
+    }
+    ASP_HIP_TRY(hipMemcpyAsync(*dst, from, (size_t)rows.n_entries * esize, hipMemcpyHostToDevice, stream));
     return ASP_OK;
 }
 
@@ -171,6 +201,24 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     if ((s = upload(&h->d_zero_windows, h->hw.zero_windows.data(), h->hw.zero_windows.size() * 4, stream))) return s;
     if ((s = upload(&h->d_ws_slot, h->hw.ws_slot.data(), h->hw.ws_slot.size() * 4, stream))) return s;
     if ((s = wcsr_build_tasks_device(h, stream))) return s;  // wavefront-scan partition on the GPU
+    HostRows rows;  // alive until the stream is synchronised below
+    std::vector<uint8_t> gathered;
+    wcsr_build_rows(m, row_ptr, col_idx, es, h->b_row, h->task_cols, h->hw, rows);
+    h->n_row_tasks = (int64_t)rows.tasks.size() / 4;
+    h->n_chunks = (int64_t)rows.chunks.size() / 4;
+    h->n_split_rows = (int64_t)rows.split.size() / 4;
+    h->n_tile_tasks = (int64_t)rows.tile_tasks.size() / 4;
+    h->n_tile_split = (int64_t)rows.tile_split.size();
+    if ((s = upload(&h->d_tile_tasks, rows.tile_tasks.data(), rows.tile_tasks.size() * 4, stream))) return s;
+    if ((s = upload(&h->d_tile_split, rows.tile_split.data(), rows.tile_split.size() * 4, stream))) return s;
+    if (h->n_row_tasks > 0 || h->n_chunks > 0) {
+        if ((s = upload(&h->d_row_tasks, rows.tasks.data(), rows.tasks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_chunks, rows.chunks.data(), rows.chunks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_split_rows, rows.split.data(), rows.split.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_e_row_ptr, rows.row_ptr.data(), rows.row_ptr.size() * 4, stream))) return s;
+        if ((s = upload_runs((void **)&h->d_e_col, col_idx, 4, rows, gathered, stream))) return s;
+        if ((s = upload_runs(&h->d_e_val, values, es, rows, gathered, stream))) return s;
+    }
     if (h->n_split_tasks > 0) {
         // set-up for asp_spmm_static_scratch: the device address of the static scratch array, once per device
         float *p = nullptr;

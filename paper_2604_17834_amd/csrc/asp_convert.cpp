@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <exception>
+#include <functional>
 #include <mutex>
 #include <system_error>
 #include <thread>
@@ -528,6 +529,170 @@ void wcsr_tasks_host(const std::vector<int32_t> &wrp, int32_t task_cols, std::ve
             tasks.push_back(split);
         }
     }
+}
+
+namespace {
+
+// Reorders tasks (four ints each, four tasks to a workgroup) so that each of the 8 XCDs, which take workgroups
+// round-robin, gets one contiguous range of the given order with an eighth of the weight: tasks that are neighbours
+// in the order then meet in one L2.  Shorter ranges are filled up with empty tasks.
+void deal_to_xcds(std::vector<int32_t> &tasks, const std::vector<int64_t> &weight) {
+    const size_t n = weight.size();
+    if (n < 256) return;  // less than a workgroup per compute unit and XCD to tell apart
+    int64_t total = 0;
+    for (int64_t w : weight) total += w;
+    size_t cut[9] = {0};
+    int64_t sum = 0;
+    int x = 1;
+    for (size_t t = 0; t < n; ++t) {
+        while (x < 8 && sum >= total * x / 8) cut[x++] = t;
+        sum += weight[t];
+    }
+    while (x < 9) cut[x++] = n;
+    size_t most = 0;
+    for (x = 0; x < 8; ++x) most = std::max(most, cut[x + 1] - cut[x]);
+    most = (most + 3) / 4 * 4;
+    std::vector<int32_t> dealt(most * 8 * 4, 0);
+    for (x = 0; x < 8; ++x)
+        for (size_t t = cut[x]; t < cut[x + 1]; ++t) {
+            const size_t i = t - cut[x], to = (i / 4 * 8 + x) * 4 + i % 4;
+            std::copy(tasks.begin() + 4 * t, tasks.begin() + 4 * t + 4, dealt.begin() + 4 * to);
+        }
+    tasks.swap(dealt);
+}
+
+}  // namespace
+
+void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, size_t esize, int32_t b_row,
+                     int32_t task_cols, const HostWcsr &in, HostRows &out) {
+    const auto &wrp = in.window_row_ptr;
+    const int64_t nw = (int64_t)wrp.size() - 1;
+    // Bytes per packed column and per entry at 128 columns of B: the gathered row in both, the tile column and index
+    // against column and value.  (Two entries in one packed column read the row of B once instead of twice.)
+    const int64_t row_b = 128 * (int64_t)esize, tile_b = b_row * (int64_t)esize + 4, entry_b = 4 + (int64_t)esize;
+    auto by_rows = [&](int64_t w) {
+        const int64_t nnz = row_ptr[std::min<int64_t>(m, (w + 1) * b_row)] - row_ptr[w * b_row];
+        int64_t padded = wrp[w + 1] - wrp[w], real = padded;
+        while (real > 0 && in.window_col_idx[wrp[w] + real - 1] < 0) --real;
+        return nnz * (row_b + entry_b) <= real * row_b + padded * tile_b;
+    };
+    out = HostRows();
+    out.row_ptr.assign(m + 1, 0);
+    int64_t entries = 0;
+    std::vector<uint8_t> sparse((size_t)nw);
+    for (int64_t w = 0; w < nw; ++w) {
+        sparse[w] = by_rows(w);
+        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
+        if (sparse[w]) {
+            if (out.runs.empty() || out.runs.back().second != row_ptr[r0]) out.runs.push_back({row_ptr[r0], row_ptr[r0]});
+            out.runs.back().second = row_ptr[r1];
+        }
+        for (int64_t r = r0; r < r1; ++r) {
+            if (sparse[w]) entries += row_ptr[r + 1] - row_ptr[r];
+            out.row_ptr[r + 1] = (int32_t)entries;
+        }
+    }
+    out.n_entries = entries;
+
+    // Nearly dense rows: chunks that cover the same columns should run together, so that a row of B is fetched into an
+    // XCD's L2 once for all of them.  An XCD holds up to 1024 waves; with R such rows cut every W columns they span
+    // W * 1024 / R columns at a time.  Short spans hit L2 more often, long chunks pay their start less often: the best
+    // time is at spans of 16 MB of B (64 rows of 200 000 entries over 2 000 000 columns, N = 64: 0.264 / 0.236 / 0.296 ms
+    // at 4 / 8 / 16 MB there, where a row of B has 256 bytes, with 80 / 64 / 37 % of the gathers hitting L2; 0.343 ms and
+    // 30 % with chunks of task_cols = 512).  The span is counted at 128 columns of B.  Taken for the R longest rows for
+    // which a chunk keeps 32 entries, when at least two of their entries meet in a column on average.
+    const int64_t FIT = (16 << 20) / (128 * (int64_t)esize), MIN_CHUNK = 32;
+    int32_t k_used = 1;
+    std::vector<int64_t> longest;
+    for (int64_t w = 0; w < nw; ++w)
+        if (sparse[w])
+            for (int64_t r = w * b_row; r < std::min<int64_t>(m, (w + 1) * b_row); ++r)
+                if (row_ptr[r + 1] - row_ptr[r] > task_cols) {
+                    longest.push_back(row_ptr[r + 1] - row_ptr[r]);
+                    k_used = std::max(k_used, col_idx[row_ptr[r + 1] - 1] + 1);
+                }
+    std::sort(longest.begin(), longest.end(), std::greater<int64_t>());
+    int64_t dense_len = INT64_MAX, dense_width = 0, sum = 0;  // rows of at least dense_len entries: cut every dense_width columns
+    for (size_t i = 0; i < longest.size(); ++i) {
+        sum += longest[i];
+        const int64_t W = FIT * (int64_t)(i + 1) / 1024;
+        if (longest[i] * W >= MIN_CHUNK * (int64_t)k_used && sum >= 2 * (int64_t)k_used) dense_len = longest[i], dense_width = W;
+    }
+
+    // Runs of whole rows: enough tasks for four rounds of the chip's 8192 waves, 32 to 256 entries each.
+    int64_t in_long_rows = 0;
+    for (int64_t len : longest) in_long_rows += len;
+    const int64_t target = std::max<int64_t>(32, std::min<int64_t>(256, (entries - in_long_rows) / 32768));
+    std::vector<int32_t> chunks, rows;
+    std::vector<std::pair<int32_t, int64_t>> chunk_key;  // (first column, index)
+    std::vector<int64_t> rows_weight;
+    int64_t first = -1, last = -1;  // open task: rows [first, last)
+    auto close = [&]() {
+        if (first < 0) return;
+        rows.insert(rows.end(), {(int32_t)first, (int32_t)(last - first), out.row_ptr[first], out.row_ptr[last]});
+        rows_weight.push_back(out.row_ptr[last] - out.row_ptr[first] + 2 * (last - first));
+        first = -1;
+    };
+    for (int64_t w = 0; w < nw; ++w) {
+        if (!sparse[w]) {
+            close();
+            continue;
+        }
+        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
+        int64_t slot = in.ws_slot[w] >= 0 ? (int64_t)in.ws_slot[w] * b_row : -1;
+        for (int64_t r = r0; r < r1; ++r) {
+            const int64_t len = row_ptr[r + 1] - row_ptr[r];
+            if (len > task_cols) {  // (then the window is split and owns at least this many rows of scratch)
+                close();
+                int64_t step = task_cols;
+                if (len >= dense_len) {  // (no more chunks than the row's share of its window's scratch rows)
+                    const int64_t rows_left = (int64_t)ceil_div(wrp[w + 1] - wrp[w], task_cols) * b_row;
+                    // whole batches of the kernel: 64 entries at the widths where it matters most
+                    step = std::max<int64_t>(1, (len * dense_width / k_used + 32) / 64) * 64;
+                    step = std::max(step, ceil_div(2 * (row_ptr[r1] - row_ptr[r0]), rows_left));
+                    step = std::min<int64_t>(task_cols, step);
+                }
+                const int64_t parts = ceil_div(len, step);
+                out.split.insert(out.split.end(), {(int32_t)r, (int32_t)slot, (int32_t)parts, 0});
+                for (int64_t j = 0; j < parts; ++j) {
+                    const int64_t lo = j * step, hi = std::min<int64_t>(len, lo + step);
+                    chunk_key.push_back({col_idx[row_ptr[r] + lo], (int64_t)chunk_key.size()});
+                    chunks.insert(chunks.end(), {(int32_t)r, (int32_t)slot, (int32_t)(out.row_ptr[r] + lo),
+                                                 (int32_t)(out.row_ptr[r] + hi)});
+                    ++slot;
+                }
+                continue;
+            }
+            if (first >= 0 && (last - first >= 63 || out.row_ptr[last] - out.row_ptr[first] + len > target)) close();
+            if (first < 0) first = r;
+            last = r + 1;
+        }
+    }
+    close();
+    std::sort(chunk_key.begin(), chunk_key.end());
+    std::vector<int64_t> chunk_weight;
+    for (auto &c : chunk_key) {
+        const int32_t *t = chunks.data() + 4 * c.second;
+        out.chunks.insert(out.chunks.end(), t, t + 4);
+        chunk_weight.push_back(t[3] - t[2]);
+    }
+    deal_to_xcds(out.chunks, chunk_weight);
+    deal_to_xcds(rows, rows_weight);
+    out.tasks.swap(rows);
+
+    // the windows that stay with the tile kernels
+    std::vector<int64_t> tile_weight;
+    for (int64_t w = 0; w < nw; ++w) {
+        if (sparse[w]) continue;
+        const int32_t lo = wrp[w], hi = wrp[w + 1], split = hi - lo > task_cols;
+        if (split) out.tile_split.push_back((int32_t)w);
+        for (int64_t c = lo; c < hi; c += task_cols) {
+            const int64_t e = std::min<int64_t>(hi, c + task_cols);
+            out.tile_tasks.insert(out.tile_tasks.end(), {(int32_t)w, (int32_t)c, (int32_t)e, split});
+            tile_weight.push_back(e - c + 16);
+        }
+    }
+    deal_to_xcds(out.tile_tasks, tile_weight);
 }
 
 void wcsr_zero_windows(const std::vector<int32_t> &wrp, int32_t task_cols, std::vector<int32_t> &zw) {

@@ -103,6 +103,19 @@ struct HostWcsr {
     std::vector<int32_t> ws_slot;         // [n_windows] first scratch slot of a split window (one per task), -1 for the others
 };
 
+// How a WCSR product is dealt to kernels (wcsr_build_rows): windows whose rows share few columns are walked entry by
+// entry (asp_wcsr_rows.hip), the others tile by tile.
+struct HostRows {
+    std::vector<int32_t> row_ptr;     // [m + 1] entries of the rows walked entry by entry, consecutive
+    std::vector<std::pair<int64_t, int64_t>> runs;  // where those entries are in the CSR arrays
+    int64_t n_entries = 0;
+    std::vector<int32_t> tasks;       // [..][4] see wcsr_rows_kernel; empty tasks fill up
+    std::vector<int32_t> chunks;      // [..][4] see wcsr_chunks_kernel; empty tasks fill up
+    std::vector<int32_t> split;       // [..][4] = {row, first scratch row, scratch rows, 0} of rows longer than task_cols
+    std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only; empty tasks fill up
+    std::vector<int32_t> tile_split;  // the split windows among those
+};
+
 // converters (asp_convert.cpp); values are only bit-copied
 void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostBcsr &out);
@@ -113,6 +126,8 @@ void bcsr_pack_fragments_f32(const HostBcsr &in, int32_t b_row, int32_t b_col, s
 bool csr_to_wcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostWcsr &out);
 void wcsr_tasks_host(const std::vector<int32_t> &window_row_ptr, int32_t task_cols, std::vector<int32_t> &tasks);
+void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, size_t esize, int32_t b_row,
+                     int32_t task_cols, const HostWcsr &in, HostRows &out);
 void wcsr_zero_windows(const std::vector<int32_t> &window_row_ptr, int32_t task_cols,
                        std::vector<int32_t> &zero_windows);
 // returns empty string when the CSR arrays are valid, else a description of the first problem
@@ -154,6 +169,11 @@ struct asp_handle {
     int32_t *d_sched = nullptr;     // BCSR: 8 tile counters of the dynamic-scheduling variant (a benchmarking switch)
     // WCSR: where the tasks of split windows put their partial tiles
     int32_t *d_ws_slot = nullptr;   // [n_windows] first scratch slot of a split window, -1 otherwise
+    // WCSR: the kernels' work lists (HostRows) and the entries of the windows that are walked entry by entry
+    int64_t n_row_tasks = 0, n_chunks = 0, n_split_rows = 0, n_tile_tasks = 0, n_tile_split = 0;
+    int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
+    int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
+    void *d_e_val = nullptr;
     float *d_ws = nullptr;          // fp32 scratch, one [b_row][N] tile per slot (asp_reserve)
     int64_t ws_floats = 0;          // its capacity
 };
@@ -192,8 +212,9 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
 // once per device, and its capacity in floats.
 asp_status_t wcsr_static_scratch(int device, float **ptr, int64_t *floats);
 int64_t wcsr_scratch_floats(const asp_handle *h, int64_t N);  // fp32 scratch elements a call of width N uses
-// clears the C rows of windows without columns (keep_split: and leaves split windows alone; else clears them too)
-void wcsr_clear_empty_windows(const asp_handle *h, void *C, int64_t N, bool keep_split, hipStream_t stream);
+// windows that are walked entry by entry (empty ones among them), and the sums of their split rows
+void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream);
+void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
 // rows of split windows = sum of their tasks' partial tiles, in task order
 void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
 // GPU task partition: fills h->d_tasks / h->n_tasks from h->d_row_ptr (wavefront scans)

@@ -50,27 +50,14 @@ asp_status_t wcsr_static_scratch(int device, float **ptr, int64_t *floats) {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// ---- zero the C rows that the main kernel will not plainly overwrite -------------------------------
-// (windows without columns; and, when they accumulate with atomics, windows split over several tasks)
-// ws_slot != nullptr: split windows (slot >= 0) are left alone, their rows come from the partial tiles.
-__global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__restrict__ zero_windows,
-                                                             const int32_t *__restrict__ ws_slot, int b_row,
-                                                             uint8_t *__restrict__ C, int esize, int M, int64_t N,
-                                                             bool vec) {
-    const int w = zero_windows[blockIdx.x];
-    if (ws_slot && ws_slot[w] >= 0) return;
-    const int64_t r0 = (int64_t)w * b_row;
+// ---- zero the C rows of windows that are empty or split: fp32 calls without scratch, whose split windows are summed
+// with atomics
+__global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__restrict__ zero_windows, int b_row,
+                                                             float *__restrict__ C, int M, int64_t N) {
+    const int64_t r0 = (int64_t)zero_windows[blockIdx.x] * b_row;
     const int64_t r1 = r0 + b_row < M ? r0 + b_row : M;
-    uint8_t *base = C + r0 * N * esize;
-    const int64_t bytes = (r1 - r0) * N * esize;
-    if (vec) {  // row size and base are multiples of 16 bytes
-        uint4 *b4 = (uint4 *)base;
-        for (int64_t i = threadIdx.x; i < bytes / 16; i += 256) b4[i] = make_uint4(0, 0, 0, 0);
-    } else if (esize == 4) {
-        for (int64_t i = threadIdx.x; i < bytes / 4; i += 256) ((uint32_t *)base)[i] = 0u;
-    } else {
-        for (int64_t i = threadIdx.x; i < bytes / 2; i += 256) ((uint16_t *)base)[i] = 0;
-    }
+    float *base = C + r0 * N;
+    for (int64_t i = threadIdx.x; i < (r1 - r0) * N; i += 256) base[i] = 0.f;
 }
 
 // ---- rows of split windows from the partial tiles of their tasks (Section III-C) ---------------------
@@ -78,16 +65,15 @@ __global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__re
 // buffer.  One thread per output element adds the tiles in task order (fixed order: bitwise reproducible)
 // and rounds once to the output type.
 template <typename OutT, int U>  // U = elements per thread and access: 4 (16-byte loads) or 1
-__global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *__restrict__ zero_windows,
+__global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *__restrict__ split_windows,
                                                                 const int32_t *__restrict__ ws_slot,
                                                                 const int32_t *__restrict__ window_row_ptr,
                                                                 int task_cols, int b_row, OutT *__restrict__ C,
                                                                 const float *__restrict__ ws, int M, int64_t N) {
     typedef float vec_t __attribute__((ext_vector_type(U)));
     typedef OutT out_t __attribute__((ext_vector_type(U)));
-    const int w = zero_windows[blockIdx.x];
+    const int w = split_windows[blockIdx.x];
     const int slot0 = ws_slot[w];
-    if (slot0 < 0) return;  // a window without columns
     const int parts = (int)(((int64_t)window_row_ptr[w + 1] - window_row_ptr[w] + task_cols - 1) / task_cols);
     const int64_t r0 = (int64_t)w * b_row, r1 = r0 + b_row < M ? r0 + b_row : M;
     const int64_t units = (r1 - r0) * N / U, tile = (int64_t)b_row * N / U;
@@ -108,34 +94,46 @@ __global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *_
     }
 }
 
-__device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, int64_t N, int n, bool vec) {
-    // 4 adjacent columns n..n+3 of row `col` of B; zeros for a pad column (col < 0) or past the edge
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (col >= 0 && n < N) {
-        const float *p = B + (int64_t)col * N + n;
-        if (vec) {
-            v = *(const float4 *)p;
-        } else {
-            v.x = p[0];
-            if (n + 1 < N) v.y = p[1];
-            if (n + 2 < N) v.z = p[2];
-            if (n + 3 < N) v.w = p[3];
+// 4 adjacent columns n..n+3 of a row, at any alignment.  VEC (N >= 4): n was moved left so that n + 3 < N (own_n, the
+// column it was moved from, tells which columns belong to this lane alone); else one column at a time.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool VEC>
+__device__ __forceinline__ int64_t lane_column(int64_t own_n, int64_t N) {
+    return VEC && own_n > N - 4 ? N - 4 : own_n;
+}
+
+template <bool VEC>
+__device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, int64_t N, int64_t n) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);  // zeros for a pad column (col < 0) or past the edge
+    if (VEC) {
+        if (col >= 0) {
+            const f32x4_any u = *(const f32x4_any *)(B + (int64_t)col * N + n);
+            v = make_float4(u.x, u.y, u.z, u.w);
         }
+    } else if (col >= 0 && n < N) {
+        const float *p = B + (int64_t)col * N + n;
+        v.x = p[0];
+        if (n + 1 < N) v.y = p[1];
+        if (n + 2 < N) v.z = p[2];
+        if (n + 3 < N) v.w = p[3];
     }
     return v;
 }
 
-__device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int M, int64_t N, int n, float4 v, bool split,
-                                     bool vec) {
-    if (row >= M || n >= N) return;
+template <bool VEC>
+__device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int64_t M, int64_t N, int64_t own_n, float4 v,
+                                     bool split) {
+    if (row >= M || own_n >= N) return;
+    const int64_t n = lane_column<VEC>(own_n, N);
     float *p = C + row * N + n;
-    if (split) {
-        unsafeAtomicAdd(p, v.x);
-        if (n + 1 < N) unsafeAtomicAdd(p + 1, v.y);
-        if (n + 2 < N) unsafeAtomicAdd(p + 2, v.z);
-        if (n + 3 < N) unsafeAtomicAdd(p + 3, v.w);
-    } else if (vec) {
-        *(float4 *)p = v;
+    if (split) {  // (columns shared with another lane are added by that one)
+        if (n >= own_n) unsafeAtomicAdd(p, v.x);
+        if (n + 1 >= own_n && n + 1 < N) unsafeAtomicAdd(p + 1, v.y);
+        if (n + 2 >= own_n && n + 2 < N) unsafeAtomicAdd(p + 2, v.z);
+        if (n + 3 >= own_n && n + 3 < N) unsafeAtomicAdd(p + 3, v.w);
+    } else if (VEC) {
+        __builtin_nontemporal_store(f32x4_any{v.x, v.y, v.z, v.w}, (f32x4_any *)p);
     } else {
         p[0] = v.x;
         if (n + 1 < N) p[1] = v.y;
@@ -171,15 +169,17 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, int n_tiles, float *__restrict__ ws,
+                                                          int64_t N, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
-    const int64_t wave_id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int task = (int)(wave_id / n_tiles), nt = (int)(wave_id % n_tiles);
+    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
     if (task >= n_tasks) return;  // whole wave leaves together
     const int lane = threadIdx.x & 63, kq = lane >> 4, jl = lane & 15;
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
-    const int n0 = nt * (64 * NG) + 4 * jl;
+    if (td.y >= td.z) return;     // fills up a list
+    int64_t n0[NG];  // first of the lane's 4 columns in each group
+#pragma unroll
+    for (int g = 0; g < NG; ++g) n0[g] = lane_column<VEC>((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N);
 
     f32x4 acc[NG][4];
 #pragma unroll
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int g = 0; g < NG; ++g) c.b[d][h][g] = gather4(B, idx[d][h], N, n0 + 64 * g, VEC);
+                for (int g = 0; g < NG; ++g) c.b[d][h][g] = gather4<VEC>(B, idx[d][h], N, n0[g]);
         }
     };
     auto multiply = [&](int base, const Chunk &c) {
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float4 v = make_float4(acc[g][0][r], acc[g][1][r], acc[g][2][r], acc[g][3][r]);
-            put4(out.base, out.row0 + 4 * kq + r, out.rows, N, n0 + 64 * g, v, out.atomic, VEC);
+            put4<VEC>(out.base, out.row0 + 4 * kq + r, out.rows, N, (int64_t)nt * (64 * NG) + 64 * g + 4 * jl, v, out.atomic);
         }
 }
 
@@ -271,16 +271,16 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, int n_tiles, float *__restrict__ ws,
+                                                          int64_t N, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
     constexpr int BRW = 32 * MTW;
-    const int64_t wave_id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int task = (int)(wave_id / n_tiles), nt = (int)(wave_id % n_tiles);
+    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
     if (task >= n_tasks) return;
     const int lane = threadIdx.x & 63, kq = lane >> 5, jl = lane & 31;
     const int4 td = tasks[task];
-    const int n0 = nt * 128 + 4 * jl;
+    if (td.y >= td.z) return;
+    const int64_t own_n0 = (int64_t)nt * 128 + 4 * jl, n0 = lane_column<VEC>(own_n0, N);
 
     f32x16 acc[MTW][4];
 #pragma unroll
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
             s.a[3][i] = a4.w;
         }
 #pragma unroll
-        for (int h = 0; h < 4; ++h) s.b[h] = gather4(B, col[h], N, n0, VEC);
+        for (int h = 0; h < 4; ++h) s.b[h] = gather4<VEC>(B, col[h], N, n0);
     };
     auto multiply = [&](const Stage &s) {
 #pragma unroll
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
         for (int r = 0; r < 16; ++r) {
             float4 v = make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
             int row = i * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
-            put4(out.base, out.row0 + row, out.rows, N, n0, v, out.atomic, VEC);
+            put4<VEC>(out.base, out.row0 + row, out.rows, N, own_n0, v, out.atomic);
         }
 }
 
@@ -519,22 +519,13 @@ WcsrPlan wcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
 
 int64_t wcsr_scratch_floats(const asp_handle *h, int64_t N) { return h->n_split_tasks * h->b_row * N; }
 
-void wcsr_clear_empty_windows(const asp_handle *h, void *C, int64_t N, bool keep_split, hipStream_t stream) {
-    if (h->n_zero_windows == 0) return;
-    const int es = (int)dtype_size(h->dtype);
-    const bool vec = ((uintptr_t)C & 15) == 0 && (N * es) % 16 == 0;
-    hipLaunchKernelGGL(wcsr_zero_rows_kernel, dim3((unsigned)h->n_zero_windows), dim3(256), 0, stream,
-                       h->d_zero_windows, keep_split ? h->d_ws_slot : nullptr, h->b_row, (uint8_t *)C, es, (int)h->m, N,
-                       vec);
-}
-
 void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream) {
-    if (h->n_split_tasks == 0) return;
+    if (h->n_tile_split == 0) return;
     const bool vec = N % 4 == 0 && ((uintptr_t)C & 15) == 0;
     const unsigned gy = (unsigned)std::min<int64_t>(64, ceil_div((int64_t)h->b_row * N, vec ? 1024 : 256));
-    dim3 grid((unsigned)h->n_zero_windows, gy), block(256);
+    dim3 grid((unsigned)h->n_tile_split, gy), block(256);
 #define ASP_SUM(T, U)                                                                                              \
-    hipLaunchKernelGGL((wcsr_sum_partials_kernel<T, U>), grid, block, 0, stream, h->d_zero_windows, h->d_ws_slot, \
+    hipLaunchKernelGGL((wcsr_sum_partials_kernel<T, U>), grid, block, 0, stream, h->d_tile_split, h->d_ws_slot,   \
                        h->d_row_ptr, h->task_cols, h->b_row, (T *)C, ws, (int)h->m, N)
     if (h->dtype == ASP_DT_BF16) {
         if (vec) ASP_SUM(__bf16, 4);
@@ -549,38 +540,41 @@ void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float
 asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws_buf, int64_t ws_floats,
                               hipStream_t stream) {
     if (h->dtype == ASP_DT_BF16) return wcsr_bf16_spmm_launch(h, B, C, N, ws_buf, ws_floats, stream);
-    const bool aligned = (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
-    const WcsrPlan p = wcsr_plan(h, N, aligned);
-    const bool vec = p.vectorized != 0;
-    if (p.workgroups >= (1ll << 31)) return fail(ASP_ERR_UNSUPPORTED, "too many wave tasks");
+    const WcsrPlan p = wcsr_plan(h, N, true);
+    const bool vec = N >= 4;
     // split windows: partial tiles in the scratch buffer when it is large enough, else atomic adds into C
     const bool partial = h->n_split_tasks > 0 && ws_buf && ws_floats >= wcsr_scratch_floats(h, N);
     float *ws = partial ? ws_buf : nullptr;
-    wcsr_clear_empty_windows(h, C, N, partial, stream);
-    if (h->n_tasks > 0) {
-        dim3 grid((unsigned)p.workgroups), block(256);
-        const int4 *tasks = (const int4 *)h->d_tasks;
+    if (h->n_split_tasks > 0 && !partial)
+        hipLaunchKernelGGL(wcsr_zero_rows_kernel, dim3((unsigned)h->n_zero_windows), dim3(256), 0, stream,
+                           h->d_zero_windows, h->b_row, (float *)C, (int)h->m, N);
+    wcsr_rows_launch(h, B, C, N, ws, stream);
+    if (h->n_tile_tasks > 0) {
+        // a workgroup's four tasks are neighbours; the column tiles follow each other, so that one slab of B is walked
+        // at a time
+        dim3 grid((unsigned)ceil_div(h->n_tile_tasks, 4), (unsigned)p.n_tiles), block(256);
+        const int4 *tasks = (const int4 *)h->d_tile_tasks;
         const float *vals = (const float *)h->d_values;
         const float *Bf = (const float *)B;
         float *Cf = (float *)C;
-        const int nt = (int)h->n_tasks, M = (int)h->m;
+        const int nt = (int)h->n_tile_tasks, M = (int)h->m;
 #define ASP_W16(NG)                                                                                                   \
     do {                                                                                                              \
         if (vec)                                                                                                      \
             hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);                  \
+                               Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);                  \
         else                                                                                                          \
             hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);          \
+                               vals, Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);          \
     } while (0)
 #define ASP_W32(MTW)                                                                                                   \
     do {                                                                                                               \
         if (vec)                                                                                                       \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
+                               Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
         else                                                                                                           \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
+                               vals, Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
     } while (0)
         if (h->b_row == 16) {
             if (p.bn == 256) ASP_W16(4);
@@ -594,7 +588,10 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
 #undef ASP_W16
 #undef ASP_W32
     }
-    if (partial) wcsr_sum_partial_tiles(h, C, N, ws, stream);
+    if (partial) {
+        wcsr_rows_sum_launch(h, C, N, ws, stream);
+        wcsr_sum_partial_tiles(h, C, N, ws, stream);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ASP_ERR_HIP, std::string("WCSR kernel launch: ") + hipGetErrorString(e));
     return ASP_OK;

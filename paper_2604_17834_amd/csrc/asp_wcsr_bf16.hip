@@ -23,6 +23,10 @@
 
 namespace asp {
 
+// 16 bytes at the alignment of their elements
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int MTW>
 __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                              const int32_t *__restrict__ window_col_idx,
@@ -30,18 +34,22 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
                                                              const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
                                                              float *__restrict__ ws, const int32_t *__restrict__ ws_slot,
                                                              const int32_t *__restrict__ window_row_ptr, int task_cols,
-                                                             int M, int64_t N, int n_tiles) {
+                                                             int M, int64_t N) {
     constexpr int BRW = 16 * MTW;
     constexpr int A_TILE = BRW * 8;  // elements of one value tile [BRW][8]
     __shared__ __attribute__((aligned(16))) uint8_t lds[4][32 * 256];  // per wave: 32 gathered rows x 128 columns
 
-    const int64_t wave_id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int task = (int)(wave_id / n_tiles), nt = (int)(wave_id % n_tiles);
+    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
     if (task >= n_tasks) return;  // whole wave leaves together
     uint8_t *sb = lds[threadIdx.x >> 6];
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
+    if (td.y >= td.z) return;     // fills up a list
     const int lane = threadIdx.x & 63, h = lane >> 4, p = lane & 15;
-    const int64_t n0 = (int64_t)nt * 128, n = n0 + p * 8;
+    // chunk c of the tile = 8 columns from chunk_col(c): chunks that would pass N end there instead and repeat columns of
+    // their neighbour (the same bits), so that every access is 16 bytes at any N >= 8 and any alignment
+    const int64_t n0 = (int64_t)nt * 128;
+    auto chunk_col = [&](int c) { return n0 + 8 * c < N - 8 ? n0 + 8 * c : N - 8; };
+    const int64_t n = chunk_col(p);
     const int tile0 = td.y >> 3, tile1 = td.z >> 3;
     const int nst = (tile1 - tile0 + 3) >> 2;  // stages of 32 packed columns
 
@@ -63,8 +71,8 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
     auto load_b = [&](const Idx &ix, uint4 (&v)[8]) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            v[q] = make_uint4(0, 0, 0, 0);  // pads (index -1) and columns past N contribute zeros
-            if (ix.c[q] >= 0 && n < N) v[q] = *(const uint4 *)(B + (int64_t)ix.c[q] * N + n);
+            v[q] = make_uint4(0, 0, 0, 0);  // pads (index -1) contribute zeros
+            if (ix.c[q] >= 0) v[q] = __builtin_bit_cast(uint4, *(const u32x4_any *)(B + (int64_t)ix.c[q] * N + n));
         }
     };
     auto load_a = [&](int st, bf16x8 (&af)[MTW]) {
@@ -135,12 +143,12 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
             const int64_t grow = row0 + i * 16 + p;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int64_t gcol = n0 + t * 32 + h * 8;
-                if (grow < M && gcol < N) {
+                const int64_t gcol = chunk_col(4 * t + h);
+                if (grow < M && n0 + t * 32 + h * 8 < N) {
                     bf16x4 a = __builtin_convertvector(acc[i][2 * t], bf16x4);      // round to nearest even
                     bf16x4 b = __builtin_convertvector(acc[i][2 * t + 1], bf16x4);
                     bf16x8 v8 = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-                    *(bf16x8 *)(C + grow * N + gcol) = v8;
+                    *(u32x4_any *)(C + grow * N + gcol) = __builtin_bit_cast(u32x4_any, v8);
                 }
             }
         }
@@ -152,17 +160,18 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
             float *wr = ws + (slot * BRW + i * 16 + p) * N;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int64_t gcol = n0 + t * 32 + h * 8;
-                if (gcol < N) {
-                    *(f32x4 *)(wr + gcol) = acc[i][2 * t];
-                    *(f32x4 *)(wr + gcol + 4) = acc[i][2 * t + 1];
+                const int64_t gcol = chunk_col(4 * t + h);
+                if (n0 + t * 32 + h * 8 < N) {
+                    *(f32x4_any *)(wr + gcol) = acc[i][2 * t];
+                    *(f32x4_any *)(wr + gcol + 4) = acc[i][2 * t + 1];
                 }
             }
         }
     }
 }
 
-// ---- element-wise path: any N, any alignment; one thread per column, whole windows, no splitting, no scratch
+// ---- one thread per column, whole windows, no splitting, no scratch: N < 8, and calls without scratch at widths or
+// alignments that do not allow 16-byte accesses (those never needed any)
 template <int BRW>
 __global__ __launch_bounds__(64) void wcsr_bf16_generic_kernel(const int32_t *__restrict__ window_row_ptr,
                                                                const int32_t *__restrict__ window_col_idx,
@@ -198,11 +207,14 @@ __global__ __launch_bounds__(64) void wcsr_bf16_generic_kernel(const int32_t *__
 asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, int64_t ws_floats,
                                    hipStream_t stream) {
     const bool aligned = (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
-    const WcsrPlan p = wcsr_plan(h, N, aligned);
     const uint16_t *vals = (const uint16_t *)h->d_values, *Bh = (const uint16_t *)B;
     uint16_t *Ch = (uint16_t *)C;
     const int M = (int)h->m;
-    if (!p.vectorized) {
+    const bool scratch = h->n_split_tasks == 0 || (ws && ws_floats >= wcsr_scratch_floats(h, N));
+    if (!scratch && aligned && N % 8 == 0)
+        return fail(ASP_ERR_BUFFER_TOO_SMALL,
+                    "bf16 WCSR with split windows needs scratch memory for this width: call asp_reserve(handle, N) first");
+    if (!scratch || (N < 8 && h->n_tile_tasks > 0)) {
         dim3 grid((unsigned)h->n_brows, (unsigned)ceil_div(N, 64)), block(64);
         if (grid.y > 65535) return fail(ASP_ERR_UNSUPPORTED, "N too large for the element-wise WCSR path");
         switch (h->b_row) {
@@ -211,23 +223,20 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
             default: hipLaunchKernelGGL(wcsr_bf16_generic_kernel<64>, grid, block, 0, stream, h->d_row_ptr, h->d_col_idx, vals, Bh, Ch, M, N); break;
         }
     } else {
-        if (p.workgroups >= (1ll << 31)) return fail(ASP_ERR_UNSUPPORTED, "too many wave tasks");
-        if (h->n_split_tasks > 0 && ws_floats < wcsr_scratch_floats(h, N))
-            return fail(ASP_ERR_BUFFER_TOO_SMALL,
-                        "bf16 WCSR with split windows needs scratch memory for this width: call asp_reserve(handle, N) first");
-        wcsr_clear_empty_windows(h, C, N, true, stream);
-        if (h->n_tasks > 0) {
-            dim3 grid((unsigned)p.workgroups), block(256);
-            const int4 *tasks = (const int4 *)h->d_tasks;
-            const int nt = (int)h->n_tasks;
+        wcsr_rows_launch(h, B, C, N, ws, stream);
+        if (h->n_tile_tasks > 0) {
+            dim3 grid((unsigned)ceil_div(h->n_tile_tasks, 4), (unsigned)ceil_div(N, 128)), block(256);
+            const int4 *tasks = (const int4 *)h->d_tile_tasks;
+            const int nt = (int)h->n_tile_tasks;
 #define ASP_WB(MTW)                                                                                                 \
     hipLaunchKernelGGL((wcsr_bf16_spmm_kernel<MTW>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bh, Ch, \
-                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N, p.n_tiles)
+                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N)
             if (h->b_row == 16) ASP_WB(1);
             else if (h->b_row == 32) ASP_WB(2);
             else ASP_WB(4);
 #undef ASP_WB
         }
+        wcsr_rows_sum_launch(h, C, N, ws, stream);
         wcsr_sum_partial_tiles(h, C, N, ws, stream);
     }
     hipError_t e = hipGetLastError();

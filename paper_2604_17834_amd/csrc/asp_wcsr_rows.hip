@@ -1,0 +1,365 @@
+// WCSR x dense SpMM for row-windows whose rows share (almost) no columns: the entries are walked row by row.
+//
+// A window tile (paper, Section II-C) stores b_row values per packed column and pays off when several rows of the
+// window meet in that column.  In graph-like matrices with scattered columns they do not: a packed column holds one
+// entry, its tile is 64 (fp32, height 16) to 256 bytes of mostly zeros beside the 4 N bytes of the gathered row of B,
+// and a window's tasks are as long as its longest row.  Such windows (wcsr_build_rows decides per window, at creation)
+// run here from plain (column, value) entries, 6-8 bytes each.
+//
+// What bounds it: the gather.  Random rows of B that miss L2 arrive at 7.5 TB/s on this chip whatever the size of B
+// (measured with rows of 128-512 bytes over 67 MB - 1 GB), so the design removes every other byte and keeps enough of
+// those in flight: one wavefront walks a run of consecutive rows, 64 to 256 entries; columns and values are uniform
+// for the wave and come through scalar loads (16 entries ahead), so an entry costs one vector load with a scalar base
+// and E multiply-adds with a scalar factor; two batches of 8 rows of B are in flight per wave, up to 8 waves per SIMD.
+// A row's entries are summed in order in fp32.  Rows longer than task_cols are cut into chunks (Section III-C) whose
+// sums go to rows of scratch memory, which wcsr_rows_sum_kernel adds up.
+//
+// Order of the work: chunks of long rows are sorted by column and dealt to the XCDs in contiguous ranges, so that the
+// chunks of different rows that cover the same columns run on one XCD at about the same time and find the rows of B in
+// its L2 (64 rows of 200 000 entries over 2 000 000 columns: 84 % of the gathers).
+//
+// Any N and any alignment: a lane owns E adjacent columns; the last lane of a row moves left so that it ends at N and
+// computes some of its neighbour's columns a second time (the same bits), so that no access leaves the row.
+#include "asp_internal.h"
+
+namespace asp {
+
+namespace {
+
+typedef __attribute__((address_space(1))) char global_char;
+
+template <typename T, int E>
+struct RowVec;
+template <int E>
+struct RowVec<float, E> {
+    typedef float type __attribute__((ext_vector_type(E), aligned(4)));
+};
+template <int E>
+struct RowVec<uint16_t, E> {
+    typedef uint16_t type __attribute__((ext_vector_type(E), aligned(2)));
+};
+
+__device__ __forceinline__ float widen(float v) { return v; }
+__device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+__device__ __forceinline__ void narrow(float v, float &out) { out = v; }
+__device__ __forceinline__ void narrow(float v, uint16_t &out) { out = __builtin_bit_cast(uint16_t, (__bf16)v); }  // to nearest even
+
+// The sum of a chunk {row, scratch row, -, -} at columns nc .. nc + E - 1 (the lane's own ones start at n): to its row of
+// ws, or without ws (fp32 only) added to C with atomics.
+template <typename T, int E>
+__device__ __forceinline__ void put_chunk(int4 td, const float (&acc)[E], int64_t n, int64_t nc, int64_t N, T *C, float *ws) {
+    if (ws) {
+        float *dst = ws + (int64_t)td.y * N + nc;
+#pragma unroll
+        for (int i = 0; i < E; ++i) dst[i] = acc[i];
+    } else if constexpr (sizeof(T) == 4) {
+        float *dst = (float *)C + (int64_t)td.x * N + nc;
+#pragma unroll
+        for (int i = 0; i < E; ++i)
+            if (nc + i >= n) unsafeAtomicAdd(dst + i, acc[i]);  // a column of two lanes is added by one of them
+    }
+}
+
+}  // namespace
+
+// tasks[t] = {first row, rows (1..63), first entry, end entry}: consecutive whole rows.  row_ptr / col / val: the entries
+// of the rows handled here; col and val are readable up to the next multiple of 8 entries plus 8.
+// CHUNK: the task is a chunk of a long row, {row, scratch row, first entry, end entry}.
+// One wave: task `task`, columns from blockIdx.y * 64 E.
+template <typename T, int E, bool CHUNK>
+__device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int task, const int32_t *__restrict__ row_ptr,
+                                          const int32_t *__restrict__ col, const T *__restrict__ val,
+                                          const T *__restrict__ B, T *__restrict__ C, int64_t N, float *__restrict__ ws) {
+    typedef typename RowVec<T, E>::type vec_t;
+    const int lane = threadIdx.x & 63;
+    const int4 td = tasks[task];
+    const int64_t n = (int64_t)blockIdx.y * (64 * E) + lane * E;
+    const int64_t nc = n < N - E ? n : N - E;  // N >= E
+    const bool owner = n < N;
+    const uint32_t voff = (uint32_t)(nc * (int64_t)sizeof(T)), row_bytes = (uint32_t)(N * (int64_t)sizeof(T));
+    const int e0 = td.z, e1 = td.w;
+
+    float acc[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) acc[i] = 0.f;
+
+    // batches of 8 entries, aligned; entries outside [e0, e1) read a row of B that the task reads anyway, times zero
+    struct Batch {
+        int c[8];
+        uint32_t v[8];  // fp32 bits (as integers, so that selections stay in scalar registers)
+    };
+    const int base0 = e0 & ~7, nb = e1 > e0 ? (e1 - base0 + 7) >> 3 : 0;
+    const int c_any = nb > 0 ? col[e0] : 0;
+    auto fetch = [&](int b, Batch &t) __attribute__((always_inline)) {
+        const int base = base0 + 8 * b;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t.c[j] = col[base + j];
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t.v[j] = __float_as_uint(widen(val[base + j]));
+        } else {  // scalar loads are whole words
+            const uint32_t *w = (const uint32_t *)(val + base);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t p = w[j];
+                t.v[2 * j] = p << 16;
+                t.v[2 * j + 1] = p & 0xffff0000u;
+            }
+        }
+        if (base < e0 || base + 8 > e1)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (base + j < e0 || base + j >= e1) t.c[j] = c_any, t.v[j] = 0u;
+    };
+    auto gather = [&](const Batch &t, vec_t (&b)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const global_char *row = (const global_char *)B + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(t.c[j]) * row_bytes;
+            uint32_t off = voff;
+            asm("" : "+s"(row), "+v"(off));  // scalar base + 32-bit offset, instead of a 64-bit vector address per row
+            b[j] = *(const __attribute__((address_space(1))) vec_t *)(row + off);
+        }
+    };
+    // Two batches in flight: while one is added, the next is on its way and the entries of the one after it are read.
+    // (The loop issues without conditions -- otherwise the waits before the additions would have to assume that the
+    // younger loads were not issued, and wait for them too.  The last batches are left to the code behind it.)
+    auto walk = [&](auto add) __attribute__((always_inline)) {
+        Batch t0, t1, t2;
+        vec_t b0[8], b1[8];
+        int b = 0;
+        if (nb > 0) {
+            fetch(0, t0);
+            gather(t0, b0);
+            if (nb > 1) fetch(1, t1);
+        }
+        for (; b + 3 < nb; b += 2) {
+            gather(t1, b1);
+            fetch(b + 2, t2);
+            add(b, t0, b0);
+            gather(t2, b0);
+            t0 = t2;
+            fetch(b + 3, t2);
+            add(b + 1, t1, b1);
+            t1 = t2;
+        }
+        if (b + 1 < nb) {
+            gather(t1, b1);
+            if (b + 2 < nb) fetch(b + 2, t2);
+            add(b, t0, b0);
+            if (b + 2 < nb) gather(t2, b0);
+            add(b + 1, t1, b1);
+            if (b + 2 < nb) add(b + 2, t2, b0);
+        } else if (b < nb) {
+            add(b, t0, b0);
+        }
+    };
+    auto fma_entry = [&](const Batch &t, const vec_t (&bv)[8], int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[i] = __builtin_fmaf(__uint_as_float(__builtin_amdgcn_readfirstlane(t.v[j])), widen((T)bv[j][i]), acc[i]);
+    };
+
+    if (CHUNK) {
+        walk([&](int, const Batch &t, const vec_t(&bv)[8]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) fma_entry(t, bv, j);
+        });
+        if (owner && e0 < e1) put_chunk<T, E>(td, acc, n, nc, N, C, ws);
+        return;
+    }
+
+    // lane i holds the end of the task's i-th row
+    int ends = 0x7fffffff;
+    if (lane < td.y) ends = row_ptr[td.x + lane + 1];
+    int k = 0, end_k = __builtin_amdgcn_readlane(ends, 0);
+    auto finish_row = [&]() __attribute__((always_inline)) {
+        global_char *row = (global_char *)C + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(td.x + k) * row_bytes;
+        uint32_t off = voff;
+        asm("" : "+s"(row), "+v"(off));
+        vec_t v;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            T o;
+            narrow(acc[i], o);
+            v[i] = o;
+            acc[i] = 0.f;
+        }
+        if (owner) __builtin_nontemporal_store(v, (__attribute__((address_space(1))) vec_t *)(row + off));
+        ++k;
+        end_k = __builtin_amdgcn_readlane(ends, k);
+    };
+    walk([&](int b, const Batch &t, const vec_t(&bv)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            while (base0 + 8 * b + j == end_k) finish_row();
+            fma_entry(t, bv, j);
+        }
+    });
+    while (k < td.y) finish_row();  // the last row, and rows without entries behind it
+}
+
+// A chunk of a long row where walk_rows would load 4 bytes or less per lane.  Chunks of nearly dense rows find most of
+// their rows of B in L2 and are bound by the address unit instead, and a 4-byte load per lane takes as long as a wider
+// one.  So here L lanes cover a row of B with up to 16 bytes each, and the G = 64 / L lane groups of the wave take
+// different entries.  A group's entries are loaded 16 at a time, lane i of every 16 lanes holding the i-th, and broadcast
+// within the 16 lanes (row_newbcast) as they are used; the groups' sums are added at the end in a fixed order.
+// (64 rows of 200 000 entries, N = 64, fp32: 0.236 -> 0.211 ms; 3.2e6 Zipf entries, N = 100, bf16: 0.146 -> 0.133 ms.
+// At 8 bytes per lane walk_rows is the better one: 16.7e6 Zipf entries, N = 128, fp32: 1.255 against 1.208 ms.)
+template <typename T, int E, int L>
+__device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int task, const int32_t *__restrict__ col,
+                                           const T *__restrict__ val, const T *__restrict__ B, T *__restrict__ C, int64_t N,
+                                           float *__restrict__ ws) {
+    typedef typename RowVec<T, E>::type vec_t;
+    constexpr int G = 64 / L;
+    const int4 td = tasks[task];
+    const int e0 = td.z, e1 = td.w;
+    if (e0 >= e1) return;  // fills up a list
+    const int lane = threadIdx.x & 63, g = lane / L, i16 = lane & 15;
+    const int64_t n = (int64_t)blockIdx.y * (L * E) + (lane % L) * E;
+    const int64_t nc = n < N - E ? n : N - E;  // N >= E
+    const char *base = (const char *)B + nc * (int64_t)sizeof(T);
+    const uint32_t row_bytes = (uint32_t)(N * (int64_t)sizeof(T));
+
+    float acc[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) acc[i] = 0.f;
+    // batch b: entries e0 + (b G + g) * 16 .. + 15 of this group; past the end: the last entry's row, times zero
+    auto fetch = [&](int b, int &c, float &v) __attribute__((always_inline)) {
+        const int e = e0 + (b * G + g) * 16 + i16;
+        const int es = e < e1 ? e : e1 - 1;
+        c = col[es];
+        v = widen(val[es]);
+        v = e < e1 ? v : 0.f;
+    };
+#define ASP_BCAST(x, i) __builtin_amdgcn_mov_dpp((int)(x), 0x150 + (i), 0xf, 0xf, true)  // row_newbcast: lane i of each 16
+#define ASP_GATHER(dst, j, i) \
+    dst[j] = *(const vec_t *)(base + (uint64_t)(uint32_t)ASP_BCAST(c, i) * row_bytes)
+#define ASP_ADD(src, j, i)                                                                                  \
+    do {                                                                                                    \
+        const float f_ = __uint_as_float(ASP_BCAST(__float_as_uint(v), i));                                 \
+        _Pragma("unroll") for (int q = 0; q < E; ++q) acc[q] = __builtin_fmaf(f_, widen((T)src[j][q]), acc[q]); \
+    } while (0)
+#define ASP_EIGHT(OP, x, o) \
+    OP(x, 0, o + 0); OP(x, 1, o + 1); OP(x, 2, o + 2); OP(x, 3, o + 3); OP(x, 4, o + 4); OP(x, 5, o + 5); OP(x, 6, o + 6); OP(x, 7, o + 7)
+    const int nb = (e1 - e0 + 16 * G - 1) / (16 * G);
+    int c, cn;
+    float v, vn;
+    vec_t lo[8], hi[8];
+    fetch(0, c, v);
+    ASP_EIGHT(ASP_GATHER, lo, 0);
+    for (int b = 0; b < nb; ++b) {  // eight gathers ahead of the additions; (the last round gathers its own rows again)
+        ASP_EIGHT(ASP_GATHER, hi, 8);
+        fetch(b + 1 < nb ? b + 1 : b, cn, vn);
+        ASP_EIGHT(ASP_ADD, lo, 0);
+        c = cn;
+        ASP_EIGHT(ASP_GATHER, lo, 0);
+        ASP_EIGHT(ASP_ADD, hi, 8);
+        v = vn;
+    }
+#undef ASP_BCAST
+#undef ASP_GATHER
+#undef ASP_ADD
+#undef ASP_EIGHT
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        if (G >= 2) acc[i] += __shfl_xor(acc[i], 32);
+        if (G >= 4) acc[i] += __shfl_xor(acc[i], 16);
+    }
+    if (g == 0 && n < N) put_chunk<T, E>(td, acc, n, nc, N, C, ws);
+}
+
+// One wave per chunk or task, the chunks first (they are the longest).  A wave covers 64 * E = CL * CE columns
+// (CL = 64: walk_rows for the chunks too); grid.y = column tiles.
+template <typename T, int E, int CE, int CL>
+__global__ __launch_bounds__(256) void wcsr_rows_kernel(const int4 *__restrict__ chunks, int n_chunks,
+                                                        const int4 *__restrict__ tasks, int n_tasks,
+                                                        const int32_t *__restrict__ row_ptr,
+                                                        const int32_t *__restrict__ col, const T *__restrict__ val,
+                                                        const T *__restrict__ B, T *__restrict__ C, int64_t N,
+                                                        float *__restrict__ ws) {
+    const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < n_chunks) {
+        if constexpr (CL < 64) walk_chunk<T, CE, CL>(chunks, wave, col, val, B, C, N, ws);
+        else walk_rows<T, E, true>(chunks, wave, row_ptr, col, val, B, C, N, ws);
+    } else if (wave - n_chunks < n_tasks) {
+        walk_rows<T, E, false>(tasks, wave - n_chunks, row_ptr, col, val, B, C, N, ws);
+    }
+}
+
+// Split rows: {row, first scratch row, scratch rows, -}: C[row] = sum of its scratch rows, rounded once.  A workgroup
+// takes COLS columns; thread (j, c) adds the scratch rows j, j + J, ... of column c, and the J sums are added in order:
+// a fixed order, bitwise reproducible.  <16, 64> for long lists (few rows: 64 rows of 3600 scratch rows, N = 64, take
+// 12 us, with <64, 16> 19 us), <64, 4> for short ones (12 000 rows of 5 on average, N = 128: with <16, 64> most of a
+// workgroup would have nothing to add).
+template <typename T, int COLS, int J>
+__global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__restrict__ split,
+                                                                const float *__restrict__ ws, T *__restrict__ C, int64_t N) {
+    __shared__ float part[J][COLS + 1];
+    const int4 s = split[blockIdx.x];
+    const int c = threadIdx.x % COLS, first = threadIdx.x / COLS;
+    const int64_t n = (int64_t)blockIdx.y * COLS + c;
+    float sum = 0.f;
+    if (n < N) {
+        const float *src = ws + (int64_t)s.y * N + n;
+        int j = first;
+        for (; j + J * 7 < s.z; j += J * 8) {
+            float t[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[e] = src[(int64_t)(j + J * e) * N];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sum += t[e];
+        }
+        for (; j < s.z; j += J) sum += src[(int64_t)j * N];
+    }
+    part[first][c] = sum;
+    __syncthreads();
+    if (first == 0 && n < N) {
+        float t = part[0][c];
+#pragma unroll
+        for (int e = 1; e < J; ++e) t += part[e][c];
+        T o;
+        narrow(t, o);
+        C[(int64_t)s.x * N + n] = o;
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------
+template <typename T>
+static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
+    // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
+#define ASP_ROWS(E, CE, CL)                                                                                           \
+    hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                              \
+                       dim3((unsigned)ceil_div(h->n_chunks + h->n_row_tasks, 4), (unsigned)ceil_div(N, 64 * (E))),    \
+                       dim3(256), 0, stream, (const int4 *)h->d_chunks, (int)h->n_chunks, (const int4 *)h->d_row_tasks, \
+                       (int)h->n_row_tasks, h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
+    if (N <= 16) ASP_ROWS(1, 1, 16);
+    else if (N <= 32) ASP_ROWS(1, 2, 16);
+    else if (N <= 64) ASP_ROWS(1, 4, 16);
+    else if (N <= 128) ASP_ROWS(2, sizeof(T) == 2 ? 8 : 2, sizeof(T) == 2 ? 16 : 64);
+    else if (N <= 256 || sizeof(T) == 4) ASP_ROWS(4, 4, 64);
+    else if constexpr (sizeof(T) == 2) ASP_ROWS(8, 8, 64);
+#undef ASP_ROWS
+}
+
+void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
+    if (h->n_chunks + h->n_row_tasks == 0) return;
+    if (h->dtype == ASP_DT_BF16) launch_rows<uint16_t>(h, B, C, N, ws, stream);
+    else launch_rows<float>(h, B, C, N, ws, stream);
+}
+
+void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream) {
+    if (h->n_split_rows == 0) return;
+    const bool many = h->n_chunks > 32 * h->n_split_rows;
+#define ASP_ROWS_SUM(T, COLS, J)                                                                                          \
+    hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>), dim3((unsigned)h->n_split_rows, (unsigned)ceil_div(N, COLS)), \
+                       dim3((COLS) * (J)), 0, stream, (const int4 *)h->d_split_rows, ws, (T *)C, N)
+    if (h->dtype == ASP_DT_BF16) {
+        if (many && N <= 65535 * 16) ASP_ROWS_SUM(uint16_t, 16, 64);
+        else ASP_ROWS_SUM(uint16_t, 64, 4);
+    } else {
+        if (many && N <= 65535 * 16) ASP_ROWS_SUM(float, 16, 64);
+        else ASP_ROWS_SUM(float, 64, 4);
+    }
+#undef ASP_ROWS_SUM
+}
+
+}  // namespace asp

@@ -1,0 +1,68 @@
+"""WCSR products whose windows are walked entry by entry (rows that share few columns), and the tile kernels at widths and
+alignments that do not allow 16-byte rows: edges of the lanes' column ranges, batches of 8 entries, chunks of long rows.
+
+Tolerances as everywhere: fp32 1e-5 * S, bf16 1e-2 * S + 1e-5, S = |A| x |B| from the oracle."""
+import numpy as np
+import pytest
+
+from paper_2604_17834_amd import binding as asp
+from paper_2604_17834_amd import synth
+from test_gpu_parity import check_against_oracle, gpu_spmm
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows_of_lengths(lengths, k, dtype, seed):
+    """One row per length, distinct random columns; U(-1, 1) values."""
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(rng.choice(k, n, replace=False)) for n in lengths]
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    v = rng.uniform(-1, 1, rp[-1]).astype(np.float32)
+    v = synth.f32_to_bf16_bits(v) if dtype == "bf16" else v
+    return synth.Csr(len(lengths), k, rp, np.concatenate(cols).astype(np.int32), v, dtype)
+
+
+# around the batch of 8 entries, empty rows in front, between and behind, rows of 1 .. 5 chunks at task_cols = 32
+LENGTHS = [0, 0, 1, 7, 8, 9, 0, 15, 16, 17, 31, 32, 33, 64, 65, 160, 0, 2, 3, 1, 1, 0, 24, 23] + [1] * 70 + [0] * 70 + [5, 0]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 7, 8, 63, 64, 65, 100, 127, 129, 255, 257, 511, 513])
+def test_rows_walked_entry_by_entry(dtype, N):
+    a = _rows_of_lengths(LENGTHS, 5000, dtype, seed=N)
+    B = synth.dense_normal(a.k, N, dtype, seed=1000 + N)
+    C = gpu_spmm(a, "wcsr", 16, 8, B, task_cols=32, misalign=N % 2 == 1)
+    check_against_oracle(a, B, C)
+    assert not C[np.diff(a.row_ptr) == 0].any()
+
+
+@pytest.mark.parametrize("N", [3, 64, 130, 257])
+def test_chunks_of_long_rows_without_scratch_are_added_with_atomics(N):
+    a = _rows_of_lengths(LENGTHS, 5000, "f32", seed=3)
+    B = synth.dense_normal(a.k, N, "f32", seed=4)
+    check_against_oracle(a, B, gpu_spmm(a, "wcsr", 16, 8, B, task_cols=32, reserve=False))
+
+
+@pytest.mark.parametrize("dtype,b_row", [("f32", 16), ("f32", 64), ("bf16", 16), ("bf16", 32)])
+@pytest.mark.parametrize("N", [64, 9])
+def test_band_and_long_rows_in_one_matrix(dtype, b_row, N):
+    # band windows go tile by tile, the long rows' windows entry by entry; enough tasks that they are dealt to the XCDs
+    a = synth.banded_plus_dense_rows(9000, seed=5, n_dense_rows=24, dense_row_nnz=3000, dtype=dtype)
+    B = synth.dense_normal(a.k, N, dtype, seed=6)
+    h = asp.asp_create_from_csr("wcsr", dtype, b_row, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values, task_cols=64)
+    try:
+        C = gpu_spmm(a, "wcsr", b_row, 8, B, handle=h)
+        assert np.array_equal(C.view(np.uint8), gpu_spmm(a, "wcsr", b_row, 8, B, handle=h).view(np.uint8))
+        check_against_oracle(a, B, C)
+    finally:
+        asp.asp_destroy(h)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("b_row", [16, 32, 64])
+@pytest.mark.parametrize("N,misalign,reserve", [(5, False, True), (9, True, True), (61, False, True), (129, True, True),
+                                                (67, True, False), (259, False, False), (64, True, False)])
+def test_dense_windows_at_any_width_and_alignment(dtype, b_row, N, misalign, reserve):
+    a = synth.random_csr(200, 300, 0.5, seed=N, dtype=dtype)
+    B = synth.dense_normal(a.k, N, dtype, seed=7 + N)
+    check_against_oracle(a, B, gpu_spmm(a, "wcsr", b_row, 8, B, task_cols=128, misalign=misalign, reserve=reserve))
