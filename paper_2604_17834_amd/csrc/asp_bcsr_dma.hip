@@ -42,7 +42,7 @@
 
 namespace asp {
 
-template <int BR, int BN, int WM, int WN, int NS>
+template <int BR, int BN, int WM, int WN, int NS, bool XT = false>
 struct DmaCfg {
     static constexpr int KS = 32;
     static constexpr int NW = WM * WN;
@@ -58,14 +58,16 @@ struct DmaCfg {
     static constexpr int A_R = A_STAGE / 1024, B_R = B_STAGE / 1024;  // 1 KB regions = wave-level loads
     static constexpr int A_LPW = A_R / NW, B_LPW = B_R / NW, LPW = A_LPW + B_LPW;
     static constexpr int CPRW = BN / 8;             // 16-byte chunks per B row
-    // epilogue: a wave stages pieces of 32 rows x RW columns, privately, inside one ring buffer
-    static constexpr int RW = (TN >= 64 && NW * 32 * (64 * 2 + 16) <= STAGE) ? 64 : 32;
+    // epilogue: a wave stages pieces of 32 rows x RW columns of the output matrix, privately, inside one ring buffer
+    // (XT: of Y, whose rows are the tile's columns)
+    static constexpr int EP_ROWS = XT ? TN : TM, EP_COLS = XT ? TM : TN;
+    static constexpr int RW = (EP_COLS >= 64 && NW * 32 * (64 * 2 + 16) <= STAGE) ? 64 : 32;
     static constexpr int JR = RW / 32;              // MFMA tiles per piece
     static constexpr int C_PITCH = RW * 2 + 16;     // bytes
     static constexpr int C_WAVE = 32 * C_PITCH;
     static constexpr int CPR = RW / 8;              // 16-byte units per staged row
     static constexpr int RPI = 64 / CPR;            // rows per wave-level store
-    static constexpr int NSTORE = MT * (TN / RW) * (32 / RPI);  // store instructions per wave and tile
+    static constexpr int NSTORE = (EP_ROWS / 32) * (EP_COLS / RW) * (32 / RPI);  // store instructions per wave and tile
     static constexpr int LDS_BYTES = NS * STAGE;
     static_assert(A_R % NW == 0 && B_R % NW == 0, "regions must split evenly over the waves");
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
@@ -78,18 +80,27 @@ struct DmaCfg {
 
 // rank_info[r] = {block-row, first stored block, number of stored blocks, block column of the first one} of the r-th heaviest block-row
 //
+// XT = true: Y[N x M] = X x A^T with K-contiguous X and Y, as in the kernel for 128x512 tiles (asp_bcsr_wide.hip), for
+// launches that do not give every compute unit such a tile, and for small blocks without a composite form.  In the argument
+// list B is X and C is Y; the tile's columns are tokens.  A slice of X is BN tokens x 64 bytes, laid out token-major in
+// 1 KB regions of 16 tokens with the 16-byte chunks of a token XOR-swizzled by (token / 4) % 4, and read with plain 16-byte
+// reads; the operands keep their order, so a lane ends with 4 adjacent outputs of one token.  Chunks past K are read
+// from 16 zero bytes, so that nothing of the next token meets the zero padding of A.  K % 8 == 0 and M % 8 == 0.
+//
 // DYN = true (a benchmarking variant, ASP_BCSR_SCHEDULE=atomic: the dynamic tile scheduling that the paper's Sections
 // III-E/III-F try on Hopper and reject): the resident workgroups of an XCD pull the tiles of its run from an atomic counter
 // (sched[xcd], zeroed before the launch) instead of taking every stride-th one.  Thread 0 claims, the index travels
 // through LDS under the barrier the tile boundary has anyway; the claim for the tile after the next one is made at each
 // boundary, so its round trip is paid once per tile by wave 0.  Every workgroup leaves when its claim passes the end of
 // the run.  Calls under this switch share the handle's counters and must be ordered on one stream.
-template <int BR, int BN, int WM, int WN, int NS, bool DYN = false>
+static __device__ const uint4 xt_zero_chunk = {0u, 0u, 0u, 0u};
+
+template <int BR, int BN, int WM, int WN, int NS, bool DYN = false, bool XT = false>
 __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) void bcsr_spmm_dma_kernel(
     const int4 *__restrict__ rank_info, const int32_t *__restrict__ block_col_idx,
     const uint16_t *__restrict__ a_packed, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int K,
     int N, int n_brows, int n_tiles, int group_n, XcdRuns runs, int *__restrict__ sched) {
-    using Cfg = DmaCfg<BR, BN, WM, WN, NS>;
+    using Cfg = DmaCfg<BR, BN, WM, WN, NS, XT>;
     constexpr int NW = Cfg::NW, KS = Cfg::KS, MT = Cfg::MT, NTL = Cfg::NTL, LPW = Cfg::LPW;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[Cfg::LDS_BYTES];
 
@@ -135,6 +146,10 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
     for (int j = 0; j < NTL; ++j) {
         const int c = (wn * Cfg::TN + j * 32) / 8 + c_lane;
         b_off[j] = krow_lane * Cfg::B_ROW + ((c ^ sw) * 16) + sub;
+        if (XT) {  // token t, chunk (2 kk + lane / 32) of its 64 bytes: kk flips bit 5
+            const int t = wn * Cfg::TN + j * 32 + (lane & 31);
+            b_off[j] = (t >> 4) * 1024 + (t & 15) * 64 + (((lane >> 5) ^ ((t >> 2) & 3)) * 16);
+        }
     }
     // B source: region jb = i*NW + wave of a slice holds the 16-byte slots [jb*64, jb*64+64); slot s is
     // row s / CPRW, position s % CPRW; the position is the swizzled chunk index.
@@ -145,6 +160,10 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         const int r = s / Cfg::CPRW, cp = s % Cfg::CPRW;
         b_row_in_slice[i] = r;
         b_chunk[i] = cp ^ (Cfg::swz(r) << 2);
+        if (XT) {  // a region is 16 tokens x 64 bytes
+            b_row_in_slice[i] = (i * NW + wave) * 16 + (lane >> 2);
+            b_chunk[i] = (lane & 3) ^ ((lane >> 4) & 3);
+        }
     }
     const uint32_t a_voff = (uint32_t)(wave * 1024 + lane * 16);
     const uint32_t lds0 = lds_offset(lds);
@@ -176,6 +195,13 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         t.n0 = nt * BN;
 #pragma unroll
         for (int i = 0; i < Cfg::B_LPW; ++i) {
+            if (XT) {
+                int tok = b_row_in_slice[i];
+                const int last = N - 1 - t.n0;
+                tok = tok < last ? tok : last;  // tokens past N only feed columns that are never stored
+                voff[i] = (uint32_t)tok * (uint32_t)K * 2 + b_chunk[i] * 16;
+                continue;
+            }
             int col = t.n0 + 8 * b_chunk[i];
             col = col < N ? col : N - 8;  // chunks past N only feed columns that are never stored
             voff[i] = (uint32_t)(((int64_t)b_row_in_slice[i] * N + col) * 2);  // byte offset inside a slice of B
@@ -194,6 +220,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
     uint32_t nxt_voff[Cfg::B_LPW], pf_voff[Cfg::B_LPW];
     int have_next = 0;
     int pf_T = 0, pf_t = 0, pf_blk = 0, pf_s = 0, pf_in_next = 0;
+    int64_t pf_tok = 0;                 // XT: first token of the cursor's tile
     int pf_bcol = 0, pf_bcol_next = 0;  // block column of the cursor's block and of the block after it
     int buf_c = 0, inflight = 0;
     int issued = 0, mark0 = 0, mark1 = 0, mark2 = 0;
@@ -204,6 +231,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         pf_blk = t.blk0;
         pf_s = 0;
         pf_bcol_next = t.bcol0;
+        pf_tok = t.n0;
 #pragma unroll
         for (int i = 0; i < Cfg::B_LPW; ++i) pf_voff[i] = voff[i];
     };
@@ -229,11 +257,18 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
             if (pf_t + Cfg::SPB < pf_T) pf_bcol_next = __builtin_amdgcn_readfirstlane(block_col_idx[pf_blk + 1]);
         }
         const int krow0 = pf_bcol * BR + pf_s * KS;
-        const uint8_t *bbase = (const uint8_t *)(B + (int64_t)krow0 * N);
+        const uint8_t *bbase = (const uint8_t *)(XT ? B + pf_tok * K + krow0 : B + (int64_t)krow0 * N);
         if (krow0 + KS <= K) {
 #pragma unroll
             for (int i = 0; i < Cfg::B_LPW; ++i)
                 dma16_to_lds(bbase, pf_voff[i], stage + Cfg::A_STAGE + (i * NW + wave) * 1024);
+        } else if (XT) {  // the slice crosses K
+#pragma unroll
+            for (int i = 0; i < Cfg::B_LPW; ++i) {
+                const bool in = krow0 + 8 * b_chunk[i] < K;
+                dma16_to_lds(in ? (const void *)(bbase + pf_voff[i]) : (const void *)&xt_zero_chunk,
+                             stage + Cfg::A_STAGE + (i * NW + wave) * 1024);
+            }
         } else {
             // the slice crosses K: rows past K are read from row K-1, they meet the zero padding of A
 #pragma unroll
@@ -289,6 +324,10 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         for (int i = 0; i < MT; ++i) f.a[i] = *(const bf16x8 *)(sa + (kk * (BR / 32) + wm * MT + i) * 1024 + a_off);
 #pragma unroll
         for (int j = 0; j < NTL; ++j) {
+            if (XT) {
+                f.b[j] = *(const bf16x8 *)(sb + (b_off[j] ^ (kk * 32)));
+                continue;
+            }
             const uint8_t *p0 = sb + kk * 16 * Cfg::B_ROW + b_off[j];
             short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3))) *)(p0));
             short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -302,8 +341,9 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int j = 0; j < NTL; ++j)
-                // operands swapped: D[n][m] = sum_k B[k][n] * A[m][k]
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
+                // operands swapped: D[n][m] = sum_k B[k][n] * A[m][k]  (XT: D[m][n])
+                acc[i][j] = XT ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0)
+                               : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
     };
     static_assert(Cfg::KK == 2, "the step below is written for two k steps per slice");
     const bool k_aligned = K % BR == 0;  // then no slice reaches past row K of B
@@ -343,7 +383,8 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
                     pf_bcol = pf_bcol_next;
                     if (pf_t + Cfg::SPB < pf_T) pf_bcol_next = __builtin_amdgcn_readfirstlane(block_col_idx[pf_blk + 1]);
                 }
-                const uint8_t *bbase = (const uint8_t *)(B + (int64_t)(pf_bcol * BR + pf_s * KS) * N);
+                const int krow0 = pf_bcol * BR + pf_s * KS;
+                const uint8_t *bbase = (const uint8_t *)(XT ? B + pf_tok * K + krow0 : B + (int64_t)krow0 * N);
 #pragma unroll
                 for (int i = 0; i < Cfg::B_LPW; ++i)
                     dma16_to_lds(bbase, pf_voff[i], stage + Cfg::A_STAGE + (i * NW + wave) * 1024);
@@ -389,37 +430,40 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         const bool interior = tc.br * BR + BR <= M && tc.n0 + BN <= N;
         int sbuf = buf_c == 0 ? NS - 1 : buf_c - 1;
         uint8_t *sc = lds + sbuf * Cfg::STAGE + wave * Cfg::C_WAVE;
-        const int grow0 = tc.br * BR + wm * Cfg::TM + lane / Cfg::CPR;
-        const int gcol0 = tc.n0 + wn * Cfg::TN + (lane % Cfg::CPR) * 8;
+        // first row and column of C (XT: of Y, rows are tokens) that this lane stores
+        const int out_ld = XT ? M : N, out_rows = XT ? N : M, out_cols = XT ? M : N;
+        const int row0 = tc.br * BR + wm * Cfg::TM, col0 = tc.n0 + wn * Cfg::TN;
+        const int grow0 = (XT ? col0 : row0) + lane / Cfg::CPR;
+        const int gcol0 = (XT ? row0 : col0) + (lane % Cfg::CPR) * 8;
         const uint8_t *scl = sc + (lane / Cfg::CPR) * Cfg::C_PITCH + (lane % Cfg::CPR) * 16;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < Cfg::EP_ROWS / 32; ++i)
 #pragma unroll
-            for (int jh = 0; jh < NTL / Cfg::JR; ++jh) {
+            for (int jh = 0; jh < Cfg::EP_COLS / Cfg::RW; ++jh) {
                 // fp32 -> bf16 (round to nearest even); lane holds row (lane & 31), 4 adjacent columns per q
 #pragma unroll
                 for (int jj = 0; jj < Cfg::JR; ++jj)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const f32x16 &a = acc[i][jh * Cfg::JR + jj];
+                        const f32x16 &a = XT ? acc[jh * Cfg::JR + jj][i] : acc[i][jh * Cfg::JR + jj];
                         f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
                         bf16x4 hv = __builtin_convertvector(v, bf16x4);
                         *(bf16x4 *)(sc + (lane & 31) * Cfg::C_PITCH + (jj * 32 + 8 * q + 4 * (lane >> 5)) * 2) = hv;
                     }
                 // LDS is in order within a wave: the reads below see the writes above
-                uint16_t *cdst = C + (int64_t)(grow0 + i * 32) * N + gcol0 + jh * Cfg::RW;
+                uint16_t *cdst = C + (int64_t)(grow0 + i * 32) * out_ld + gcol0 + jh * Cfg::RW;
                 if (interior) {
 #pragma unroll
                     for (int it = 0; it < 32 / Cfg::RPI; ++it) {
                         uint4 v = *(const uint4 *)(scl + it * Cfg::RPI * Cfg::C_PITCH);
-                        store_c16(cdst + (int64_t)it * Cfg::RPI * N, v);
+                        store_c16(cdst + (int64_t)it * Cfg::RPI * out_ld, v);
                     }
                 } else {
 #pragma unroll
                     for (int it = 0; it < 32 / Cfg::RPI; ++it) {
                         uint4 v = *(const uint4 *)(scl + it * Cfg::RPI * Cfg::C_PITCH);
-                        if (grow0 + i * 32 + it * Cfg::RPI < M && gcol0 + jh * Cfg::RW < N)
-                            store_c16(cdst + (int64_t)it * Cfg::RPI * N, v);
+                        if (grow0 + i * 32 + it * Cfg::RPI < out_rows && gcol0 + jh * Cfg::RW < out_cols)
+                            store_c16(cdst + (int64_t)it * Cfg::RPI * out_ld, v);
                     }
                 }
             }
@@ -495,13 +539,15 @@ __global__ void bcsr_zero_sched_kernel(int *__restrict__ sched) {
     if (threadIdx.x < 8) sched[threadIdx.x] = 0;
 }
 
-template <int BR, int BN, int WM, int WN, int NS>
+template <int BR, int BN, int WM, int WN, int NS, bool XT>
 static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n, env_wgs = switches().bcsr_wgs_per_cu;  // benchmarking switches
-    int group_n = env_group > 0 ? env_group : 4;
+    // N-tiles walked together.  K-contiguous with 32-row tiles: 2, so that their columns of X have a chance in the 4 MB of
+    // L2 (K = 18944: 4096 tokens in 64- / 128- / 256-wide tiles 290 / 341 / 366 us with 4, 228 / 278 / 285 with 2)
+    int group_n = env_group > 0 ? env_group : XT && BR == 32 ? 2 : 4;
     if (group_n > p.n_tiles) group_n = p.n_tiles;
     // resident workgroups per CU: as many as LDS allows (the kernel is built for 2 waves per SIMD)
-    const int fit = (int)(163840 / DmaCfg<BR, BN, WM, WN, NS>::LDS_BYTES);
+    const int fit = (int)(163840 / DmaCfg<BR, BN, WM, WN, NS, XT>::LDS_BYTES);
     const int per_cu = std::max(1, std::min(fit, 8 / (WM * WN)));
     int64_t workers = (int64_t)h->n_cus * (env_wgs > 0 ? env_wgs : per_cu);
     if (workers > p.workgroups) workers = p.workgroups;
@@ -511,7 +557,7 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
     // benchmarking switch: tiles pulled from per-XCD atomic counters (built for the 128 x 256 tiles of the ladder;
     // everything else keeps the static schedule)
     const bool env_atomic = switches().bcsr_atomic;
-    if constexpr (BR == 128 && BN == 256) {
+    if constexpr (BR == 128 && BN == 256 && !XT) {
         if (env_atomic && h->d_sched) {
             hipLaunchKernelGGL(bcsr_zero_sched_kernel, dim3(1), dim3(64), 0, stream, h->d_sched);
             hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS, true>), grid, block, 0, stream,
@@ -521,26 +567,35 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
             return;
         }
     }
-    hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
+    hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS, false, XT>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
                        h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m,
                        (int)h->k, (int)N, (int)h->n_brows, p.n_tiles, group_n, runs, (int *)nullptr);
 }
 
-// needs N % 8 == 0, 8 <= N < 2^25 and 16-byte aligned B and C (the caller checked)
-bool bcsr_dma_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
+template <bool XT>
+static bool launch_dma_tile(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     switch (h->b_row * 1000 + p.bn) {
-        case 128256: launch_dma<128, 256, 2, 2, 3>(h, B, C, N, p, stream); return true;
-        case 128128: launch_dma<128, 128, 2, 2, 3>(h, B, C, N, p, stream); return true;
-        case 128064: launch_dma<128, 64, 2, 2, 3>(h, B, C, N, p, stream); return true;
-        case 64256: launch_dma<64, 256, 1, 4, 3>(h, B, C, N, p, stream); return true;
-        case 64128: launch_dma<64, 128, 2, 2, 3>(h, B, C, N, p, stream); return true;
-        case 64064: launch_dma<64, 64, 1, 2, 3>(h, B, C, N, p, stream); return true;
-        case 32256: launch_dma<32, 256, 1, 2, 3>(h, B, C, N, p, stream); return true;
-        case 32128: launch_dma<32, 128, 1, 2, 3>(h, B, C, N, p, stream); return true;
-        case 32064: launch_dma<32, 64, 1, 2, 3>(h, B, C, N, p, stream); return true;
+        case 128256: launch_dma<128, 256, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 128128: launch_dma<128, 128, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 128064: launch_dma<128, 64, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 64256: launch_dma<64, 256, 1, 4, 3, XT>(h, B, C, N, p, stream); return true;
+        case 64128: launch_dma<64, 128, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 64064: launch_dma<64, 64, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 32256: launch_dma<32, 256, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 32128: launch_dma<32, 128, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 32064: launch_dma<32, 64, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
     }
     return false;
 }
 
+// needs N % 8 == 0, 8 <= N < 2^25 and 16-byte aligned B and C (the caller checked)
+bool bcsr_dma_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
+    return launch_dma_tile<false>(h, B, C, N, p, stream);
+}
+
+// needs K % 8 == 0, M % 8 == 0, K < 2^22, N < 2^25 and 16-byte aligned X and Y (the caller checked)
+bool bcsr_dma_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, const BcsrPlan &p, hipStream_t stream) {
+    return launch_dma_tile<true>(h, X, Y, N, p, stream);
+}
 
 }  // namespace asp

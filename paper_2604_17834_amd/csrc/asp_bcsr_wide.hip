@@ -711,85 +711,9 @@ bool bcsr_wide_launch(const asp_handle *h, const void *B, void *C, int64_t N, co
     return true;
 }
 
-// ---- Y = X x A^T with K-contiguous X and Y (Section IV-D's layout) -------------------------------------
-
-// Any block size, any alignment, any N: one thread per (token, quarter of the block-row's outputs), fp32
-// multiply-adds over the stored blocks in order.  The safety net under the MFMA path below; two orders of
-// magnitude slower.  grid = (block-rows, ceil(N / 64)), 256 threads.
-template <int BR>
-__global__ __launch_bounds__(256) void bcsr_xt_generic_kernel(const int32_t *__restrict__ block_row_ptr,
-                                                              const int32_t *__restrict__ block_col_idx,
-                                                              const uint16_t *__restrict__ a_packed,
-                                                              const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
-                                                              int M, int K, int64_t N) {
-    constexpr int RPT = BR / 4;  // outputs per thread
-    const int br = blockIdx.x, rg = threadIdx.x >> 6;
-    const int64_t n = (int64_t)blockIdx.y * 64 + (threadIdx.x & 63);
-    if (n >= N) return;
-    float acc[RPT];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) acc[r] = 0.f;
-    const uint16_t *x = X + n * K;
-    for (int p = block_row_ptr[br]; p < block_row_ptr[br + 1]; ++p) {
-        const int k0 = block_col_idx[p] * BR;
-        const uint16_t *blk = a_packed + (int64_t)p * BR * BR;
-        for (int k = 0; k < BR && k0 + k < K; ++k) {
-            const float xv = __uint_as_float((uint32_t)x[k0 + k] << 16);
-#pragma unroll
-            for (int r = 0; r < RPT; ++r) {
-                const int row = rg * RPT + r;
-                // fragment order: [16-wide k slice][group of 32 rows][lane = row % 32 + 32 * (k % 16 / 8)][k % 8]
-                const int idx = (((k >> 4) * (BR / 32) + (row >> 5)) * 64 + (row & 31) + 32 * ((k & 15) >> 3)) * 8 + (k & 7);
-                acc[r] = fmaf(__uint_as_float((uint32_t)blk[idx] << 16), xv, acc[r]);
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int m = br * BR + rg * RPT + r;
-        if (m < M) {
-            // round to nearest even (inputs are finite sums; NaN payloads are not preserved)
-            uint32_t u = __float_as_uint(acc[r]);
-            u += 0x7FFFu + ((u >> 16) & 1u);
-            Y[n * M + m] = (uint16_t)(u >> 16);
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void bcsr_fill_zero_kernel(uint16_t *__restrict__ p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
-}
-
-asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream) {
-    const bool wide_ok = bcsr_wide_capable(h);
-    const int64_t n_rows = !h->has_comp ? h->hb.n_nonempty : h->hc.n_nonempty;
-    if (n_rows == 0) {
-        hipLaunchKernelGGL(bcsr_fill_zero_kernel, dim3(1024), dim3(256), 0, stream, (uint16_t *)Y, N * h->m);
-    } else {
-        const bool aligned = (((uintptr_t)X | (uintptr_t)Y) & 15) == 0;
-        const int64_t n_tiles = ceil_div(N, 512);
-        const bool force_generic = switches().xt_generic;  // benchmarking switch: forces the fallback
-        // (no lower bound on the number of tiles: with fewer 128 x 512 tiles than compute units part of the chip
-        // idles, which still is two orders of magnitude faster than the generic kernel -- the down projection of
-        // the case study has 28 block-rows and would need 4600 tokens to give every compute unit a tile)
-        if (!force_generic && wide_ok && aligned && h->k % 8 == 0 && h->m % 8 == 0 && N < (1ll << 25) &&
-            h->k < (1ll << 22)) {
-            launch_wide<true>(h, X, Y, N, (int)n_tiles, stream);
-        } else {
-            dim3 grid((unsigned)h->n_brows, (unsigned)ceil_div(N, 64)), block(256);
-            if (grid.y > 65535) return fail(ASP_ERR_UNSUPPORTED, "N too large for the generic K-contiguous path");
-#define ASP_XT_GENERIC(BR)                                                                                          \
-    hipLaunchKernelGGL(bcsr_xt_generic_kernel<BR>, grid, block, 0, stream, h->d_row_ptr, h->d_col_idx,              \
-                       (const uint16_t *)h->d_values, (const uint16_t *)X, (uint16_t *)Y, (int)h->m, (int)h->k, N)
-            if (h->b_row == 128) ASP_XT_GENERIC(128);
-            else if (h->b_row == 64) ASP_XT_GENERIC(64);
-            else ASP_XT_GENERIC(32);
-#undef ASP_XT_GENERIC
-        }
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(ASP_ERR_HIP, std::string("BCSR K-contiguous kernel launch: ") + hipGetErrorString(e));
-    return ASP_OK;
+// Y = X x A^T; needs bcsr_wide_capable, K % 8 == 0, M % 8 == 0, K < 2^22, N < 2^25, 16-byte aligned X and Y and a stored block
+void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream) {
+    launch_wide<true>(h, X, Y, N, (int)ceil_div(N, 512), stream);
 }
 
 }  // namespace asp

@@ -1,0 +1,325 @@
+// Y = X x A^T with K-contiguous activations (paper, Section IV-D's layout) for few tokens, and for any token count where
+// the operands do not allow the 16-byte paths of the tile kernels: a decoded batch through a pruned projection.
+//
+// What bounds it: with a few tokens the product is one read of A (13.6 MB for the 18944 x 3584 projection at 90 %), and
+// what costs time is not the bytes but that they be requested early and by the whole chip.  A 128 x 512 tile per
+// workgroup, most of it padding, left 28 of 256 compute units working on the 28 block-rows of the down projection.
+// So here the unit is a strip of 32 to 128 outputs x 32 or 64 tokens, and the W waves of a workgroup split the strip's K
+// loop, every wave a contiguous part of the stored blocks.  A's fragment order and the K-contiguous X are what
+// v_mfma_f32_32x32x16_bf16 wants in registers, so both operands go straight from memory to registers, 32 or 64 k at a
+// time, one such unit ahead -- no LDS stage, no barrier in the loop.  The waves' partial tiles meet in LDS once and are
+// added in wave order (bitwise reproducible), rounded once, and stored.
+// us a call at 16 tokens, before (128 x 512 tiles) -> now: gate 24.7 -> 6.5, down 84.5 -> 7.2, down in 64 x 64 / 32 x 32
+// blocks 123 -> 6.4 / 196 -> 6.5 (6.4 is what launching a call costs); down at 256 tokens 87.6 -> 18.5.
+// With more tokens each strip's reads (A once per token tile, X once per strip) run into the L1s' miss rate, and the ring
+// kernel's larger tiles take over (bcsr_spmm_xt_launch).
+//
+// Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; the lanes of a unit that crosses K
+// take their elements one by one, zeros past the end.
+#include "asp_bcsr_pipe.h"
+
+namespace asp {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+
+}  // namespace
+
+// grid = units_m strips of 32 MT rows x token tiles of 32 NT; row_ptr / col_idx / a_packed: the stored blocks,
+// fragment-ordered; UKT: k per unit
+template <int BR, int MT, int NT, int W, int UKT, bool VEC>
+__global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int32_t *__restrict__ row_ptr,
+                                                               const int32_t *__restrict__ col_idx,
+                                                               const uint16_t *__restrict__ a_packed,
+                                                               const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
+                                                               int M, int K, int64_t N, int units_m) {
+    constexpr int STRIPS = BR / (32 * MT);
+    constexpr int UK = BR < UKT ? BR : UKT, KK = UK / 16, UPB = BR / UK;  // k of a unit, MFMA steps, units per block
+    constexpr int PITCH = 32 * MT + 4;                                          // floats per token of a partial tile
+    __shared__ __attribute__((aligned(16))) float part[W][NT * 32][PITCH];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // every XCD (workgroups go to them round-robin) takes a run of strips with all their token tiles: A stays in its L2
+    const int units_n = gridDim.x / units_m, xcd = blockIdx.x & 7, q = gridDim.x >> 3, r = gridDim.x & 7;
+    const int id = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
+    const int un = id % units_n, um = id / units_n;
+    const int br = um / STRIPS, strip = um % STRIPS;
+    const int64_t n0 = (int64_t)un * (32 * NT);
+    const int blk0 = row_ptr[br], n_units = (row_ptr[br + 1] - blk0) * UPB;
+    const int u0 = (int)((int64_t)n_units * wave / W), u1 = (int)((int64_t)n_units * (wave + 1) / W);
+
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    if (u0 < u1) {
+        const int kl = 8 * (lane >> 5);  // this lane's 8 k inside an MFMA step
+        const uint16_t *x[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int64_t t = n0 + j * 32 + (lane & 31);
+            x[j] = X + (t < N ? t : N - 1) * K;  // tokens past N feed columns that are never stored
+        }
+        const uint16_t *a_lane = a_packed + (int64_t)blk0 * (BR * BR) + strip * (MT * 512) + lane * 8;
+        // lane i holds the block column of the wave's i-th block, 64 at a time
+        int col_base = u0 / UPB, cols;
+        auto load_cols = [&]() __attribute__((always_inline)) {
+            const int last = n_units / UPB - 1, p = col_base + lane;
+            cols = col_idx[blk0 + (p < last ? p : last)];
+        };
+        load_cols();
+        struct Unit {
+            u32x4 a[MT][KK], x[NT][KK];
+        };
+        auto load = [&](int u, Unit &f) __attribute__((always_inline)) {
+            const int p = u / UPB, s = u % UPB;
+            if (p - col_base >= 64) {
+                col_base = p;
+                load_cols();
+            }
+            const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));
+#pragma unroll
+            for (int i = 0; i < KK; ++i)
+#pragma unroll
+                for (int g = 0; g < MT; ++g) f.a[g][i] = a[i * (BR * 2) + g * 64];
+            const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * UK;
+            if (k0 + UK <= K) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int i = 0; i < KK; ++i) {
+                        const uint16_t *src = x[j] + k0 + i * 16 + kl;
+                        f.x[j][i] = VEC ? *(const u32x4 *)src : *(const u32x4_a2 *)src;
+                    }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int i = 0; i < KK; ++i) {
+                        const int k = k0 + i * 16 + kl;
+                        u32x4 v = {0u, 0u, 0u, 0u};
+                        if (VEC) {
+                            if (k < K) v = *(const u32x4 *)(x[j] + k);  // K % 8 == 0
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                if (k + e < K) v[e >> 1] |= (uint32_t)x[j][k + e] << (16 * (e & 1));
+                        }
+                        f.x[j][i] = v;
+                    }
+            }
+        };
+        auto multiply = [&](const Unit &f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < KK; ++i)
+#pragma unroll
+                for (int g = 0; g < MT; ++g)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, f.a[g][i]), __builtin_bit_cast(bf16x8, f.x[j][i]), acc[g][j], 0, 0, 0);
+        };
+        Unit f0, f1;
+        load(u0, f0);
+        int u = u0;
+        for (; u + 2 < u1; u += 2) {
+            load(u + 1, f1);
+            multiply(f0);
+            load(u + 2, f0);
+            multiply(f1);
+        }
+        if (u + 1 < u1) {
+            load(u + 1, f1);
+            multiply(f0);
+            multiply(f1);
+        } else {
+            multiply(f0);
+        }
+    }
+
+    // D of the MFMA: lane l holds token l % 32, rows 8 q + 4 (l / 32) + 0..3
+#pragma unroll
+    for (int g = 0; g < MT; ++g)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = {acc[g][j][4 * q], acc[g][j][4 * q + 1], acc[g][j][4 * q + 2], acc[g][j][4 * q + 3]};
+                *(f32x4 *)&part[wave][j * 32 + (lane & 31)][g * 32 + 8 * q + 4 * (lane >> 5)] = v;
+            }
+    __syncthreads();
+    const int m0 = br * BR + strip * (32 * MT);
+    for (int i = tid; i < NT * 32 * 16 * MT; i += W * 64) {  // two adjacent outputs of a token
+        const int t = i / (16 * MT), r = (i % (16 * MT)) * 2;
+        float s0 = part[0][t][r], s1 = part[0][t][r + 1];
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            s0 += part[w][t][r];
+            s1 += part[w][t][r + 1];
+        }
+        const uint32_t lo = __builtin_bit_cast(uint16_t, (__bf16)s0), hi = __builtin_bit_cast(uint16_t, (__bf16)s1);
+        if (n0 + t < N) {
+            uint16_t *dst = Y + (n0 + t) * M + m0 + r;
+            if (VEC) {
+                if (m0 + r < M) *(uint32_t *)dst = lo | (hi << 16);  // M % 8 == 0
+            } else {
+                if (m0 + r < M) dst[0] = (uint16_t)lo;
+                if (m0 + r + 1 < M) dst[1] = (uint16_t)hi;
+            }
+        }
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------
+template <int BR, int MT, int NT, int W, int UK>
+static void launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+    const int units_m = (int)h->n_brows * (BR / 32 / MT);
+    dim3 grid((unsigned)(units_m * ceil_div(N, 32 * NT))), block(W * 64);  // < M x N / 2^9 <= 2^31
+#define ASP_STRIP(VEC)                                                                                             \
+    hipLaunchKernelGGL((bcsr_xt_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, h->d_row_ptr,       \
+                       h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)X, (uint16_t *)Y, (int)h->m, \
+                       (int)h->k, N, units_m)
+    if (vec) ASP_STRIP(true);
+    else ASP_STRIP(false);
+#undef ASP_STRIP
+}
+
+// Shape of the wave tiles: the largest that still gives the chip enough of them, since a larger one reads fewer bytes
+// per MFMA.  18944 x 3584 (gate) and 3584 x 18944 (down), 90 % sparse, us a call, tiles of 32 x 32 / 64 x 32 / 64 x 64 /
+// 128 x 64: gate at 64 tokens 8.3 / 7.7 / 8.6 / 10.3, at 256 22 / 19 / 18 / 20; down at 64 tokens 9.3 / 10.9 / 17 / 21,
+// at 256 22 / 18 / 19 / 23, at 768 52 / 39 / 43 / 33.  128 x 64 needs block-rows long enough that every wave of the
+// workgroup gets blocks: 512 tokens 31 / 24 us (64 x 64 / 128 x 64) with 15 blocks a row, 29 / 34 us with 3.
+template <int BR>
+static void launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64);
+    if constexpr (BR == 128) {
+        if (h->n_units >= 8 * h->n_brows && h->n_brows * n64 >= cus * 3 / 4)
+            return launch_strip<BR, 4, 2, 4, 32>(h, X, Y, N, vec, stream);
+    }
+    if constexpr (BR >= 64) {
+        const int64_t strips = h->n_brows * (BR / 64);
+        if (strips * n64 >= 3 * cus) return launch_strip<BR, 2, 2, 4, 32>(h, X, Y, N, vec, stream);
+        if (strips * n32 >= cus / 2) {
+            if (strips * n32 >= cus * 5 / 4) return launch_strip<BR, 2, 1, 4, 64>(h, X, Y, N, vec, stream);
+            return launch_strip<BR, 2, 1, 8, 64>(h, X, Y, N, vec, stream);
+        }
+    }
+    if (h->n_brows * (BR / 32) * n32 > 2 * cus) return launch_strip<BR, 1, 1, 4, 64>(h, X, Y, N, vec, stream);
+    launch_strip<BR, 1, 1, 8, 64>(h, X, Y, N, vec, stream);
+}
+
+// any K, M, N <= ASP_MAX_N and alignment; vec: 16-byte aligned X and Y, K % 8 == 0, M % 8 == 0
+static void launch_any_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+    if (h->b_row == 128) launch_strips<128>(h, X, Y, N, vec, stream);
+    else if (h->b_row == 64) launch_strips<64>(h, X, Y, N, vec, stream);
+    else launch_strips<32>(h, X, Y, N, vec, stream);
+}
+
+// Kernel without matrix cores (a benchmarking switch, for the comparison): one thread per (token, quarter of the
+// block-row's outputs), fp32 multiply-adds over the stored blocks in order.  grid = (block-rows, ceil(N / 64)), 256 threads.
+template <int BR>
+__global__ __launch_bounds__(256) void bcsr_xt_generic_kernel(const int32_t *__restrict__ block_row_ptr,
+                                                              const int32_t *__restrict__ block_col_idx,
+                                                              const uint16_t *__restrict__ a_packed,
+                                                              const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
+                                                              int M, int K, int64_t N) {
+    constexpr int RPT = BR / 4;  // outputs per thread
+    const int br = blockIdx.x, rg = threadIdx.x >> 6;
+    const int64_t n = (int64_t)blockIdx.y * 64 + (threadIdx.x & 63);
+    if (n >= N) return;
+    float acc[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) acc[r] = 0.f;
+    const uint16_t *x = X + n * K;
+    for (int p = block_row_ptr[br]; p < block_row_ptr[br + 1]; ++p) {
+        const int k0 = block_col_idx[p] * BR;
+        const uint16_t *blk = a_packed + (int64_t)p * BR * BR;
+        for (int k = 0; k < BR && k0 + k < K; ++k) {
+            const float xv = __uint_as_float((uint32_t)x[k0 + k] << 16);
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                const int row = rg * RPT + r;
+                // fragment order: [16-wide k slice][group of 32 rows][lane = row % 32 + 32 * (k % 16 / 8)][k % 8]
+                const int idx = (((k >> 4) * (BR / 32) + (row >> 5)) * 64 + (row & 31) + 32 * ((k & 15) >> 3)) * 8 + (k & 7);
+                acc[r] = fmaf(__uint_as_float((uint32_t)blk[idx] << 16), xv, acc[r]);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const int m = br * BR + rg * RPT + r;
+        if (m < M) {
+            // round to nearest even (inputs are finite sums; NaN payloads are not preserved)
+            uint32_t u = __float_as_uint(acc[r]);
+            u += 0x7FFFu + ((u >> 16) & 1u);
+            Y[n * M + m] = (uint16_t)(u >> 16);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void bcsr_fill_zero_kernel(uint16_t *__restrict__ p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
+}
+
+// Which kernel: the one with the shortest estimate, in us on 256 compute units.  A ring kernel's launch takes as long as
+// its longest block-row at the pace of a lone tile plus all its work at the pace of the full chip; the strip kernel,
+// which splits the K loop, takes about 4 us plus its work.  Costs per K slice of 32 (fitted to 18944 x 3584, 3584 x 18944
+// and 4096 x 4096 at 90 %, 1 to 8192 tokens, 4 % from the best choice on average, 1.2 times at worst):
+struct XtCost {
+    double slice_alone[3], slice[3];  // tiles 64, 128, 256 tokens wide
+    double strip;                     // per stored element and token
+};
+static XtCost xt_cost(int b) {
+    if (b == 128) return XtCost{{0.40, 0.53, 0.75}, {0.25, 0.30, 0.44}, 6.5e-9};
+    if (b == 64) return XtCost{{0.44, 0.50, 0.61}, {0.14, 0.27, 0.41}, 6.5e-9};
+    return XtCost{{0.38, 0.51, 0.70}, {0.13, 0.17, 0.37}, 12e-9};
+}
+
+asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream) {
+    const double cus = h->n_cus > 0 ? h->n_cus : 256;
+    if (h->n_units == 0) {
+        hipLaunchKernelGGL(bcsr_fill_zero_kernel, dim3(1024), dim3(256), 0, stream, (uint16_t *)Y, N * h->m);
+    } else if (switches().xt_generic) {
+        dim3 grid((unsigned)h->n_brows, (unsigned)ceil_div(N, 64)), block(256);
+#define ASP_XT_GENERIC(BR)                                                                                          \
+    hipLaunchKernelGGL(bcsr_xt_generic_kernel<BR>, grid, block, 0, stream, h->d_row_ptr, h->d_col_idx,              \
+                       (const uint16_t *)h->d_values, (const uint16_t *)X, (uint16_t *)Y, (int)h->m, (int)h->k, N)
+        if (h->b_row == 128) ASP_XT_GENERIC(128);
+        else if (h->b_row == 64) ASP_XT_GENERIC(64);
+        else ASP_XT_GENERIC(32);
+#undef ASP_XT_GENERIC
+    } else {
+        const bool vec = (((uintptr_t)X | (uintptr_t)Y) & 15) == 0 && h->k % 8 == 0 && h->m % 8 == 0;
+        const bool tiles_ok = vec && N < (1ll << 25) && h->k < (1ll << 22);
+        // the kernel for 128 x 512 tiles, once there are 1.5 of them per compute unit (at 0.75 / 1 / 1.75 per unit: down
+        // 95 / 89 / 127 us, the ring kernel 76 / 82 / 126)
+        const int64_t wide_rows = !bcsr_wide_capable(h) ? 0 : h->has_comp ? h->hc.n_nonempty : h->hb.n_nonempty;
+        if (tiles_ok && 2 * wide_rows * ceil_div(N, 512) >= 3 * (int64_t)cus) {
+            bcsr_wide_xt_launch(h, X, Y, N, stream);
+        } else {
+            const XtCost c = xt_cost(h->b_row);
+            const double slices = (double)h->n_units * (h->b_row / 32), longest = (double)h->hb.max_blocks * (h->b_row / 32);
+            double best = 4.0 + c.strip * (double)h->n_units * h->b_row * h->b_row * (double)N * 256 / cus;
+            int bn = 0;
+            for (int i = 0; i < 3 && tiles_ok; ++i) {
+                const double t = c.slice_alone[i] * longest + c.slice[i] * slices * (double)ceil_div(N, 64 << i) / cus;
+                if (t < best) best = t, bn = 64 << i;
+            }
+            BcsrPlan p = {bn, bn ? (int32_t)ceil_div(N, bn) : 0, 1, 0};
+            p.workgroups = h->n_brows * p.n_tiles;
+            if (bn == 0 || p.workgroups * 8 >= (1ll << 31)) launch_any_strips(h, X, Y, N, vec, stream);
+            else bcsr_dma_xt_launch(h, X, Y, N, p, stream);
+        }
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(ASP_ERR_HIP, std::string("BCSR K-contiguous kernel launch: ") + hipGetErrorString(e));
+    return ASP_OK;
+}
+
+}  // namespace asp

@@ -90,6 +90,7 @@ struct HostBcsr {
     std::vector<int32_t> rank_info;            // [n_brows][4]
     std::vector<int64_t> sorted_weight_prefix; // [n_brows + 1]
     int64_t n_nonempty = 0;                    // block-rows with at least one stored block (they come first)
+    int64_t max_blocks = 0;                    // stored blocks of the longest block-row
     std::vector<int32_t> slice_rows;           // composite form only: [blocks][4] first row of B of each K slice
     std::vector<int32_t> piece_rows;           // composite form only: [super-rows][4] first row of C of each 32-row piece, -1 = none
 };
@@ -190,6 +191,8 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned);
 // the 128x512-tile kernel can take this handle: 128x128 blocks with K % 128 == 0, or a composite form
 inline bool bcsr_wide_capable(const asp_handle *h) { return h->has_comp || (h->b_row == 128 && h->k % 128 == 0); }
 bool bcsr_dma_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
+bool bcsr_dma_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, const BcsrPlan &p, hipStream_t stream);
+void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
 bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 bool bcsr_wide_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
