@@ -72,8 +72,7 @@ struct DmaCfg {
     static_assert(A_R % NW == 0 && B_R % NW == 0, "regions must split evenly over the waves");
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
     static_assert(NW * C_WAVE <= STAGE, "epilogue staging must fit into one ring buffer");
-    static_assert(NS == 3, "the wait table below is written for a ring of three");
-    static_assert(NSTORE + 2 * LPW < 64, "vmcnt is a 6-bit counter");
+    static_assert(NS >= 3 && LDS_BYTES <= 163840, "ring");
     // swizzle of a row's 64-byte units: rows k..k+3 of a transposing read must not share banks
     __device__ static __forceinline__ int swz(int r) { return BN >= 128 ? (r & 3) : ((r >> 1) & 1); }
 };
@@ -93,6 +92,19 @@ struct DmaCfg {
 // through LDS under the barrier the tile boundary has anyway; the claim for the tile after the next one is made at each
 // boundary, so its round trip is paid once per tile by wave 0.  Every workgroup leaves when its claim passes the end of
 // the run.  Calls under this switch share the handle's counters and must be ordered on one stream.
+// waits until at most j * LPW + EXTRA of the wave's vector-memory operations are outstanding (j <= J, wave-uniform;
+// the counter has 6 bits), and for its LDS accesses and scalar loads
+template <int LPW, int EXTRA, int J>
+__device__ __forceinline__ void wait_slices(int j) {
+    constexpr int n = J * LPW + EXTRA;
+    if constexpr (J <= 0) {
+        wait_vmcnt_and_lds<(n < 63 ? n : 63)>();
+    } else {
+        if (j >= J) wait_vmcnt_and_lds<(n < 63 ? n : 63)>();
+        else wait_slices<LPW, EXTRA, J - 1>(j);
+    }
+}
+
 static __device__ const uint4 xt_zero_chunk = {0u, 0u, 0u, 0u};
 
 template <int BR, int BN, int WM, int WN, int NS, bool DYN = false, bool XT = false>
@@ -213,9 +225,9 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
     // the next slice to request; it carries its own copy of what it needs (pf_*), sits in the current tile
     // or, once that is fully requested, in the next one (pf_in_next), never further.
     // Buffers buf_c, buf_c+1, .. (mod NS) hold the `inflight` slices requested but not yet multiplied.
-    // issued counts the vector-memory operations of this wave; mark[b] is its value right after the
-    // loads into buffer b were issued, so issued - mark[b] operations may remain outstanding when the
-    // content of b is needed (the counter retires in order).
+    // The counter of outstanding vector-memory operations retires in order: when the content of buf_c is needed, the
+    // loads of the inflight - 1 slices behind it may be outstanding, and so may the NSTORE stores of the latest tile
+    // while slices requested before them are still to be multiplied (`before_stores` of them).
     Tile cur_t, nxt_t;
     uint32_t nxt_voff[Cfg::B_LPW], pf_voff[Cfg::B_LPW];
     int have_next = 0;
@@ -223,8 +235,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
     int64_t pf_tok = 0;                 // XT: first token of the cursor's tile
     int pf_bcol = 0, pf_bcol_next = 0;  // block column of the cursor's block and of the block after it
     int buf_c = 0, inflight = 0;
-    int issued = 0, mark0 = 0, mark1 = 0, mark2 = 0;
-    auto mark_of = [&](int b) { return b == 0 ? mark0 : (b == 1 ? mark1 : mark2); };
+    int before_stores = 0;
     auto cursor_enter = [&](const Tile &t, const uint32_t (&voff)[Cfg::B_LPW]) {
         pf_T = t.T;
         pf_t = 0;
@@ -294,24 +305,17 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
         int buf = buf_c + inflight;
         buf = buf >= NS ? buf - NS : buf;
         issue_slice(buf);
-        issued += LPW;
-        mark0 = buf == 0 ? issued : mark0;
-        mark1 = buf == 1 ? issued : mark1;
-        mark2 = buf == 2 ? issued : mark2;
         ++inflight;
         return true;
     };
-    // wait until at most `allowed` of this wave's vector-memory operations are outstanding (rounded
-    // down to one of the counts that can occur), and until its LDS accesses and scalar loads are done
-    auto wait_outstanding = [&](int allowed) {
-        constexpr int S = Cfg::NSTORE;
-        if (allowed >= S + 2 * LPW) wait_vmcnt_and_lds<S + 2 * LPW>();
-        else if (allowed >= S + LPW) wait_vmcnt_and_lds<S + LPW>();
-        else if (allowed >= S && S > 2 * LPW) wait_vmcnt_and_lds<S>();
-        else if (allowed >= 2 * LPW) wait_vmcnt_and_lds<2 * LPW>();
-        else if (allowed >= S) wait_vmcnt_and_lds<S>();
-        else if (allowed >= LPW) wait_vmcnt_and_lds<LPW>();
-        else wait_vmcnt_and_lds<0>();
+    // wait until the slice in buf_c has landed, and until this wave's LDS accesses and scalar loads are done
+    auto wait_slice = [&]() {
+        if (before_stores > 0) {
+            --before_stores;
+            wait_slices<LPW, Cfg::NSTORE, NS - 2>(inflight - 1);
+        } else {
+            wait_slices<LPW, 0, NS - 2>(inflight - 1);
+        }
     };
 
     // MFMA operand fragments of one 16-wide k step of the slice in ring buffer buf
@@ -363,12 +367,11 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
         for (int t = 0; t < tc.T; ++t) {
-            // Steady state: the NS-1 slices t .. t+NS-2 are in flight or landed, no store sits between them
-            // (the previous tile's stores are older than slice NS-1), and the cursor is inside this tile at
-            // slice t+NS-1.  Then the wait is a constant and the request code is straight-line.
-            const bool steady = k_aligned && t >= NS - 1 && t + NS - 1 < tc.T && inflight == NS - 1 && !pf_in_next;
+            // Steady state: the NS-1 slices t .. t+NS-2 are in flight or landed, no store is younger than any of them,
+            // and the cursor is inside this tile at slice t+NS-1.  Then the wait is a constant and the request code is straight-line.
+            const bool steady = k_aligned && before_stores == 0 && t + NS - 1 < tc.T && inflight == NS - 1 && !pf_in_next;
             if (steady) wait_vmcnt_and_lds<(NS - 2) * LPW>();
-            else wait_outstanding(issued - mark_of(buf_c));  // this wave's part of the slice in buf_c has landed
+            else wait_slice();  // this wave's part of the slice in buf_c has landed
             barrier_no_fence();  // everybody's part has landed; the buffer behind buf_c is free
             Frags f0, f1;
             load_frags(buf_c, 0, f0);  // LDS reads first: their latency runs under the request code below
@@ -388,10 +391,6 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
 #pragma unroll
                 for (int i = 0; i < Cfg::B_LPW; ++i)
                     dma16_to_lds(bbase, pf_voff[i], stage + Cfg::A_STAGE + (i * NW + wave) * 1024);
-                issued += LPW;
-                mark0 = buf == 0 ? issued : mark0;
-                mark1 = buf == 1 ? issued : mark1;
-                mark2 = buf == 2 ? issued : mark2;
                 ++pf_t;
                 if (++pf_s == Cfg::SPB) {
                     pf_s = 0;
@@ -468,11 +467,11 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
                 }
             }
         if (interior) {
-            issued += Cfg::NSTORE;  // exactly NSTORE stores were issued, none is waited for
+            before_stores = inflight;  // exactly NSTORE stores were issued, none is waited for
         } else {
             // an edge tile issues a data-dependent number of stores: drain once so the count is exact again
             wait_vmcnt_and_lds<0>();
-            mark0 = mark1 = mark2 = issued;
+            before_stores = 0;
         }
 
         // ---- advance to the next tile ---------------------------------------------------------------
@@ -574,16 +573,20 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
 
 template <bool XT>
 static bool launch_dma_tile(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
+    // Buffers: as many as leave room for the workgroups that a compute unit can hold (two of four waves, four of two).
+    // Against three everywhere: 3584 x 18944 at 90 %, N = 256, 64 x 64 / 32 x 32 blocks 45.5 -> 40.8 / 43.8 -> 41.5 us, N = 512
+    // 51.9 -> 46.5 / 51.0 -> 46.3; 4096 x 4096 at 80 %, N = 2048, 128 / 64 / 32-row blocks 45.3 -> 42.2 / 37.1 -> 34.8 /
+    // 48.0 -> 42.8.  (Eight buffers for one workgroup a compute unit: no faster, and slower where there are two.)
     switch (h->b_row * 1000 + p.bn) {
         case 128256: launch_dma<128, 256, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 128128: launch_dma<128, 128, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 128064: launch_dma<128, 64, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 64256: launch_dma<64, 256, 1, 4, 3, XT>(h, B, C, N, p, stream); return true;
-        case 64128: launch_dma<64, 128, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 64064: launch_dma<64, 64, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 128128: launch_dma<128, 128, 2, 2, 5, XT>(h, B, C, N, p, stream); return true;
+        case 128064: launch_dma<128, 64, 2, 2, 6, XT>(h, B, C, N, p, stream); return true;
+        case 64256: launch_dma<64, 256, 1, 4, 4, XT>(h, B, C, N, p, stream); return true;
+        case 64128: launch_dma<64, 128, 2, 2, 6, XT>(h, B, C, N, p, stream); return true;
+        case 64064: launch_dma<64, 64, 1, 2, 5, XT>(h, B, C, N, p, stream); return true;
         case 32256: launch_dma<32, 256, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 32128: launch_dma<32, 128, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
-        case 32064: launch_dma<32, 64, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 32128: launch_dma<32, 128, 1, 2, 4, XT>(h, B, C, N, p, stream); return true;
+        case 32064: launch_dma<32, 64, 1, 2, 6, XT>(h, B, C, N, p, stream); return true;
     }
     return false;
 }
