@@ -368,8 +368,12 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
 
         for (int t = 0; t < tc.T; ++t) {
             // Steady state: the NS-1 slices t .. t+NS-2 are in flight or landed, no store is younger than any of them,
-            // and the cursor is inside this tile at slice t+NS-1.  Then the wait is a constant and the request code is straight-line.
-            const bool steady = k_aligned && before_stores == 0 && t + NS - 1 < tc.T && inflight == NS - 1 && !pf_in_next;
+            // and the cursor is inside this tile at slice t+NS-1, which does not reach past K (only the last block of a
+            // block-row can).  Then the wait is a constant and the request code is straight-line.  us, steady from the first slice
+            // on and for any K, against from slice NS-1 on and K % BR == 0 only (rings of three): 5003 x 3331 at 80 %,
+            // N = 2048, 128 / 64 / 32-row blocks 51 / 47.5 / 63 -> 41 / 36 / 46; 4096 x 4096, 64-row 36.3 -> 34.5.
+            const bool steady = (k_aligned || pf_t < pf_T - Cfg::SPB) && before_stores == 0 && t + NS - 1 < tc.T &&
+                                inflight == NS - 1 && !pf_in_next;
             if (steady) wait_vmcnt_and_lds<(NS - 2) * LPW>();
             else wait_slice();  // this wave's part of the slice in buf_c has landed
             barrier_no_fence();  // everybody's part has landed; the buffer behind buf_c is free
@@ -573,15 +577,14 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
 
 template <bool XT>
 static bool launch_dma_tile(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
-    // Buffers: as many as leave room for the workgroups that a compute unit can hold (two of four waves, four of two).
-    // Against three everywhere: 3584 x 18944 at 90 %, N = 256, 64 x 64 / 32 x 32 blocks 45.5 -> 40.8 / 43.8 -> 41.5 us, N = 512
-    // 51.9 -> 46.5 / 51.0 -> 46.3; 4096 x 4096 at 80 %, N = 2048, 128 / 64 / 32-row blocks 45.3 -> 42.2 / 37.1 -> 34.8 /
-    // 48.0 -> 42.8.  (Eight buffers for one workgroup a compute unit: no faster, and slower where there are two.)
+    // Buffers: as many as leave room for the workgroups that a compute unit can hold (two of four waves, four of two),
+    // except 64 x 256, where a fourth one costs (3584 x 18944 at 90 %, N = 4096: 125.6 us with 3, 132 with 4).  Eight for
+    // one workgroup a compute unit is no faster than these, and slower where there are two.
     switch (h->b_row * 1000 + p.bn) {
         case 128256: launch_dma<128, 256, 2, 2, 3, XT>(h, B, C, N, p, stream); return true;
         case 128128: launch_dma<128, 128, 2, 2, 5, XT>(h, B, C, N, p, stream); return true;
         case 128064: launch_dma<128, 64, 2, 2, 6, XT>(h, B, C, N, p, stream); return true;
-        case 64256: launch_dma<64, 256, 1, 4, 4, XT>(h, B, C, N, p, stream); return true;
+        case 64256: launch_dma<64, 256, 1, 4, 3, XT>(h, B, C, N, p, stream); return true;
         case 64128: launch_dma<64, 128, 2, 2, 6, XT>(h, B, C, N, p, stream); return true;
         case 64064: launch_dma<64, 64, 1, 2, 5, XT>(h, B, C, N, p, stream); return true;
         case 32256: launch_dma<32, 256, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
