@@ -1,4 +1,5 @@
 // C ABI entry points: argument checking, handle life cycle, export.  See include/asyncsparse.h.
+#include <algorithm>
 #include <cstring>
 #include <new>
 
@@ -100,6 +101,12 @@ static asp_status_t upload_runs(void **dst, const void *src, size_t esize, const
     return ASP_OK;
 }
 
+static int64_t longest_row(const std::vector<int32_t> &row_ptr) {
+    int64_t n = 0;
+    for (size_t r = 0; r + 1 < row_ptr.size(); ++r) n = std::max<int64_t>(n, row_ptr[r + 1] - row_ptr[r]);
+    return n;
+}
+
 static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, int64_t nnz,
                                 const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                                 hipStream_t stream, asp_handle *h) {
@@ -121,10 +128,9 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         h->n_units = (int64_t)h->hb.block_col_idx.size();
         // (the plan counts tiles of non-empty block-rows, also for host-only handles, which get no schedule)
         h->hb.n_nonempty = 0;
-        for (size_t r = 0; r + 1 < h->hb.block_row_ptr.size(); ++r) {
+        for (size_t r = 0; r + 1 < h->hb.block_row_ptr.size(); ++r)
             h->hb.n_nonempty += h->hb.block_row_ptr[r + 1] > h->hb.block_row_ptr[r] ? 1 : 0;
-            h->hb.max_blocks = std::max<int64_t>(h->hb.max_blocks, h->hb.block_row_ptr[r + 1] - h->hb.block_row_ptr[r]);
-        }
+        h->hb.max_blocks = longest_row(h->hb.block_row_ptr);
         // Smaller blocks: the kernel for 128-row tiles on the composite form (asp_convert.cpp) beats the small-block
         // kernel, which reads twice / four times the LDS bytes per MFMA, until the zero fill outweighs that.
         // Measured on 8192 x 8192 matrices with geometric block-row lengths (N = 65536) at 50 / 75 / 90 / 95 / 99 %
@@ -140,6 +146,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
                 const double limit = cfg->b_row == 128 ? 1.0 : cfg->b_row == 64 ? 2.6 : 4.3;  // 128: no fill
                 h->has_comp = env_comp == 1 || h->comp_inflation <= limit;
                 h->c_n_brows = (int64_t)h->hc.block_row_ptr.size() - 1;
+                h->hc.max_blocks = longest_row(h->hc.block_row_ptr);
                 h->c_n_units = (int64_t)h->hc.block_col_idx.size();
                 if (!h->has_comp || host_only) h->hc.packed = std::vector<uint8_t>();
                 if (!h->has_comp) h->hc = HostBcsr();

@@ -23,18 +23,9 @@
 #include <cstdlib>
 #include <cstring>
 
-#include "asp_internal.h"
+#include "asp_bcsr_pipe.h"
 
 namespace asp {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(4))) short short4v;
-typedef __attribute__((ext_vector_type(8))) short short8v;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;  // staging registers: a plain vector type, so that
-                                                                 // arrays of it are split into registers
 
 template <int BR, int BC, int BN, int WM, int WN, bool VEC>
 struct BcsrCfg {
@@ -61,19 +52,6 @@ struct BcsrCfg {
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
     static_assert(BC % KS == 0, "block width must be a multiple of the stage depth");
 };
-
-__device__ __forceinline__ u32x4 load_b_chunk_scalar(const uint16_t *__restrict__ B, int64_t row_off, int col, int N) {
-    // slow path: N or the base pointers do not allow 16-byte accesses
-    uint16_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = (col + i < N) ? B[row_off + col + i] : (uint16_t)0;
-    u32x4 v;
-    v.x = e[0] | ((uint32_t)e[1] << 16);
-    v.y = e[2] | ((uint32_t)e[3] << 16);
-    v.z = e[4] | ((uint32_t)e[5] << 16);
-    v.w = e[6] | ((uint32_t)e[7] << 16);
-    return v;
-}
 
 template <int BR, int BC, int BN, int WM, int WN, bool VEC>
 __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
@@ -130,7 +108,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
                     if (VEC)
                         v = *(const u32x4 *)(B + (int64_t)krow * N + col);
                     else
-                        v = load_b_chunk_scalar(B, (int64_t)krow * N, col, N);
+                        v = load_tail8(B + (int64_t)krow * N, col, N);
                 }
                 rb[i] = v;
             }
@@ -225,6 +203,8 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
             uint16_t *dst = C + (int64_t)grow * N + gcol;
             if (VEC) {
                 *(uint4 *)dst = v;
+            } else if (gcol + 8 <= N) {
+                *(u32x4_a2 *)dst = u32x4{v.x, v.y, v.z, v.w};
             } else {
                 uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -334,7 +314,9 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     }
     const int key = h->b_row * 1000 + p.bn;
     const bool force_regstage = switches().bcsr_regstage;  // benchmarking switch: the synchronous-copy kernel
-    if (p.vectorized && !force_regstage && N < (1ll << 25)) {
+    if (!force_regstage && switches().bcsr_bn == 0 && bcsr_strip_launch(h, B, C, N, p, stream)) {
+        // small launch: strips of block-rows
+    } else if (p.vectorized && !force_regstage && N < (1ll << 25)) {
         if (!bcsr_wide_launch(h, B, C, N, p, stream) && !bcsr_dma_launch(h, B, C, N, p, stream))
             return fail(ASP_ERR_UNSUPPORTED, "no kernel for this block size / tile width");
     } else if (!p.vectorized) {  // element-wise path

@@ -57,6 +57,29 @@ __device__ __forceinline__ void store_c16(uint16_t *dst, uint4 v) {
     __builtin_nontemporal_store(w, (u32x4 *)dst);
 }
 
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));  // 16-byte accesses at element alignment
+
+// Elements pos .. pos + 7 of a row of `end` bf16 elements, zeros from `end` on: the row's last 8 elements, moved down.
+// (Loaded one by one they made the last column tile set the time of a launch: strips of 5003 x 3331, 80 %, 64 x 64 blocks,
+// 1023 columns 58 us, 33 this way.)
+__device__ __forceinline__ u32x4 load_tail8(const uint16_t *row, int pos, int end) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (pos >= end) return v;
+    if (end < 8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (pos + e < end) v[e >> 1] |= (uint32_t)row[pos + e] << (16 * (e & 1));
+        return v;
+    }
+    const int first = pos + 8 <= end ? pos : end - 8, by = pos - first;
+    v = *(const u32x4_a2 *)(row + first);
+    if (by & 4) v = u32x4{v.z, v.w, 0u, 0u};
+    if (by & 2) v = u32x4{v.y, v.z, v.w, 0u};
+    if (by & 1) v = u32x4{v.x >> 16 | v.y << 16, v.y >> 16 | v.z << 16, v.z >> 16 | v.w << 16, v.w >> 16};
+    return v;
+}
+
 // first tile of each XCD's run of the tile order, start[8] = number of tiles
 struct XcdRuns {
     int start[9];

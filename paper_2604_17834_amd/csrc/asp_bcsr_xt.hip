@@ -14,23 +14,17 @@
 // With more tokens each strip's reads (A once per token tile, X once per strip) run into the L1s' miss rate, and the ring
 // kernel's larger tiles take over (bcsr_spmm_xt_launch).
 //
-// Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; the lanes of a unit that crosses K
-// take their elements one by one, zeros past the end.
+// Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; elements past K count
+// as zeros.
 #include "asp_bcsr_pipe.h"
 
 namespace asp {
 
-namespace {
-
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-
-}  // namespace
-
-// grid = units_m strips of 32 MT rows x token tiles of 32 NT; row_ptr / col_idx / a_packed: the stored blocks,
+// grid = units_m strips of 32 MT rows x token tiles of 32 NT; rank_info: {block-row, first block, blocks, -} in
+// the schedule's order; col_idx / a_packed: the stored blocks,
 // fragment-ordered; UKT: k per unit
 template <int BR, int MT, int NT, int W, int UKT, bool VEC>
-__global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int32_t *__restrict__ row_ptr,
+__global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int4 *__restrict__ rank_info,
                                                                const int32_t *__restrict__ col_idx,
                                                                const uint16_t *__restrict__ a_packed,
                                                                const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
@@ -41,13 +35,16 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int32_t *__
     __shared__ __attribute__((aligned(16))) float part[W][NT * 32][PITCH];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // every XCD (workgroups go to them round-robin) takes a run of strips with all their token tiles: A stays in its L2
+    // every XCD (workgroups go to them round-robin) takes a run of strips with all their column tiles, so that A stays in
+    // its L2; the runs are cut from the schedule's lists (rank % 8), which have nearly the same number of blocks
     const int units_n = gridDim.x / units_m, xcd = blockIdx.x & 7, q = gridDim.x >> 3, r = gridDim.x & 7;
     const int id = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
     const int un = id % units_n, um = id / units_n;
-    const int br = um / STRIPS, strip = um % STRIPS;
+    const int n_brows = units_m / STRIPS, per = n_brows >> 3, more = n_brows & 7, at = um / STRIPS, strip = um % STRIPS;
+    const int list = at < more * (per + 1) ? at / (per + 1) : more + (at - more * (per + 1)) / per;
+    const int4 ri = rank_info[list + 8 * (at - list * per - (list < more ? list : more))];
+    const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
     const int64_t n0 = (int64_t)un * (32 * NT);
-    const int blk0 = row_ptr[br], n_units = (row_ptr[br + 1] - blk0) * UPB;
     const int u0 = (int)((int64_t)n_units * wave / W), u1 = (int)((int64_t)n_units * (wave + 1) / W);
 
     f32x16 acc[MT][NT];
@@ -104,13 +101,8 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int32_t *__
                     for (int i = 0; i < KK; ++i) {
                         const int k = k0 + i * 16 + kl;
                         u32x4 v = {0u, 0u, 0u, 0u};
-                        if (VEC) {
-                            if (k < K) v = *(const u32x4 *)(x[j] + k);  // K % 8 == 0
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e)
-                                if (k + e < K) v[e >> 1] |= (uint32_t)x[j][k + e] << (16 * (e & 1));
-                        }
+                        if (!VEC) v = load_tail8(x[j], k, K);
+                        else if (k < K) v = *(const u32x4 *)(x[j] + k);  // K % 8 == 0
                         f.x[j][i] = v;
                     }
             }
@@ -182,7 +174,7 @@ static void launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N,
     const int units_m = (int)h->n_brows * (BR / 32 / MT);
     dim3 grid((unsigned)(units_m * ceil_div(N, 32 * NT))), block(W * 64);  // < M x N / 2^9 <= 2^31
 #define ASP_STRIP(VEC)                                                                                             \
-    hipLaunchKernelGGL((bcsr_xt_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, h->d_row_ptr,       \
+    hipLaunchKernelGGL((bcsr_xt_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, (const int4 *)h->d_rank_info,       \
                        h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)X, (uint16_t *)Y, (int)h->m, \
                        (int)h->k, N, units_m)
     if (vec) ASP_STRIP(true);
