@@ -103,8 +103,8 @@ typedef enum { ASP_ARR_ROW_PTR = 0, ASP_ARR_COL_IDX = 1, ASP_ARR_VALUES = 2, ASP
  * the handle keeps them -- with at least one tile per compute unit), the one with the
  * least padded width x cost per column, costs 135 / 96 / 74 / 64 (ties: the wider), and then the next narrower
  * width while non-empty block-rows x ceil(N / width) tiles are fewer than the GPU's compute units (256 assumed for
- * host-only handles); launches too small for these tiles, or whose rows are not aligned, may run in narrower strips
- * instead; fp32 BCSR and WCSR take the widest of their widths that divides N, else the one that pads least. */
+ * host-only handles); fp32 BCSR and WCSR take the widest of their widths that divides N, else the one that pads least.
+ * BCSR launches too small for these tiles, or whose rows are not aligned, run in narrower strips instead. */
 typedef struct {
     int32_t bn;          /* columns of B/C handled by one workgroup (BCSR) or one wave (WCSR) */
     int32_t n_tiles;     /* ceil(N / bn): tiles along N, the last one masked if bn does not divide N */

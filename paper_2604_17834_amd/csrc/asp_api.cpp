@@ -163,7 +163,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload(&h->d_col_idx, h->hb.block_col_idx.data(), h->hb.block_col_idx.size() * 4, stream))) return s;
         if ((s = upload(&h->d_values, h->hb.packed.data(), h->hb.packed.size(), stream))) return s;
         ASP_HIP_TRY(hipDeviceGetAttribute(&h->n_cus, hipDeviceAttributeMultiprocessorCount, h->device));
-        bcsr_build_schedule(h->hb);
+        bcsr_build_schedule(h->hb, cfg->dtype == ASP_DT_F32);
         if ((s = upload(&h->d_rank_info, h->hb.rank_info.data(), h->hb.rank_info.size() * 4, stream))) return s;
         ASP_HIP_TRY(hipMalloc((void **)&h->d_sched, 64));
         if (h->has_comp) {

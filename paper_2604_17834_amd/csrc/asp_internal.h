@@ -120,7 +120,7 @@ struct HostRows {
 // converters (asp_convert.cpp); values are only bit-copied
 void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostBcsr &out);
-void bcsr_build_schedule(HostBcsr &b);
+void bcsr_build_schedule(HostBcsr &b, bool by_length = false);
 double bcsr_build_composite(const HostBcsr &in, int64_t m, int64_t k, int32_t b, HostBcsr &out);
 void bcsr_pack_fragments_bf16(const HostBcsr &in, int32_t b_row, int32_t b_col, std::vector<uint8_t> &packed);
 void bcsr_pack_fragments_f32(const HostBcsr &in, int32_t b_row, int32_t b_col, std::vector<uint8_t> &packed);
@@ -194,7 +194,7 @@ bool bcsr_dma_launch(const asp_handle *h, const void *B, void *C, int64_t N, con
 bool bcsr_dma_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, const BcsrPlan &p, hipStream_t stream);
 void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
-bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
+void bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
 bool bcsr_wide_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
 asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
