@@ -669,11 +669,16 @@ template <bool XT>
 static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, int n_tiles, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n;  // benchmarking switch
     // two N-tiles walked together: an A block is fetched once per pair while the pair's slab of B (K x 1024)
-    // still has a chance in the 4 MB of L2 (measured: 1, 3 and 4 are 3-10 % slower on the 90 %-sparse projection)
-    int group_n = env_group > 0 ? env_group : 2;
-    if (group_n > n_tiles) group_n = n_tiles;
+    // still has a chance in the 4 MB of L2 (measured: 1, 3 and 4 are 3-10 % slower on the 90 %-sparse projection).
+    // With 8 N-tiles one: every XCD then has one to itself, half the slab, instead of a share of four pairs; and up to 15
+    // where the block-rows are many enough to balance without the pairs.  us, one / two: 18944 x 3584 at 90 %, N = 4096,
+    // 128 / 64 / 32-row blocks 70.6 / 78.9, 88.6 / 100.4, 126 / 130, N = 6144 109 / 117, 134 / 143, 190 / 190; 4096 x 4096 at 80 %,
+    // N = 4096, 128 / 64-row 35.8 / 38.5, 45.8 / 56.3, but N = 5120 50.5 / 45.2, 66.2 / 61.2 (32 rows of tiles).
     const WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
+    const bool one = n_tiles == 8 || (n_tiles > 8 && n_tiles < 16 && n_rows >= 128);
+    int group_n = env_group > 0 ? env_group : one ? 1 : 2;
+    if (group_n > n_tiles) group_n = n_tiles;
     int64_t workers = h->n_cus;  // one resident workgroup per CU: the ring takes the whole LDS
     if (workers > n_rows * n_tiles) workers = n_rows * n_tiles;
     // benchmarking switch: fewer resident workgroups, i.e. part of the compute units idle (the schedule's 16 lists
