@@ -104,7 +104,7 @@ typedef enum { ASP_ARR_ROW_PTR = 0, ASP_ARR_COL_IDX = 1, ASP_ARR_VALUES = 2, ASP
  * least padded width x cost per column, costs 135 / 96 / 74 / 64 (ties: the wider), and then the next narrower
  * width while non-empty block-rows x ceil(N / width) tiles are fewer than the GPU's compute units (256 assumed for
  * host-only handles); fp32 BCSR and WCSR take the widest of their widths that divides N, else the one that pads least.
- * BCSR launches too small for these tiles, or whose rows are not aligned, run in narrower strips instead. */
+ * BCSR launches too small for these tiles, or whose rows are not aligned, may run in tiles of other widths. */
 typedef struct {
     int32_t bn;          /* columns of B/C handled by one workgroup (BCSR) or one wave (WCSR) */
     int32_t n_tiles;     /* ceil(N / bn): tiles along N, the last one masked if bn does not divide N */

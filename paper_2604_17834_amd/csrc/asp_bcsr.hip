@@ -3,8 +3,9 @@
 //
 // The register-staged kernel is the synchronous-copy design (the analogue of the paper's Section III-A
 // kernel with cooperative loads, plus one slice of prefetch): global loads go to VGPRs, then to LDS.  It
-// serves operands that do not allow 16-byte accesses (element-wise path) and stays selectable for
-// comparison runs; aligned operands take the direct-to-LDS ring kernel in asp_bcsr_dma.hip.
+// serves operands whose rows are not 16-byte aligned (16-byte accesses at element alignment, which a direct-to-LDS load
+// does not take) and stays selectable for comparison runs; aligned operands take the direct-to-LDS ring kernel in
+// asp_bcsr_dma.hip.
 //
 // One workgroup computes one (block-row, N-tile) output tile of b_row x BN: it walks the stored blocks
 // of its block-row (Section II-C), and for each K slice of a block stages the A slice and the matching
@@ -266,7 +267,7 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
     static const int cost[4] = {135, 96, 74, 64};
     const int env_bn = switches().bcsr_bn;  // benchmarking switch: caps the tile width
     if (!p.vectorized) {
-        p.bn = 64;  // the element-wise path is only built for BN = 64
+        p.bn = 64;
     } else {
         // 512-wide tiles (one resident workgroup per compute unit) exist for 128x128 blocks and only pay
         // when every compute unit gets at least one tile
@@ -318,11 +319,24 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     } else if (p.vectorized && !force_regstage && N < (1ll << 25)) {
         if (!bcsr_wide_launch(h, B, C, N, p, stream) && !bcsr_dma_launch(h, B, C, N, p, stream))
             return fail(ASP_ERR_UNSUPPORTED, "no kernel for this block size / tile width");
-    } else if (!p.vectorized) {  // element-wise path
-        switch (h->b_row) {
-            case 128: launch<128, 64, 2, 2, false>(h, B, C, N, p, stream); break;
-            case 64: launch<64, 64, 2, 2, false>(h, B, C, N, p, stream); break;
-            default: launch<32, 64, 1, 2, false>(h, B, C, N, p, stream); break;
+    } else if (!p.vectorized) {  // 16-byte accesses at element alignment
+        // 128-wide tiles where that leaves enough of them: with the workgroups that a compute unit holds it reads A half as
+        // often, with fewer tiles the longest block-rows set the time.  us, 64 / 128 wide: 18944 x 3584 at 90 %, N = 8001,
+        // 128 / 64 / 32-row blocks 346 / 271, 356 / 316, 502 / 403; 5003 x 3331 at 80 %, N = 3001 58.7 / 53.7, 67 / 67, 100 / 86;
+        // 1500 x 8001 at 75 %, N = 8001, 64-row (1512 tiles) 148 / 180.  (256 wide: slower than both.)
+        BcsrPlan w = p;
+        if (h->n_brows * ceil_div(N, 128) >= (h->b_row == 128 ? 3 : h->b_row == 64 ? 8 : 4) * (int64_t)h->n_cus) {
+            w.bn = 128;
+            w.n_tiles = (int32_t)ceil_div(N, 128);
+            w.workgroups = h->n_brows * w.n_tiles;
+        }
+        switch (h->b_row * 1000 + w.bn) {
+            case 128128: launch<128, 128, 2, 2, false>(h, B, C, N, w, stream); break;
+            case 128064: launch<128, 64, 2, 2, false>(h, B, C, N, w, stream); break;
+            case 64128: launch<64, 128, 2, 2, false>(h, B, C, N, w, stream); break;
+            case 64064: launch<64, 64, 2, 2, false>(h, B, C, N, w, stream); break;
+            case 32128: launch<32, 128, 1, 4, false>(h, B, C, N, w, stream); break;
+            default: launch<32, 64, 1, 2, false>(h, B, C, N, w, stream); break;
         }
     } else {
         switch (key) {
