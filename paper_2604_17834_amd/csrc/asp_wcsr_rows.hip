@@ -83,7 +83,8 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.f;
 
-    // batches of 8 entries, aligned; entries outside [e0, e1) read a row of B that the task reads anyway, times zero
+    // batches of 8 entries, aligned; entries outside [e0, e1) read a row of B that the task reads anyway, and what they
+    // add is dropped (no row of A that does not store a column may see its values: zero times Inf is NaN)
     struct Batch {
         int c[8];
         uint32_t v[8];  // fp32 bits (as integers, so that selections stay in scalar registers)
@@ -109,7 +110,7 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
         if (base < e0 || base + 8 > e1)
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                if (base + j < e0 || base + j >= e1) t.c[j] = c_any, t.v[j] = 0u;
+                if (base + j < e0 || base + j >= e1) t.c[j] = c_any;
     };
     auto gather = [&](const Batch &t, vec_t (&b)[8]) __attribute__((always_inline)) {
 #pragma unroll
@@ -159,18 +160,27 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
     };
 
     if (CHUNK) {
-        walk([&](int, const Batch &t, const vec_t(&bv)[8]) __attribute__((always_inline)) {
+        walk([&](int b, const Batch &t, const vec_t(&bv)[8]) __attribute__((always_inline)) {
+            const int base = base0 + 8 * b;
+            if (base < e0 || base + 8 > e1) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) fma_entry(t, bv, j);
+                for (int j = 0; j < 8; ++j)
+                    if (base + j >= e0 && base + j < e1) fma_entry(t, bv, j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) fma_entry(t, bv, j);
+            }
         });
         if (owner && e0 < e1) put_chunk<T, E>(td, acc, n, nc, N, C, ws);
         return;
     }
 
-    // lane i holds the end of the task's i-th row
+    // lane i holds the end of the task's i-th row.  Entries of the first batch before e0 count as a
+    // row -1 that ends at e0 and is not stored.
     int ends = 0x7fffffff;
     if (lane < td.y) ends = row_ptr[td.x + lane + 1];
     int k = 0, end_k = __builtin_amdgcn_readlane(ends, 0);
+    if (nb > 0 && base0 < e0) k = -1, end_k = e0;
     auto finish_row = [&]() __attribute__((always_inline)) {
         global_char *row = (global_char *)C + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(td.x + k) * row_bytes;
         uint32_t off = voff;
@@ -183,7 +193,7 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
             v[i] = o;
             acc[i] = 0.f;
         }
-        if (owner) __builtin_nontemporal_store(v, (__attribute__((address_space(1))) vec_t *)(row + off));
+        if (owner && k >= 0) __builtin_nontemporal_store(v, (__attribute__((address_space(1))) vec_t *)(row + off));
         ++k;
         end_k = __builtin_amdgcn_readlane(ends, k);
     };
@@ -222,13 +232,12 @@ __device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int t
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.f;
-    // batch b: entries e0 + (b G + g) * 16 .. + 15 of this group; past the end: the last entry's row, times zero
+    // batch b: entries (b G + g) * 16 .. + 15 of the chunk for this group; past the end: the last entry, and nothing is added
+    const int len = e1 - e0;
     auto fetch = [&](int b, int &c, float &v) __attribute__((always_inline)) {
-        const int e = e0 + (b * G + g) * 16 + i16;
-        const int es = e < e1 ? e : e1 - 1;
+        const int e = e0 + (b * G + g) * 16 + i16, es = e < e1 ? e : e1 - 1;
         c = col[es];
         v = widen(val[es]);
-        v = e < e1 ? v : 0.f;
     };
 #define ASP_BCAST(x, i) __builtin_amdgcn_mov_dpp((int)(x), 0x150 + (i), 0xf, 0xf, true)  // row_newbcast: lane i of each 16
 #define ASP_GATHER(dst, j, i) \
@@ -238,26 +247,36 @@ __device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int t
         const float f_ = __uint_as_float(ASP_BCAST(__float_as_uint(v), i));                                 \
         _Pragma("unroll") for (int q = 0; q < E; ++q) acc[q] = __builtin_fmaf(f_, widen((T)src[j][q]), acc[q]); \
     } while (0)
+#define ASP_ADD_LAST(src, j, i)                                                                                    \
+    do {                                                                                                           \
+        const float f_ = __uint_as_float(ASP_BCAST(__float_as_uint(v), i));                                        \
+        const bool in_ = ((nb - 1) * G + g) * 16 + (i) < len;                                                      \
+        _Pragma("unroll") for (int q = 0; q < E; ++q) acc[q] = in_ ? __builtin_fmaf(f_, widen((T)src[j][q]), acc[q]) : acc[q]; \
+    } while (0)
 #define ASP_EIGHT(OP, x, o) \
     OP(x, 0, o + 0); OP(x, 1, o + 1); OP(x, 2, o + 2); OP(x, 3, o + 3); OP(x, 4, o + 4); OP(x, 5, o + 5); OP(x, 6, o + 6); OP(x, 7, o + 7)
-    const int nb = (e1 - e0 + 16 * G - 1) / (16 * G);
+    const int nb = (len + 16 * G - 1) / (16 * G);
     int c, cn;
     float v, vn;
     vec_t lo[8], hi[8];
     fetch(0, c, v);
     ASP_EIGHT(ASP_GATHER, lo, 0);
-    for (int b = 0; b < nb; ++b) {  // eight gathers ahead of the additions; (the last round gathers its own rows again)
+    for (int b = 0; b + 1 < nb; ++b) {  // eight gathers ahead of the additions
         ASP_EIGHT(ASP_GATHER, hi, 8);
-        fetch(b + 1 < nb ? b + 1 : b, cn, vn);
+        fetch(b + 1, cn, vn);
         ASP_EIGHT(ASP_ADD, lo, 0);
         c = cn;
         ASP_EIGHT(ASP_GATHER, lo, 0);
         ASP_EIGHT(ASP_ADD, hi, 8);
         v = vn;
     }
+    ASP_EIGHT(ASP_GATHER, hi, 8);
+    ASP_EIGHT(ASP_ADD_LAST, lo, 0);
+    ASP_EIGHT(ASP_ADD_LAST, hi, 8);
 #undef ASP_BCAST
 #undef ASP_GATHER
 #undef ASP_ADD
+#undef ASP_ADD_LAST
 #undef ASP_EIGHT
 #pragma unroll
     for (int i = 0; i < E; ++i) {

@@ -66,3 +66,28 @@ def test_dense_windows_at_any_width_and_alignment(dtype, b_row, N, misalign, res
     a = synth.random_csr(200, 300, 0.5, seed=N, dtype=dtype)
     B = synth.dense_normal(a.k, N, dtype, seed=7 + N)
     check_against_oracle(a, B, gpu_spmm(a, "wcsr", b_row, 8, B, task_cols=128, misalign=misalign, reserve=reserve))
+
+
+@pytest.mark.parametrize("dtype,reserve", [("f32", True), ("bf16", True), ("f32", False)])
+@pytest.mark.parametrize("N", [16, 32, 64, 100, 128, 256, 512])
+def test_only_rows_that_store_a_column_see_its_values(dtype, reserve, N):
+    # Inf and NaN in some rows of B; tasks that begin with empty rows and at entries that are no multiple of 8, chunks of
+    # every length: a row is Inf or NaN exactly where the sum of its own products is
+    rng = np.random.default_rng(N)
+    lengths = rng.choice([0, 0, 0, 1, 1, 2, 3, 5], 6000)
+    lengths[rng.integers(0, 6000, 60)] = rng.integers(33, 400, 60)
+    a = _rows_of_lengths(list(lengths), 5000, dtype, seed=N)
+    a.values[:] = a.values & 0x7FFF if dtype == "bf16" else np.abs(a.values)
+    B = synth.dense_normal(a.k, N, dtype, seed=8)
+    bad = rng.random(a.k)
+    B[bad < 0.05] = 0x7F80 if dtype == "bf16" else np.inf
+    B[bad > 0.99] = 0x7FC1 if dtype == "bf16" else np.nan
+    C = synth.to_f64(gpu_spmm(a, "wcsr", 16, 8, B, task_cols=32, reserve=reserve), dtype)
+    inf, nan = (bad < 0.05)[a.col_idx], (bad > 0.99)[a.col_idx]
+    row = np.repeat(np.arange(a.m), np.diff(a.row_ptr))
+    has_inf, has_nan = np.bincount(row[inf], minlength=a.m) > 0, np.bincount(row[nan], minlength=a.m) > 0
+    assert (has_inf & ~has_nan).sum() > 100 and has_nan.sum() > 50
+    assert np.isnan(C[has_nan]).all()
+    assert np.isposinf(C[has_inf & ~has_nan]).all()
+    assert np.isfinite(C[~has_inf & ~has_nan]).all()
+    assert not C[np.diff(a.row_ptr) == 0].any()
