@@ -44,6 +44,16 @@ __device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uin
 __device__ __forceinline__ void narrow(float v, float &out) { out = v; }
 __device__ __forceinline__ void narrow(float v, uint16_t &out) { out = __builtin_bit_cast(uint16_t, (__bf16)v); }  // to nearest even
 
+// Entry positions go up to 2^31 - 1 and are ints, so nothing is added to an end.
+// Batch of 8 from `base` (a multiple of 8): whether all of it, and whether its j-th entry, is in [e0, e1).
+constexpr bool batch_inside(int base, int e0, int e1) { return base >= e0 && e1 - base >= 8; }
+constexpr bool entry_inside(int base, int j, int e0, int e1) { return base + j >= e0 && j < e1 - base; }
+// i-th entry of [e0, e1), the last one for those behind it
+constexpr int entry_clamped(int e0, int e1, int i) { return e0 + (i < e1 - e0 ? i : e1 - e0 - 1); }
+static_assert(!batch_inside(0x7ffffff8, 0, 0x7fffffff) && entry_inside(0x7ffffff8, 6, 0, 0x7fffffff) &&
+                  !entry_inside(0x7ffffff8, 7, 0, 0x7fffffff) && entry_clamped(0x7ffffff0, 0x7fffffff, 63) == 0x7ffffffe,
+              "the last entries of 2^31 - 1");
+
 // The sum of a chunk {row, scratch row, -, -} at columns nc .. nc + E - 1 (the lane's own ones start at n): to its row of
 // ws, or without ws (fp32 only) added to C with atomics.
 template <typename T, int E>
@@ -107,10 +117,10 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
                 t.v[2 * j + 1] = p & 0xffff0000u;
             }
         }
-        if (base < e0 || base + 8 > e1)
+        if (!batch_inside(base, e0, e1))
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                if (base + j < e0 || base + j >= e1) t.c[j] = c_any;
+                if (!entry_inside(base, j, e0, e1)) t.c[j] = c_any;
     };
     auto gather = [&](const Batch &t, vec_t (&b)[8]) __attribute__((always_inline)) {
 #pragma unroll
@@ -162,10 +172,10 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
     if (CHUNK) {
         walk([&](int b, const Batch &t, const vec_t(&bv)[8]) __attribute__((always_inline)) {
             const int base = base0 + 8 * b;
-            if (base < e0 || base + 8 > e1) {
+            if (!batch_inside(base, e0, e1)) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    if (base + j >= e0 && base + j < e1) fma_entry(t, bv, j);
+                    if (entry_inside(base, j, e0, e1)) fma_entry(t, bv, j);
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) fma_entry(t, bv, j);
@@ -175,9 +185,9 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
         return;
     }
 
-    // lane i holds the end of the task's i-th row.  Entries of the first batch before e0 count as a
+    // lane i holds the end of the task's i-th row (-1: no entry is there).  Entries of the first batch before e0 count as a
     // row -1 that ends at e0 and is not stored.
-    int ends = 0x7fffffff;
+    int ends = -1;
     if (lane < td.y) ends = row_ptr[td.x + lane + 1];
     int k = 0, end_k = __builtin_amdgcn_readlane(ends, 0);
     if (nb > 0 && base0 < e0) k = -1, end_k = e0;
@@ -235,7 +245,7 @@ __device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int t
     // batch b: entries (b G + g) * 16 .. + 15 of the chunk for this group; past the end: the last entry, and nothing is added
     const int len = e1 - e0;
     auto fetch = [&](int b, int &c, float &v) __attribute__((always_inline)) {
-        const int e = e0 + (b * G + g) * 16 + i16, es = e < e1 ? e : e1 - 1;
+        const int es = entry_clamped(e0, e1, (b * G + g) * 16 + i16);
         c = col[es];
         v = widen(val[es]);
     };
