@@ -575,6 +575,8 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         const int64_t nnz = row_ptr[std::min<int64_t>(m, (w + 1) * b_row)] - row_ptr[w * b_row];
         int64_t padded = wrp[w + 1] - wrp[w], real = padded;
         while (real > 0 && in.window_col_idx[wrp[w] + real - 1] < 0) --real;
+        // (the kernels' lists hold scratch rows as ints)
+        if (in.ws_slot[w] >= 0 && (in.ws_slot[w] + ceil_div(padded, task_cols)) * b_row > (1ll << 31)) return false;
         return nnz * (row_b + entry_b) <= real * row_b + padded * tile_b;
     };
     out = HostRows();

@@ -1,0 +1,39 @@
+// Prints the work lists that wcsr_build_rows makes of a synthetic matrix, for tests/test_wcsr_lists.py.
+//   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "asp_internal.h"
+
+static void print(const char *name, const std::vector<int32_t> &v, size_t width) {
+    for (size_t i = 0; i < v.size(); i += width) {
+        std::printf("%s", name);
+        for (size_t j = 0; j < width; ++j) std::printf(" %d", v[i + j]);
+        std::printf("\n");
+    }
+}
+
+static int slots(int32_t first) {
+    const int64_t m = 32, per_row = 20, k = m * per_row;
+    std::vector<int32_t> rp(m + 1), ci(k);
+    for (int64_t r = 0; r <= m; ++r) rp[r] = (int32_t)(r * per_row);
+    for (int64_t r = 0; r < m; ++r)
+        for (int64_t j = 0; j < per_row; ++j) ci[r * per_row + j] = (int32_t)(j * m + r);
+    std::vector<float> values(k, 1.f);
+    asp::HostWcsr w;
+    if (!asp::csr_to_wcsr(m, k, rp.data(), ci.data(), values.data(), 4, 16, 8, w)) return 1;
+    w.ws_slot = {first, first + 40};
+    asp::HostRows rows;
+    asp::wcsr_build_rows(m, rp.data(), ci.data(), 4, 16, 8, w, rows);
+    print("split", rows.split, 4);
+    print("chunk", rows.chunks, 4);
+    print("tile", rows.tile_tasks, 4);
+    print("tile_split", rows.tile_split, 1);
+    return 0;
+}
+
+int main(int argc, char **argv) {
+    if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
+    return 2;
+}
