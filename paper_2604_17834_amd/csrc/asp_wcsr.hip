@@ -17,7 +17,7 @@
 #include <cstdlib>
 #include <mutex>
 
-#include "asp_internal.h"
+#include "asp_wcsr_tile.h"
 
 // Scratch for callers that cannot allocate (asp_spmm_static_scratch): the partial tiles of split windows go here
 // instead of into a buffer from asp_reserve.  Every GPU the library runs on holds its own copy at its own address
@@ -169,10 +169,10 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, float *__restrict__ ws,
+                                                          int64_t N, int n_tiles, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
-    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
+    const auto [task, nt] = wave_task(n_tiles);
     if (task >= n_tasks) return;  // whole wave leaves together
     const int lane = threadIdx.x & 63, kq = lane >> 4, jl = lane & 15;
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
@@ -271,11 +271,11 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, float *__restrict__ ws,
+                                                          int64_t N, int n_tiles, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
     constexpr int BRW = 32 * MTW;
-    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
+    const auto [task, nt] = wave_task(n_tiles);
     if (task >= n_tasks) return;
     const int lane = threadIdx.x & 63, kq = lane >> 5, jl = lane & 31;
     const int4 td = tasks[task];
@@ -549,32 +549,31 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         hipLaunchKernelGGL(wcsr_zero_rows_kernel, dim3((unsigned)h->n_zero_windows), dim3(256), 0, stream,
                            h->d_zero_windows, h->b_row, (float *)C, (int)h->m, N);
     wcsr_rows_launch(h, B, C, N, ws, stream);
-    if (h->n_tile_tasks > 0) {
-        // a workgroup's four tasks are neighbours; the column tiles follow each other, so that one slab of B is walked
-        // at a time
-        dim3 grid((unsigned)ceil_div(h->n_tile_tasks, 4), (unsigned)p.n_tiles), block(256);
-        const int4 *tasks = (const int4 *)h->d_tile_tasks;
+    const int64_t step = tasks_per_launch(p.n_tiles);
+    for (int64_t first = 0; first < h->n_tile_tasks; first += step) {
+        const int nt = (int)std::min(step, h->n_tile_tasks - first), M = (int)h->m;
+        const dim3 grid = tile_grid(nt, p.n_tiles), block(256);
+        const int4 *tasks = (const int4 *)h->d_tile_tasks + first;
         const float *vals = (const float *)h->d_values;
         const float *Bf = (const float *)B;
         float *Cf = (float *)C;
-        const int nt = (int)h->n_tile_tasks, M = (int)h->m;
 #define ASP_W16(NG)                                                                                                   \
     do {                                                                                                              \
         if (vec)                                                                                                      \
             hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);                  \
+                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);       \
         else                                                                                                          \
             hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);          \
+                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
     } while (0)
 #define ASP_W32(MTW)                                                                                                   \
     do {                                                                                                               \
         if (vec)                                                                                                       \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
+                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
         else                                                                                                           \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
+                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
     } while (0)
         if (h->b_row == 16) {
             if (p.bn == 256) ASP_W16(4);

@@ -20,6 +20,7 @@
 // (Section III-C) store their fp32 partial tiles in the handle's scratch buffer (asp_reserve); a last kernel
 // adds them up in task order and rounds to bf16 once.
 #include "asp_bcsr_pipe.h"
+#include "asp_wcsr_tile.h"
 
 namespace asp {
 
@@ -34,12 +35,12 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
                                                              const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
                                                              float *__restrict__ ws, const int32_t *__restrict__ ws_slot,
                                                              const int32_t *__restrict__ window_row_ptr, int task_cols,
-                                                             int M, int64_t N) {
+                                                             int M, int64_t N, int n_tiles) {
     constexpr int BRW = 16 * MTW;
     constexpr int A_TILE = BRW * 8;  // elements of one value tile [BRW][8]
     __shared__ __attribute__((aligned(16))) uint8_t lds[4][32 * 256];  // per wave: 32 gathered rows x 128 columns
 
-    const int task = blockIdx.x * 4 + (threadIdx.x >> 6), nt = blockIdx.y;
+    const auto [task, nt] = wave_task(n_tiles);
     if (task >= n_tasks) return;  // whole wave leaves together
     uint8_t *sb = lds[threadIdx.x >> 6];
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
@@ -224,13 +225,15 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
         }
     } else {
         wcsr_rows_launch(h, B, C, N, ws, stream);
-        if (h->n_tile_tasks > 0) {
-            dim3 grid((unsigned)ceil_div(h->n_tile_tasks, 4), (unsigned)ceil_div(N, 128)), block(256);
-            const int4 *tasks = (const int4 *)h->d_tile_tasks;
-            const int nt = (int)h->n_tile_tasks;
+        const int n_tiles = (int)ceil_div(N, 128);
+        const int64_t step = tasks_per_launch(n_tiles);
+        for (int64_t first = 0; first < h->n_tile_tasks; first += step) {
+            const int nt = (int)std::min(step, h->n_tile_tasks - first);
+            const dim3 grid = tile_grid(nt, n_tiles), block(256);
+            const int4 *tasks = (const int4 *)h->d_tile_tasks + first;
 #define ASP_WB(MTW)                                                                                                 \
     hipLaunchKernelGGL((wcsr_bf16_spmm_kernel<MTW>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bh, Ch, \
-                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N)
+                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N, n_tiles)
             if (h->b_row == 16) ASP_WB(1);
             else if (h->b_row == 32) ASP_WB(2);
             else ASP_WB(4);
