@@ -684,7 +684,6 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
     out.tasks.swap(rows);
 
     // the windows that stay with the tile kernels
-    std::vector<int64_t> tile_weight;
     for (int64_t w = 0; w < nw; ++w) {
         if (sparse[w]) continue;
         const int32_t lo = wrp[w], hi = wrp[w + 1], split = hi - lo > task_cols;
@@ -692,10 +691,8 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         for (int64_t c = lo; c < hi; c += task_cols) {
             const int64_t e = std::min<int64_t>(hi, c + task_cols);
             out.tile_tasks.insert(out.tile_tasks.end(), {(int32_t)w, (int32_t)c, (int32_t)e, split});
-            tile_weight.push_back(e - c + 16);
         }
     }
-    deal_to_xcds(out.tile_tasks, tile_weight);
 }
 
 void wcsr_zero_windows(const std::vector<int32_t> &wrp, int32_t task_cols, std::vector<int32_t> &zw) {

@@ -113,7 +113,7 @@ struct HostRows {
     std::vector<int32_t> tasks;       // [..][4] see wcsr_rows_kernel; empty tasks fill up
     std::vector<int32_t> chunks;      // [..][4] see wcsr_chunks_kernel; empty tasks fill up
     std::vector<int32_t> split;       // [..][4] = {row, first scratch row, scratch rows, 0} of rows longer than task_cols
-    std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only; empty tasks fill up
+    std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only
     std::vector<int32_t> tile_split;  // the split windows among those
 };
 

@@ -176,7 +176,6 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
     if (task >= n_tasks) return;  // whole wave leaves together
     const int lane = threadIdx.x & 63, kq = lane >> 4, jl = lane & 15;
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
-    if (td.y >= td.z) return;     // fills up a list
     int64_t n0[NG];  // first of the lane's 4 columns in each group
 #pragma unroll
     for (int g = 0; g < NG; ++g) n0[g] = lane_column<VEC>((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N);
@@ -279,7 +278,6 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
     if (task >= n_tasks) return;
     const int lane = threadIdx.x & 63, kq = lane >> 5, jl = lane & 31;
     const int4 td = tasks[task];
-    if (td.y >= td.z) return;
     const int64_t own_n0 = (int64_t)nt * 128 + 4 * jl, n0 = lane_column<VEC>(own_n0, N);
 
     f32x16 acc[MTW][4];

@@ -44,7 +44,6 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
     if (task >= n_tasks) return;  // whole wave leaves together
     uint8_t *sb = lds[threadIdx.x >> 6];
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
-    if (td.y >= td.z) return;     // fills up a list
     const int lane = threadIdx.x & 63, h = lane >> 4, p = lane & 15;
     // chunk c of the tile = 8 columns from chunk_col(c): chunks that would pass N end there instead and repeat columns of
     // their neighbour (the same bits), so that every access is 16 bytes at any N >= 8 and any alignment
