@@ -103,11 +103,12 @@ __device__ __forceinline__ int64_t lane_column(int64_t own_n, int64_t N) {
     return VEC && own_n > N - 4 ? N - 4 : own_n;
 }
 
+// wanted: whether the lane has a column of its own (a lane without one may load or not)
 template <bool VEC>
-__device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, int64_t N, int64_t n) {
+__device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, int64_t N, int64_t n, bool wanted = true) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);  // zeros for a pad column (col < 0) or past the edge
     if (VEC) {
-        if (col >= 0) {
+        if (col >= 0 && wanted) {
             const f32x4_any u = *(const f32x4_any *)(B + (int64_t)col * N + n);
             v = make_float4(u.x, u.y, u.z, u.w);
         }
@@ -121,7 +122,7 @@ __device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, 
     return v;
 }
 
-template <bool VEC>
+template <bool VEC, bool NONTEMPORAL = true>
 __device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int64_t M, int64_t N, int64_t own_n, float4 v,
                                      bool split) {
     if (row >= M || own_n >= N) return;
@@ -132,8 +133,10 @@ __device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int64_t
         if (n + 1 >= own_n && n + 1 < N) unsafeAtomicAdd(p + 1, v.y);
         if (n + 2 >= own_n && n + 2 < N) unsafeAtomicAdd(p + 2, v.z);
         if (n + 3 >= own_n && n + 3 < N) unsafeAtomicAdd(p + 3, v.w);
-    } else if (VEC) {
+    } else if (VEC && NONTEMPORAL) {
         __builtin_nontemporal_store(f32x4_any{v.x, v.y, v.z, v.w}, (f32x4_any *)p);
+    } else if (VEC) {
+        *(f32x4_any *)p = f32x4_any{v.x, v.y, v.z, v.w};
     } else {
         p[0] = v.x;
         if (n + 1 < N) p[1] = v.y;
@@ -164,7 +167,10 @@ __device__ __forceinline__ SplitTarget split_target(int4 td, int b_row, float *C
 // ---- window height 16: v_mfma_f32_16x16x4_f32 ----------------------------------------------------
 // lane l: kq = l / 16 picks one of 4 packed columns of a k step, jl = l % 16 is the MFMA N index.
 // NG = 64-column groups per wave (tile width BN = 64 * NG).
-template <int NG, bool VEC>
+// RAGGED, for 256-wide tiles whose rows end inside a cache line: lanes past N load nothing, and stores are ordinary ones, so
+// that L2 completes the lines that two rows share (band of 27, 500 000 rows, N = 200: 262 -> 254 us; narrower tiles
+// gain nothing from either, and lose up to 20 % with ordinary stores).
+template <int NG, bool VEC, bool RAGGED>
 __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
@@ -179,6 +185,9 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
     int64_t n0[NG];  // first of the lane's 4 columns in each group
 #pragma unroll
     for (int g = 0; g < NG; ++g) n0[g] = lane_column<VEC>((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N);
+    bool wanted[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wanted[g] = !RAGGED || (int64_t)nt * (64 * NG) + 64 * g + 4 * jl < N;
 
     f32x4 acc[NG][4];
 #pragma unroll
@@ -217,7 +226,7 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int g = 0; g < NG; ++g) c.b[d][h][g] = gather4<VEC>(B, idx[d][h], N, n0[g]);
+                for (int g = 0; g < NG; ++g) c.b[d][h][g] = gather4<VEC>(B, idx[d][h], N, n0[g], wanted[g]);
         }
     };
     auto multiply = [&](int base, const Chunk &c) {
@@ -258,7 +267,8 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float4 v = make_float4(acc[g][0][r], acc[g][1][r], acc[g][2][r], acc[g][3][r]);
-            put4<VEC>(out.base, out.row0 + 4 * kq + r, out.rows, N, (int64_t)nt * (64 * NG) + 64 * g + 4 * jl, v, out.atomic);
+            put4<VEC, !RAGGED>(out.base, out.row0 + 4 * kq + r, out.rows, N, (int64_t)nt * (64 * NG) + 64 * g + 4 * jl, v,
+                               out.atomic);
         }
 }
 
@@ -555,15 +565,9 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         const float *vals = (const float *)h->d_values;
         const float *Bf = (const float *)B;
         float *Cf = (float *)C;
-#define ASP_W16(NG)                                                                                                   \
-    do {                                                                                                              \
-        if (vec)                                                                                                      \
-            hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);       \
-        else                                                                                                          \
-            hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols); \
-    } while (0)
+#define ASP_W16(NG, VEC, RAGGED)                                                                                         \
+    hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, VEC, RAGGED>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bf, \
+                       Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
 #define ASP_W32(MTW)                                                                                                   \
     do {                                                                                                               \
         if (vec)                                                                                                       \
@@ -574,9 +578,11 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
                                vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
     } while (0)
         if (h->b_row == 16) {
-            if (p.bn == 256) ASP_W16(4);
-            else if (p.bn == 128) ASP_W16(2);
-            else ASP_W16(1);
+            if (!vec) ASP_W16(1, false, false);  // N < 4: one tile of any width
+            else if (p.bn == 256 && N % 32 != 0) ASP_W16(4, true, true);
+            else if (p.bn == 256) ASP_W16(4, true, false);
+            else if (p.bn == 128) ASP_W16(2, true, false);
+            else ASP_W16(1, true, false);
         } else if (h->b_row == 32) {
             ASP_W32(1);
         } else {
