@@ -218,6 +218,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     h->n_split_rows = (int64_t)rows.split.size() / 4;
     h->n_tile_tasks = (int64_t)rows.tile_tasks.size() / 4;
     h->n_tile_split = (int64_t)rows.tile_split.size();
+    h->tiles_dealt = rows.tiles_dealt;
     if ((s = upload(&h->d_tile_tasks, rows.tile_tasks.data(), rows.tile_tasks.size() * 4, stream))) return s;
     if ((s = upload(&h->d_tile_split, rows.tile_split.data(), rows.tile_split.size() * 4, stream))) return s;
     if (h->n_row_tasks > 0 || h->n_chunks > 0) {

@@ -536,10 +536,10 @@ namespace {
 
 // Reorders tasks (four ints each, four tasks to a workgroup) so that each of the 8 XCDs, which take workgroups
 // round-robin, gets one contiguous range of the given order with an eighth of the weight: tasks that are neighbours
-// in the order then meet in one L2.  Shorter ranges are filled up with empty tasks.
-void deal_to_xcds(std::vector<int32_t> &tasks, const std::vector<int64_t> &weight) {
+// in the order then meet in one L2.  Shorter ranges are filled up with empty tasks.  Lists too short for that stay (false).
+bool deal_to_xcds(std::vector<int32_t> &tasks, const std::vector<int64_t> &weight) {
     const size_t n = weight.size();
-    if (n < 256) return;  // less than a workgroup per compute unit and XCD to tell apart
+    if (n < 256) return false;  // less than a workgroup per compute unit and XCD to tell apart
     int64_t total = 0;
     for (int64_t w : weight) total += w;
     size_t cut[9] = {0};
@@ -560,6 +560,7 @@ void deal_to_xcds(std::vector<int32_t> &tasks, const std::vector<int64_t> &weigh
             std::copy(tasks.begin() + 4 * t, tasks.begin() + 4 * t + 4, dealt.begin() + 4 * to);
         }
     tasks.swap(dealt);
+    return true;
 }
 
 }  // namespace
@@ -684,6 +685,7 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
     out.tasks.swap(rows);
 
     // the windows that stay with the tile kernels
+    std::vector<int64_t> tile_weight;
     for (int64_t w = 0; w < nw; ++w) {
         if (sparse[w]) continue;
         const int32_t lo = wrp[w], hi = wrp[w + 1], split = hi - lo > task_cols;
@@ -691,8 +693,13 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         for (int64_t c = lo; c < hi; c += task_cols) {
             const int64_t e = std::min<int64_t>(hi, c + task_cols);
             out.tile_tasks.insert(out.tile_tasks.end(), {(int32_t)w, (int32_t)c, (int32_t)e, split});
+            tile_weight.push_back(e - c + 16);
         }
     }
+    // Neighbouring windows of a band share rows of B.  Lists that the chip holds at once: one range for each XCD (60 000 rows,
+    // band of 27, N = 256, height 16: bf16 19.3 against 16.8 us, fp32 34.9 / 34.6; 20 000 rows, band of 9, fp32 9.5 / 8.5).  Longer ones
+    // round-robin: they sweep the band anyway, and ranges are up to 3 % slower (1 000 000 rows, band of 13 and 24 long rows).
+    if (tile_weight.size() <= 4096) out.tiles_dealt = deal_to_xcds(out.tile_tasks, tile_weight);
 }
 
 void wcsr_zero_windows(const std::vector<int32_t> &wrp, int32_t task_cols, std::vector<int32_t> &zw) {

@@ -113,7 +113,8 @@ struct HostRows {
     std::vector<int32_t> tasks;       // [..][4] see wcsr_rows_kernel; empty tasks fill up
     std::vector<int32_t> chunks;      // [..][4] see wcsr_chunks_kernel; empty tasks fill up
     std::vector<int32_t> split;       // [..][4] = {row, first scratch row, scratch rows, 0} of rows longer than task_cols
-    std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only
+    std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only; empty tasks fill up
+    bool tiles_dealt = false;         // tile_tasks holds one range for each XCD (deal_to_xcds)
     std::vector<int32_t> tile_split;  // the split windows among those
 };
 
@@ -172,6 +173,7 @@ struct asp_handle {
     int32_t *d_ws_slot = nullptr;   // [n_windows] first scratch slot of a split window, -1 otherwise
     // WCSR: the kernels' work lists (HostRows) and the entries of the windows that are walked entry by entry
     int64_t n_row_tasks = 0, n_chunks = 0, n_split_rows = 0, n_tile_tasks = 0, n_tile_split = 0;
+    bool tiles_dealt = false;
     int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;

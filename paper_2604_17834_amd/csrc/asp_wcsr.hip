@@ -170,18 +170,19 @@ __device__ __forceinline__ SplitTarget split_target(int4 td, int b_row, float *C
 // RAGGED, for 256-wide tiles whose rows end inside a cache line: lanes past N load nothing, and stores are ordinary ones, so
 // that L2 completes the lines that two rows share (band of 27, 500 000 rows, N = 200: 262 -> 254 us; narrower tiles
 // gain nothing from either, and lose up to 20 % with ordinary stores).
-template <int NG, bool VEC, bool RAGGED>
+template <int NG, bool VEC, bool RAGGED, bool UNIFORM>
 __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, int n_tiles, float *__restrict__ ws,
+                                                          int64_t N, int n_tiles, bool dealt, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
-    const auto [task, nt] = wave_task(n_tiles);
+    const auto [task, nt] = wave_task<UNIFORM>(n_tiles, dealt);
     if (task >= n_tasks) return;  // whole wave leaves together
     const int lane = threadIdx.x & 63, kq = lane >> 4, jl = lane & 15;
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
+    if (td.y >= td.z) return;     // fills up a list
     int64_t n0[NG];  // first of the lane's 4 columns in each group
 #pragma unroll
     for (int g = 0; g < NG; ++g) n0[g] = lane_column<VEC>((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N);
@@ -280,14 +281,15 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
                                                           const float *__restrict__ B, float *__restrict__ C, int M,
-                                                          int64_t N, int n_tiles, float *__restrict__ ws,
+                                                          int64_t N, int n_tiles, bool dealt, float *__restrict__ ws,
                                                           const int32_t *__restrict__ ws_slot,
                                                           const int32_t *__restrict__ window_row_ptr, int task_cols) {
     constexpr int BRW = 32 * MTW;
-    const auto [task, nt] = wave_task(n_tiles);
+    const auto [task, nt] = wave_task<false>(n_tiles, dealt);
     if (task >= n_tasks) return;
     const int lane = threadIdx.x & 63, kq = lane >> 5, jl = lane & 31;
     const int4 td = tasks[task];
+    if (td.y >= td.z) return;
     const int64_t own_n0 = (int64_t)nt * 128 + 4 * jl, n0 = lane_column<VEC>(own_n0, N);
 
     f32x16 acc[MTW][4];
@@ -560,29 +562,35 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     const int64_t step = tasks_per_launch(p.n_tiles);
     for (int64_t first = 0; first < h->n_tile_tasks; first += step) {
         const int nt = (int)std::min(step, h->n_tile_tasks - first), M = (int)h->m;
-        const dim3 grid = tile_grid(nt, p.n_tiles), block(256);
+        const dim3 grid = tile_grid(nt, p.n_tiles, h->tiles_dealt), block(256);
         const int4 *tasks = (const int4 *)h->d_tile_tasks + first;
         const float *vals = (const float *)h->d_values;
         const float *Bf = (const float *)B;
         float *Cf = (float *)C;
-#define ASP_W16(NG, VEC, RAGGED)                                                                                         \
-    hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, VEC, RAGGED>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bf, \
-                       Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
+#define ASP_W16(NG, VEC, RAGGED, UNIFORM)                                                                           \
+    hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, VEC, RAGGED, UNIFORM>), grid, block, 0, stream, tasks, nt, h->d_col_idx, \
+                       vals, Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
 #define ASP_W32(MTW)                                                                                                   \
     do {                                                                                                               \
         if (vec)                                                                                                       \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
+                               Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
         else                                                                                                           \
             hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, p.n_tiles, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
+                               vals, Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
     } while (0)
         if (h->b_row == 16) {
-            if (!vec) ASP_W16(1, false, false);  // N < 4: one tile of any width
-            else if (p.bn == 256 && N % 32 != 0) ASP_W16(4, true, true);
-            else if (p.bn == 256) ASP_W16(4, true, false);
-            else if (p.bn == 128) ASP_W16(2, true, false);
-            else ASP_W16(1, true, false);
+            // 256-wide tiles in 168 registers, 3 waves per SIMD, where B and C are well past the 256 MB behind the L2s; in
+            // 176, 2 waves, where they are not: the waves of one moment then reach over less of them.  us, N = 256, 3 / 2 waves:
+            // 60 000 rows, band of 27 43 / 34, 500 000 rows 270 / 301; N = 200, 300 000 rows, band of 9 126 / 121.
+            const bool far = (h->m + h->k) * N * 4 >= (512ll << 20);
+            if (!vec) ASP_W16(1, false, false, false);  // N < 4: one tile of any width
+            else if (p.bn == 256 && N % 32 != 0 && far) ASP_W16(4, true, true, true);
+            else if (p.bn == 256 && N % 32 != 0) ASP_W16(4, true, true, false);
+            else if (p.bn == 256 && far) ASP_W16(4, true, false, true);
+            else if (p.bn == 256) ASP_W16(4, true, false, false);
+            else if (p.bn == 128) ASP_W16(2, true, false, false);
+            else ASP_W16(1, true, false, false);
         } else if (h->b_row == 32) {
             ASP_W32(1);
         } else {

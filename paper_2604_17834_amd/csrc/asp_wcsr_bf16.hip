@@ -35,15 +35,16 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
                                                              const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
                                                              float *__restrict__ ws, const int32_t *__restrict__ ws_slot,
                                                              const int32_t *__restrict__ window_row_ptr, int task_cols,
-                                                             int M, int64_t N, int n_tiles) {
+                                                             int M, int64_t N, int n_tiles, bool dealt) {
     constexpr int BRW = 16 * MTW;
     constexpr int A_TILE = BRW * 8;  // elements of one value tile [BRW][8]
     __shared__ __attribute__((aligned(16))) uint8_t lds[4][32 * 256];  // per wave: 32 gathered rows x 128 columns
 
-    const auto [task, nt] = wave_task(n_tiles);
+    const auto [task, nt] = wave_task<true>(n_tiles, dealt);
     if (task >= n_tasks) return;  // whole wave leaves together
     uint8_t *sb = lds[threadIdx.x >> 6];
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
+    if (td.y >= td.z) return;     // fills up a list
     const int lane = threadIdx.x & 63, h = lane >> 4, p = lane & 15;
     // chunk c of the tile = 8 columns from chunk_col(c): chunks that would pass N end there instead and repeat columns of
     // their neighbour (the same bits), so that every access is 16 bytes at any N >= 8 and any alignment
@@ -228,11 +229,11 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
         const int64_t step = tasks_per_launch(n_tiles);
         for (int64_t first = 0; first < h->n_tile_tasks; first += step) {
             const int nt = (int)std::min(step, h->n_tile_tasks - first);
-            const dim3 grid = tile_grid(nt, n_tiles), block(256);
+            const dim3 grid = tile_grid(nt, n_tiles, h->tiles_dealt), block(256);
             const int4 *tasks = (const int4 *)h->d_tile_tasks + first;
 #define ASP_WB(MTW)                                                                                                 \
     hipLaunchKernelGGL((wcsr_bf16_spmm_kernel<MTW>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bh, Ch, \
-                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N, n_tiles)
+                       ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N, n_tiles, h->tiles_dealt)
             if (h->b_row == 16) ASP_WB(1);
             else if (h->b_row == 32) ASP_WB(2);
             else ASP_WB(4);
