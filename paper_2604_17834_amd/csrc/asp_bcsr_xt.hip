@@ -16,6 +16,8 @@
 //
 // Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; elements past K count
 // as zeros.
+#include <algorithm>
+
 #include "asp_bcsr_pipe.h"
 
 namespace asp {
@@ -169,17 +171,26 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int4 *__res
 }
 
 // ---- host side ------------------------------------------------------------------------------------
+// false: too many rows for a launch
 template <int BR, int MT, int NT, int W, int UK>
-static void launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+static bool launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
     const int units_m = (int)h->n_brows * (BR / 32 / MT);
-    dim3 grid((unsigned)(units_m * ceil_div(N, 32 * NT))), block(W * 64);  // < M x N / 2^9 <= 2^31
-#define ASP_STRIP(VEC)                                                                                             \
-    hipLaunchKernelGGL((bcsr_xt_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, (const int4 *)h->d_rank_info,       \
-                       h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)X, (uint16_t *)Y, (int)h->m, \
-                       (int)h->k, N, units_m)
-    if (vec) ASP_STRIP(true);
-    else ASP_STRIP(false);
+    if (!launch_fits(units_m, W * 64)) return false;
+    // as many tokens at a time as the threads of a launch allow
+    const int64_t step = ((1ll << 32) - 1) / ((int64_t)units_m * W * 64) * (32 * NT);
+    for (int64_t first = 0; first < N; first += step) {
+        const int64_t tokens = std::min(step, N - first);
+        const uint16_t *x = (const uint16_t *)X + first * h->k;
+        uint16_t *y = (uint16_t *)Y + first * h->m;
+        dim3 grid((unsigned)(units_m * ceil_div(tokens, 32 * NT))), block(W * 64);
+#define ASP_STRIP(VEC)                                                                                                       \
+    hipLaunchKernelGGL((bcsr_xt_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, (const int4 *)h->d_rank_info, \
+                       h->d_col_idx, (const uint16_t *)h->d_values, x, y, (int)h->m, (int)h->k, tokens, units_m)
+        if (vec) ASP_STRIP(true);
+        else ASP_STRIP(false);
 #undef ASP_STRIP
+    }
+    return true;
 }
 
 // Shape of the wave tiles: the largest that still gives the chip enough of them, since a larger one reads fewer bytes
@@ -188,10 +199,11 @@ static void launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N,
 // at 256 22 / 18 / 19 / 23, at 768 52 / 39 / 43 / 33.  128 x 64 needs block-rows long enough that every wave of the
 // workgroup gets blocks: 512 tokens 31 / 24 us (64 x 64 / 128 x 64) with 15 blocks a row, 29 / 34 us with 3.
 template <int BR>
-static void launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64);
     if constexpr (BR == 128) {
-        if (h->n_units >= 8 * h->n_brows && h->n_brows * n64 >= cus * 3 / 4)
+        // (or too many rows for a launch of 64-row strips)
+        if ((h->n_units >= 8 * h->n_brows && h->n_brows * n64 >= cus * 3 / 4) || h->n_brows >= (1 << 23))
             return launch_strip<BR, 4, 2, 4, 32>(h, X, Y, N, vec, stream);
     }
     if constexpr (BR >= 64) {
@@ -203,14 +215,14 @@ static void launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N
         }
     }
     if (h->n_brows * (BR / 32) * n32 > 2 * cus) return launch_strip<BR, 1, 1, 4, 64>(h, X, Y, N, vec, stream);
-    launch_strip<BR, 1, 1, 8, 64>(h, X, Y, N, vec, stream);
+    return launch_strip<BR, 1, 1, 8, 64>(h, X, Y, N, vec, stream);
 }
 
 // any K, M, N <= ASP_MAX_N and alignment; vec: 16-byte aligned X and Y, K % 8 == 0, M % 8 == 0
-static void launch_any_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
-    if (h->b_row == 128) launch_strips<128>(h, X, Y, N, vec, stream);
-    else if (h->b_row == 64) launch_strips<64>(h, X, Y, N, vec, stream);
-    else launch_strips<32>(h, X, Y, N, vec, stream);
+static bool launch_any_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
+    if (h->b_row == 128) return launch_strips<128>(h, X, Y, N, vec, stream);
+    if (h->b_row == 64) return launch_strips<64>(h, X, Y, N, vec, stream);
+    return launch_strips<32>(h, X, Y, N, vec, stream);
 }
 
 // Kernel without matrix cores (a benchmarking switch, for the comparison): one thread per (token, quarter of the
@@ -305,8 +317,10 @@ asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, in
             }
             BcsrPlan p = {bn, bn ? (int32_t)ceil_div(N, bn) : 0, 1, 0};
             p.workgroups = h->n_brows * p.n_tiles;
-            if (bn == 0 || p.workgroups * 8 >= (1ll << 31)) launch_any_strips(h, X, Y, N, vec, stream);
-            else bcsr_dma_xt_launch(h, X, Y, N, p, stream);
+            if (bn != 0 && p.workgroups * 8 < (1ll << 31)) bcsr_dma_xt_launch(h, X, Y, N, p, stream);
+            else if (launch_any_strips(h, X, Y, N, vec, stream)) {}
+            else if (tiles_ok && wide_rows > 0) bcsr_wide_xt_launch(h, X, Y, N, stream);
+            else return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
         }
     }
     hipError_t e = hipGetLastError();

@@ -44,6 +44,8 @@ const Switches &switches();
 
 inline size_t dtype_size(int32_t dt) { return dt == ASP_DT_BF16 ? 2 : 4; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// HIP takes fewer than 2^32 threads along a dimension of a launch
+constexpr bool launch_fits(int64_t workgroups, int64_t threads) { return workgroups * threads < (1ll << 32); }
 
 // ---- host-side converted forms -------------------------------------------------------------
 // Zero-filled byte buffer taken from calloc: for gigabytes the pages arrive zeroed from the system and are first
