@@ -307,7 +307,7 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     const BcsrPlan p = bcsr_plan(h, N, aligned);
     if (p.workgroups * 8 >= (1ll << 31)) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
     if (h->dtype == ASP_DT_F32) {
-        bcsr_f32_launch(h, B, C, N, stream);
+        if (!bcsr_f32_launch(h, B, C, N, stream)) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
         hipError_t e32 = hipGetLastError();
         if (e32 != hipSuccess) return fail(ASP_ERR_HIP, std::string("BCSR fp32 kernel launch: ") + hipGetErrorString(e32));
         return ASP_OK;

@@ -204,17 +204,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32
 }
 
 // ---- host side ------------------------------------------------------------------------------------
+// false: too many threads for a launch
 template <int BR, int MT, int V, int WM, int WN, int WK>
-static void launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+static bool launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
     const int64_t n_tiles = ceil_div(N, 32 * V * WN);
     // as many groups of XCDs as can share the column tiles out evenly (within an eighth)
     int xcd_cols = 8;
     while (xcd_cols > 1 && 8 * ceil_div(n_tiles, xcd_cols) * xcd_cols > 9 * n_tiles) xcd_cols /= 2;
     const int64_t per_xcd = ceil_div(h->n_brows * (BR / (32 * MT * WM)), 8 / xcd_cols) * ceil_div(n_tiles, xcd_cols);
+    if (!launch_fits(8 * per_xcd, 64 * WM * WN * WK)) return false;
     dim3 grid((unsigned)(8 * per_xcd)), block(64 * WM * WN * WK);
     hipLaunchKernelGGL((bcsr_f32_spmm_kernel<BR, MT, V, WM, WN, WK>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
                        h->d_col_idx, (const float *)h->d_values, (const float *)B, (float *)C, (int)h->m, (int)h->k, N,
                        (int)h->n_brows, (int)n_tiles, xcd_cols);
+    return true;
 }
 
 // The largest wave tile that still gives the chip enough of them, and the narrower one where N would fill the wider one
@@ -222,7 +225,7 @@ static void launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, h
 // 18944 x 3584 at 2048 columns 239 / 258 / 267 / -, at 1024 151 / 133 / 140 / 160, at 64 - / - / 19.5 / 16.2;
 // 3584 x 9000 at 2048 163 / 124 / 128 / -, at 256 - / 42 / 29.6 / 29; 3000 x 3000 at 2048 - / 47 / 43 / 50, at 72 - / - / 12 / 9.
 template <int BR>
-static void launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+static bool launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
     constexpr int MT = BR >= 64 ? 2 : 1;
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64), n128 = ceil_div(N, 128);
     const int64_t tall = h->n_brows * BR / 64 * n128;  // tiles of 64 x 128 elements
@@ -232,14 +235,23 @@ static void launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t
     }
     if (N >= 2 && 2 * n64 * 8 <= n32 * 9 && 2 * h->n_brows * (BR / 32) * n64 >= 5 * cus)
         return launch_f32<BR, 1, 2, 1, 1, 4>(h, B, C, N, stream);
-    launch_f32<BR, 1, 1, 1, 1, 8>(h, B, C, N, stream);
+    return launch_f32<BR, 1, 1, 1, 1, 8>(h, B, C, N, stream);
 }
 
-// any N <= ASP_MAX_N and alignment
-void bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
-    if (h->b_row == 128) launch_f32_rows<128>(h, B, C, N, stream);
-    else if (h->b_row == 64) launch_f32_rows<64>(h, B, C, N, stream);
-    else launch_f32_rows<32>(h, B, C, N, stream);
+// Hundreds of millions of rows can take more threads than a launch has: then the shapes with the fewest threads
+template <int BR>
+static bool launch_f32_any(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+    constexpr int MT = BR >= 64 ? 2 : 1;
+    if (launch_f32_rows<BR>(h, B, C, N, stream)) return true;
+    if (N >= 4) return launch_f32<BR, MT, 4, BR / (32 * MT), 2, 1>(h, B, C, N, stream);
+    return launch_f32<BR, 1, 1, BR / 32, 1, 1>(h, B, C, N, stream);
+}
+
+// any N <= ASP_MAX_N and alignment; false: too many output tiles
+bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
+    if (h->b_row == 128) return launch_f32_any<128>(h, B, C, N, stream);
+    if (h->b_row == 64) return launch_f32_any<64>(h, B, C, N, stream);
+    return launch_f32_any<32>(h, B, C, N, stream);
 }
 
 }  // namespace asp

@@ -38,3 +38,32 @@ def test_xt_strips_of_four_million_tokens():
     tok = torch.from_numpy(np.r_[0:16, 1234567:1234583, step - 16:step + 16, N - 16:N]).cuda()
     _check(a, np.ascontiguousarray(_bits(X[tok]).T), np.ascontiguousarray(_bits(Y[tok]).T))
     assert _written(Y)
+
+
+@pytest.mark.parametrize("b,N", [(128, 1), (32, 9)])
+def test_fp32_blocks_of_268_million_rows(b, N):
+    # 32 x 32 tiles of eight waves would take 2^32 threads from 2^28 rows on; the rows around the middle and the end are not empty
+    m, k = (1 << 28) + 5, 300
+    part = synth.block_sparse_bernoulli(4 * b, k, b, b, 0.3, seed=912, dtype="f32", std=1.0)
+    first = [0, (m // 2) // b * b, m - (m % b) - 3 * b]
+    lens = np.diff(part.row_ptr)
+    row_ptr = np.zeros(m + 1, np.int32)
+    rows = np.concatenate([np.arange(f, min(m, f + 4 * b)) for f in first])
+    keep = np.concatenate([lens[:min(m, f + 4 * b) - f] for f in first])
+    row_ptr[rows + 1] = keep
+    np.cumsum(row_ptr, out=row_ptr, dtype=np.int32)
+    take = np.concatenate([np.arange(part.row_ptr[min(m, f + 4 * b) - f]) for f in first])
+    a = synth.Csr(m, k, row_ptr, part.col_idx[take], part.values[take], "f32")
+    print("case fp32 rows", m, "b", b, "N", N, flush=True)
+    B = _device_normal(k, N, "f32", seed=913)
+    C = _poisoned(m, N, "f32")
+    h = asp.asp_create_from_csr("bcsr", "f32", b, b, a.m, a.k, a.row_ptr, a.col_idx, a.values)
+    try:
+        asp.asp_spmm(h, B.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        asp.asp_destroy(h)
+    assert _written(C, 1 << 26)
+    sub = synth.Csr(len(rows), k, np.concatenate([[0], np.cumsum(keep)]).astype(np.int32), a.col_idx, a.values, "f32")
+    _check(sub, _bits(B), _bits(C[torch.from_numpy(rows).cuda()]))
+    assert int((C != 0).any(dim=1).sum()) == int((keep > 0).sum())
