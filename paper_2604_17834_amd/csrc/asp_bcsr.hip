@@ -292,14 +292,17 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
     return p;
 }
 
+// false: too many threads for a launch
 template <int BR, int BN, int WM, int WN, bool VEC>
-static void launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
+static bool launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     const int64_t total = p.workgroups;
     const int tiles_per_xcd = (int)ceil_div(total, 8);
+    if (!launch_fits(tiles_per_xcd * 8ll, WM * WN * 64)) return false;
     dim3 grid((unsigned)(tiles_per_xcd * 8)), block(WM * WN * 64);
     hipLaunchKernelGGL((bcsr_spmm_kernel<BR, BR, BN, WM, WN, VEC>), grid, block, 0, stream, h->d_row_ptr, h->d_col_idx,
                        (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m, (int)h->k, (int)N,
                        (int)h->n_brows, p.n_tiles, tiles_per_xcd);
+    return true;
 }
 
 asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
@@ -324,33 +327,38 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         // often, with fewer tiles the longest block-rows set the time.  us, 64 / 128 wide: 18944 x 3584 at 90 %, N = 8001,
         // 128 / 64 / 32-row blocks 346 / 271, 356 / 316, 502 / 403; 5003 x 3331 at 80 %, N = 3001 58.7 / 53.7, 67 / 67, 100 / 86;
         // 1500 x 8001 at 75 %, N = 8001, 64-row (1512 tiles) 148 / 180.  (256 wide: slower than both.)
-        BcsrPlan w = p;
+        // (64-wide ones again where a single column tile of 2^29 rows would pass the threads of a launch)
+        bool done = false;
         if (h->n_brows * ceil_div(N, 128) >= (h->b_row == 128 ? 3 : h->b_row == 64 ? 8 : 4) * (int64_t)h->n_cus) {
+            BcsrPlan w = p;
             w.bn = 128;
             w.n_tiles = (int32_t)ceil_div(N, 128);
             w.workgroups = h->n_brows * w.n_tiles;
+            if (h->b_row == 128) done = launch<128, 128, 2, 2, false>(h, B, C, N, w, stream);
+            else if (h->b_row == 64) done = launch<64, 128, 2, 2, false>(h, B, C, N, w, stream);
+            else done = launch<32, 128, 1, 4, false>(h, B, C, N, w, stream);
         }
-        switch (h->b_row * 1000 + w.bn) {
-            case 128128: launch<128, 128, 2, 2, false>(h, B, C, N, w, stream); break;
-            case 128064: launch<128, 64, 2, 2, false>(h, B, C, N, w, stream); break;
-            case 64128: launch<64, 128, 2, 2, false>(h, B, C, N, w, stream); break;
-            case 64064: launch<64, 64, 2, 2, false>(h, B, C, N, w, stream); break;
-            case 32128: launch<32, 128, 1, 4, false>(h, B, C, N, w, stream); break;
-            default: launch<32, 64, 1, 2, false>(h, B, C, N, w, stream); break;
+        if (!done) {
+            if (h->b_row == 128) done = launch<128, 64, 2, 2, false>(h, B, C, N, p, stream);
+            else if (h->b_row == 64) done = launch<64, 64, 2, 2, false>(h, B, C, N, p, stream);
+            else done = launch<32, 64, 1, 2, false>(h, B, C, N, p, stream);
         }
+        if (!done) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
     } else {
+        bool done = false;
         switch (key) {
-            case 128256: launch<128, 256, 2, 2, true>(h, B, C, N, p, stream); break;
-            case 128128: launch<128, 128, 2, 2, true>(h, B, C, N, p, stream); break;
-            case 128064: launch<128, 64, 2, 2, true>(h, B, C, N, p, stream); break;
-            case 64256: launch<64, 256, 1, 4, true>(h, B, C, N, p, stream); break;
-            case 64128: launch<64, 128, 2, 2, true>(h, B, C, N, p, stream); break;
-            case 64064: launch<64, 64, 2, 2, true>(h, B, C, N, p, stream); break;
-            case 32256: launch<32, 256, 1, 4, true>(h, B, C, N, p, stream); break;
-            case 32128: launch<32, 128, 1, 4, true>(h, B, C, N, p, stream); break;
-            case 32064: launch<32, 64, 1, 2, true>(h, B, C, N, p, stream); break;
+            case 128256: done = launch<128, 256, 2, 2, true>(h, B, C, N, p, stream); break;
+            case 128128: done = launch<128, 128, 2, 2, true>(h, B, C, N, p, stream); break;
+            case 128064: done = launch<128, 64, 2, 2, true>(h, B, C, N, p, stream); break;
+            case 64256: done = launch<64, 256, 1, 4, true>(h, B, C, N, p, stream); break;
+            case 64128: done = launch<64, 128, 2, 2, true>(h, B, C, N, p, stream); break;
+            case 64064: done = launch<64, 64, 2, 2, true>(h, B, C, N, p, stream); break;
+            case 32256: done = launch<32, 256, 1, 4, true>(h, B, C, N, p, stream); break;
+            case 32128: done = launch<32, 128, 1, 4, true>(h, B, C, N, p, stream); break;
+            case 32064: done = launch<32, 64, 1, 2, true>(h, B, C, N, p, stream); break;
             default: return fail(ASP_ERR_UNSUPPORTED, "no kernel for this block size / tile width");
         }
+        if (!done) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ASP_ERR_HIP, std::string("BCSR kernel launch: ") + hipGetErrorString(e));

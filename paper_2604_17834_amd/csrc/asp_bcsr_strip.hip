@@ -186,9 +186,11 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
 }
 
 // ---- host side ------------------------------------------------------------------------------------
+// false: too many threads for a launch
 template <int BR, int MT, int NT, int W, int UK>
-static void launch_strip(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
+static bool launch_strip(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
     const int units_m = (int)h->n_brows * (BR / 32 / MT);
+    if (!launch_fits(units_m * ceil_div(N, 32 * NT), W * 64)) return false;
     dim3 grid((unsigned)(units_m * ceil_div(N, 32 * NT))), block(W * 64);
 #define ASP_STRIP(VEC)                                                                                             \
     hipLaunchKernelGGL((bcsr_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, (const int4 *)h->d_rank_info,          \
@@ -197,6 +199,7 @@ static void launch_strip(const asp_handle *h, const void *B, void *C, int64_t N,
     if (vec) ASP_STRIP(true);
     else ASP_STRIP(false);
 #undef ASP_STRIP
+    return true;
 }
 
 // Shape of the wave tiles, the largest that still gives the chip enough of them.  At 90 %, us a call, 32 x 32 x 8 waves /
@@ -204,7 +207,7 @@ static void launch_strip(const asp_handle *h, const void *B, void *C, int64_t N,
 // 18944 x 3584, whose strips have too few units for 8 waves, at 64 columns 8.2 / 8.4 / 6.7, at 512 - / 45 / 25.6.
 // 32-row blocks, 32 x 64 / 32 x 128: 3584 x 18944 at 512 columns 34 / 29, 18944 x 3584 27 / 23.5 (aligned rows only).
 template <int BR>
-static void launch_strips(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
+static bool launch_strips(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n64 = ceil_div(N, 64);
     const bool short_rows = h->n_units * (BR / 32) < 14 * h->n_brows;
     if constexpr (BR >= 64) {
@@ -217,8 +220,8 @@ static void launch_strips(const asp_handle *h, const void *B, void *C, int64_t N
         if (vec && 2 * h->n_brows * ceil_div(N, 128) >= 3 * cus) return launch_strip<BR, 1, 4, 2, 32>(h, B, C, N, vec, stream);
         if (2 * h->n_brows * n64 >= 3 * cus) return launch_strip<BR, 1, 2, 4, 64>(h, B, C, N, vec, stream);
     }
-    if (short_rows) launch_strip<BR, 1, 1, 4, 64>(h, B, C, N, vec, stream);
-    else launch_strip<BR, 1, 1, 8, 64>(h, B, C, N, vec, stream);
+    if (short_rows) return launch_strip<BR, 1, 1, 4, 64>(h, B, C, N, vec, stream);
+    return launch_strip<BR, 1, 1, 8, 64>(h, B, C, N, vec, stream);
 }
 
 // Whether strips are the faster choice: estimates in us, linear in the longest block-row (K slices of 32) and in the
@@ -251,10 +254,9 @@ static bool strips_win(const asp_handle *h, int64_t N, const BcsrPlan &p) {
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     if (h->n_units == 0 || N >= (1ll << 25) || !strips_win(h, N, p)) return false;
     const bool vec = p.vectorized != 0;
-    if (h->b_row == 128) launch_strips<128>(h, B, C, N, vec, stream);
-    else if (h->b_row == 64) launch_strips<64>(h, B, C, N, vec, stream);
-    else launch_strips<32>(h, B, C, N, vec, stream);
-    return true;
+    if (h->b_row == 128) return launch_strips<128>(h, B, C, N, vec, stream);
+    if (h->b_row == 64) return launch_strips<64>(h, B, C, N, vec, stream);
+    return launch_strips<32>(h, B, C, N, vec, stream);
 }
 
 }  // namespace asp

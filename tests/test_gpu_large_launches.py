@@ -40,11 +40,9 @@ def test_xt_strips_of_four_million_tokens():
     assert _written(Y)
 
 
-@pytest.mark.parametrize("b,N", [(128, 1), (32, 9)])
-def test_fp32_blocks_of_268_million_rows(b, N):
-    # 32 x 32 tiles of eight waves would take 2^32 threads from 2^28 rows on; the rows around the middle and the end are not empty
-    m, k = (1 << 28) + 5, 300
-    part = synth.block_sparse_bernoulli(4 * b, k, b, b, 0.3, seed=912, dtype="f32", std=1.0)
+def _few_block_rows(m, k, b, N, dtype):
+    """m rows of which 12 block-rows (at both ends and in the middle) are not empty, against the oracle."""
+    part = synth.block_sparse_bernoulli(4 * b, k, b, b, 0.3, seed=912, dtype=dtype)
     first = [0, (m // 2) // b * b, m - (m % b) - 3 * b]
     lens = np.diff(part.row_ptr)
     row_ptr = np.zeros(m + 1, np.int32)
@@ -53,17 +51,26 @@ def test_fp32_blocks_of_268_million_rows(b, N):
     row_ptr[rows + 1] = keep
     np.cumsum(row_ptr, out=row_ptr, dtype=np.int32)
     take = np.concatenate([np.arange(part.row_ptr[min(m, f + 4 * b) - f]) for f in first])
-    a = synth.Csr(m, k, row_ptr, part.col_idx[take], part.values[take], "f32")
-    print("case fp32 rows", m, "b", b, "N", N, flush=True)
-    B = _device_normal(k, N, "f32", seed=913)
-    C = _poisoned(m, N, "f32")
-    h = asp.asp_create_from_csr("bcsr", "f32", b, b, a.m, a.k, a.row_ptr, a.col_idx, a.values)
+    a = synth.Csr(m, k, row_ptr, part.col_idx[take], part.values[take], dtype)
+    print("case rows", m, dtype, "b", b, "N", N, flush=True)
+    B = _device_normal(k, N, dtype, seed=913)
+    C = _poisoned(m, N, dtype)
+    h = asp.asp_create_from_csr("bcsr", dtype, b, b, a.m, a.k, a.row_ptr, a.col_idx, a.values)
     try:
         asp.asp_spmm(h, B.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
     finally:
         asp.asp_destroy(h)
     assert _written(C, 1 << 26)
-    sub = synth.Csr(len(rows), k, np.concatenate([[0], np.cumsum(keep)]).astype(np.int32), a.col_idx, a.values, "f32")
+    sub = synth.Csr(len(rows), k, np.concatenate([[0], np.cumsum(keep)]).astype(np.int32), a.col_idx, a.values, dtype)
     _check(sub, _bits(B), _bits(C[torch.from_numpy(rows).cuda()]))
-    assert int((C != 0).any(dim=1).sum()) == int((keep > 0).sum())
+    assert sum(int((C[r:r + (1 << 26)] != 0).any(dim=1).sum()) for r in range(0, m, 1 << 26)) == int((keep > 0).sum())
+
+
+@pytest.mark.parametrize("b,N", [(128, 1), (32, 9)])
+def test_fp32_blocks_of_268_million_rows(b, N):
+    _few_block_rows((1 << 28) + 5, 300, b, N, "f32")       # 32 x 32 tiles of eight waves: 2^32 threads from 2^28 rows on
+
+
+def test_strips_of_537_million_rows():
+    _few_block_rows((1 << 29) + 5, 300, 32, 1, "bf16")     # strips of 32 rows, four waves each: 2^32 threads from 2^29 rows on
