@@ -52,12 +52,14 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // ---- zero the C rows of windows that are empty or split: fp32 calls without scratch, whose split windows are summed
 // with atomics
-__global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__restrict__ zero_windows, int b_row,
-                                                             float *__restrict__ C, int M, int64_t N) {
-    const int64_t r0 = (int64_t)zero_windows[blockIdx.x] * b_row;
-    const int64_t r1 = r0 + b_row < M ? r0 + b_row : M;
-    float *base = C + r0 * N;
-    for (int64_t i = threadIdx.x; i < (r1 - r0) * N; i += 256) base[i] = 0.f;
+__global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__restrict__ zero_windows, int n_windows,
+                                                             int b_row, float *__restrict__ C, int M, int64_t N) {
+    for (int w = blockIdx.x; w < n_windows; w += gridDim.x) {
+        const int64_t r0 = (int64_t)zero_windows[w] * b_row;
+        const int64_t r1 = r0 + b_row < M ? r0 + b_row : M;
+        float *base = C + r0 * N;
+        for (int64_t i = threadIdx.x; i < (r1 - r0) * N; i += 256) base[i] = 0.f;
+    }
 }
 
 // ---- rows of split windows from the partial tiles of their tasks (Section III-C) ---------------------
@@ -65,32 +67,34 @@ __global__ __launch_bounds__(256) void wcsr_zero_rows_kernel(const int32_t *__re
 // buffer.  One thread per output element adds the tiles in task order (fixed order: bitwise reproducible)
 // and rounds once to the output type.
 template <typename OutT, int U>  // U = elements per thread and access: 4 (16-byte loads) or 1
-__global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *__restrict__ split_windows,
+__global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *__restrict__ split_windows, int n_windows,
                                                                 const int32_t *__restrict__ ws_slot,
                                                                 const int32_t *__restrict__ window_row_ptr,
                                                                 int task_cols, int b_row, OutT *__restrict__ C,
                                                                 const float *__restrict__ ws, int M, int64_t N) {
     typedef float vec_t __attribute__((ext_vector_type(U)));
     typedef OutT out_t __attribute__((ext_vector_type(U)));
-    const int w = split_windows[blockIdx.x];
-    const int slot0 = ws_slot[w];
-    const int parts = (int)(((int64_t)window_row_ptr[w + 1] - window_row_ptr[w] + task_cols - 1) / task_cols);
-    const int64_t r0 = (int64_t)w * b_row, r1 = r0 + b_row < M ? r0 + b_row : M;
-    const int64_t units = (r1 - r0) * N / U, tile = (int64_t)b_row * N / U;
-    const vec_t *src = (const vec_t *)(ws + (int64_t)slot0 * b_row * N);
-    out_t *dst = (out_t *)(C + r0 * N);
-    for (int64_t i = (int64_t)blockIdx.y * 256 + threadIdx.x; i < units; i += (int64_t)gridDim.y * 256) {
-        vec_t sum = src[i];
-        int j = 1;
-        for (; j + 8 <= parts; j += 8) {  // 8 independent loads in flight, added in task order
-            vec_t t[8];
+    for (int sw = blockIdx.x; sw < n_windows; sw += gridDim.x) {
+        const int w = split_windows[sw];
+        const int slot0 = ws_slot[w];
+        const int parts = (int)(((int64_t)window_row_ptr[w + 1] - window_row_ptr[w] + task_cols - 1) / task_cols);
+        const int64_t r0 = (int64_t)w * b_row, r1 = r0 + b_row < M ? r0 + b_row : M;
+        const int64_t units = (r1 - r0) * N / U, tile = (int64_t)b_row * N / U;
+        const vec_t *src = (const vec_t *)(ws + (int64_t)slot0 * b_row * N);
+        out_t *dst = (out_t *)(C + r0 * N);
+        for (int64_t i = (int64_t)blockIdx.y * 256 + threadIdx.x; i < units; i += (int64_t)gridDim.y * 256) {
+            vec_t sum = src[i];
+            int j = 1;
+            for (; j + 8 <= parts; j += 8) {  // 8 independent loads in flight, added in task order
+                vec_t t[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) t[e] = src[(j + e) * tile + i];
+                for (int e = 0; e < 8; ++e) t[e] = src[(j + e) * tile + i];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += t[e];
+                for (int e = 0; e < 8; ++e) sum += t[e];
+            }
+            for (; j < parts; ++j) sum += src[j * tile + i];
+            dst[i] = __builtin_convertvector(sum, out_t);  // bf16: round to nearest even
         }
-        for (; j < parts; ++j) sum += src[j * tile + i];
-        dst[i] = __builtin_convertvector(sum, out_t);  // bf16: round to nearest even
     }
 }
 
@@ -533,10 +537,10 @@ void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float
     if (h->n_tile_split == 0) return;
     const bool vec = N % 4 == 0 && ((uintptr_t)C & 15) == 0;
     const unsigned gy = (unsigned)std::min<int64_t>(64, ceil_div((int64_t)h->b_row * N, vec ? 1024 : 256));
-    dim3 grid((unsigned)h->n_tile_split, gy), block(256);
+    dim3 grid((unsigned)std::min<int64_t>(h->n_tile_split, 1 << 23), gy), block(256);
 #define ASP_SUM(T, U)                                                                                              \
-    hipLaunchKernelGGL((wcsr_sum_partials_kernel<T, U>), grid, block, 0, stream, h->d_tile_split, h->d_ws_slot,   \
-                       h->d_row_ptr, h->task_cols, h->b_row, (T *)C, ws, (int)h->m, N)
+    hipLaunchKernelGGL((wcsr_sum_partials_kernel<T, U>), grid, block, 0, stream, h->d_tile_split,                  \
+                       (int)h->n_tile_split, h->d_ws_slot, h->d_row_ptr, h->task_cols, h->b_row, (T *)C, ws, (int)h->m, N)
     if (h->dtype == ASP_DT_BF16) {
         if (vec) ASP_SUM(__bf16, 4);
         else ASP_SUM(__bf16, 1);
@@ -556,8 +560,8 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
     const bool partial = h->n_split_tasks > 0 && ws_buf && ws_floats >= wcsr_scratch_floats(h, N);
     float *ws = partial ? ws_buf : nullptr;
     if (h->n_split_tasks > 0 && !partial)
-        hipLaunchKernelGGL(wcsr_zero_rows_kernel, dim3((unsigned)h->n_zero_windows), dim3(256), 0, stream,
-                           h->d_zero_windows, h->b_row, (float *)C, (int)h->m, N);
+        hipLaunchKernelGGL(wcsr_zero_rows_kernel, dim3((unsigned)std::min<int64_t>(h->n_zero_windows, 1 << 23)), dim3(256), 0,
+                           stream, h->d_zero_windows, (int)h->n_zero_windows, h->b_row, (float *)C, (int)h->m, N);
     wcsr_rows_launch(h, B, C, N, ws, stream);
     const int64_t step = tasks_per_launch(p.n_tiles);
     for (int64_t first = 0; first < h->n_tile_tasks; first += step) {

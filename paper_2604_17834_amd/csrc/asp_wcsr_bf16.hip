@@ -217,7 +217,8 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
                     "bf16 WCSR with split windows needs scratch memory for this width: call asp_reserve(handle, N) first");
     if (!scratch || (N < 8 && h->n_tile_tasks > 0)) {
         dim3 grid((unsigned)h->n_brows, (unsigned)ceil_div(N, 64)), block(64);
-        if (grid.y > 65535) return fail(ASP_ERR_UNSUPPORTED, "N too large for the element-wise WCSR path");
+        if (grid.y > 65535 || !launch_fits(h->n_brows, 64))
+            return fail(ASP_ERR_UNSUPPORTED, "M or N too large for the element-wise WCSR path");
         switch (h->b_row) {
             case 16: hipLaunchKernelGGL(wcsr_bf16_generic_kernel<16>, grid, block, 0, stream, h->d_row_ptr, h->d_col_idx, vals, Bh, Ch, M, N); break;
             case 32: hipLaunchKernelGGL(wcsr_bf16_generic_kernel<32>, grid, block, 0, stream, h->d_row_ptr, h->d_col_idx, vals, Bh, Ch, M, N); break;

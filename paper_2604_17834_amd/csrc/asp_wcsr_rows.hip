@@ -20,6 +20,8 @@
 //
 // Any N and any alignment: a lane owns E adjacent columns; the last lane of a row moves left so that it ends at N and
 // computes some of its neighbour's columns a second time (the same bits), so that no access leaves the row.
+#include <algorithm>
+
 #include "asp_internal.h"
 
 namespace asp {
@@ -320,57 +322,65 @@ __global__ __launch_bounds__(256) void wcsr_rows_kernel(const int4 *__restrict__
 // 12 us, with <64, 16> 19 us), <64, 4> for short ones (12 000 rows of 5 on average, N = 128: with <16, 64> most of a
 // workgroup would have nothing to add).
 template <typename T, int COLS, int J>
-__global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__restrict__ split,
+__global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__restrict__ split, int n_split,
                                                                 const float *__restrict__ ws, T *__restrict__ C, int64_t N) {
     __shared__ float part[J][COLS + 1];
-    const int4 s = split[blockIdx.x];
     const int c = threadIdx.x % COLS, first = threadIdx.x / COLS;
     const int64_t n = (int64_t)blockIdx.y * COLS + c;
-    float sum = 0.f;
-    if (n < N) {
-        const float *src = ws + (int64_t)s.y * N + n;
-        int j = first;
-        for (; j + J * 7 < s.z; j += J * 8) {
-            float t[8];
+    for (int row = blockIdx.x; row < n_split; row += gridDim.x) {  // (once, but for millions of rows)
+        const int4 s = split[row];
+        float sum = 0.f;
+        if (n < N) {
+            const float *src = ws + (int64_t)s.y * N + n;
+            int j = first;
+            for (; j + J * 7 < s.z; j += J * 8) {
+                float t[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) t[e] = src[(int64_t)(j + J * e) * N];
+                for (int e = 0; e < 8; ++e) t[e] = src[(int64_t)(j + J * e) * N];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += t[e];
+                for (int e = 0; e < 8; ++e) sum += t[e];
+            }
+            for (; j < s.z; j += J) sum += src[(int64_t)j * N];
         }
-        for (; j < s.z; j += J) sum += src[(int64_t)j * N];
-    }
-    part[first][c] = sum;
-    __syncthreads();
-    if (first == 0 && n < N) {
-        float t = part[0][c];
+        __syncthreads();  // `part` may still be read for the row before
+        part[first][c] = sum;
+        __syncthreads();
+        if (first == 0 && n < N) {
+            float t = part[0][c];
 #pragma unroll
-        for (int e = 1; e < J; ++e) t += part[e][c];
-        T o;
-        narrow(t, o);
-        C[(int64_t)s.x * N + n] = o;
+            for (int e = 1; e < J; ++e) t += part[e][c];
+            T o;
+            narrow(t, o);
+            C[(int64_t)s.x * N + n] = o;
+        }
     }
 }
 
 // ---- host side ------------------------------------------------------------------------------------
 template <typename T>
 static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
-    // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
-#define ASP_ROWS(E, CE, CL)                                                                                           \
-    hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                              \
-                       dim3((unsigned)ceil_div(h->n_chunks + h->n_row_tasks, 4), (unsigned)ceil_div(N, 64 * (E))),    \
-                       dim3(256), 0, stream, (const int4 *)h->d_chunks, (int)h->n_chunks, (const int4 *)h->d_row_tasks, \
-                       (int)h->n_row_tasks, h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
-    if (N <= 16) ASP_ROWS(1, 1, 16);
-    else if (N <= 32) ASP_ROWS(1, 2, 16);
-    else if (N <= 64) ASP_ROWS(1, 4, 16);
-    else if (N <= 128) ASP_ROWS(2, sizeof(T) == 2 ? 8 : 2, sizeof(T) == 2 ? 16 : 64);
-    else if (N <= 256 || sizeof(T) == 4) ASP_ROWS(4, 4, 64);
-    else if constexpr (sizeof(T) == 2) ASP_ROWS(8, 8, 64);
+    // a launch takes fewer than 2^32 threads
+    const int64_t waves = h->n_chunks + h->n_row_tasks, step = (1 << 26) - 32;
+    for (int64_t first = 0; first < waves; first += step) {
+        const int64_t end = std::min(waves, first + step);
+        const int64_t c0 = std::min(first, h->n_chunks), c1 = std::min(end, h->n_chunks), t0 = first - c0, t1 = end - c1;
+        // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
+#define ASP_ROWS(E, CE, CL)                                                                                          \
+    hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                             \
+                       dim3((unsigned)ceil_div(end - first, 4), (unsigned)ceil_div(N, 64 * (E))), dim3(256), 0, stream, \
+                       (const int4 *)h->d_chunks + c0, (int)(c1 - c0), (const int4 *)h->d_row_tasks + t0, (int)(t1 - t0), \
+                       h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
+        if (N <= 16) ASP_ROWS(1, 1, 16);
+        else if (N <= 32) ASP_ROWS(1, 2, 16);
+        else if (N <= 64) ASP_ROWS(1, 4, 16);
+        else if (N <= 128) ASP_ROWS(2, sizeof(T) == 2 ? 8 : 2, sizeof(T) == 2 ? 16 : 64);
+        else if (N <= 256 || sizeof(T) == 4) ASP_ROWS(4, 4, 64);
+        else if constexpr (sizeof(T) == 2) ASP_ROWS(8, 8, 64);
 #undef ASP_ROWS
+    }
 }
 
 void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
-    if (h->n_chunks + h->n_row_tasks == 0) return;
     if (h->dtype == ASP_DT_BF16) launch_rows<uint16_t>(h, B, C, N, ws, stream);
     else launch_rows<float>(h, B, C, N, ws, stream);
 }
@@ -379,8 +389,9 @@ void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *
     if (h->n_split_rows == 0) return;
     const bool many = h->n_chunks > 32 * h->n_split_rows;
 #define ASP_ROWS_SUM(T, COLS, J)                                                                                          \
-    hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>), dim3((unsigned)h->n_split_rows, (unsigned)ceil_div(N, COLS)), \
-                       dim3((COLS) * (J)), 0, stream, (const int4 *)h->d_split_rows, ws, (T *)C, N)
+    hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>),                                                                \
+                       dim3((unsigned)std::min<int64_t>(h->n_split_rows, 1 << 21), (unsigned)ceil_div(N, COLS)),          \
+                       dim3((COLS) * (J)), 0, stream, (const int4 *)h->d_split_rows, (int)h->n_split_rows, ws, (T *)C, N)
     if (h->dtype == ASP_DT_BF16) {
         if (many && N <= 65535 * 16) ASP_ROWS_SUM(uint16_t, 16, 64);
         else ASP_ROWS_SUM(uint16_t, 64, 4);

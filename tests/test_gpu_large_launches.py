@@ -74,3 +74,49 @@ def test_fp32_blocks_of_268_million_rows(b, N):
 
 def test_strips_of_537_million_rows():
     _few_block_rows((1 << 29) + 5, 300, 32, 1, "bf16")     # strips of 32 rows, four waves each: 2^32 threads from 2^29 rows on
+
+
+def test_wcsr_seventeen_million_split_rows():
+    # every row is longer than task_cols: one sum per row, 256 threads each
+    m, per_row, k, N = (1 << 24) + 24, 9, 16 * 9 * 7, 1
+    r = np.arange(m, dtype=np.int32)
+    # row r of a window takes columns first(window) + r + 16 j: ascending, no two rows of a window share one
+    col_idx = ((r // 16 % 7) * 144 + r % 16)[:, None] + 16 * np.arange(per_row, dtype=np.int32)[None, :]
+    row_ptr = np.arange(m + 1, dtype=np.int32) * per_row
+    values = np.random.default_rng(914).uniform(-1.0, 1.0, m * per_row).astype(np.float32)
+    a = synth.Csr(m, k, row_ptr, col_idx.ravel(), values, "f32")
+    print("case wcsr split rows", m, "nnz", m * per_row, flush=True)
+    h = asp.asp_create_from_csr("wcsr", "f32", 16, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values, task_cols=8)
+    try:
+        B = _device_normal(k, N, "f32", seed=915)
+        C = _poisoned(m, N, "f32")
+        asp.asp_reserve(h, N)
+        asp.asp_spmm(h, B.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        asp.asp_destroy(h)
+    _check(a, _bits(B), _bits(C))
+
+
+def test_wcsr_seventeen_million_empty_windows_without_scratch():
+    # 2^24 windows to clear before the atomics of the one that is split
+    m, k, N = (1 << 28) + 5, 4000, 2
+    row_ptr = np.zeros(m + 1, np.int32)
+    row_ptr[m // 2 + 1:] = 2000
+    row_ptr[m:] = 2003
+    col_idx = np.r_[np.arange(0, 4000, 2), 5, 17, 3999].astype(np.int32)
+    values = np.random.default_rng(916).uniform(-1.0, 1.0, 2003).astype(np.float32)
+    a = synth.Csr(m, k, row_ptr, col_idx, values, "f32")
+    print("case wcsr empty windows, rows", m, flush=True)
+    B = _device_normal(k, N, "f32", seed=917)
+    C = _poisoned(m, N, "f32")
+    h = asp.asp_create_from_csr("wcsr", "f32", 16, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values)
+    try:
+        asp.asp_spmm(h, B.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        asp.asp_destroy(h)
+    assert _written(C, 1 << 26)
+    sub = synth.Csr(2, k, np.array([0, 2000, 2003], np.int32), col_idx, values, "f32")
+    _check(sub, _bits(B), _bits(C[[m // 2, m - 1]]))
+    assert int((C != 0).any(dim=1).sum()) == 2
