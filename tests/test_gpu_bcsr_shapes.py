@@ -1,0 +1,88 @@
+"""bf16 BCSR products that reach the kernel shapes which the dispatch rules choose beyond those of test_gpu_strips.py and
+test_gpu_xt_short.py (on 256 compute units): strips of every wave tile and K split, with and without 16-byte rows, and
+the row-major ring kernel at every tile size, with K a multiple of the block and not.
+
+Tolerance as everywhere in bf16: 1e-2 * S + 1e-5, S = |A| x |B| from the oracle."""
+import functools
+
+import numpy as np
+import pytest
+
+from paper_2604_17834_amd import synth
+from test_gpu_parity import check_against_oracle, gpu_spmm, gpu_spmm_xt
+
+pytestmark = pytest.mark.gpu
+
+
+def _edges(N):
+    return np.arange(N) if N <= 96 else np.r_[0:40, N // 2 - 8:N // 2 + 8, N - 40:N]
+
+
+# (rows x columns of a wave tile in units of 32) x waves that split the K loop
+@pytest.mark.parametrize("b,m,k,N,sparsity", [
+    (32, 512, 500, 64, 0.8), (32, 513, 501, 129, 0.95),        # 1 x 1, 4 waves
+    (64, 512, 1000, 64, 0.95), (128, 512, 500, 16, 0.8),
+    (32, 512, 500, 2000, 0.8), (32, 513, 501, 1501, 0.9),      # 1 x 2, 4
+    (32, 1000, 500, 1496, 0.8),                                # 1 x 4, 2
+    (64, 512, 1000, 2000, 0.5), (64, 513, 1001, 1001, 0.5),    # 2 x 2, 8
+    (128, 512, 1000, 2000, 0.5), (128, 1001, 9001, 1001, 0.95),
+    (64, 2048, 500, 296, 0.9), (128, 2048, 500, 200, 0.9),     # 2 x 2, 4
+])
+def test_row_major_strips(b, m, k, N, sparsity):
+    a = synth.block_sparse_bernoulli(m, k, b, b, sparsity, seed=1, dtype="bf16")
+    B = synth.dense_normal(k, N, "bf16", seed=N)
+    C = gpu_spmm(a, "bcsr", b, b, B)
+    assert not ((C & 0x7F80) == 0x7F80).any()   # no element left unwritten (the poison is a NaN)
+    check_against_oracle(a, B, C, _edges(N))
+
+
+@pytest.mark.parametrize("b,m,k,N,sparsity", [
+    (32, 512, 2000, 1496, 0.9), (32, 513, 501, 1001, 0.95),       # 1 x 1, 4 waves
+    (64, 512, 1000, 696, 0.8), (64, 1000, 500, 256, 0.95),        # 2 x 1, 8
+    (128, 512, 2000, 512, 0.95), (128, 513, 501, 401, 0.95),
+    (64, 1000, 1000, 696, 0.8), (64, 1000, 500, 696, 0.95),       # 2 x 1, 4
+    (128, 512, 1000, 1496, 0.8), (128, 513, 501, 1001, 0.95),
+    (64, 2048, 1000, 2000, 0.8), (64, 2048, 500, 1496, 0.95),     # 2 x 2, 4
+    (128, 1536, 1000, 2000, 0.8), (128, 1536, 500, 2000, 0.95),
+    (128, 1536, 2000, 3000, 0.5), (128, 513, 2001, 3001, 0.5),    # 4 x 2, 4
+    (128, 8000, 2000, 3000, 0.5),                                 # the ring kernel's 128 x 256 tiles
+])
+def test_k_contiguous(b, m, k, N, sparsity):
+    a = synth.block_sparse_bernoulli(m, k, b, b, sparsity, seed=1, dtype="bf16")
+    X = synth.dense_normal(N, k, "bf16", seed=N)
+    Y = gpu_spmm_xt(a, b, X)
+    assert not ((Y & 0x7F80) == 0x7F80).any()
+    tok = _edges(N)
+    check_against_oracle(a, np.ascontiguousarray(X[tok].T), np.ascontiguousarray(Y[tok].T))
+
+
+# more than 64 MB of B: no strips; the number of block-rows sets the tile width
+@pytest.mark.parametrize("mask", ["bernoulli", "geometric"])
+@pytest.mark.parametrize("k", [4096, 4104])
+@pytest.mark.parametrize("rows,bn", [(10, 256), (5, 128), (3, 64)])
+@pytest.mark.parametrize("b", [32, 64, 128])
+def test_row_major_ring(b, rows, bn, k, mask):
+    gen = synth.block_sparse_bernoulli if mask == "bernoulli" else synth.block_sparse_geometric
+    N = 8200
+    a = gen(rows * b - 8, k, b, b, 0.5 if mask == "bernoulli" else 0.8, seed=rows + b, dtype="bf16")
+    B = synth.dense_normal(k, N, "bf16", seed=rows)
+    C = gpu_spmm(a, "bcsr", b, b, B)
+    assert not C[np.diff(a.row_ptr) == 0].any() and not ((C & 0x7F80) == 0x7F80).any()
+    check_against_oracle(a, B, C, np.r_[0:24, 4000:4136, N - 72:N])
+
+
+@functools.lru_cache(maxsize=1)
+def _many_rows(b, rows, sparsity, k):
+    return synth.block_sparse_geometric(rows * b - 8, k, b, b, sparsity, seed=rows + b, dtype="bf16")
+
+
+# one column tile and more block-rows than resident workgroups: requests run on into the next tiles, empty ones among them
+@pytest.mark.parametrize("b,rows,sparsity", [(32, 6000, 0.7), (64, 3000, 0.75), (128, 1500, 0.75)])
+@pytest.mark.parametrize("k", [1000, 1024])
+@pytest.mark.parametrize("N", [64, 128, 256, 248])
+def test_row_major_ring_over_many_tiles(b, rows, sparsity, k, N):
+    a = _many_rows(b, rows, sparsity, k)
+    B = synth.dense_normal(k, N, "bf16", seed=N)
+    C = gpu_spmm(a, "bcsr", b, b, B)
+    assert not C[np.diff(a.row_ptr) == 0].any() and not ((C & 0x7F80) == 0x7F80).any()
+    check_against_oracle(a, B, C, np.r_[0:8, N // 2:N // 2 + 8, N - 8:N])

@@ -423,7 +423,7 @@ def test_bcsr_xt_matrix_core_path_parity(m, k, N, sparsity):
 
 @pytest.mark.parametrize("b", [32, 64, 128])
 @pytest.mark.parametrize("m,k,N,misalign", [(300, 200, 77, False), (256, 256, 64, True), (130, 96, 1, False)])
-def test_bcsr_xt_generic_path_parity(b, m, k, N, misalign):
+def test_bcsr_xt_scattered_entries_and_any_alignment(b, m, k, N, misalign):
     a = synth.random_csr(m, k, 0.05, seed=43 + b, dtype="bf16", dist="normal", empty_row_frac=0.3)
     X = synth.dense_normal(N, k, "bf16", seed=44)
     Y = gpu_spmm_xt(a, b, X, misalign=misalign)

@@ -29,7 +29,7 @@ def test_strips(b, m, k, misalign, N):
 
 @pytest.mark.parametrize("b", [32, 64, 128])
 @pytest.mark.parametrize("m,k,N,sparsity", [
-    (512, 20000, 300, 0.9),     # few long block-rows: 64- and 128-row strips, more blocks than one look-up of columns holds
+    (512, 20000, 300, 0.9),     # few long block-rows, more blocks than one look-up of columns holds
     (128, 20000, 40, 0.2),
     (6000, 1000, 700, 0.9),     # many short ones
 ])

@@ -17,8 +17,11 @@ HOT = {
     "asp_bcsr_wide.hip": ["bcsr_spmm_wide_kernel"],
     "asp_bcsr.hip": ["bcsr_spmm_kernel"],
     "asp_bcsr_dma.hip": ["bcsr_spmm_dma_kernel"],
+    "asp_bcsr_strip.hip": ["bcsr_strip_kernel"],
+    "asp_bcsr_xt.hip": ["bcsr_xt_strip_kernel"],
     "asp_bcsr_f32.hip": ["bcsr_f32_spmm_kernel"],
     "asp_wcsr.hip": ["wcsr16_spmm_kernel", "wcsr32_spmm_kernel"],
+    "asp_wcsr_rows.hip": ["wcsr_rows_kernel"],
     "asp_wcsr_bf16.hip": ["wcsr_bf16_spmm_kernel"],
 }
 
