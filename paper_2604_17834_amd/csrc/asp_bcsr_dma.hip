@@ -587,7 +587,10 @@ static bool launch_dma_tile(const asp_handle *h, const void *B, void *C, int64_t
         case 64256: launch_dma<64, 256, 1, 4, 3, XT>(h, B, C, N, p, stream); return true;
         case 64128: launch_dma<64, 128, 2, 2, 6, XT>(h, B, C, N, p, stream); return true;
         case 64064: launch_dma<64, 64, 1, 2, 5, XT>(h, B, C, N, p, stream); return true;
-        case 32256: launch_dma<32, 256, 1, 2, 3, XT>(h, B, C, N, p, stream); return true;
+        case 32256:
+            if constexpr (XT) return false;
+            else launch_dma<32, 256, 1, 2, 3, XT>(h, B, C, N, p, stream);
+            return true;
         case 32128: launch_dma<32, 128, 1, 2, 4, XT>(h, B, C, N, p, stream); return true;
         case 32064: launch_dma<32, 64, 1, 2, 6, XT>(h, B, C, N, p, stream); return true;
     }

@@ -214,7 +214,9 @@ static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N
             return launch_strip<BR, 2, 1, 8, 64>(h, X, Y, N, vec, stream);
         }
     }
-    if (h->n_brows * (BR / 32) * n32 > 2 * cus) return launch_strip<BR, 1, 1, 4, 64>(h, X, Y, N, vec, stream);
+    if constexpr (BR == 32) {  // (with larger blocks there are fewer than 256 here)
+        if (h->n_brows * n32 > 2 * cus) return launch_strip<BR, 1, 1, 4, 64>(h, X, Y, N, vec, stream);
+    }
     return launch_strip<BR, 1, 1, 8, 64>(h, X, Y, N, vec, stream);
 }
 
@@ -311,7 +313,7 @@ asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, in
             const double slices = (double)h->n_units * (h->b_row / 32), longest = (double)h->hb.max_blocks * (h->b_row / 32);
             double best = 4.0 + c.strip * (double)h->n_units * h->b_row * h->b_row * (double)N * 256 / cus;
             int bn = 0;
-            for (int i = 0; i < 3 && tiles_ok; ++i) {
+            for (int i = 0; i < (h->b_row == 32 ? 2 : 3) && tiles_ok; ++i) {  // (256 wide never pays with 32 rows)
                 const double t = c.slice_alone[i] * longest + c.slice[i] * slices * (double)ceil_div(N, 64 << i) / cus;
                 if (t < best) best = t, bn = 64 << i;
             }
