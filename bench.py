@@ -175,24 +175,26 @@ def run_workload(name, steps, warmup, torch, asp, synth, with_cpu_baseline, cpu_
         tasks = asp.asp_export(h, asp.ASP_ARR_TASKS)
         real_cols = int((wci >= 0).sum())
         split_windows = int(len(np.unique(tasks[tasks[:, 3] != 0, 0]))) if len(tasks) else 0
-        # per packed column: b_row values + 1 index of A, one gathered B row; per window one C tile
-        # (every task of a split window writes a fp32 partial tile that is read back once)
-        split_tasks = int((tasks[:, 3] != 0).sum()) if len(tasks) else 0
-        bytes_alg = (info.n_units * (b_row * esz + 4) + real_cols * N * esz + a.m * N * esz
-                     + 2 * split_tasks * b_row * N * 4)
+        # compulsory bytes: every entry of A (value and column), every row of B that has one and all of C once.  What a
+        # product moves besides (rows of B gathered again, tiles, partial sums) depends on the windows' kernels and on
+        # the caches: the counted bytes are in "traffic"
+        used = np.zeros(a.k, dtype=bool)
+        used[a.col_idx] = True
+        bytes_alg = a.nnz * (esz + 4) + 4 * (a.m + 1) + int(used.sum()) * N * esz + a.m * N * esz
         roof = {"bound": "hbm", "achieved": bytes_alg / (kern_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s"}
         extra = {"packed_cols": int(info.n_units), "real_cols": real_cols, "tasks": int(info.n_tasks),
-                 "split_windows": split_windows, "algorithmic_bytes": int(bytes_alg),
-                 "mfma_flops_padded": 2.0 * info.n_units * b_row * N}
+                 "split_windows": split_windows, "algorithmic_bytes": int(bytes_alg)}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    if fmt == "bcsr" and dt == "bf16":
-        # (counter evidence, not measured in this run: profiles/bench_default_pmc.txt)
+    if name == "bcsr_gate_proj":
+        # (counter evidence on this workload, not measured in this run: profiles/bench_default_pmc.txt)
         roof["limiter"] = ("the memory side shared by the compute units: 1.68e9 B per launch (2.2 x compulsory; the 4 MB L2 of an "
                            "XCD holds half of the 7.3 MB slab of B its workgroups share) at 6.5-6.7 TB/s; on half of the compute units "
                            "the same launch is 1.27 x slower, not 2 x; matrix cores busy 0.40 of the cycles")
     roof["traffic"], traffic_kernel = _measured_traffic(name)
     if traffic_kernel:
         roof["traffic_source"] = "profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled), kernel " + traffic_kernel
+        if fmt == "wcsr":   # (through L2's memory side: the memory-side cache serves a part)
+            roof["traffic_GBs"] = roof["traffic"] / (kern_ms * 1e-3) / 1e9
     roof["kernel_ms_avg"] = kern_ms
     if per is not None:   # the second pass ran
         roof["single_launch_ms_median"] = float(np.median(per))
