@@ -14,9 +14,10 @@
  *     memory of the GPU that was current when the handle was created.
  *   - A handle is immutable after creation: concurrent asp_spmm calls on
  *     different streams with different C buffers are safe.  The one exception
- *     is a WCSR handle whose split windows go through the handle's scratch
- *     buffer (asp_reserve): those calls must be ordered on one stream; calls
- *     of asp_spmm_static_scratch share one scratch array per GPU in the same way.
+ *     is a WCSR handle with split windows for which scratch was reserved
+ *     (asp_reserve): all its calls, of any width and alignment, use the one
+ *     buffer and must be ordered on one stream; calls of
+ *     asp_spmm_static_scratch share one scratch array per GPU in the same way.
  *   - asp_spmm, asp_spmm_xt and asp_spmm_static_scratch only launch kernels on
  *     the caller's stream (no allocation, no memset, no host synchronisation),
  *     so they may be recorded into a HIP graph; handle creation, asp_reserve
@@ -77,7 +78,7 @@ typedef struct {
     int64_t n_brows;    /* block-rows (BCSR) or windows (WCSR) = ceil(m / b_row) */
     int64_t n_units;    /* stored blocks (BCSR) or packed columns incl. pads (WCSR) */
     int64_t n_tasks;    /* WCSR sub-tasks; 0 for BCSR */
-    int64_t n_zero_rows_units; /* WCSR: windows whose C rows are cleared before the kernel (empty or split) */
+    int64_t n_zero_rows_units; /* WCSR: windows that are empty or split (f32 calls without scratch clear their C rows first) */
     double fill_ratio;  /* nnz / stored value slots (Section II-C, fill ratio) */
 } asp_info_t;
 
@@ -104,12 +105,13 @@ typedef enum { ASP_ARR_ROW_PTR = 0, ASP_ARR_COL_IDX = 1, ASP_ARR_VALUES = 2, ASP
  * least padded width x cost per column, costs 135 / 96 / 74 / 64 (ties: the wider), and then the next narrower
  * width while non-empty block-rows x ceil(N / width) tiles are fewer than the GPU's compute units (256 assumed for
  * host-only handles); fp32 BCSR and WCSR take the widest of their widths that divides N, else the one that pads least.
- * BCSR launches too small for these tiles, or whose rows are not aligned, may run in tiles of other widths. */
+ * BCSR launches too small for these tiles, or whose rows are not aligned, may run in tiles of other widths, and WCSR windows
+ * whose rows share few columns run entry by entry: for WCSR the plan describes all windows as tasks of tiles. */
 typedef struct {
     int32_t bn;          /* columns of B/C handled by one workgroup (BCSR) or one wave (WCSR) */
     int32_t n_tiles;     /* ceil(N / bn): tiles along N, the last one masked if bn does not divide N */
     int32_t vectorized;  /* 1: 16-byte row accesses (needs N*sizeof(dtype) % 16 == 0 and 16-byte aligned B, C) */
-    int64_t workgroups;  /* output tiles of the main kernel (one workgroup each, or the work list of its resident workgroups) */
+    int64_t workgroups;  /* output tiles of that shape (BCSR: one workgroup each, or the work list of resident ones; WCSR: four to one) */
     int64_t padded_n;    /* n_tiles * bn: width actually computed on */
 } asp_plan_t;
 
@@ -145,7 +147,8 @@ asp_status_t asp_spmm(const asp_handle_t *h, const void *B, void *C, int64_t N, 
  * is split into several tasks have to meet somewhere).  With scratch, every task of a split window stores
  * its fp32 partial tile (4 * b_row * N bytes per task) and a last kernel adds the tiles in task order: the
  * result is bitwise reproducible.  bf16 WCSR handles with split windows need it (bf16 C cannot take fp32
- * atomic adds); f32 WCSR handles use it when it is there and otherwise add into C with fp32 atomics.  BCSR
+ * atomic adds; only widths or alignments without 16-byte rows also run without it, one thread per column, two orders of
+ * magnitude slower); f32 WCSR handles use it when it is there and otherwise add into C with fp32 atomics.  BCSR
  * handles and WCSR handles without split windows use none: the call does nothing for them.
  * Allocates (and frees a smaller earlier buffer, which synchronises the device); asp_spmm itself never
  * allocates and returns ASP_ERR_BUFFER_TOO_SMALL when a bf16 call needs more scratch than was reserved.
@@ -177,10 +180,11 @@ asp_status_t asp_spmm_static_scratch(const asp_handle_t *h, const void *B, void 
  * X: DEVICE, N x k row-major (leading dimension k).  Y: DEVICE, N x m row-major (leading dimension m), fully
  * overwritten; Y must not alias X.  1 <= N <= ASP_MAX_N.  BCSR handles (bf16) only; others return ASP_ERR_UNSUPPORTED.
  * Asynchronous, never synchronises, never allocates.  fp32 accumulation, round-to-nearest-even to bf16;
- * bitwise reproducible.  128x128 blocks (and 64x64 / 32x32 blocks when k >= 32 and grouping their block-rows
- * into 128-row tiles adds at most 2.6x / 4.3x zero fill) with k % 8 == 0,
- * m % 8 == 0 and 16-byte aligned X and Y run on the matrix cores (128 outputs x 512 tokens per workgroup);
- * everything else takes a slow generic kernel.
+ * bitwise reproducible.  Every size and alignment runs on the matrix cores: few tokens, and operands that are not 16-byte
+ * aligned with k % 8 == 0 and m % 8 == 0, in strips of 32 to 128 outputs x 32 or 64 tokens whose waves split the K loop; more
+ * tokens in tiles of a block-row x 64 to 256 tokens, and once these are 1.5 per compute unit in tiles of 128 outputs x 512
+ * tokens (128x128 blocks, or smaller ones when k >= 32 and grouping their block-rows into 128-row tiles adds at most
+ * 2.6x / 4.3x zero fill).
  */
 asp_status_t asp_spmm_xt(const asp_handle_t *h, const void *X, void *Y, int64_t N, void *stream);
 

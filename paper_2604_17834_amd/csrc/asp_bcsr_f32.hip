@@ -7,8 +7,9 @@
 // a barrier every 1024 MFMA cycles that all waves of the workgroup had to reach).  The waves that share a strip of A or a
 // slab of B meet in the L1.  Block-rows are walked longest first, so that the launch ends with short ones: in the order of
 // the bf16 schedule the last heavy tiles were a fifth of it.
-// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, before -> now: N = 8192 947 / 898 / 1117 -> 864 / 868 / 953 us (129 TFLOP/s;
-// the same MFMAs on registers reach 149), N = 2048 296 / 262 / 305 -> 239 / 239 / 254, N = 64 140 / 91 / 61 -> 20 / 16 / 18.
+// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, before -> now: N = 8192 999 / 958 / 1141 -> 923 / 919 / 1000 us (121 TFLOP/s;
+// the same MFMAs on registers reach 149), N = 2048 301 / 276 / 306 -> 253 / 253 / 260, N = 64 140 / 83 / 63 -> 17 / 16 / 15
+// (both builds in turn in one process; clocks move all of them by 5 % together).
 //
 // Operand layouts
 //   A  blocks are pre-permuted on the host (bcsr_pack_fragments_f32): for every 32-row tile and group of

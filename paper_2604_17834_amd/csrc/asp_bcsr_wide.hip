@@ -672,8 +672,10 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
     // still has a chance in the 4 MB of L2 (measured: 1, 3 and 4 are 3-10 % slower on the 90 %-sparse projection).
     // With 8 N-tiles one: every XCD then has one to itself, half the slab, instead of a share of four pairs; and up to 15
     // where the block-rows are many enough to balance without the pairs.  us, one / two: 18944 x 3584 at 90 %, N = 4096,
-    // 128 / 64 / 32-row blocks 70.6 / 78.9, 88.6 / 100.4, 126 / 130, N = 6144 109 / 117, 134 / 143, 190 / 190; 4096 x 4096 at 80 %,
-    // N = 4096, 128 / 64-row 35.8 / 38.5, 45.8 / 56.3, but N = 5120 50.5 / 45.2, 66.2 / 61.2 (32 rows of tiles).
+    // 128 / 64 / 32-row blocks 73.8 / 76.9, 94.0 / 100.2, 133 / 137, N = 6144 111 / 115, 139 / 143, 198 / 199; 4096 x 4096 at 80 %,
+    // N = 4096 42.2 / 43.0, 56.5 / 58.6, 57.7 / 84.0, but N = 5120 58.4 / 55.4 (128-row; 32 rows of tiles).  K-contiguous,
+    // 18944 x 3584 at 90 %: 4096 tokens 76 / 78, 98 / 105, 150 / 156, 6144 tokens 114 / 120, 145 / 151, 227 / 241; at 50 % within 1 %
+    // either way but for 488 / 471 (64-row, 6144 tokens).
     const WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
     const bool one = n_tiles == 8 || (n_tiles > 8 && n_tiles < 16 && n_rows >= 128);

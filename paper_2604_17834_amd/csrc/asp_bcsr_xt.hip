@@ -9,8 +9,9 @@
 // v_mfma_f32_32x32x16_bf16 wants in registers, so both operands go straight from memory to registers, 32 or 64 k at a
 // time, one such unit ahead -- no LDS stage, no barrier in the loop.  The waves' partial tiles meet in LDS once and are
 // added in wave order (bitwise reproducible), rounded once, and stored.
-// us a call at 16 tokens, before (128 x 512 tiles) -> now: gate 24.7 -> 6.5, down 84.5 -> 7.2, down in 64 x 64 / 32 x 32
-// blocks 123 -> 6.4 / 196 -> 6.5 (6.4 is what launching a call costs); down at 256 tokens 87.6 -> 18.5.
+// us a call at 16 tokens, before (128 x 512 tiles) -> now: gate 26 -> 5.6, down 78 -> 6.4, down in 64 x 64 / 32 x 32
+// blocks 122 -> 6.7 / 196 -> 5.8; down at 256 tokens 87.6 -> 18.5.  (The host takes 4.0 us to enqueue a call, 6.9 through
+// SparseLinear; the gate and down kernels alone 6.5 and 7.5 in a trace: the chain block-row -> columns -> X of a wave.)
 // With more tokens each strip's reads (A once per token tile, X once per strip) run into the L1s' miss rate, and the ring
 // kernel's larger tiles take over (bcsr_spmm_xt_launch).
 //

@@ -602,8 +602,8 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
     // XCD's L2 once for all of them.  An XCD holds up to 1024 waves; with R such rows cut every W columns they span
     // W * 1024 / R columns at a time.  Short spans hit L2 more often, long chunks pay their start less often: the best
     // time is at spans of 16 MB of B (64 rows of 200 000 entries over 2 000 000 columns, N = 64: 0.264 / 0.236 / 0.296 ms
-    // at 4 / 8 / 16 MB there, where a row of B has 256 bytes, with 80 / 64 / 37 % of the gathers hitting L2; 0.343 ms and
-    // 30 % with chunks of task_cols = 512).  The span is counted at 128 columns of B.  Taken for the R longest rows for
+    // at 4 / 8 / 16 MB there, where a row of B has 256 bytes, with one wave to a chunk's columns; 0.343 ms
+    // with chunks of task_cols = 512; the present kernel takes 0.207 ms at 8 MB and finds 80 % of its lines in L2).  The span is counted at 128 columns of B.  Taken for the R longest rows for
     // which a chunk keeps 32 entries, when at least two of their entries meet in a column on average.
     const int64_t FIT = (16 << 20) / (128 * (int64_t)esize), MIN_CHUNK = 32;
     int32_t k_used = 1;

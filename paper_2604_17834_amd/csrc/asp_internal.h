@@ -112,8 +112,8 @@ struct HostRows {
     std::vector<int32_t> row_ptr;     // [m + 1] entries of the rows walked entry by entry, consecutive
     std::vector<std::pair<int64_t, int64_t>> runs;  // where those entries are in the CSR arrays
     int64_t n_entries = 0;
-    std::vector<int32_t> tasks;       // [..][4] see wcsr_rows_kernel; empty tasks fill up
-    std::vector<int32_t> chunks;      // [..][4] see wcsr_chunks_kernel; empty tasks fill up
+    std::vector<int32_t> tasks;       // [..][4] whole rows, see walk_rows (asp_wcsr_rows.hip); empty tasks fill up
+    std::vector<int32_t> chunks;      // [..][4] a chunk of a long row each, see walk_rows; empty tasks fill up
     std::vector<int32_t> split;       // [..][4] = {row, first scratch row, scratch rows, 0} of rows longer than task_cols
     std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only; empty tasks fill up
     bool tiles_dealt = false;         // tile_tasks holds one range for each XCD (deal_to_xcds)

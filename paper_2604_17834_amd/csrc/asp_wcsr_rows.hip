@@ -16,7 +16,7 @@
 //
 // Order of the work: chunks of long rows are sorted by column and dealt to the XCDs in contiguous ranges, so that the
 // chunks of different rows that cover the same columns run on one XCD at about the same time and find the rows of B in
-// its L2 (64 rows of 200 000 entries over 2 000 000 columns: 84 % of the gathers).
+// its L2 (64 rows of 200 000 entries over 2 000 000 columns, N = 64: 80 % of the line requests).
 //
 // Any N and any alignment: a lane owns E adjacent columns; the last lane of a row moves left so that it ends at N and
 // computes some of its neighbour's columns a second time (the same bits), so that no access leaves the row.
