@@ -11,6 +11,8 @@ from test_gpu_parity import check_against_oracle, gpu_spmm
 
 pytestmark = pytest.mark.gpu
 
+torch = pytest.importorskip("torch")
+
 
 def _rows_of_lengths(lengths, k, dtype, seed):
     """One row per length, distinct random columns; U(-1, 1) values."""
@@ -91,3 +93,31 @@ def test_only_rows_that_store_a_column_see_its_values(dtype, reserve, N):
     assert np.isposinf(C[has_inf & ~has_nan]).all()
     assert np.isfinite(C[~has_inf & ~has_nan]).all()
     assert not C[np.diff(a.row_ptr) == 0].any()
+
+
+@pytest.mark.parametrize("dtype,b_row,N", [
+    ("f32", 16, 320), ("f32", 16, 384), ("f32", 16, 512),       # 64-, 128- and 256-wide tiles, several of each
+    ("f32", 16, 456), ("f32", 16, 905), ("f32", 16, 1024),      # 256 wide, rows that end inside a cache line; B and C past 512 MB
+    ("f32", 32, 300), ("f32", 64, 129), ("bf16", 16, 200), ("bf16", 32, 385), ("bf16", 64, 129), ("bf16", 16, 64),
+])
+@pytest.mark.parametrize("windows", [1500, 5003])
+def test_several_column_tiles_of_a_task(dtype, b_row, N, windows):
+    # lists that are dealt to the XCDs (up to 4096 tasks) and lists that are not; a ragged last window
+    a = synth.banded_plus_dense_rows(windows * b_row - 5, seed=7, n_dense_rows=0, dense_row_nnz=0, half_band=4, dtype=dtype)
+    rng = np.random.default_rng(N)
+    cols = np.unique(np.r_[0:8, N - 8:N, rng.integers(0, N, 16)])
+    g = torch.Generator(device="cuda").manual_seed(N)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Bd = torch.randn((a.k, N), dtype=tdt, device="cuda", generator=g)
+    Cd = torch.full((a.m, N), float("nan"), dtype=tdt, device="cuda")
+    h = asp.asp_create_from_csr("wcsr", dtype, b_row, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values)
+    try:
+        asp.asp_spmm(h, Bd.data_ptr(), Cd.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        asp.asp_destroy(h)
+    assert not bool(torch.isnan(Cd).any())       # every output written
+    ct = torch.from_numpy(cols).cuda()
+    bits = (lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)) if dtype == "bf16" else \
+        (lambda t: t.contiguous().cpu().numpy())
+    check_against_oracle(a, bits(Bd[:, ct]), bits(Cd[:, ct]))
