@@ -1,4 +1,4 @@
-"""The work lists of WCSR handles (host code, no GPU) at sizes that no matrix of a test reaches: a small C++ driver calls the
+"""The work lists of WCSR handles (host code, no GPU) at sizes that no matrix of a test reaches: a small C++ program calls the
 list builder itself."""
 import os
 import shutil
@@ -12,12 +12,12 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
 @pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def lists_of(tmp_path_factory):
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not found")
-    exe = str(tmp_path_factory.mktemp("lists") / "driver")
+    exe = str(tmp_path_factory.mktemp("lists") / "lists")
     subprocess.check_call([HIPCC, "-x", "hip", "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"),
-                           "-I", os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "wcsr_lists_driver.cpp"),
+                           "-I", os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "wcsr_lists_main.cpp"),
                            "-L", PKG, "-lasyncsparse", "-Wl,-rpath," + PKG, "-o", exe])
 
     def run(*args):
@@ -30,15 +30,15 @@ def driver(tmp_path_factory):
     return run
 
 
-def test_scratch_rows_that_pass_int32_stay_with_the_tiles(driver):
+def test_scratch_rows_that_pass_int32_stay_with_the_tiles(lists_of):
     for first in (0, 2**27 - 80):                 # scratch rows 16 * slot: the last one is 2^31 - 1
-        got = driver("slots", first)
+        got = lists_of("slots", first)
         assert len(got["split"]) == 32 and "tile" not in got
         rows = sorted(c[1] for c in got["chunk"] if c[2] < c[3])
         assert rows == sorted(set(rows)) and rows[0] == 16 * first and rows[-1] < 2**31
         assert all(s[1] >= 0 and s[1] + s[2] <= 16 * (first + 80) for s in got["split"])
-    got = driver("slots", 2**27 - 60)             # the second window's scratch rows would pass 2^31 - 1
+    got = lists_of("slots", 2**27 - 60)             # the second window's scratch rows would pass 2^31 - 1
     assert len(got["split"]) == 16 and all(s[0] < 16 and s[1] >= 0 for s in got["split"])
     assert got["tile_split"] == [[1]] and all(t[0] == 1 for t in got["tile"])
-    got = driver("slots", 2**27 - 1)
+    got = lists_of("slots", 2**27 - 1)
     assert "split" not in got and "chunk" not in got and got["tile_split"] == [[0], [1]]
