@@ -65,6 +65,9 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_e_col);
     (void)hipFree(h->d_e_val);
     (void)hipFree(h->d_c_rank_info);
+    (void)hipFree(h->d_c_rank_info_32);
+    (void)hipFree(h->d_rank_info_32);
+    (void)hipFree(h->d_rank_info_64);
     (void)hipFree(h->d_c_slice_rows);
     (void)hipFree(h->d_c_piece_rows);
     (void)hipFree(h->d_c_values);
@@ -166,7 +169,12 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         bcsr_build_schedule(h->hb, cfg->dtype == ASP_DT_F32);
         if ((s = upload(&h->d_rank_info, h->hb.rank_info.data(), h->hb.rank_info.size() * 4, stream))) return s;
         ASP_HIP_TRY(hipMalloc((void **)&h->d_sched, 64));
+        if (cfg->dtype == ASP_DT_BF16) {
+            if ((s = upload(&h->d_rank_info_32, h->hb.rank_info_32.data(), h->hb.rank_info_32.size() * 4, stream))) return s;
+            if ((s = upload(&h->d_rank_info_64, h->hb.rank_info_64.data(), h->hb.rank_info_64.size() * 4, stream))) return s;
+        }
         if (h->has_comp) {
+            if ((s = upload(&h->d_c_rank_info_32, h->hc.rank_info_32.data(), h->hc.rank_info_32.size() * 4, stream))) return s;
             if ((s = upload(&h->d_c_rank_info, h->hc.rank_info.data(), h->hc.rank_info.size() * 4, stream))) return s;
             if ((s = upload(&h->d_c_slice_rows, h->hc.slice_rows.data(), h->hc.slice_rows.size() * 4, stream))) return s;
             if ((s = upload(&h->d_c_piece_rows, h->hc.piece_rows.data(), h->hc.piece_rows.size() * 4, stream))) return s;

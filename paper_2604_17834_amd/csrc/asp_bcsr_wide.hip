@@ -668,19 +668,23 @@ static WideOperand wide_operand(const asp_handle *h) {
 template <bool XT>
 static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, int n_tiles, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n;  // benchmarking switch
-    // two N-tiles walked together: an A block is fetched once per pair while the pair's slab of B (K x 1024)
-    // still has a chance in the 4 MB of L2 (measured: 1, 3 and 4 are 3-10 % slower on the 90 %-sparse projection).
-    // With 8 N-tiles one: every XCD then has one to itself, half the slab, instead of a share of four pairs; and up to 15
-    // where the block-rows are many enough to balance without the pairs.  us, one / two: 18944 x 3584 at 90 %, N = 4096,
-    // 128 / 64 / 32-row blocks 73.8 / 76.9, 94.0 / 100.2, 133 / 137, N = 6144 111 / 115, 139 / 143, 198 / 199; 4096 x 4096 at 80 %,
-    // N = 4096 42.2 / 43.0, 56.5 / 58.6, 57.7 / 84.0, but N = 5120 58.4 / 55.4 (128-row; 32 rows of tiles).  K-contiguous,
-    // 18944 x 3584 at 90 %: 4096 tokens 76 / 78, 98 / 105, 150 / 156, 6144 tokens 114 / 120, 145 / 151, 227 / 241; at 50 % within 1 %
-    // either way but for 488 / 471 (64-row, 6144 tokens).
-    const WideOperand op = wide_operand(h);
+    // N-tiles walked together.  One: an XCD has half the slab of B (K x 512) in its 4 MB of L2; two: an A block is fetched once
+    // per pair.  One where the block-rows are many enough that the 32 workgroups of an XCD get even lists of them, and with 8
+    // N-tiles (else an XCD gets a share of a pair); but two again where rows of B are a multiple of 32 KB apart: the slab of one
+    // tile then falls into a part of L2's sets (18944 x 3584, 128-row blocks, us per N-tile and XCD: N = 12288 61, 16384 68, 20480
+    // 60, 24576 60, 32768 68).  us, one / two, 18944 x 3584 at 90 %, 128 / 64 / 32-row blocks: N = 4096 64 / 79, 85 / 102,
+    // 121 / 130, N = 8192 125 / 135, 164 / 180, 236 / 254, N = 16384 273 / 257, 374 / 349, 522 / 508, N = 24576 361 / 385, 484 / 519,
+    // 706 / 749; K-contiguous: 4096 tokens 68 / 80, 93 / 107, 138 / 153, 16384 256 / 277, 353 / 381, 545 / 623.  Fewer block-rows
+    // (8192 x 8192, 64 rows of tiles; 4096 x 4096, 32) are 18 % slower to 8 % faster with one.
+    WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
-    const bool one = n_tiles == 8 || (n_tiles > 8 && n_tiles < 16 && n_rows >= 128);
+    const bool one = n_tiles == 8 || (n_tiles > 8 && n_rows >= 128 && (XT || N % 16384 != 0));
     int group_n = env_group > 0 ? env_group : one ? 1 : 2;
     if (group_n > n_tiles) group_n = n_tiles;
+    if (group_n == 1) {
+        op.rank_info = (const int4 *)(h->has_comp ? h->d_c_rank_info_32 : h->d_rank_info_32);
+        op.weight_prefix = &(h->has_comp ? h->hc : h->hb).weight_prefix_32;
+    }
     int64_t workers = h->n_cus;  // one resident workgroup per CU: the ring takes the whole LDS
     if (workers > n_rows * n_tiles) workers = n_rows * n_tiles;
     // benchmarking switch: fewer resident workgroups, i.e. part of the compute units idle (the schedule's 16 lists

@@ -1,4 +1,5 @@
-// Prints the work lists that wcsr_build_rows makes of a synthetic matrix, for tests/test_wcsr_lists.py.
+// Prints the work lists that the converters make of a synthetic matrix, for tests/test_wcsr_lists.py and test_bcsr_order.py.
+//   order L..        BCSR block-rows of L blocks each: the orders of the tile kernels in 16, 32 and 64 lists
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
@@ -33,7 +34,29 @@ static int slots(int32_t first) {
     return 0;
 }
 
+static int order(const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    b.block_row_ptr.assign(1, 0);
+    for (int32_t n : lengths) {
+        for (int32_t j = 0; j < n; ++j) b.block_col_idx.push_back(j);
+        b.block_row_ptr.push_back((int32_t)b.block_col_idx.size());
+    }
+    asp::bcsr_build_schedule(b);
+    print("16", b.rank_info, 4);
+    print("32", b.rank_info_32, 4);
+    print("64", b.rank_info_64, 4);
+    const std::vector<int64_t> *prefix[3] = {&b.sorted_weight_prefix, &b.weight_prefix_32, &b.weight_prefix_64};
+    for (int i = 0; i < 3; ++i)
+        for (int64_t v : *prefix[i]) std::printf("prefix%d %lld\n", 16 << i, (long long)v);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
+    if (argc > 2 && std::strcmp(argv[1], "order") == 0) {
+        std::vector<int32_t> lengths;
+        for (int i = 2; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
+        return order(lengths);
+    }
     return 2;
 }
