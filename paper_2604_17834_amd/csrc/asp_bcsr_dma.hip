@@ -545,17 +545,35 @@ __global__ void bcsr_zero_sched_kernel(int *__restrict__ sched) {
 template <int BR, int BN, int WM, int WN, int NS, bool XT>
 static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n, env_wgs = switches().bcsr_wgs_per_cu;  // benchmarking switches
-    // N-tiles walked together.  K-contiguous with 32-row tiles: 2, so that their columns of X have a chance in the 4 MB of
-    // L2 (K = 18944: 4096 tokens in 64- / 128- / 256-wide tiles 290 / 341 / 366 us with 4, 228 / 278 / 285 with 2)
-    int group_n = env_group > 0 ? env_group : XT && BR == 32 ? 2 : 4;
-    if (group_n > p.n_tiles) group_n = p.n_tiles;
     // resident workgroups per CU: as many as LDS allows (the kernel is built for 2 waves per SIMD)
     const int fit = (int)(163840 / DmaCfg<BR, BN, WM, WN, NS, XT>::LDS_BYTES);
     const int per_cu = std::max(1, std::min(fit, 8 / (WM * WN)));
     int64_t workers = (int64_t)h->n_cus * (env_wgs > 0 ? env_wgs : per_cu);
     if (workers > p.workgroups) workers = p.workgroups;
     workers = std::max<int64_t>(8, workers / 8 * 8);  // the same number of workgroups on every XCD
-    const XcdRuns runs = cut_runs(h->hb.sorted_weight_prefix, h->n_brows, p.n_tiles, group_n);
+    // N-tiles walked together.  Few of them: an XCD reads the slab of B of one N-tile for many block-rows, whose requests meet
+    // in its 4 MB of L2; many: a block of A is fetched once for all of them.  Per tile that costs about BN / R and
+    // density x BR / group_n, with R the block-rows that an XCD walks at a time, so small blocks take few.  us, groups of
+    // 1 / 2 / 4, 3584 x 18944 at 90 %: 32-row blocks N = 2048 62 / 91 / 109, N = 4096 126 / 185 / 228, K-contiguous (4 x 128 wide
+    // on a compute unit) 108 / 112 / 159, 258 / 265 / 318; 64-row N = 2048 52 / 75 / 70, K-contiguous 57 / 80 / 73; 128-row
+    // N = 2048 63 / 49 / 57, N = 4096 97 / 77 / 90, K-contiguous 63 / 48 / 58 and 121 / 90 / 80; 10240 x 2560, 64-row, N = 2048
+    // 26 / 29 / 31, K-contiguous 24 / 26 / 30, 128-row 22 / 29 / 25 (more tiles than the chip holds); 8192 x 2048, 32-row, N = 1024
+    // (the slab of four in L2) 30.5 / 29 / 28.
+    const bool one_round = h->n_brows * (int64_t)p.n_tiles <= (int64_t)h->n_cus * per_cu;
+    int group_n = env_group;
+    if (group_n <= 0) {
+        if (BR == 32) group_n = XT ? 2 : h->k * (8ll * BN) <= (9 << 19) ? 4 : 1;
+        else if (BR == 64) group_n = 1;
+        else group_n = !XT && one_round ? 2 : 4;
+    }
+    if (group_n > p.n_tiles) group_n = p.n_tiles;
+    // the order whose lists are as many as the block-rows of a round (bcsr_build_schedule); 128-row blocks: 16, whose rounds
+    // start in nearer block columns (3584 x 18944, N = 4096, groups of 2: 77 us, with 32 lists 89)
+    const int64_t per_round = workers / 8 / group_n;
+    const int lists = BR == 128 || per_round < 24 ? 16 : per_round < 48 ? 32 : 64;
+    const int4 *rank_info = (const int4 *)(lists == 64 ? h->d_rank_info_64 : lists == 32 ? h->d_rank_info_32 : h->d_rank_info);
+    const XcdRuns runs = cut_runs(lists == 64 ? h->hb.weight_prefix_64 : lists == 32 ? h->hb.weight_prefix_32 : h->hb.sorted_weight_prefix,
+                                  h->n_brows, p.n_tiles, group_n);
     dim3 grid((unsigned)workers), block(WM * WN * 64);
     // benchmarking switch: tiles pulled from per-XCD atomic counters (built for the 128 x 256 tiles of the ladder;
     // everything else keeps the static schedule)
@@ -564,13 +582,13 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
         if (env_atomic && h->d_sched) {
             hipLaunchKernelGGL(bcsr_zero_sched_kernel, dim3(1), dim3(64), 0, stream, h->d_sched);
             hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS, true>), grid, block, 0, stream,
-                               (const int4 *)h->d_rank_info, h->d_col_idx, (const uint16_t *)h->d_values,
+                               rank_info, h->d_col_idx, (const uint16_t *)h->d_values,
                                (const uint16_t *)B, (uint16_t *)C, (int)h->m, (int)h->k, (int)N, (int)h->n_brows,
                                p.n_tiles, group_n, runs, h->d_sched);
             return;
         }
     }
-    hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS, false, XT>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
+    hipLaunchKernelGGL((bcsr_spmm_dma_kernel<BR, BN, WM, WN, NS, false, XT>), grid, block, 0, stream, rank_info,
                        h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m,
                        (int)h->k, (int)N, (int)h->n_brows, p.n_tiles, group_n, runs, (int *)nullptr);
 }

@@ -86,3 +86,27 @@ def test_row_major_ring_over_many_tiles(b, rows, sparsity, k, N):
     C = gpu_spmm(a, "bcsr", b, b, B)
     assert not C[np.diff(a.row_ptr) == 0].any() and not ((C & 0x7F80) == 0x7F80).any()
     check_against_oracle(a, B, C, np.r_[0:8, N // 2:N // 2 + 8, N - 8:N])
+
+
+# groups of one, two and four N-tiles, in 16, 32 and 64 lists: (block, m, k, N) with more tiles than the chip holds and fewer
+@pytest.mark.parametrize("b,m,k,N", [
+    (32, 2048, 5000, 2504), (32, 2100, 600, 2056),     # one; four, whose slab fits L2
+    (64, 2048, 3000, 2504), (64, 8192, 500, 2056),
+    (128, 2048, 3000, 4104), (128, 10240, 500, 2056),  # one round of tiles, and more
+    (64, 16500, 512, 4616), (128, 16512, 256, 8704), (128, 16400, 256, 16384),   # 128x512 tiles, more than 128 rows of them
+])
+@pytest.mark.parametrize("xt", [False, True])
+def test_groups_of_column_tiles(b, m, k, N, xt):
+    m -= m % 8 if xt else 0
+    a = synth.block_sparse_bernoulli(m, k, b, b, 0.75, seed=3, dtype="bf16")
+    e = _edges(N)
+    if xt:
+        X = synth.dense_normal(N, k, "bf16", seed=N)
+        Y = gpu_spmm_xt(a, b, X)
+        assert not ((Y & 0x7F80) == 0x7F80).any()
+        check_against_oracle(a, np.ascontiguousarray(X[e].T), np.ascontiguousarray(Y[e].T))
+    else:
+        B = synth.dense_normal(k, N, "bf16", seed=N)
+        C = gpu_spmm(a, "bcsr", b, b, B)
+        assert not ((C & 0x7F80) == 0x7F80).any()
+        check_against_oracle(a, B, C, e)
