@@ -69,6 +69,7 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_rank_info_32);
     (void)hipFree(h->d_rank_info_64);
     (void)hipFree(h->d_c_slice_rows);
+    (void)hipFree(h->d_share_lists);
     (void)hipFree(h->d_c_piece_rows);
     (void)hipFree(h->d_c_values);
     if (cur >= 0 && cur != h->device) (void)hipSetDevice(cur);
@@ -180,9 +181,15 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
             if ((s = upload(&h->d_c_piece_rows, h->hc.piece_rows.data(), h->hc.piece_rows.size() * 4, stream))) return s;
             if ((s = upload(&h->d_c_values, h->hc.packed.data(), h->hc.packed.size(), stream))) return s;
         }
+        if (cfg->dtype == ASP_DT_BF16 && bcsr_wide_capable(h)) {
+            bcsr_build_shares(h->has_comp ? h->hc : h->hb, h->shares);
+            if (!h->shares.lists.empty() &&
+                (s = upload(&h->d_share_lists, h->shares.lists.data(), h->shares.lists.size() * 4, stream))) return s;
+        }
         ASP_HIP_TRY(hipStreamSynchronize(stream));
         std::vector<uint8_t>().swap(h->hb.packed);  // the device copy is the only user
         std::vector<uint8_t>().swap(h->hc.packed);
+        std::vector<int32_t>().swap(h->shares.lists);
         return ASP_OK;
     }
 

@@ -62,6 +62,12 @@ struct WideCfg {
 
 }  // namespace
 
+// The N-tiles first_tile .. n_tiles - 1, shared by the workgroups: per_tile lists of block-rows each (bcsr_build_shares),
+// entries skip, skip + 1, ... of rank_info, the l-th list from share_first[l] on.  per_tile = 0: none.
+struct WideShares {
+    int first_tile, per_tile, skip;
+};
+
 // rank_info[r] = {block-row, first stored block, number of stored blocks, block column of the first one} of the r-th
 // block-row of the schedule; only the first n_rows (non-empty) ones are walked.  No slice of the dense operand
 // reaches past K: K is a multiple of the block size, or the blocks come in the composite form (GATHER).
@@ -88,7 +94,7 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
     const int4 *__restrict__ rank_info, const int32_t *__restrict__ block_col_idx,
     const uint16_t *__restrict__ a_packed, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int K,
     int N, int n_rows, int n_brows, int n_blocks, int n_tiles, int group_n, int xcd_aware, XcdRuns runs,
-    const int4 *__restrict__ piece_rows) {
+    const int4 *__restrict__ piece_rows, WideShares shares, const int32_t *__restrict__ share_first) {
     using Cfg = WideCfg;
     constexpr int NS = Cfg::NS, NW = Cfg::NW, KS = Cfg::KS, BR = Cfg::BR, BN = Cfg::BN, MT = Cfg::MT, NTL = Cfg::NTL;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[Cfg::LDS_BYTES];
@@ -105,8 +111,19 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
     const int wg = xcd_aware ? blockIdx.x >> 3 : blockIdx.x;
     const int run_begin = __builtin_amdgcn_readfirstlane(runs.start[xcd]);
     const int run_end = __builtin_amdgcn_readfirstlane(runs.start[xcd + 1]);
+    // Then one list of the block-rows of one of the shared N-tiles (shares.per_tile > 0): workgroup g of all takes list
+    // g % per_tile of tile g / per_tile.
+    const int rounds = run_end - run_begin > wg ? (run_end - run_begin - wg - 1) / stride + 1 : 0;
+    int n_rounds = rounds, share_idx = 0;
+    if (shares.per_tile > 0) {
+        const int g = xcd * stride + wg, tile = __builtin_amdgcn_readfirstlane(g / shares.per_tile);
+        const int list = g - tile * shares.per_tile;
+        share_idx = (shares.first_tile + tile) * n_rows + __builtin_amdgcn_readfirstlane(share_first[list]) - rounds;
+        if (shares.first_tile + tile < n_tiles)
+            n_rounds = rounds + __builtin_amdgcn_readfirstlane(share_first[list + 1] - share_first[list]);
+    }
     auto tile_of_round = [&](int r) __attribute__((always_inline)) {
-        return run_begin + r * stride + wg;
+        return r < rounds ? run_begin + r * stride + wg : share_idx + r;
     };
     // Rows of C of block-rows without stored blocks (ranks n_rows .. n_brows-1; GATHER: four pieces of 32 rows per
     // super-row, placed by piece_rows) are cleared by the workgroups when their streams have ended.  Every such
@@ -169,7 +186,7 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
     };
     int round = 0;
     int idx_cur = tile_of_round(0);
-    if (idx_cur >= run_end) {
+    if (n_rounds == 0) {
         clear_empty_rows();
         return;
     }
@@ -233,7 +250,8 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
         // heaviest block-row first in even groups, lightest first in odd ones: neighbours in the order,
         // which run at the same time, then have similar weights across group boundaries too
         const int pos = in_grp / gw, nt = grp * group_n + (in_grp - pos * gw);
-        const int rank = (grp & 1) ? n_rows - 1 - pos : pos;
+        const bool shared = grp >= shares.first_tile;  // (group_n is 1 where there are shares)
+        const int rank = shared ? shares.skip + pos : (grp & 1) ? n_rows - 1 - pos : pos;
         const int4 ri = rank_info[rank];
         br = __builtin_amdgcn_readfirstlane(ri.x);
         blk0 = __builtin_amdgcn_readfirstlane(ri.y);
@@ -477,7 +495,7 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
         pf_bcol = bcol0;
         cursor_set_tile(colb);
         cursor_set_block();
-        if (tile_of_round(1) < run_end) {
+        if (n_rounds > 1) {
             have_next = 1;
             decode(tile_of_round(1), n_br, n_n0, n_nb, n_blk0, n_bcol0, n_col, n_srow);
         }
@@ -523,7 +541,7 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
         int nn_br = 0, nn_n0 = 0, nn_nb = 0, nn_blk0 = 0, nn_bcol0 = 0;
         uint32_t nn_col = 0;
         int4 nn_srow = {0, 0, 0, 0};
-        if (idx_nn < run_end) decode(idx_nn, nn_br, nn_n0, nn_nb, nn_blk0, nn_bcol0, nn_col, nn_srow);
+        if (round + 2 < n_rounds) decode(idx_nn, nn_br, nn_n0, nn_nb, nn_blk0, nn_bcol0, nn_col, nn_srow);
 
         // the buffer of the slice just finished (always the last one of the ring) is the spare one
         // until the next barrier
@@ -601,12 +619,11 @@ __global__ __launch_bounds__(256, 1) void bcsr_spmm_wide_kernel(
         wait_vmcnt_and_lds<63>();
         barrier_no_fence();
         ++round;
-        idx_cur = tile_of_round(round);
         c_br = n_br;
         c_n0 = n_n0;
         c_nb = n_nb;
         pf_in_next = 0;  // the cursor entered this tile three slices ago
-        if (idx_nn < run_end) {
+        if (round + 1 < n_rounds) {
             n_br = nn_br;
             n_n0 = nn_n0;
             n_nb = nn_nb;
@@ -669,16 +686,15 @@ template <bool XT>
 static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, int n_tiles, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n;  // benchmarking switch
     // N-tiles walked together.  One: an XCD has half the slab of B (K x 512) in its 4 MB of L2; two: an A block is fetched once
-    // per pair.  One where the block-rows are many enough that the 32 workgroups of an XCD get even lists of them, and with 8
-    // N-tiles (else an XCD gets a share of a pair); but two again where rows of B are a multiple of 32 KB apart: the slab of one
-    // tile then falls into a part of L2's sets (18944 x 3584, 128-row blocks, us per N-tile and XCD: N = 12288 61, 16384 68, 20480
-    // 60, 24576 60, 32768 68).  us, one / two, 18944 x 3584 at 90 %, 128 / 64 / 32-row blocks: N = 4096 64 / 79, 85 / 102,
-    // 121 / 130, N = 8192 125 / 135, 164 / 180, 236 / 254, N = 16384 273 / 257, 374 / 349, 522 / 508, N = 24576 361 / 385, 484 / 519,
-    // 706 / 749; K-contiguous: 4096 tokens 68 / 80, 93 / 107, 138 / 153, 16384 256 / 277, 353 / 381, 545 / 623.  Fewer block-rows
-    // (8192 x 8192, 64 rows of tiles; 4096 x 4096, 32) are 18 % slower to 8 % faster with one.
+    // per pair.  One with 8 N-tiles (else an XCD gets a share of a pair), and where the slabs of two are more than L2 and the
+    // block-rows are enough for even lists of them; but two again where rows of B are a multiple of 32 KB apart: the slab of
+    // one tile then falls into a part of L2's sets (18944 x 3584, 128-row blocks, us per N-tile and XCD: N = 12288 61, 16384
+    // 68, 20480 60, 24576 60, 32768 68).  us, one / two, at 90 %, 128 / 32-row blocks: 18944 x 3584 N = 4096 64 / 79, 121 / 130,
+    // N = 8192 124 / 132, 235 / 250, N = 16384 273 / 257, 522 / 508; 8192 x 8192 N = 8192 118 / 129, 228 / 239, K-contiguous
+    // 121 / 137, 272 / 360; 4096 x 4096 36 / 33, 64 / 61; 8192 x 2048 38.6 / 37.7, 66 / 65.
     WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
-    const bool one = n_tiles == 8 || (n_tiles > 8 && n_rows >= 128 && (XT || N % 16384 != 0));
+    const bool one = n_tiles == 8 || (n_rows >= 64 && h->k >= 3072 && (XT || N % 16384 != 0));
     int group_n = env_group > 0 ? env_group : one ? 1 : 2;
     if (group_n > n_tiles) group_n = n_tiles;
     if (group_n == 1) {
@@ -693,14 +709,44 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
     if (env_workers > 0 && env_workers < workers) workers = env_workers;
     workers = std::max<int64_t>(8, workers / 8 * 8);  // the same number of workgroups on every XCD
     const int env_xcd = switches().bcsr_xcd_aware ? 1 : 0;  // benchmarking switch: 0 = ignore the XCDs when dealing tiles
-    XcdRuns runs = cut_runs(*op.weight_prefix, n_rows, n_tiles, group_n);
-    if (!env_xcd)
-        for (int x = 1; x <= 8; ++x) runs.start[x] = runs.start[8];
+    XcdRuns runs;
+    WideShares shares = {0x7fffffff, 0, 0};
+    const int32_t *share_first = nullptr;
+    const BcsrShares &sh = h->shares;
+    if (n_tiles % 8 != 0 && sh.pass > 0 && env_group <= 0 && env_workers <= 0 && env_xcd) {
+        // The N-tiles do not divide among the XCDs, and an XCD's run of the schedule would end inside its lists: the heaviest
+        // workgroup then has 1.3 to 2.4 times the mean.  Instead every XCD takes as many whole tiles, and the t others are
+        // dealt to all workgroups in lists made for that t (heaviest over mean 1.03 to 1.4).  Of the t there are (the
+        // remainder, or 8 or 16 more) the one with the lightest heaviest workgroup; with more than 8 an XCD has two or three
+        // slabs of B in flight, which costs (16 tiles, 2 over 1: K = 2048 0.97, 3584 1.05, 8192 1.05 to 1.3).  us, before /
+        // now, at 90 %: 18944 x 3584, 128-row blocks, N = 2048 50 / 38, N = 3072 74 / 57, K-contiguous 50 / 39, 78 / 57; 8192 x
+        // 8192 K-contiguous, 3072 tokens 68 / 54; 3584 x 18944, N = 5120 119 / 95.  (With 8, 16, ... tiles the lists above are
+        // even, and walking a pair from them is up to 5 % faster than from shares of 16.)
+        const double crowd = std::max(0.0, (double)h->k / 32768 - 0.05);
+        double best = 0;
+        int t = 0;
+        for (int c = n_tiles % 8; c <= BcsrShares::MAX_TILES && c <= n_tiles; c += 8) {
+            const int passes = (n_tiles - c) / 8;
+            const double w = passes / 2 * (double)sh.two_passes + passes % 2 * (double)sh.pass +
+                             (double)sh.longest[c] * (1 + crowd * ((c - 1) / 8));
+            if (t == 0 || w < best) best = w, t = c;
+        }
+        group_n = 1;
+        workers = BcsrShares::WORKERS;
+        op.rank_info = (const int4 *)h->d_share_lists;
+        for (int x = 0; x <= 8; ++x) runs.start[x] = (int)((n_tiles - t) / 8 * x * n_rows);
+        shares = {n_tiles - t, BcsrShares::WORKERS / t, (int)(op.n_brows + (t - 1) * n_rows)};
+        share_first = h->d_share_lists + sh.infos * 4 + (t - 1) * BcsrShares::FIRST_PITCH;
+    } else {
+        runs = cut_runs(*op.weight_prefix, n_rows, n_tiles, group_n);
+        if (!env_xcd)
+            for (int x = 1; x <= 8; ++x) runs.start[x] = runs.start[8];
+    }
     dim3 grid((unsigned)workers), block(256);
 #define ASP_LAUNCH_WIDE(GATHER)                                                                                        \
     hipLaunchKernelGGL((bcsr_spmm_wide_kernel<XT, GATHER>), grid, block, 0, stream, op.rank_info, op.cols, op.values,  \
                        (const uint16_t *)B, (uint16_t *)C, (int)h->m, (int)h->k, (int)N, (int)n_rows, (int)op.n_brows,  \
-                       (int)op.n_blocks, n_tiles, group_n, env_xcd, runs, op.piece_rows)
+                       (int)op.n_blocks, n_tiles, group_n, env_xcd, runs, op.piece_rows, shares, share_first)
     if (op.composite) ASP_LAUNCH_WIDE(true);
     else ASP_LAUNCH_WIDE(false);  // K % 128 == 0 (bcsr_wide_capable)
 #undef ASP_LAUNCH_WIDE

@@ -152,13 +152,12 @@ void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *co
     });
 }
 
-// Exchanges entries between the heaviest list and the others while the heavier one of the two gets lighter.
+// Exchanges entries between the heaviest list and another one while that makes the heavier of the two lighter.
 template <class Len>
-static void balance_lists(std::vector<std::vector<int32_t>> &lists, std::vector<int64_t> &load, Len len) {
+static void exchange_entries(std::vector<std::vector<int32_t>> &lists, std::vector<int64_t> &load, Len len) {
     const int n = (int)lists.size();
     for (int step = 0; step < 4 * n; ++step) {
         const int h = (int)(std::max_element(load.begin(), load.end()) - load.begin());
-        // the exchange that brings both loads closest to each other
         int64_t best = 0;
         int to = -1;
         size_t from_i = 0, to_i = 0;
@@ -167,13 +166,24 @@ static void balance_lists(std::vector<std::vector<int32_t>> &lists, std::vector<
                 for (size_t j = 0; j < lists[l].size(); ++j) {
                     const int64_t d = len(lists[h][i]) - len(lists[l][j]);  // moves from h to l
                     const int64_t gain = load[h] - std::max(load[h] - d, load[l] + d);
-                    if (d > 0 && gain > best) best = gain, to = l, from_i = i, to_i = j;
+                    if (gain > best) best = gain, to = l, from_i = i, to_i = j;
                 }
-        if (to < 0) return;
+        if (to < 0) break;
         const int64_t d = len(lists[h][from_i]) - len(lists[to][to_i]);
         std::swap(lists[h][from_i], lists[to][to_i]);
         load[h] -= d, load[to] += d;
     }
+}
+
+// Inside a list the order is free (the sum stays).  Entries go by the block column of their first block: the block-rows
+// that run at the same time then start in the same few block columns, their first slabs of B are requested by several
+// workgroups of the XCD at about the same time and cross the memory side of L2 once (7 % less time on 90 % Bernoulli
+// masks than lists in order of weight).
+static void sort_by_first_column(const HostBcsr &b, std::vector<std::vector<int32_t>> &lists) {
+    for (auto &l : lists)
+        std::stable_sort(l.begin(), l.end(), [&](int32_t x, int32_t y) {
+            return b.block_col_idx[b.block_row_ptr[x]] < b.block_col_idx[b.block_row_ptr[y]];
+        });
 }
 
 // The order of the main BCSR kernels: they deal its consecutive entries to the workgroups of an XCD round-robin, n_lists
@@ -196,38 +206,14 @@ static void order_in_lists(const HostBcsr &b, const std::vector<int32_t> &sorted
         lists[best].push_back(sorted[r]);
         load[best] += len(sorted[r]) + 1;
     }
-    // Entries are exchanged between the heaviest list and another one while that makes the heavier of the two lighter.
     // (Few entries to a list leave the rule above far off: 18944 x 3584 at 90 %, 32 lists, heaviest over mean 1.31 to 1.37
     // with 128-row blocks, 1.20 with 64, 1.15 with 32; after the exchanges 1.01 to 1.05.  Long lists are even as they are.)
-    for (int step = 0; n_nonempty > n_lists && n_nonempty <= 64 * n_lists && step < 4 * n_lists; ++step) {
-        const int h = (int)(std::max_element(load.begin(), load.end()) - load.begin());
-        int64_t best = 0;
-        int to = -1;
-        size_t from_i = 0, to_i = 0;
-        for (int l = 0; l < n_lists; ++l)
-            for (size_t i = 0; l != h && i < lists[h].size(); ++i)
-                for (size_t j = 0; j < lists[l].size(); ++j) {
-                    const int64_t d = len(lists[h][i]) - len(lists[l][j]);  // moves from h to l
-                    const int64_t gain = load[h] - std::max(load[h] - d, load[l] + d);
-                    if (gain > best) best = gain, to = l, from_i = i, to_i = j;
-                }
-        if (to < 0) break;
-        const int64_t d = len(lists[h][from_i]) - len(lists[to][to_i]);
-        std::swap(lists[h][from_i], lists[to][to_i]);
-        load[h] -= d, load[to] += d;
-    }
+    if (n_nonempty > n_lists && n_nonempty <= 64 * n_lists) exchange_entries(lists, load, len);
     // Lists with one entry more go first, so that the entries of the last, incomplete round are those of lists
     // 0, 1, ... and "entry j belongs to list j % n_lists" holds for every j.
     std::stable_sort(lists.begin(), lists.end(),
                      [](const std::vector<int32_t> &x, const std::vector<int32_t> &y) { return x.size() > y.size(); });
-    // Inside a list the order is free (the sum stays).  Entries go by the block column of their first block:
-    // the block-rows of one round then start in the same few block columns, their first slabs of B are requested
-    // by several workgroups of the XCD at about the same time and cross the memory side of L2 once
-    // (7 % less time on 90 % Bernoulli masks than lists in order of weight).
-    for (auto &l : lists)
-        std::stable_sort(l.begin(), l.end(), [&](int32_t x, int32_t y) {
-            return b.block_col_idx[b.block_row_ptr[x]] < b.block_col_idx[b.block_row_ptr[y]];
-        });
+    sort_by_first_column(b, lists);
     order.reserve(sorted.size());
     for (size_t e = 0; order.size() < (size_t)n_nonempty; ++e)
         for (auto &l : lists)
@@ -266,6 +252,68 @@ void bcsr_build_schedule(HostBcsr &b, bool by_length) {
     if (by_length) return;
     fill(32, b.rank_info_32, b.weight_prefix_32);
     fill(64, b.rank_info_64, b.weight_prefix_64);
+}
+
+// Lists for the N-tiles that are left when every XCD has had the same number of whole ones: t of them (1 to 24) are dealt to
+// 256 workgroups, 256 / t to a tile, and a workgroup walks one list of its tile's block-rows.  Longest block-row first, each
+// to the lightest of the lists with the fewest entries, then exchanges; without regard to the entries where that makes the
+// heaviest list 5 % lighter (lists of one length keep the workgroups of an XCD in the same block columns).  Also what the
+// lists weigh, from which a launch takes its t.
+void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
+    const int64_t n = b.n_nonempty;
+    out = BcsrShares();
+    const int64_t tile = 2;  // what a tile costs beside its blocks, in blocks
+    if (n == 0 || n > BcsrShares::MAX_ROWS) return;
+    auto len = [&](int32_t r) { return b.block_row_ptr[r + 1] - b.block_row_ptr[r]; };
+    std::vector<int32_t> sorted(n);
+    for (int64_t r = 0; r < n; ++r) sorted[r] = b.rank_info[4 * r];
+    std::stable_sort(sorted.begin(), sorted.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
+    out.infos = (int64_t)b.rank_info_32.size() / 4 + BcsrShares::MAX_TILES * n;
+    out.lists = b.rank_info_32;
+    out.lists.resize((size_t)out.infos * 4 + BcsrShares::MAX_TILES * BcsrShares::FIRST_PITCH);
+    parallel_chunks(BcsrShares::MAX_TILES, 1, [&](unsigned, int64_t lo, int64_t hi) {
+        for (int64_t i = lo; i < hi; ++i) {
+            const int n_lists = BcsrShares::WORKERS / (int)(i + 1);
+            std::vector<std::vector<int32_t>> lists;
+            int64_t longest = 0;
+            for (int even = 1; even >= 0; --even) {
+                std::vector<std::vector<int32_t>> cand(n_lists);
+                std::vector<int64_t> load(n_lists, 0);
+                for (int64_t r = 0; r < n; ++r) {
+                    const size_t most = even ? (size_t)(r / n_lists) : (size_t)n;  // entries that a list may have already
+                    int best = -1;
+                    for (int l = 0; l < n_lists; ++l)
+                        if (cand[l].size() <= most && (best < 0 || load[l] < load[best])) best = l;
+                    cand[best].push_back(sorted[r]);
+                    load[best] += len(sorted[r]) + tile;
+                }
+                if (n > n_lists) exchange_entries(cand, load, len);
+                const int64_t w = *std::max_element(load.begin(), load.end());
+                if (even || w * 100 < longest * 95) longest = w, lists.swap(cand);
+            }
+            sort_by_first_column(b, lists);
+            int32_t *info = out.lists.data() + b.rank_info_32.size() + i * n * 4;
+            int32_t *first = out.lists.data() + out.infos * 4 + i * BcsrShares::FIRST_PITCH;
+            int32_t at = 0;
+            for (int l = 0; l < n_lists; ++l) {
+                first[l] = at;
+                for (int32_t r : lists[l]) {
+                    const int32_t v[4] = {r, b.block_row_ptr[r], len(r), b.block_col_idx[b.block_row_ptr[r]]};
+                    std::copy(v, v + 4, info + 4 * at++);
+                }
+            }
+            std::fill(first + n_lists, first + BcsrShares::FIRST_PITCH, at);
+            out.longest[i + 1] = longest;
+        }
+    });
+    // one pass and two passes (there and back) over the 32 lists of rank_info_32
+    std::vector<int64_t> once(32, 0), back(32, 0);
+    for (int64_t r = 0; r < n; ++r) {
+        once[r % 32] += b.rank_info_32[4 * r + 2] + tile;
+        back[r % 32] += b.rank_info_32[4 * (n - 1 - r) + 2] + tile;
+    }
+    out.pass = *std::max_element(once.begin(), once.end());
+    for (int l = 0; l < 32; ++l) out.two_passes = std::max(out.two_passes, once[l] + back[l]);
 }
 
 // Composite form of a bf16 BCSR matrix with 64x64 or 32x32 blocks, for the kernel written for 128x128 blocks

@@ -31,7 +31,7 @@ asp_status_t fail(asp_status_t s, const std::string &msg);
 struct Switches {
     int bcsr_bn;          // ASP_BCSR_BN=64|128|256: widest BCSR tile to consider (0: no cap)
     bool bcsr_regstage;   // ASP_BCSR_KERNEL=regstage: the synchronous register-staged kernel
-    int bcsr_group_n;     // ASP_BCSR_GROUP_N=<n>: N-tiles walked together (0: the kernels' defaults, 2 and 4)
+    int bcsr_group_n;     // ASP_BCSR_GROUP_N=<n>: N-tiles walked together (0: the kernels' own rules)
     int bcsr_wgs_per_cu;  // ASP_BCSR_WGS_PER_CU=<n>: resident workgroups of the ring kernel (0: as many as LDS allows)
     int bcsr_workgroups;  // ASP_BCSR_WORKGROUPS=<n>: resident workgroups of the 128x512-tile kernel (0: one per compute unit)
     bool bcsr_xcd_aware;  // ASP_BCSR_XCD_AWARE=0: deal tiles without regard to XCDs
@@ -99,6 +99,19 @@ struct HostBcsr {
     std::vector<int32_t> piece_rows;           // composite form only: [super-rows][4] first row of C of each 32-row piece, -1 = none
 };
 
+// BCSR, 128 x 512 tiles: shares of 1 to 24 N-tiles (bcsr_build_shares); empty where block-rows are so many that whole rounds
+// of them are even enough
+struct BcsrShares {
+    static constexpr int MAX_TILES = 24, WORKERS = 256, FIRST_PITCH = WORKERS + 1;
+    static constexpr int64_t MAX_ROWS = 512;
+    // rank_info_32; [MAX_TILES][n_nonempty][4] in its form, the block-rows list after list for 1, 2, ... tiles (together
+    // `infos` entries); [MAX_TILES][FIRST_PITCH] the first entry of every list
+    std::vector<int32_t> lists;
+    int64_t infos = 0;
+    int64_t longest[MAX_TILES + 1] = {0};  // stored blocks + 2 per tile, of the heaviest list
+    int64_t pass = 0, two_passes = 0;      // the same for whole N-tiles dealt from rank_info_32
+};
+
 struct HostWcsr {
     std::vector<int32_t> window_row_ptr;  // [n_windows + 1]
     std::vector<int32_t> window_col_idx;  // [padded_cols]
@@ -126,6 +139,7 @@ struct HostRows {
 void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostBcsr &out);
 void bcsr_build_schedule(HostBcsr &b, bool by_length = false);
+void bcsr_build_shares(const HostBcsr &b, BcsrShares &out);
 double bcsr_build_composite(const HostBcsr &in, int64_t m, int64_t k, int32_t b, HostBcsr &out);
 void bcsr_pack_fragments_bf16(const HostBcsr &in, int32_t b_row, int32_t b_col, std::vector<uint8_t> &packed);
 void bcsr_pack_fragments_f32(const HostBcsr &in, int32_t b_row, int32_t b_col, std::vector<uint8_t> &packed);
@@ -160,6 +174,8 @@ struct asp_handle {
     int64_t c_n_brows = 0, c_n_units = 0;  // super-rows, composite blocks
     int32_t *d_c_rank_info = nullptr;
     int32_t *d_c_rank_info_32 = nullptr;
+    asp::BcsrShares shares;         // of hc, or of hb with 128-row blocks; its lists live on the device only
+    int32_t *d_share_lists = nullptr;
     int32_t *d_c_slice_rows = nullptr;     // [composite blocks][4]
     int32_t *d_c_piece_rows = nullptr;     // [super-rows][4]
     void *d_c_values = nullptr;

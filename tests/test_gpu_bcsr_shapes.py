@@ -110,3 +110,14 @@ def test_groups_of_column_tiles(b, m, k, N, xt):
         C = gpu_spmm(a, "bcsr", b, b, B)
         assert not ((C & 0x7F80) == 0x7F80).any()
         check_against_oracle(a, B, C, e)
+
+
+# 128x512 tiles whose number does not divide among the XCDs, with empty block-rows: (block, m, k, N); 4, 10, 13, 21, 9, 15 and 26
+# N-tiles, shared whole, after one or two rounds of whole tiles, in two or three to an XCD
+@pytest.mark.parametrize("b,m,k,N", [
+    (128, 17000, 512, 1544), (64, 8200, 512, 4616), (32, 4160, 256, 6168), (128, 3200, 640, 10248), (128, 5004, 1000, 4104),
+    (64, 3400, 300, 7680), (32, 2048, 96, 13000),
+])
+@pytest.mark.parametrize("xt", [False, True])
+def test_shared_column_tiles(b, m, k, N, xt):
+    test_groups_of_column_tiles(b, m, k, N, xt)

@@ -1,5 +1,6 @@
 // Prints the work lists that the converters make of a synthetic matrix, for tests/test_wcsr_lists.py and test_bcsr_order.py.
 //   order L..        BCSR block-rows of L blocks each: the orders of the tile kernels in 16, 32 and 64 lists
+//   shares L..       the lists for shared N-tiles, and what the heaviest of each weighs
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
@@ -34,14 +35,40 @@ static int slots(int32_t first) {
     return 0;
 }
 
-static int order(const std::vector<int32_t> &lengths) {
-    asp::HostBcsr b;
+static void schedule(const std::vector<int32_t> &lengths, asp::HostBcsr &b) {
     b.block_row_ptr.assign(1, 0);
     for (int32_t n : lengths) {
         for (int32_t j = 0; j < n; ++j) b.block_col_idx.push_back(j);
         b.block_row_ptr.push_back((int32_t)b.block_col_idx.size());
     }
     asp::bcsr_build_schedule(b);
+}
+
+static int shares(const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    schedule(lengths, b);
+    asp::BcsrShares s;
+    asp::bcsr_build_shares(b, s);
+    std::printf("passes %lld %lld\n", (long long)s.pass, (long long)s.two_passes);
+    if (s.lists.empty()) return 0;
+    const size_t whole = lengths.size() * 4, n = (size_t)b.n_nonempty * 4;
+    print("whole", std::vector<int32_t>(s.lists.begin(), s.lists.begin() + whole), 4);
+    for (int t = 1; t <= asp::BcsrShares::MAX_TILES; ++t) {
+        char name[16];
+        std::snprintf(name, sizeof name, "t%d", t);
+        const auto info = s.lists.begin() + whole + (t - 1) * n;
+        print(name, std::vector<int32_t>(info, info + n), 4);
+        std::snprintf(name, sizeof name, "first%d", t);
+        const auto first = s.lists.begin() + s.infos * 4 + (t - 1) * asp::BcsrShares::FIRST_PITCH;
+        print(name, std::vector<int32_t>(first, first + asp::BcsrShares::FIRST_PITCH), 1);
+        std::printf("longest%d %lld\n", t, (long long)s.longest[t]);
+    }
+    return 0;
+}
+
+static int order(const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    schedule(lengths, b);
     print("16", b.rank_info, 4);
     print("32", b.rank_info_32, 4);
     print("64", b.rank_info_64, 4);
@@ -53,10 +80,10 @@ static int order(const std::vector<int32_t> &lengths) {
 
 int main(int argc, char **argv) {
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
-    if (argc > 2 && std::strcmp(argv[1], "order") == 0) {
+    if (argc > 2 && (std::strcmp(argv[1], "order") == 0 || std::strcmp(argv[1], "shares") == 0)) {
         std::vector<int32_t> lengths;
         for (int i = 2; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
-        return order(lengths);
+        return std::strcmp(argv[1], "order") == 0 ? order(lengths) : shares(lengths);
     }
     return 2;
 }
