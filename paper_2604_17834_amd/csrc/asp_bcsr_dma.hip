@@ -549,6 +549,7 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
     const int fit = (int)(163840 / DmaCfg<BR, BN, WM, WN, NS, XT>::LDS_BYTES);
     const int per_cu = std::max(1, std::min(fit, 8 / (WM * WN)));
     int64_t workers = (int64_t)h->n_cus * (env_wgs > 0 ? env_wgs : per_cu);
+    const int64_t full = workers;
     if (workers > p.workgroups) workers = p.workgroups;
     workers = std::max<int64_t>(8, workers / 8 * 8);  // the same number of workgroups on every XCD
     // N-tiles walked together.  Few of them: an XCD reads the slab of B of one N-tile for many block-rows, whose requests meet
@@ -574,6 +575,11 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
     const int4 *rank_info = (const int4 *)(lists == 64 ? h->d_rank_info_64 : lists == 32 ? h->d_rank_info_32 : h->d_rank_info);
     const XcdRuns runs = cut_runs(lists == 64 ? h->hb.weight_prefix_64 : lists == 32 ? h->hb.weight_prefix_32 : h->hb.sorted_weight_prefix,
                                   h->n_brows, p.n_tiles, group_n);
+    // A workgroup for every tile of the longest run where the chip holds them: runs of equal weight differ in tiles, and with
+    // the mean number of workgroups one of them walked two (us, before / now: 3584 x 18944 at 90 %, 128-row, N = 3584 137 / 85,
+    // N = 3072 100 / 79; 3392 x 4864 at 50 %, N = 1464 75 / 54; 1664 x 3264 at 80 %, 32-row, K-contiguous, 1736 tokens 26.5 / 17.6).
+    for (int x = 0; x < 8; ++x) workers = std::max<int64_t>(workers, 8ll * (runs.start[x + 1] - runs.start[x]));
+    workers = std::min(workers, std::max<int64_t>(8, full / 8 * 8));
     dim3 grid((unsigned)workers), block(WM * WN * 64);
     // benchmarking switch: tiles pulled from per-XCD atomic counters (built for the 128 x 256 tiles of the ladder;
     // everything else keeps the static schedule)
