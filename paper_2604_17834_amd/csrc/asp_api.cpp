@@ -68,6 +68,7 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_c_rank_info_32);
     (void)hipFree(h->d_rank_info_32);
     (void)hipFree(h->d_rank_info_64);
+    (void)hipFree(h->d_by_length);
     (void)hipFree(h->d_c_slice_rows);
     (void)hipFree(h->d_share_lists);
     (void)hipFree(h->d_c_piece_rows);
@@ -173,6 +174,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if (cfg->dtype == ASP_DT_BF16) {
             if ((s = upload(&h->d_rank_info_32, h->hb.rank_info_32.data(), h->hb.rank_info_32.size() * 4, stream))) return s;
             if ((s = upload(&h->d_rank_info_64, h->hb.rank_info_64.data(), h->hb.rank_info_64.size() * 4, stream))) return s;
+            if ((s = upload(&h->d_by_length, h->hb.by_length.data(), h->hb.by_length.size() * 4, stream))) return s;
         }
         if (h->has_comp) {
             if ((s = upload(&h->d_c_rank_info_32, h->hc.rank_info_32.data(), h->hc.rank_info_32.size() * 4, stream))) return s;

@@ -58,19 +58,20 @@ template <int BR, int BC, int BN, int WM, int WN, bool VEC>
 __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     const int32_t *__restrict__ block_row_ptr, const int32_t *__restrict__ block_col_idx,
     const uint16_t *__restrict__ a_packed, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int K,
-    int N, int n_brows, int n_tiles, int tiles_per_xcd) {
+    int N, int n_brows, const int32_t *__restrict__ order, XcdRuns runs) {
     using Cfg = BcsrCfg<BR, BC, BN, WM, WN, VEC>;
     constexpr int NT = Cfg::NT, KS = Cfg::KS, MT = Cfg::MT, NTL = Cfg::NTL;
     __shared__ __attribute__((aligned(16))) uint8_t lds[Cfg::LDS_BYTES];
 
-    // Workgroups are handed to the 8 XCDs round-robin by flat id.  Give each XCD a contiguous run of
+    // Workgroups are handed to the 8 XCDs round-robin by flat id.  Each XCD gets a contiguous run of
     // the (N-tile major, block-row minor) tile order so that the workgroups sharing one XCD's L2 work
-    // on the same column slab of B.
+    // on the same column slab of B.  With an order, longest block-row first, the runs weigh the same: a compute unit takes
+    // the next workgroup when one ends, so the last ones should be short.
     const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int64_t total = (int64_t)n_brows * n_tiles;
-    const int64_t u = (int64_t)xcd * tiles_per_xcd + local;
-    if (local >= tiles_per_xcd || u >= total) return;
-    const int nt = (int)(u / n_brows), br = (int)(u % n_brows);
+    const int u = runs.start[xcd] + local;
+    if (u >= runs.start[xcd + 1]) return;
+    const int nt = __builtin_amdgcn_readfirstlane(u / n_brows), pos = u - nt * n_brows;
+    const int br = __builtin_amdgcn_readfirstlane(order ? order[pos] : pos);
     const int n0 = nt * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -295,13 +296,25 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
 // false: too many threads for a launch
 template <int BR, int BN, int WM, int WN, bool VEC>
 static bool launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
-    const int64_t total = p.workgroups;
-    const int tiles_per_xcd = (int)ceil_div(total, 8);
-    if (!launch_fits(tiles_per_xcd * 8ll, WM * WN * 64)) return false;
-    dim3 grid((unsigned)(tiles_per_xcd * 8)), block(WM * WN * 64);
+    const int64_t total = p.workgroups, even = ceil_div(total, 8);
+    if (!launch_fits(even * 8, WM * WN * 64)) return false;
+    // Longest block-rows first where the tiles are more than the 4 or so that a compute unit holds at once (us, as stored / longest
+    // first: 4519 x 8812 at 90 %, 128-row, N = 4037 105 / 90; 1869 x 3209 at 50 %, 32-row, N = 4093 112 / 100; geometric lengths,
+    // 6593 x 6251 at 95 %, 64-row, N = 1437 53 / 45; with fewer tiles 8960 x 8011 at 75 %, 128-row, N = 535 75 / 80).
+    // Not for a run of next to nothing but empty block-rows, which would be most of the grid.
+    const int32_t *order = total > 4ll * h->n_cus ? h->d_by_length : nullptr;
+    XcdRuns runs;
+    int64_t longest = 0;
+    if (order) runs = cut_runs(h->hb.length_prefix, h->n_brows, p.n_tiles, 1, false);
+    for (int x = 0; order && x < 8; ++x) longest = std::max<int64_t>(longest, runs.start[x + 1] - runs.start[x]);
+    if (!order || longest > 2 * even || !launch_fits(longest * 8, WM * WN * 64)) {
+        longest = even;
+        for (int x = 0; x <= 8; ++x) runs.start[x] = (int)std::min(total, x * even);
+    }
+    dim3 grid((unsigned)(longest * 8)), block(WM * WN * 64);
     hipLaunchKernelGGL((bcsr_spmm_kernel<BR, BR, BN, WM, WN, VEC>), grid, block, 0, stream, h->d_row_ptr, h->d_col_idx,
                        (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m, (int)h->k, (int)N,
-                       (int)h->n_brows, p.n_tiles, tiles_per_xcd);
+                       (int)h->n_brows, order, runs);
     return true;
 }
 

@@ -501,7 +501,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BR / WM) * (BN / WN) > 8192 ? 1 : 2) 
 // Cut the tile order into 8 runs of equal weight.  Tile weight = stored blocks of its block-row + 1
 // (the 1 stands for the epilogue).  Groups of N-tiles repeat the same sorted list of block-rows, so a
 // cut is found from the per-handle prefix sums over that list.
-XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t nbr, int n_tiles, int group_n) {
+XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t nbr, int n_tiles, int group_n, bool turn) {
     const int64_t rows_weight = pre[nbr];
     const int64_t n_groups = ceil_div(n_tiles, group_n);
     const int64_t total_weight = rows_weight * n_tiles;
@@ -509,22 +509,17 @@ XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t nbr, int n_tiles, int 
     r.start[0] = 0;
     for (int x = 1; x < 8; ++x) {
         const int64_t target = total_weight * x / 8;
-        // whole groups before the cut
-        int64_t g = 0, acc = 0;
-        for (; g < n_groups; ++g) {
-            const int64_t gw = std::min<int64_t>(group_n, n_tiles - g * group_n);
-            if (acc + gw * rows_weight > target) break;
-            acc += gw * rows_weight;
-        }
-        if (g >= n_groups) {
+        if (target >= total_weight) {  // (nothing to weigh)
             r.start[x] = (int)(nbr * n_tiles);
             continue;
         }
+        const int64_t g = std::min(target / (group_n * rows_weight), n_groups - 1);  // whole groups before the cut
+        const int64_t acc = g * group_n * rows_weight;
         const int64_t gw = std::min<int64_t>(group_n, n_tiles - g * group_n);
         // first position whose prefix (times the group width) reaches the remainder; odd groups walk
-        // the block-rows lightest first
+        // the block-rows lightest first (turn)
         const int64_t rem = target - acc;
-        auto prefix = [&](int64_t j) { return (g & 1) ? rows_weight - pre[nbr - j] : pre[j]; };
+        auto prefix = [&](int64_t j) { return turn && (g & 1) ? rows_weight - pre[nbr - j] : pre[j]; };
         int64_t lo = 0, hi = nbr;
         while (lo < hi) {
             int64_t mid = (lo + hi) / 2;

@@ -250,6 +250,9 @@ void bcsr_build_schedule(HostBcsr &b, bool by_length) {
     };
     fill(by_length ? 0 : 16, b.rank_info, b.sorted_weight_prefix);
     if (by_length) return;
+    b.by_length = sorted;
+    b.length_prefix.assign(nbr + 1, 0);
+    for (int64_t r = 0; r < nbr; ++r) b.length_prefix[r + 1] = b.length_prefix[r] + len(b.by_length[r]) + 1;
     fill(32, b.rank_info_32, b.weight_prefix_32);
     fill(64, b.rank_info_64, b.weight_prefix_64);
 }

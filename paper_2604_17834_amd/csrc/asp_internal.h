@@ -93,6 +93,8 @@ struct HostBcsr {
     std::vector<int64_t> sorted_weight_prefix; // [n_brows + 1]
     std::vector<int32_t> rank_info_32, rank_info_64;        // the same in 32 and 64 lists instead of 16
     std::vector<int64_t> weight_prefix_32, weight_prefix_64;
+    std::vector<int32_t> by_length;            // bf16: block-rows, longest first,
+    std::vector<int64_t> length_prefix;        // and the prefix sums of their weights
     int64_t n_nonempty = 0;                    // block-rows with at least one stored block (they come first)
     int64_t max_blocks = 0;                    // stored blocks of the longest block-row
     std::vector<int32_t> slice_rows;           // composite form only: [blocks][4] first row of B of each K slice
@@ -189,6 +191,7 @@ struct asp_handle {
     int32_t *d_zero_windows = nullptr;
     int32_t *d_rank_info = nullptr; // BCSR: [n_brows][4] = {block-row, first block, stored blocks, block column of the first one}, heaviest first
     int32_t *d_rank_info_32 = nullptr, *d_rank_info_64 = nullptr;
+    int32_t *d_by_length = nullptr;
     int n_cus = 0;                  // compute units of the owning device
     int32_t *d_sched = nullptr;     // BCSR: 8 tile counters of the dynamic-scheduling variant (a benchmarking switch)
     // WCSR: where the tasks of split windows put their partial tiles

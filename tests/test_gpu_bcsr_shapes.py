@@ -3,6 +3,7 @@ test_gpu_xt_short.py (on 256 compute units): strips of every wave tile and K spl
 the row-major ring kernel at every tile size, with K a multiple of the block and not.
 
 Tolerance as everywhere in bf16: 1e-2 * S + 1e-5, S = |A| x |B| from the oracle."""
+import dataclasses
 import functools
 
 import numpy as np
@@ -121,3 +122,19 @@ def test_groups_of_column_tiles(b, m, k, N, xt):
 @pytest.mark.parametrize("xt", [False, True])
 def test_shared_column_tiles(b, m, k, N, xt):
     test_groups_of_column_tiles(b, m, k, N, xt)
+
+
+# register-staged tiles with rows of C that are not aligned: fewer tiles than the chip holds at once, more (longest block-rows
+# first), and one dense block-row above empty ones (which would be most of a run of equal weight)
+@pytest.mark.parametrize("b,m,k,N,dense", [
+    (64, 1000, 700, 65, False), (32, 4001, 300, 1021, False), (64, 3000, 333, 2001, False), (128, 5000, 400, 4097, False),
+    (32, 38400, 200000, 33, True),
+])
+def test_register_staged_tile_order(b, m, k, N, dense):
+    a = synth.block_sparse_bernoulli(b if dense else m, k, b, b, 0.0 if dense else 0.75, seed=9, dtype="bf16")
+    if dense:
+        a = dataclasses.replace(a, m=m, row_ptr=np.r_[a.row_ptr, np.full(m - b, a.row_ptr[-1], a.row_ptr.dtype)])
+    B = synth.dense_normal(k, N, "bf16", seed=N)
+    C = gpu_spmm(a, "bcsr", b, b, B)
+    assert not C[np.diff(a.row_ptr) == 0].any() and not ((C & 0x7F80) == 0x7F80).any()
+    check_against_oracle(a, B, C, _edges(N))
