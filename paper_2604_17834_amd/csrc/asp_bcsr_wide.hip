@@ -719,8 +719,8 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
         // dealt to all workgroups in lists made for that t (heaviest over mean 1.03 to 1.4).  Of the t there are (the
         // remainder, or 8 or 16 more) the one with the lightest heaviest workgroup; with more than 8 an XCD has two or three
         // slabs of B in flight, which costs (16 tiles, 2 over 1: K = 2048 0.97, 3584 1.05, 8192 1.05 to 1.3).  us, before /
-        // now, at 90 %: 18944 x 3584, 128-row blocks, N = 2048 50 / 38, N = 3072 74 / 57, K-contiguous 50 / 39, 78 / 57; 8192 x
-        // 8192 K-contiguous, 3072 tokens 68 / 54; 3584 x 18944, N = 5120 119 / 95.  (With 8, 16, ... tiles the lists above are
+        // now, at 90 %: 18944 x 3584, 128-row blocks, N = 2048 50 / 37, N = 3072 63 / 53, K-contiguous 50 / 39, 68 / 57; 8192 x
+        // 8192 K-contiguous, 3072 tokens 67 / 53; 3584 x 18944, N = 5120 111 / 91.  (With 8, 16, ... tiles the lists above are
         // even, and walking a pair from them is up to 5 % faster than from shares of 16.)
         const double crowd = std::max(0.0, (double)h->k / 32768 - 0.05);
         double best = 0;
