@@ -293,24 +293,31 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned) {
     return p;
 }
 
+// Runs of the XCDs over the register-staged kernel's tiles.  True: in the order longest block-row first, runs of equal weight;
+// false: in the stored order, runs of as many tiles.
+// Longest first where the tiles are more than the 4 or so that a compute unit holds at once (us, as stored / longest
+// first: 4519 x 8812 at 90 %, 128-row, N = 4037 105 / 90; 1869 x 3209 at 50 %, 32-row, N = 4093 112 / 100; geometric lengths,
+// 6593 x 6251 at 95 %, 64-row, N = 1437 53 / 45; with fewer tiles 8960 x 8011 at 75 %, 128-row, N = 535 75 / 80).
+// Not where one XCD would get half of all tiles, next to nothing but empty block-rows to clear: the stored order then, an eighth
+// of the tiles each (in the order of length the first eighth holds the longest ones).
+bool register_staged_runs(const HostBcsr &b, int n_tiles, int64_t n_cus, int threads, XcdRuns &runs) {
+    const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1, total = nbr * n_tiles, even = ceil_div(total, 8);
+    if (total > 4 * n_cus) {
+        runs = cut_runs(b.length_prefix, nbr, n_tiles, 1, false);
+        const int64_t longest = longest_run(runs);
+        if (longest <= 4 * even && launch_fits(longest * 8, threads)) return true;
+    }
+    for (int x = 0; x <= 8; ++x) runs.start[x] = (int)std::min(total, x * even);
+    return false;
+}
+
 // false: too many threads for a launch
 template <int BR, int BN, int WM, int WN, bool VEC>
 static bool launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
-    const int64_t total = p.workgroups, even = ceil_div(total, 8);
-    if (!launch_fits(even * 8, WM * WN * 64)) return false;
-    // Longest block-rows first where the tiles are more than the 4 or so that a compute unit holds at once (us, as stored / longest
-    // first: 4519 x 8812 at 90 %, 128-row, N = 4037 105 / 90; 1869 x 3209 at 50 %, 32-row, N = 4093 112 / 100; geometric lengths,
-    // 6593 x 6251 at 95 %, 64-row, N = 1437 53 / 45; with fewer tiles 8960 x 8011 at 75 %, 128-row, N = 535 75 / 80).
-    // Not for a run of next to nothing but empty block-rows, which would be most of the grid.
-    const int32_t *order = total > 4ll * h->n_cus ? h->d_by_length : nullptr;
+    if (!launch_fits(ceil_div(p.workgroups, 8) * 8, WM * WN * 64)) return false;
     XcdRuns runs;
-    int64_t longest = 0;
-    if (order) runs = cut_runs(h->hb.length_prefix, h->n_brows, p.n_tiles, 1, false);
-    for (int x = 0; order && x < 8; ++x) longest = std::max<int64_t>(longest, runs.start[x + 1] - runs.start[x]);
-    if (!order || longest > 2 * even || !launch_fits(longest * 8, WM * WN * 64)) {
-        longest = even;
-        for (int x = 0; x <= 8; ++x) runs.start[x] = (int)std::min(total, x * even);
-    }
+    const int32_t *order = register_staged_runs(h->hb, p.n_tiles, h->n_cus, WM * WN * 64, runs) ? h->d_by_length : nullptr;
+    const int64_t longest = longest_run(runs);
     dim3 grid((unsigned)(longest * 8)), block(WM * WN * 64);
     hipLaunchKernelGGL((bcsr_spmm_kernel<BR, BR, BN, WM, WN, VEC>), grid, block, 0, stream, h->d_row_ptr, h->d_col_idx,
                        (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m, (int)h->k, (int)N,

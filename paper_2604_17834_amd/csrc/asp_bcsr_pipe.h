@@ -84,10 +84,16 @@ __device__ __forceinline__ u32x4 load_tail8(const uint16_t *row, int pos, int en
 struct XcdRuns {
     int start[9];
 };
+inline int64_t longest_run(const XcdRuns &r) {
+    int64_t n = 0;
+    for (int x = 0; x < 8; ++x) n = std::max<int64_t>(n, r.start[x + 1] - r.start[x]);
+    return n;
+}
 
 // Cut the tile order (groups of group_n N-tiles, inside a group the n_rows heaviest block-rows, each repeated over the group's
 // N-tiles, in the handle's order in even groups and backwards in odd ones, or always in order: turn = false) into 8 runs of
 // equal weight; pre[] are the prefix sums of the block-rows' tile weights in that order.
 XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t n_rows, int n_tiles, int group_n, bool turn = true);
+bool register_staged_runs(const HostBcsr &b, int n_tiles, int64_t n_cus, int threads, XcdRuns &runs);
 
 }  // namespace asp

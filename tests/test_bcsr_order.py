@@ -58,3 +58,32 @@ def test_shares_hold_every_block_row_once_per_tile(lists_of, lengths):  # noqa: 
         assert got["longest%d" % t][0] == [max(sums)]
         # no worse than a longest-first deal: below the mean plus the heaviest block-row
         assert max(sums) <= sum(sums) / per_tile + max(lengths) + 2
+
+
+def _partly_empty(rows, empty, seed):
+    rng = np.random.default_rng(seed)
+    return np.where(rng.random(rows) < empty, 0, rng.binomial(64, 0.3, rows))
+
+
+# (column tiles, block-row lengths): few tiles, many, half and more of the block-rows empty (whose runs of equal weight are short
+# of work to launch or too long), one filled block-row
+@pytest.mark.parametrize("n_tiles,lengths", [
+    (2, _partly_empty(400, 0, 1)), (16, _partly_empty(400, 0, 2)), (16, np.random.default_rng(3).geometric(0.05, 300)),
+    (3, _partly_empty(2048, 0.5, 4)), (3, _partly_empty(2048, 0.6, 5)), (6, _partly_empty(2048, 0.75, 6)),
+    (16, _partly_empty(2048, 0.75, 7)), (1, np.r_[6250, np.zeros(1199, int)]), (64, np.zeros(40, int)),
+])
+def test_register_staged_runs_weigh_the_same(lists_of, n_tiles, lengths):  # noqa: F811
+    got = lists_of("staged", n_tiles, 256, *lengths)
+    start, rows = [v[0] for v in got["start"]], len(lengths)
+    assert start[0] == 0 and start[8] == rows * n_tiles and start == sorted(start)
+    by_length = got["sorted"][0][0]
+    order = [v[0] for v in got["order"]] if by_length else range(rows)
+    assert sorted(order) == list(range(rows))
+    assert max(np.diff(start)) <= 4 * -(-rows * n_tiles // 8)
+    tile = 3 if 2 * np.count_nonzero(lengths) <= rows else 1   # a tile's own cost, in blocks
+    weight = np.tile(lengths[np.array(order)] + tile, n_tiles)
+    runs = [int(weight[a:b].sum()) for a, b in zip(start, start[1:])]
+    # in the order of length runs of equal weight, to one tile; in the stored order an eighth of the tiles, wherever the long ones are
+    eighth = -(-rows * n_tiles // 8)
+    even = [int(c.sum()) for c in np.split(np.tile(lengths + tile, n_tiles), range(eighth, rows * n_tiles, eighth))]
+    assert max(runs) <= (weight.sum() / 8 + max(lengths) + tile if by_length else max(even))

@@ -1,12 +1,14 @@
 // Prints the work lists that the converters make of a synthetic matrix, for tests/test_wcsr_lists.py and test_bcsr_order.py.
 //   order L..        BCSR block-rows of L blocks each: the orders of the tile kernels in 16, 32 and 64 lists
 //   shares L..       the lists for shared N-tiles, and what the heaviest of each weighs
+//   staged T C L..   the register-staged kernel's launch of T column tiles on C compute units: 1 (longest block-row first) or 0
+//                    (as stored), the starts of the XCDs' runs, the order longest first
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 
-#include "asp_internal.h"
+#include "asp_bcsr_pipe.h"
 
 static void print(const char *name, const std::vector<int32_t> &v, size_t width) {
     for (size_t i = 0; i < v.size(); i += width) {
@@ -78,8 +80,23 @@ static int order(const std::vector<int32_t> &lengths) {
     return 0;
 }
 
+static int staged(int n_tiles, int64_t n_cus, const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    schedule(lengths, b);
+    asp::XcdRuns runs;
+    std::printf("sorted %d\n", (int)asp::register_staged_runs(b, n_tiles, n_cus, 256, runs));
+    for (int x = 0; x <= 8; ++x) std::printf("start %d\n", runs.start[x]);
+    print("order", b.by_length, 1);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
+    if (argc > 4 && std::strcmp(argv[1], "staged") == 0) {
+        std::vector<int32_t> lengths;
+        for (int i = 4; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
+        return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths);
+    }
     if (argc > 2 && (std::strcmp(argv[1], "order") == 0 || std::strcmp(argv[1], "shares") == 0)) {
         std::vector<int32_t> lengths;
         for (int i = 2; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
