@@ -32,6 +32,8 @@
 // workgroups once their streams have ended).  At the end of its stream a workgroup keeps requesting the last block again (into
 // free buffers, never read), so every step issues the same loads and the wait counts are constants.
 // Scheduling, swizzling, store accounting: as in the 64 x 128 kernel.
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -682,6 +684,80 @@ static WideOperand wide_operand(const asp_handle *h) {
                        h->c_n_units,                   true,                  (const int4 *)h->d_c_piece_rows};
 }
 
+// What the heaviest of the 256 workgroups walks, in stored blocks and 2 for every tile: t N-tiles in shares after whole ones, or
+// (t = 0) pairs of N-tiles.  Tile after tile, as the kernel deals them: a workgroup's tiles run on from one N-tile into the next.
+int64_t wide_heaviest(const HostBcsr &b, const BcsrShares &s, int n_tiles, int t) {
+    constexpr int WGS = BcsrShares::WORKERS / 8;
+    const int64_t n = b.n_nonempty;
+    const int group_n = t > 0 || n_tiles == 1 ? 1 : 2;
+    const std::vector<int32_t> &info = group_n == 1 ? b.rank_info_32 : b.rank_info;
+    const int whole = (n_tiles - t) / 8;
+    XcdRuns runs;
+    if (t == 0) runs = cut_runs(group_n == 1 ? b.weight_prefix_32 : b.sorted_weight_prefix, n, n_tiles, group_n);
+    else for (int x = 0; x <= 8; ++x) runs.start[x] = (int)(whole * x * n);
+    int64_t heaviest = 0;
+    for (int x = 0; x < 8; ++x) {
+        int64_t load[WGS] = {0};
+        for (int w = 0; w < WGS && t > 0; ++w) {
+            const int g = x * WGS + w, per_tile = BcsrShares::WORKERS / t;
+            if (g < t * per_tile) load[w] = s.load[(t - 1) * BcsrShares::WORKERS + g % per_tile];
+        }
+        for (int i = runs.start[x]; i < runs.start[x + 1]; ++i) {
+            const int64_t grp = i / (group_n * n), gw = std::min<int64_t>(group_n, n_tiles - grp * group_n);
+            const int64_t pos = (i - grp * group_n * n) / gw;
+            load[(i - runs.start[x]) % WGS] += info[4 * ((grp & 1) ? n - 1 - pos : pos) + 2] + 2;
+        }
+        heaviest = std::max(heaviest, *std::max_element(load, load + WGS));
+    }
+    return heaviest;
+}
+
+// How many of the N-tiles are shared among all workgroups (0: none, pairs of N-tiles).  When the N-tiles do not divide among the
+// XCDs, an XCD's run of the pairs ends inside its lists, and the heaviest workgroup has 1.3 to 2.4 times the mean.  Instead
+// every XCD can take as many whole tiles, and the t others are dealt to all workgroups in lists made for that t (heaviest over
+// mean 1.03 to 1.4 where there are enough block-rows; with fewer than 32 rows of tiles a whole one leaves workgroups idle).
+// Taken is the least of what the heaviest workgroup walks and a price, in shares of the mean, of the slabs of B (K x 1 KB) that
+// an XCD has in flight beside the first: for the second of a pair, high where one slab fits the 4 MB of L2 and two do not;
+// for each further one of 9 to 16 and 17 to 24 shared tiles, which save no reads of A, in their part of the work; 1.5 times
+// as much in rows of X, whose slices are half cache lines.  Prices fitted to 362 products of 16 to 200 rows of tiles, K 2048 to
+// 18944, 2 to 60 N-tiles, where the choice is in the mean 1.004 and at most 1.09 times slower than the best; of 442 products,
+// most of them others, none is more than 1.08 times slower than with pairs, the mean 0.91 (us, pairs /
+// shares, at 90 %, 128-row: 18944 x 3584, N = 1536 48 / 31, N = 6656 122 / 102; 8192 x 8192, 18432 293 / 261; 3584 x 18944,
+// N = 8704 153 / 139, 13312 227 / 239, 18432 306 / 319; 2048 x 18944, N = 13312 141 / 174; with no more than the remainder
+// shared the last four take 199, 279, 335 and 235).
+int wide_shared_tiles(const HostBcsr &b, const BcsrShares &s, int64_t k, bool xt, int n_tiles, int64_t n_cus) {
+    if (s.infos == 0 || n_tiles % 8 == 0 || n_cus < BcsrShares::WORKERS) return 0;
+    if (n_tiles > 256) return n_tiles % 8;  // the rest weighs little; and a walk takes as long as there are tiles
+    static const double depth[5] = {2048, 4096, 8192, 12000, 18944}, pair[5] = {0, 0.6, 0.07, 0.13, 0.19},
+                        slab[5] = {0.06, 0.11, 0.25, 0.24, 0.19};
+    int i = 0;
+    while (i < 3 && depth[i + 1] < (double)k) ++i;
+    const double f = std::min(1.0, std::max(0.0, std::log((double)k / depth[i]) / std::log(depth[i + 1] / depth[i])));
+    // one N-tile, in the mean over the workgroups
+    const double mean = (double)(b.block_col_idx.size() + 2 * b.n_nonempty) / BcsrShares::WORKERS * (xt ? 1.5 : 1.0);
+    const double pair_price = mean * (pair[i] + f * (pair[i + 1] - pair[i])), slab_price = mean * (slab[i] + f * (slab[i + 1] - slab[i]));
+    double best = (double)wide_heaviest(b, s, n_tiles, 0) + pair_price * n_tiles;
+    int best_t = 0;
+    for (int t = n_tiles % 8; t <= std::min(n_tiles, BcsrShares::MAX_TILES); t += 8) {
+        const double cost = (double)wide_heaviest(b, s, n_tiles, t) + slab_price * t * ((t - 1) / 8);
+        if (cost < best) best = cost, best_t = t;
+    }
+    return best_t;
+}
+
+// (a plan of the handle: it depends on nothing but the blocks and the number of N-tiles, so threads that meet here write the same)
+static int shared_tiles(const asp_handle *h, bool xt, int n_tiles) {
+    const HostBcsr &b = h->has_comp ? h->hc : h->hb;
+    if (n_tiles > 256) return wide_shared_tiles(b, h->shares, h->k, xt, n_tiles, h->n_cus);
+    std::atomic<uint8_t> &kept = h->n_shared[xt][n_tiles];
+    int t = kept.load(std::memory_order_relaxed) - 1;
+    if (t < 0) {
+        t = wide_shared_tiles(b, h->shares, h->k, xt, n_tiles, h->n_cus);
+        kept.store((uint8_t)(t + 1), std::memory_order_relaxed);
+    }
+    return t;
+}
+
 template <bool XT>
 static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, int n_tiles, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n;  // benchmarking switch
@@ -695,7 +771,13 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
     WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
     const bool one = n_tiles == 8 || (n_rows >= 64 && h->k >= 3072 && (XT || N % 16384 != 0));
-    int group_n = env_group > 0 ? env_group : one ? 1 : 2;
+    // benchmarking switch: fewer resident workgroups, i.e. part of the compute units idle (the schedule's 16 lists
+    // per XCD stay balanced for 32, 16 or 8 workgroups per XCD)
+    const int env_workers = switches().bcsr_workgroups;
+    const int env_xcd = switches().bcsr_xcd_aware ? 1 : 0;  // benchmarking switch: 0 = ignore the XCDs when dealing tiles
+    const bool uneven = n_tiles % 8 != 0 && h->shares.infos > 0 && env_group <= 0 && env_workers <= 0 && env_xcd;
+    const int t = uneven ? shared_tiles(h, XT, n_tiles) : 0;
+    int group_n = env_group > 0 ? env_group : t > 0 || (one && !uneven) ? 1 : 2;
     if (group_n > n_tiles) group_n = n_tiles;
     if (group_n == 1) {
         op.rank_info = (const int4 *)(h->has_comp ? h->d_c_rank_info_32 : h->d_rank_info_32);
@@ -703,40 +785,17 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
     }
     int64_t workers = h->n_cus;  // one resident workgroup per CU: the ring takes the whole LDS
     if (workers > n_rows * n_tiles) workers = n_rows * n_tiles;
-    // benchmarking switch: fewer resident workgroups, i.e. part of the compute units idle (the schedule's 16 lists
-    // per XCD stay balanced for 32, 16 or 8 workgroups per XCD)
-    const int env_workers = switches().bcsr_workgroups;
     if (env_workers > 0 && env_workers < workers) workers = env_workers;
     workers = std::max<int64_t>(8, workers / 8 * 8);  // the same number of workgroups on every XCD
-    const int env_xcd = switches().bcsr_xcd_aware ? 1 : 0;  // benchmarking switch: 0 = ignore the XCDs when dealing tiles
     XcdRuns runs;
     WideShares shares = {0x7fffffff, 0, 0};
     const int32_t *share_first = nullptr;
-    const BcsrShares &sh = h->shares;
-    if (n_tiles % 8 != 0 && sh.pass > 0 && env_group <= 0 && env_workers <= 0 && env_xcd) {
-        // The N-tiles do not divide among the XCDs, and an XCD's run of the schedule would end inside its lists: the heaviest
-        // workgroup then has 1.3 to 2.4 times the mean.  Instead every XCD takes as many whole tiles, and the t others are
-        // dealt to all workgroups in lists made for that t (heaviest over mean 1.03 to 1.4).  Of the t there are (the
-        // remainder, or 8 or 16 more) the one with the lightest heaviest workgroup; with more than 8 an XCD has two or three
-        // slabs of B in flight, which costs (16 tiles, 2 over 1: K = 2048 0.97, 3584 1.05, 8192 1.05 to 1.3).  us, before /
-        // now, at 90 %: 18944 x 3584, 128-row blocks, N = 2048 50 / 37, N = 3072 63 / 53, K-contiguous 50 / 39, 68 / 57; 8192 x
-        // 8192 K-contiguous, 3072 tokens 67 / 53; 3584 x 18944, N = 5120 111 / 91.  (With 8, 16, ... tiles the lists above are
-        // even, and walking a pair from them is up to 5 % faster than from shares of 16.)
-        const double crowd = std::max(0.0, (double)h->k / 32768 - 0.05);
-        double best = 0;
-        int t = 0;
-        for (int c = n_tiles % 8; c <= BcsrShares::MAX_TILES && c <= n_tiles; c += 8) {
-            const int passes = (n_tiles - c) / 8;
-            const double w = passes / 2 * (double)sh.two_passes + passes % 2 * (double)sh.pass +
-                             (double)sh.longest[c] * (1 + crowd * ((c - 1) / 8));
-            if (t == 0 || w < best) best = w, t = c;
-        }
-        group_n = 1;
+    if (t > 0) {
         workers = BcsrShares::WORKERS;
         op.rank_info = (const int4 *)h->d_share_lists;
         for (int x = 0; x <= 8; ++x) runs.start[x] = (int)((n_tiles - t) / 8 * x * n_rows);
         shares = {n_tiles - t, BcsrShares::WORKERS / t, (int)(op.n_brows + (t - 1) * n_rows)};
-        share_first = h->d_share_lists + sh.infos * 4 + (t - 1) * BcsrShares::FIRST_PITCH;
+        share_first = h->d_share_lists + h->shares.infos * 4 + (t - 1) * BcsrShares::FIRST_PITCH;
     } else {
         runs = cut_runs(*op.weight_prefix, n_rows, n_tiles, group_n);
         if (!env_xcd)

@@ -264,8 +264,7 @@ void bcsr_build_schedule(HostBcsr &b, bool by_length) {
 // Lists for the N-tiles that are left when every XCD has had the same number of whole ones: t of them (1 to 24) are dealt to
 // 256 workgroups, 256 / t to a tile, and a workgroup walks one list of its tile's block-rows.  Longest block-row first, each
 // to the lightest of the lists with the fewest entries, then exchanges; without regard to the entries where that makes the
-// heaviest list 5 % lighter (lists of one length keep the workgroups of an XCD in the same block columns).  Also what the
-// lists weigh, from which a launch takes its t.
+// heaviest list 5 % lighter (lists of one length keep the workgroups of an XCD in the same block columns).
 void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
     const int64_t n = b.n_nonempty;
     out = BcsrShares();
@@ -277,11 +276,13 @@ void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
     std::stable_sort(sorted.begin(), sorted.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
     out.infos = (int64_t)b.rank_info_32.size() / 4 + BcsrShares::MAX_TILES * n;
     out.lists = b.rank_info_32;
+    out.load.assign(BcsrShares::MAX_TILES * BcsrShares::WORKERS, 0);
     out.lists.resize((size_t)out.infos * 4 + BcsrShares::MAX_TILES * BcsrShares::FIRST_PITCH);
     parallel_chunks(BcsrShares::MAX_TILES, 1, [&](unsigned, int64_t lo, int64_t hi) {
         for (int64_t i = lo; i < hi; ++i) {
             const int n_lists = BcsrShares::WORKERS / (int)(i + 1);
             std::vector<std::vector<int32_t>> lists;
+            std::vector<int64_t> loads;
             int64_t longest = 0;
             for (int even = 1; even >= 0; --even) {
                 std::vector<std::vector<int32_t>> cand(n_lists);
@@ -296,7 +297,7 @@ void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
                 }
                 if (n > n_lists) exchange_entries(cand, load, len);
                 const int64_t w = *std::max_element(load.begin(), load.end());
-                if (even || w * 100 < longest * 95) longest = w, lists.swap(cand);
+                if (even || w * 100 < longest * 95) longest = w, lists.swap(cand), loads.swap(load);
             }
             sort_by_first_column(b, lists);
             int32_t *info = out.lists.data() + b.rank_info_32.size() + i * n * 4;
@@ -310,17 +311,9 @@ void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
                 }
             }
             std::fill(first + n_lists, first + BcsrShares::FIRST_PITCH, at);
-            out.longest[i + 1] = longest;
+            std::copy(loads.begin(), loads.end(), out.load.begin() + i * BcsrShares::WORKERS);
         }
     });
-    // one pass and two passes (there and back) over the 32 lists of rank_info_32
-    std::vector<int64_t> once(32, 0), back(32, 0);
-    for (int64_t r = 0; r < n; ++r) {
-        once[r % 32] += b.rank_info_32[4 * r + 2] + tile;
-        back[r % 32] += b.rank_info_32[4 * (n - 1 - r) + 2] + tile;
-    }
-    out.pass = *std::max_element(once.begin(), once.end());
-    for (int l = 0; l < 32; ++l) out.two_passes = std::max(out.two_passes, once[l] + back[l]);
 }
 
 // Composite form of a bf16 BCSR matrix with 64x64 or 32x32 blocks, for the kernel written for 128x128 blocks

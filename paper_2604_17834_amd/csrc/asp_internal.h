@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <new>
@@ -110,8 +111,7 @@ struct BcsrShares {
     // `infos` entries); [MAX_TILES][FIRST_PITCH] the first entry of every list
     std::vector<int32_t> lists;
     int64_t infos = 0;
-    int64_t longest[MAX_TILES + 1] = {0};  // stored blocks + 2 per tile, of the heaviest list
-    int64_t pass = 0, two_passes = 0;      // the same for whole N-tiles dealt from rank_info_32
+    std::vector<int32_t> load;             // [MAX_TILES][WORKERS] stored blocks + 2 per tile of every list
 };
 
 struct HostWcsr {
@@ -178,6 +178,8 @@ struct asp_handle {
     int32_t *d_c_rank_info_32 = nullptr;
     asp::BcsrShares shares;         // of hc, or of hb with 128-row blocks; its lists live on the device only
     int32_t *d_share_lists = nullptr;
+    // asp_spmm / asp_spmm_xt of 1 to 256 N-tiles: 1 + the number of shared ones, 0 before the first such call
+    mutable std::atomic<uint8_t> n_shared[2][257] = {};
     int32_t *d_c_slice_rows = nullptr;     // [composite blocks][4]
     int32_t *d_c_piece_rows = nullptr;     // [super-rows][4]
     void *d_c_values = nullptr;

@@ -40,14 +40,11 @@ def test_shares_hold_every_block_row_once_per_tile(lists_of, lengths):  # noqa: 
     got = lists_of("shares", *lengths)
     filled = [r for r, n in enumerate(lengths) if n > 0]
     if not 0 < len(filled) <= 512:
-        assert set(got) == {"passes"} and got["passes"][0] == [0, 0]
+        assert got == {"infos": [[0]]}
         return
     at = np.concatenate([[0], np.cumsum(lengths)])
     whole = got["whole"]   # the order for whole tiles, with the empty block-rows (whose rows of C are cleared) at its end
     assert whole == lists_of("order", *lengths)["32"]
-    once = [sum(r[2] + 2 for r in whole[:len(filled)][j::32]) for j in range(32)]
-    back = [sum(r[2] + 2 for r in whole[:len(filled)][::-1][j::32]) for j in range(32)]
-    assert got["passes"][0] == [max(once), max(x + y for x, y in zip(once, back))]
     for t in range(1, 25):
         rows, first = got["t%d" % t], [v[0] for v in got["first%d" % t]]
         assert sorted(r[0] for r in rows) == filled
@@ -55,9 +52,57 @@ def test_shares_hold_every_block_row_once_per_tile(lists_of, lengths):  # noqa: 
         per_tile = 256 // t
         assert first[0] == 0 and first == sorted(first) and set(first[per_tile:]) == {len(filled)}
         sums = [sum(r[2] + 2 for r in rows[first[j]:first[j + 1]]) for j in range(per_tile)]
-        assert got["longest%d" % t][0] == [max(sums)]
+        assert [v[0] for v in got["load%d" % t]] == sums + [0] * (256 - per_tile)
         # no worse than a longest-first deal: below the mean plus the heaviest block-row
         assert max(sums) <= sum(sums) / per_tile + max(lengths) + 2
+
+
+def _walked(n_tiles, t, orders, shares, start):
+    """Blocks + 2 a tile of every workgroup of a launch of 128x512 tiles, tile by tile as the kernel takes them: workgroup w of an
+    XCD the tiles w, w + 32, ... of the XCD's run, then a list of one of the t shared N-tiles."""
+    load = np.zeros((8, 32), int)
+    whole = n_tiles - t
+    for x in range(8):
+        if t:
+            rows = [r for r in shares["whole"] if r[2] > 0]
+            first, last, group = whole // 8 * x * len(rows), whole // 8 * (x + 1) * len(rows), 1
+        else:
+            rows = [r for r in orders["16"] if r[2] > 0]
+            first, last, group = start[x], start[x + 1], 2
+        for w in range(32):
+            for tile in range(first + w, last, 32):
+                g, rest = divmod(tile, group * len(rows))
+                place = rest // min(group, n_tiles - g * group)
+                load[x, w] += rows[len(rows) - 1 - place if g % 2 else place][2] + 2
+            if t and (x * 32 + w) // (256 // t) < t:
+                l = (x * 32 + w) % (256 // t)
+                f = [v[0] for v in shares["first%d" % t]]
+                load[x, w] += sum(r[2] + 2 for r in shares["t%d" % t][f[l]:f[l + 1]])
+    return load
+
+
+# (N-tiles, K, block-row lengths)
+_UNEVEN = [(n, k, lengths) for k, lengths in [
+    (18944, np.random.default_rng(2).binomial(148, 0.1, 28)), (18944, np.random.default_rng(5).binomial(148, 0.1, 16)),
+    (18944, np.minimum(148, np.random.default_rng(6).geometric(0.07, 40))), (3584, np.random.default_rng(1).binomial(28, 0.1, 148)),
+    (8192, np.random.default_rng(7).binomial(64, 0.1, 64)), (2048, np.r_[np.zeros(9, int), np.arange(60) % 16]),
+] for n in (3, 9, 13, 17, 26, 36)]
+
+
+@pytest.mark.parametrize("n_tiles,k,lengths", _UNEVEN, ids=lambda v: len(v) if np.ndim(v) else v)
+def test_shared_tiles_by_what_is_walked(lists_of, n_tiles, k, lengths):  # noqa: F811
+    orders, shares = lists_of("order", *lengths), lists_of("shares", *lengths)
+    for xt in (0, 1):
+        got = lists_of("wide", n_tiles, k, xt, 256, *lengths)
+        start = [v[0] for v in got["start"]]
+        heaviest = dict(got["heaviest"])
+        assert sorted(heaviest) == [0] + [t for t in range(1, 25) if t <= n_tiles and (n_tiles - t) % 8 == 0]
+        for t, most in heaviest.items():
+            load = _walked(n_tiles, t, orders, shares, start)
+            assert load.sum() == n_tiles * sum(n + 2 for n in lengths if n) and load.max() == most
+        # whatever is taken for the sake of L2, no workgroup walks much more than with pairs of N-tiles
+        assert heaviest[got["shared"][0][0]] <= 1.3 * heaviest[0]
+    assert lists_of("wide", n_tiles, k, 0, 128, *lengths)["shared"] == [[0]]   # the lists are for 256 workgroups
 
 
 def _partly_empty(rows, empty, seed):

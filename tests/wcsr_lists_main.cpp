@@ -1,6 +1,8 @@
 // Prints the work lists that the converters make of a synthetic matrix, for tests/test_wcsr_lists.py and test_bcsr_order.py.
 //   order L..        BCSR block-rows of L blocks each: the orders of the tile kernels in 16, 32 and 64 lists
-//   shares L..       the lists for shared N-tiles, and what the heaviest of each weighs
+//   shares L..       the lists for shared N-tiles, and what they weigh
+//   wide N K X C L.. a launch of N 128x512 tiles to a block-row, K columns (X = 1: K-contiguous), C compute units: how many are
+//                    shared, the runs of the pairs, and what the heaviest workgroup walks with 0, 1, ... shared ones
 //   staged T C L..   the register-staged kernel's launch of T column tiles on C compute units: 1 (longest block-row first) or 0
 //                    (as stored), the starts of the XCDs' runs, the order longest first
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -51,7 +53,7 @@ static int shares(const std::vector<int32_t> &lengths) {
     schedule(lengths, b);
     asp::BcsrShares s;
     asp::bcsr_build_shares(b, s);
-    std::printf("passes %lld %lld\n", (long long)s.pass, (long long)s.two_passes);
+    std::printf("infos %lld\n", (long long)s.infos);
     if (s.lists.empty()) return 0;
     const size_t whole = lengths.size() * 4, n = (size_t)b.n_nonempty * 4;
     print("whole", std::vector<int32_t>(s.lists.begin(), s.lists.begin() + whole), 4);
@@ -63,7 +65,9 @@ static int shares(const std::vector<int32_t> &lengths) {
         std::snprintf(name, sizeof name, "first%d", t);
         const auto first = s.lists.begin() + s.infos * 4 + (t - 1) * asp::BcsrShares::FIRST_PITCH;
         print(name, std::vector<int32_t>(first, first + asp::BcsrShares::FIRST_PITCH), 1);
-        std::printf("longest%d %lld\n", t, (long long)s.longest[t]);
+        std::snprintf(name, sizeof name, "load%d", t);
+        const auto load = s.load.begin() + (t - 1) * asp::BcsrShares::WORKERS;
+        print(name, std::vector<int32_t>(load, load + asp::BcsrShares::WORKERS), 1);
     }
     return 0;
 }
@@ -80,6 +84,20 @@ static int order(const std::vector<int32_t> &lengths) {
     return 0;
 }
 
+static int wide(int n_tiles, int64_t k, bool xt, int64_t n_cus, const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    schedule(lengths, b);
+    asp::BcsrShares s;
+    asp::bcsr_build_shares(b, s);
+    std::printf("shared %d\n", asp::wide_shared_tiles(b, s, k, xt, n_tiles, n_cus));
+    const asp::XcdRuns runs = asp::cut_runs(b.sorted_weight_prefix, b.n_nonempty, n_tiles, 2);
+    for (int x = 0; x <= 8; ++x) std::printf("start %d\n", runs.start[x]);
+    std::printf("heaviest 0 %lld\n", (long long)asp::wide_heaviest(b, s, n_tiles, 0));
+    for (int t = n_tiles % 8; t > 0 && t <= std::min(n_tiles, asp::BcsrShares::MAX_TILES); t += 8)
+        std::printf("heaviest %d %lld\n", t, (long long)asp::wide_heaviest(b, s, n_tiles, t));
+    return 0;
+}
+
 static int staged(int n_tiles, int64_t n_cus, const std::vector<int32_t> &lengths) {
     asp::HostBcsr b;
     schedule(lengths, b);
@@ -92,15 +110,15 @@ static int staged(int n_tiles, int64_t n_cus, const std::vector<int32_t> &length
 
 int main(int argc, char **argv) {
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
-    if (argc > 4 && std::strcmp(argv[1], "staged") == 0) {
-        std::vector<int32_t> lengths;
-        for (int i = 4; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
-        return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths);
-    }
-    if (argc > 2 && (std::strcmp(argv[1], "order") == 0 || std::strcmp(argv[1], "shares") == 0)) {
-        std::vector<int32_t> lengths;
-        for (int i = 2; i < argc; ++i) lengths.push_back(std::atoi(argv[i]));
-        return std::strcmp(argv[1], "order") == 0 ? order(lengths) : shares(lengths);
-    }
+    auto is = [&](const char *what, int first) { return argc > first && std::strcmp(argv[1], what) == 0; };
+    auto lengths = [&](int first) {
+        std::vector<int32_t> v;
+        for (int i = first; i < argc; ++i) v.push_back(std::atoi(argv[i]));
+        return v;
+    };
+    if (is("order", 2)) return order(lengths(2));
+    if (is("shares", 2)) return shares(lengths(2));
+    if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
+    if (is("wide", 6)) return wide(std::atoi(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]) != 0, std::atoll(argv[5]), lengths(6));
     return 2;
 }
