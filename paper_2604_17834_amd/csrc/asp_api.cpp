@@ -168,12 +168,13 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload(&h->d_col_idx, h->hb.block_col_idx.data(), h->hb.block_col_idx.size() * 4, stream))) return s;
         if ((s = upload(&h->d_values, h->hb.packed.data(), h->hb.packed.size(), stream))) return s;
         ASP_HIP_TRY(hipDeviceGetAttribute(&h->n_cus, hipDeviceAttributeMultiprocessorCount, h->device));
-        bcsr_build_schedule(h->hb, cfg->dtype == ASP_DT_F32);
+        bcsr_build_schedule(h->hb, cfg->dtype == ASP_DT_F32 ? Orders::LENGTH : cfg->b_row == 128 ? Orders::ROWS_128 : Orders::ALL);
         if ((s = upload(&h->d_rank_info, h->hb.rank_info.data(), h->hb.rank_info.size() * 4, stream))) return s;
         ASP_HIP_TRY(hipMalloc((void **)&h->d_sched, 64));
         if (cfg->dtype == ASP_DT_BF16) {
             if ((s = upload(&h->d_rank_info_32, h->hb.rank_info_32.data(), h->hb.rank_info_32.size() * 4, stream))) return s;
-            if ((s = upload(&h->d_rank_info_64, h->hb.rank_info_64.data(), h->hb.rank_info_64.size() * 4, stream))) return s;
+            if (cfg->b_row < 128 &&
+                (s = upload(&h->d_rank_info_64, h->hb.rank_info_64.data(), h->hb.rank_info_64.size() * 4, stream))) return s;
             if ((s = upload(&h->d_by_length, h->hb.by_length.data(), h->hb.by_length.size() * 4, stream))) return s;
         }
         if (h->has_comp) {

@@ -700,7 +700,7 @@ int64_t wide_heaviest(const HostBcsr &b, const BcsrShares &s, int n_tiles, int t
         int64_t load[WGS] = {0};
         for (int w = 0; w < WGS && t > 0; ++w) {
             const int g = x * WGS + w, per_tile = BcsrShares::WORKERS / t;
-            if (g < t * per_tile) load[w] = s.load[(t - 1) * BcsrShares::WORKERS + g % per_tile];
+            if (g < t * per_tile) load[w] = s.load[BcsrShares::slot(t) * BcsrShares::WORKERS + g % per_tile];
         }
         for (int i = runs.start[x]; i < runs.start[x + 1]; ++i) {
             const int64_t grp = i / (group_n * n), gw = std::min<int64_t>(group_n, n_tiles - grp * group_n);
@@ -794,8 +794,8 @@ static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, 
         workers = BcsrShares::WORKERS;
         op.rank_info = (const int4 *)h->d_share_lists;
         for (int x = 0; x <= 8; ++x) runs.start[x] = (int)((n_tiles - t) / 8 * x * n_rows);
-        shares = {n_tiles - t, BcsrShares::WORKERS / t, (int)(op.n_brows + (t - 1) * n_rows)};
-        share_first = h->d_share_lists + h->shares.infos * 4 + (t - 1) * BcsrShares::FIRST_PITCH;
+        shares = {n_tiles - t, BcsrShares::WORKERS / t, (int)(op.n_brows + BcsrShares::slot(t) * n_rows)};
+        share_first = h->d_share_lists + h->shares.infos * 4 + BcsrShares::slot(t) * BcsrShares::FIRST_PITCH;
     } else {
         runs = cut_runs(*op.weight_prefix, n_rows, n_tiles, group_n);
         if (!env_xcd)

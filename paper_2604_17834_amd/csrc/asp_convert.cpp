@@ -28,9 +28,10 @@ unsigned worker_count(int64_t items) {
 }
 
 // run fn(worker_index, first, last) over [0, n) in dynamically claimed chunks
+// (by as many threads as `items` of the usual size are worth)
 template <class F>
-void parallel_chunks(int64_t n, int64_t chunk, F fn) {
-    unsigned nw = worker_count(n);
+void parallel_chunks(int64_t n, int64_t chunk, F fn, int64_t items = 0) {
+    unsigned nw = worker_count(std::max(n, items));
     std::atomic<int64_t> next{0};
     // An exception inside a worker (an allocation that fails) must not leave its thread: the first one is kept,
     // the other workers stop claiming chunks, and it is thrown again on the calling thread after all have joined.
@@ -152,26 +153,53 @@ void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *co
     });
 }
 
-// Exchanges entries between the heaviest list and another one while that makes the heavier of the two lighter.
+// Exchanges entries between the heaviest list and another one while that makes the heavier of the two lighter: each time the
+// pair of entries that makes it lightest.  With the lengths of every list in order the best difference between two lists
+// takes one walk along both, not all pairs of their entries.
 template <class Len>
 static void exchange_entries(std::vector<std::vector<int32_t>> &lists, std::vector<int64_t> &load, Len len) {
     const int n = (int)lists.size();
+    std::vector<std::vector<int32_t>> lens(n);
+    for (int l = 0; l < n; ++l) {
+        for (int32_t r : lists[l]) lens[l].push_back(len(r));
+        std::sort(lens[l].begin(), lens[l].end());
+    }
+    auto replace = [](std::vector<int32_t> &v, int32_t from, int32_t by) {
+        v.erase(std::lower_bound(v.begin(), v.end(), from));
+        v.insert(std::lower_bound(v.begin(), v.end(), by), by);
+    };
     for (int step = 0; step < 4 * n; ++step) {
         const int h = (int)(std::max_element(load.begin(), load.end()) - load.begin());
+        // moving d blocks from h to l makes the heavier of the two min(d, load[h] - load[l] - d) lighter
         int64_t best = 0;
         int to = -1;
-        size_t from_i = 0, to_i = 0;
-        for (int l = 0; l < n; ++l)
-            for (size_t i = 0; l != h && i < lists[h].size(); ++i)
-                for (size_t j = 0; j < lists[l].size(); ++j) {
-                    const int64_t d = len(lists[h][i]) - len(lists[l][j]);  // moves from h to l
-                    const int64_t gain = load[h] - std::max(load[h] - d, load[l] + d);
-                    if (gain > best) best = gain, to = l, from_i = i, to_i = j;
+        for (int l = 0; l < n; ++l) {
+            const int64_t apart = load[h] - load[l];
+            if (l == h || apart <= 2 * best) continue;
+            const std::vector<int32_t> &other = lens[l];
+            size_t j = 0;
+            for (int32_t mine : lens[h]) {
+                while (j < other.size() && 2 * (int64_t)other[j] < 2 * (int64_t)mine - apart) ++j;  // the best partners: j - 1 and j
+                for (size_t p = j > 0 ? j - 1 : 0; p < other.size() && p <= j; ++p) {
+                    const int64_t d = mine - other[p], gain = std::min(d, apart - d);
+                    if (gain > best) best = gain, to = l;
                 }
+            }
+        }
         if (to < 0) break;
-        const int64_t d = len(lists[h][from_i]) - len(lists[to][to_i]);
-        std::swap(lists[h][from_i], lists[to][to_i]);
-        load[h] -= d, load[to] += d;
+        const int64_t apart = load[h] - load[to];
+        bool found = false;
+        for (size_t i = 0; i < lists[h].size() && !found; ++i)
+            for (size_t j = 0; j < lists[to].size() && !found; ++j) {
+                const int32_t mine = len(lists[h][i]), other = len(lists[to][j]);
+                const int64_t d = mine - other;
+                if (std::min(d, apart - d) != best) continue;
+                found = true;
+                std::swap(lists[h][i], lists[to][j]);
+                load[h] -= d, load[to] += d;
+                replace(lens[h], mine, other);
+                replace(lens[to], other, mine);
+            }
     }
 }
 
@@ -221,9 +249,11 @@ static void order_in_lists(const HostBcsr &b, const std::vector<int32_t> &sorted
 }
 
 // Scheduling data of the BCSR kernels: rank_info and the prefix sums of the tile weights in its order (and the same for
-// groups of one N-tile), empty block-rows last.  by_length (the fp32 kernel, one workgroup per tile): longest block-row first
-// (ties: lower block-row first), nothing else.
-void bcsr_build_schedule(HostBcsr &b, bool by_length) {
+// groups of one N-tile), empty block-rows last.  LENGTH (the fp32 kernel, one workgroup per tile): longest block-row first
+// (ties: lower block-row first), nothing else.  TILES: in 16 and 32 lists, all that 128x512 tiles take; ROWS_128: and longest
+// first, for the register-staged kernel; ALL: and in 64 lists, which the ring kernel takes with smaller blocks.
+void bcsr_build_schedule(HostBcsr &b, Orders orders) {
+    const bool by_length = orders == Orders::LENGTH;
     const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1;
     std::vector<int32_t> sorted(nbr);
     for (int64_t i = 0; i < nbr; ++i) sorted[i] = (int32_t)i;
@@ -250,6 +280,8 @@ void bcsr_build_schedule(HostBcsr &b, bool by_length) {
     };
     fill(by_length ? 0 : 16, b.rank_info, b.sorted_weight_prefix);
     if (by_length) return;
+    fill(32, b.rank_info_32, b.weight_prefix_32);
+    if (orders == Orders::TILES) return;
     b.by_length = sorted;
     b.length_prefix.assign(nbr + 1, 0);
     // What a tile costs beside its blocks, in blocks: 1, but a tile that is only cleared takes as long as 3 or 4 of them, which tells
@@ -257,12 +289,11 @@ void bcsr_build_schedule(HostBcsr &b, bool by_length) {
     // 104 / 88, 5 139 / 126, 8 153 / 152; lengths alike 68 / 70, 102 / 103, 151 / 151; 30 % empty, 4 tiles 100 / 106.)
     const int64_t tile = 2 * n_nonempty <= nbr ? 3 : 1;
     for (int64_t r = 0; r < nbr; ++r) b.length_prefix[r + 1] = b.length_prefix[r] + len(b.by_length[r]) + tile;
-    fill(32, b.rank_info_32, b.weight_prefix_32);
-    fill(64, b.rank_info_64, b.weight_prefix_64);
+    if (orders == Orders::ALL) fill(64, b.rank_info_64, b.weight_prefix_64);
 }
 
-// Lists for the N-tiles that are left when every XCD has had the same number of whole ones: t of them (1 to 24) are dealt to
-// 256 workgroups, 256 / t to a tile, and a workgroup walks one list of its tile's block-rows.  Longest block-row first, each
+// Lists for the N-tiles that are left when every XCD has had the same number of whole ones: t of them (1 to 23, no multiple of 8)
+// are dealt to 256 workgroups, 256 / t to a tile, and a workgroup walks one list of its tile's block-rows.  Longest block-row first, each
 // to the lightest of the lists with the fewest entries, then exchanges; without regard to the entries where that makes the
 // heaviest list 5 % lighter (lists of one length keep the workgroups of an XCD in the same block columns).
 void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
@@ -274,13 +305,14 @@ void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
     std::vector<int32_t> sorted(n);
     for (int64_t r = 0; r < n; ++r) sorted[r] = b.rank_info[4 * r];
     std::stable_sort(sorted.begin(), sorted.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
-    out.infos = (int64_t)b.rank_info_32.size() / 4 + BcsrShares::MAX_TILES * n;
+    constexpr int SLOTS = BcsrShares::slot(BcsrShares::MAX_TILES) + 1;
+    out.infos = (int64_t)b.rank_info_32.size() / 4 + SLOTS * n;
     out.lists = b.rank_info_32;
-    out.load.assign(BcsrShares::MAX_TILES * BcsrShares::WORKERS, 0);
-    out.lists.resize((size_t)out.infos * 4 + BcsrShares::MAX_TILES * BcsrShares::FIRST_PITCH);
-    parallel_chunks(BcsrShares::MAX_TILES, 1, [&](unsigned, int64_t lo, int64_t hi) {
+    out.load.assign(SLOTS * BcsrShares::WORKERS, 0);
+    out.lists.resize((size_t)out.infos * 4 + SLOTS * BcsrShares::FIRST_PITCH);
+    parallel_chunks(SLOTS, 1, [&](unsigned, int64_t lo, int64_t hi) {
         for (int64_t i = lo; i < hi; ++i) {
-            const int n_lists = BcsrShares::WORKERS / (int)(i + 1);
+            const int n_lists = BcsrShares::WORKERS / (int)(i + i / 7 + 1);  // slot(t) = i
             std::vector<std::vector<int32_t>> lists;
             std::vector<int64_t> loads;
             int64_t longest = 0;
@@ -313,7 +345,7 @@ void bcsr_build_shares(const HostBcsr &b, BcsrShares &out) {
             std::fill(first + n_lists, first + BcsrShares::FIRST_PITCH, at);
             std::copy(loads.begin(), loads.end(), out.load.begin() + i * BcsrShares::WORKERS);
         }
-    });
+    }, n);
 }
 
 // Composite form of a bf16 BCSR matrix with 64x64 or 32x32 blocks, for the kernel written for 128x128 blocks
@@ -473,7 +505,7 @@ double bcsr_build_composite(const HostBcsr &in, int64_t m, int64_t k, int32_t b,
             }
         }
     });
-    bcsr_build_schedule(out);
+    bcsr_build_schedule(out, Orders::TILES);
     bcsr_pack_fragments_bf16(out, 128, 128, out.packed);
     out.blocks = std::vector<uint8_t>();  // only the packed form is used
     const double stored = (double)in.block_col_idx.size() * b * b;

@@ -92,7 +92,7 @@ struct HostBcsr {
     // prefix sums of their tile weights (stored blocks + 1) in that order
     std::vector<int32_t> rank_info;            // [n_brows][4]
     std::vector<int64_t> sorted_weight_prefix; // [n_brows + 1]
-    std::vector<int32_t> rank_info_32, rank_info_64;        // the same in 32 and 64 lists instead of 16
+    std::vector<int32_t> rank_info_32, rank_info_64;        // the same in 32 and 64 lists instead of 16 (Orders)
     std::vector<int64_t> weight_prefix_32, weight_prefix_64;
     std::vector<int32_t> by_length;            // bf16: block-rows, longest first,
     std::vector<int64_t> length_prefix;        // and the prefix sums of their weights
@@ -102,16 +102,17 @@ struct HostBcsr {
     std::vector<int32_t> piece_rows;           // composite form only: [super-rows][4] first row of C of each 32-row piece, -1 = none
 };
 
-// BCSR, 128 x 512 tiles: shares of 1 to 24 N-tiles (bcsr_build_shares); empty where block-rows are so many that whole rounds
+// BCSR, 128 x 512 tiles: shares of 1 to 23 N-tiles (bcsr_build_shares); empty where block-rows are so many that whole rounds
 // of them are even enough
 struct BcsrShares {
-    static constexpr int MAX_TILES = 24, WORKERS = 256, FIRST_PITCH = WORKERS + 1;
+    static constexpr int MAX_TILES = 23, WORKERS = 256, FIRST_PITCH = WORKERS + 1;
     static constexpr int64_t MAX_ROWS = 512;
-    // rank_info_32; [MAX_TILES][n_nonempty][4] in its form, the block-rows list after list for 1, 2, ... tiles (together
-    // `infos` entries); [MAX_TILES][FIRST_PITCH] the first entry of every list
+    static constexpr int slot(int t) { return t - 1 - t / 8; }  // multiples of 8 are never shared
+    // rank_info_32; [slot][n_nonempty][4] in its form, the block-rows list after list for 1, 2, ... tiles (together
+    // `infos` entries); [slot][FIRST_PITCH] the first entry of every list
     std::vector<int32_t> lists;
     int64_t infos = 0;
-    std::vector<int32_t> load;             // [MAX_TILES][WORKERS] stored blocks + 2 per tile of every list
+    std::vector<int32_t> load;             // [slot][WORKERS] stored blocks + 2 per tile of every list
 };
 
 struct HostWcsr {
@@ -140,7 +141,8 @@ struct HostRows {
 // converters (asp_convert.cpp); values are only bit-copied
 void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostBcsr &out);
-void bcsr_build_schedule(HostBcsr &b, bool by_length = false);
+enum class Orders { LENGTH, TILES, ROWS_128, ALL };
+void bcsr_build_schedule(HostBcsr &b, Orders orders);
 void bcsr_build_shares(const HostBcsr &b, BcsrShares &out);
 double bcsr_build_composite(const HostBcsr &in, int64_t m, int64_t k, int32_t b, HostBcsr &out);
 void bcsr_pack_fragments_bf16(const HostBcsr &in, int32_t b_row, int32_t b_col, std::vector<uint8_t> &packed);

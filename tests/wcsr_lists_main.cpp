@@ -45,7 +45,7 @@ static void schedule(const std::vector<int32_t> &lengths, asp::HostBcsr &b) {
         for (int32_t j = 0; j < n; ++j) b.block_col_idx.push_back(j);
         b.block_row_ptr.push_back((int32_t)b.block_col_idx.size());
     }
-    asp::bcsr_build_schedule(b);
+    asp::bcsr_build_schedule(b, asp::Orders::ALL);
 }
 
 static int shares(const std::vector<int32_t> &lengths) {
@@ -58,15 +58,17 @@ static int shares(const std::vector<int32_t> &lengths) {
     const size_t whole = lengths.size() * 4, n = (size_t)b.n_nonempty * 4;
     print("whole", std::vector<int32_t>(s.lists.begin(), s.lists.begin() + whole), 4);
     for (int t = 1; t <= asp::BcsrShares::MAX_TILES; ++t) {
+        if (t % 8 == 0) continue;
+        const int slot = asp::BcsrShares::slot(t);
         char name[16];
         std::snprintf(name, sizeof name, "t%d", t);
-        const auto info = s.lists.begin() + whole + (t - 1) * n;
+        const auto info = s.lists.begin() + whole + slot * n;
         print(name, std::vector<int32_t>(info, info + n), 4);
         std::snprintf(name, sizeof name, "first%d", t);
-        const auto first = s.lists.begin() + s.infos * 4 + (t - 1) * asp::BcsrShares::FIRST_PITCH;
+        const auto first = s.lists.begin() + s.infos * 4 + slot * asp::BcsrShares::FIRST_PITCH;
         print(name, std::vector<int32_t>(first, first + asp::BcsrShares::FIRST_PITCH), 1);
         std::snprintf(name, sizeof name, "load%d", t);
-        const auto load = s.load.begin() + (t - 1) * asp::BcsrShares::WORKERS;
+        const auto load = s.load.begin() + slot * asp::BcsrShares::WORKERS;
         print(name, std::vector<int32_t>(load, load + asp::BcsrShares::WORKERS), 1);
     }
     return 0;
