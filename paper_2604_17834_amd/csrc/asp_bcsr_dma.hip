@@ -35,6 +35,8 @@
 // weight, one per XCD (workgroup id mod 8 -- workgroups are dealt to XCDs round-robin), so the B column
 // slabs of a group stay in that XCD's private L2 and A blocks are fetched once per group; inside a run
 // the XCD's workgroups take tiles round-robin, which deals sorted weights evenly.
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -537,44 +539,122 @@ __global__ void bcsr_zero_sched_kernel(int *__restrict__ sched) {
     if (threadIdx.x < 8) sched[threadIdx.x] = 0;
 }
 
+static const std::vector<int64_t> &weight_prefix(const HostBcsr &b, int lists) {
+    return lists == 64 ? b.weight_prefix_64 : lists == 32 ? b.weight_prefix_32 : b.sorted_weight_prefix;
+}
+
+// Workgroups of a ring launch, the same number on every XCD: one for every tile of the longest run where the chip holds them.
+// Runs of equal weight differ in tiles, and with the mean number of workgroups one of them walked two (us, mean / longest:
+// 3584 x 18944 at 90 %, 128-row, N = 3584 137 / 85, N = 3072 100 / 79; 3392 x 4864 at 50 %, N = 1464 75 / 54; 1664 x 3264 at
+// 80 %, 32-row, K-contiguous, 1736 tokens 26.5 / 17.6).
+static int64_t ring_workgroups(int64_t tiles, const XcdRuns &runs, int64_t resident) {
+    const int64_t mean = std::max<int64_t>(8, std::min(tiles, resident) / 8 * 8);
+    return std::min(std::max(mean, 8 * longest_run(runs)), std::max<int64_t>(8, resident / 8 * 8));
+}
+
+// as many lists as block-rows in a round
+static int ring_lists(int b_row, int64_t tiles, int64_t resident, int group_n) {
+    const int64_t per_round = std::max<int64_t>(1, std::min(tiles, resident) / 8) / group_n;
+    return b_row == 128 || per_round < 24 ? 16 : per_round < 48 ? 32 : 64;
+}
+
+// What the heaviest workgroup walks, in stored blocks and 1 for every tile, and the heaviest compute unit (every 32nd workgroup
+// of its XCD), per workgroup that it holds.
+RingLoad ring_heaviest(const HostBcsr &b, const RingWalk &walk, int n_tiles, int64_t n_cus, int per_cu) {
+    const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1, cus = std::max<int64_t>(1, n_cus / 8);
+    const std::vector<int32_t> &info = walk.lists == 64 ? b.rank_info_64 : walk.lists == 32 ? b.rank_info_32 : b.rank_info;
+    const XcdRuns runs = cut_runs(weight_prefix(b, walk.lists), nbr, n_tiles, walk.group_n);
+    const int64_t wgs = ring_workgroups(nbr * n_tiles, runs, n_cus * per_cu) / 8;
+    RingLoad most = {0, 0};
+    for (int x = 0; x < 8; ++x) {
+        std::vector<int64_t> load(wgs, 0), unit(cus, 0);
+        int64_t w = 0;
+        for (int i = runs.start[x]; i < runs.start[x + 1]; ++i) {
+            const int64_t grp = i / (walk.group_n * nbr), gw = std::min<int64_t>(walk.group_n, n_tiles - grp * walk.group_n);
+            const int64_t pos = (i - grp * walk.group_n * nbr) / gw;
+            load[w] += info[4 * ((grp & 1) ? nbr - 1 - pos : pos) + 2] + 1;
+            if (++w == wgs) w = 0;
+        }
+        for (w = 0; w < wgs; ++w) unit[w % cus] += load[w];
+        most.workgroup = std::max(most.workgroup, *std::max_element(load.begin(), load.end()));
+        most.unit = std::max(most.unit, (double)*std::max_element(unit.begin(), unit.end()) / per_cu);
+    }
+    return most;
+}
+
+// How many N-tiles are walked together (group_n), and in which of the orders (bcsr_build_schedule).
+// Few N-tiles: an XCD reads the slab of B of one N-tile for many block-rows, whose requests meet in its 4 MB of L2; many: a
+// block of A is fetched once for all of them.  Per tile that costs about BN / R and density x BR / group_n, with R the
+// block-rows that an XCD walks at a time, so small blocks take few.  Us, groups of 1 / 2 / 4, 3584 x 18944 at 90 %: 32-row
+// blocks N = 2048 64 / 87 / 110, N = 4096 129 / 183 / 229, K-contiguous 108 / 112 / 166, 259 / 267 / 345; 64-row N = 2048
+// 53 / 60 / 66, K-contiguous 59 / 65 / 68; 128-row N = 2048 64 / 48 / 57, N = 4096 97 / 75 / 91, K-contiguous 62 / 48 / 58 and
+// 125 / 89 / 79.
+// The order: with as many lists as block-rows in a round the heaviest workgroup is even; 128-row blocks 16, whose rounds start
+// in nearer block columns (3584 x 18944, N = 4096, groups of 2: 77 us, with 32 lists 89).
+// That is the rule where there are many tiles.  With few rounds of them more depends on where the XCDs' runs end in the lists,
+// so another group or order is taken where what the heaviest workgroup and compute unit walk, and the price of slabs of B
+// that pass 1.8 MB and of fetching A for every group, is 4.5 % less.  (Us, rule / taken, at 90 %: 64-row, 10240 x 2560, N = 1144
+// 25 / 19; 2816 x 1536, N = 1472 11.3 / 9.0; 3584 x 18944 K-contiguous, 2344 tokens 100 / 77; 128-row, 6912 x 2688, N = 1104
+// 17.0 / 14.6.  Fitted to 192 launches, of which the rule is in the mean 1.07 and up to 1.34 times slower than the best of
+// the nine, what is taken 1.04 and 1.21.)
+RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int n_tiles, int64_t n_cus, int per_cu) {
+    const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1, tiles = nbr * n_tiles;
+    RingWalk rule;
+    if (b_row == 32) rule.group_n = xt ? 2 : k * (8ll * bn) <= (9 << 19) ? 4 : 1;
+    else if (b_row == 64) rule.group_n = 1;
+    else rule.group_n = !xt && tiles <= n_cus * per_cu ? 2 : 4;
+    rule.group_n = std::min(rule.group_n, n_tiles);
+    rule.lists = ring_lists(b_row, tiles, n_cus * per_cu, rule.group_n);
+    if (n_tiles > 128 || tiles > 32768) return rule;
+    const double mean = (double)(b.block_col_idx.size() + nbr) * n_tiles / (double)(n_cus * per_cu);
+    auto cost = [&](const RingWalk &w) {
+        const RingLoad most = ring_heaviest(b, w, n_tiles, n_cus, per_cu);
+        const double slabs = std::log2(std::max(1.0, (double)k * bn * 2 * w.group_n / 1.8e6));
+        return (double)most.workgroup + 0.8 * most.unit +
+               mean * (0.23 * (xt ? 1.45 : 1.0) * std::min(3.0, slabs) + 1.5 * b_row / bn / w.group_n);
+    };
+    double best = cost(rule) / 1.045;
+    RingWalk taken = rule;
+    for (int group_n = 1; group_n <= 4 && group_n <= n_tiles; group_n *= 2)
+        for (int lists = 16; lists <= (b_row == 128 ? 32 : 64); lists *= 2) {
+            const RingWalk w = {group_n, lists};
+            const double c = cost(w);
+            if (c < best) best = c, taken = w;
+        }
+    return taken;
+}
+
+// (a plan of the handle: it depends on nothing but the blocks and the tiles, so threads that meet here write the same)
+static RingWalk kept_ring_walk(const asp_handle *h, int bn, bool xt, int n_tiles, int per_cu) {
+    if (n_tiles > 128) return ring_walk(h->hb, h->k, h->b_row, bn, xt, n_tiles, h->n_cus, per_cu);
+    std::atomic<uint8_t> &kept = h->ring_walks[xt][bn / 128][n_tiles];
+    int v = kept.load(std::memory_order_relaxed);
+    if (v == 0) {
+        const RingWalk w = ring_walk(h->hb, h->k, h->b_row, bn, xt, n_tiles, h->n_cus, per_cu);
+        v = w.group_n + w.lists;  // 1 .. 4 and 16, 32 or 64
+        kept.store((uint8_t)v, std::memory_order_relaxed);
+    }
+    return RingWalk{v % 16, v / 16 * 16};
+}
+
 template <int BR, int BN, int WM, int WN, int NS, bool XT>
 static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n, env_wgs = switches().bcsr_wgs_per_cu;  // benchmarking switches
     // resident workgroups per CU: as many as LDS allows (the kernel is built for 2 waves per SIMD)
     const int fit = (int)(163840 / DmaCfg<BR, BN, WM, WN, NS, XT>::LDS_BYTES);
-    const int per_cu = std::max(1, std::min(fit, 8 / (WM * WN)));
-    int64_t workers = (int64_t)h->n_cus * (env_wgs > 0 ? env_wgs : per_cu);
-    const int64_t full = workers;
-    if (workers > p.workgroups) workers = p.workgroups;
-    workers = std::max<int64_t>(8, workers / 8 * 8);  // the same number of workgroups on every XCD
-    // N-tiles walked together.  Few of them: an XCD reads the slab of B of one N-tile for many block-rows, whose requests meet
-    // in its 4 MB of L2; many: a block of A is fetched once for all of them.  Per tile that costs about BN / R and
-    // density x BR / group_n, with R the block-rows that an XCD walks at a time, so small blocks take few.  us, groups of
-    // 1 / 2 / 4, 3584 x 18944 at 90 %: 32-row blocks N = 2048 62 / 91 / 109, N = 4096 126 / 185 / 228, K-contiguous (4 x 128 wide
-    // on a compute unit) 108 / 112 / 159, 258 / 265 / 318; 64-row N = 2048 52 / 75 / 70, K-contiguous 57 / 80 / 73; 128-row
-    // N = 2048 63 / 49 / 57, N = 4096 97 / 77 / 90, K-contiguous 63 / 48 / 58 and 121 / 90 / 80; 10240 x 2560, 64-row, N = 2048
-    // 26 / 29 / 31, K-contiguous 24 / 26 / 30, 128-row 22 / 29 / 25 (more tiles than the chip holds); 8192 x 2048, 32-row, N = 1024
-    // (the slab of four in L2) 30.5 / 29 / 28.
-    const bool one_round = h->n_brows * (int64_t)p.n_tiles <= (int64_t)h->n_cus * per_cu;
-    int group_n = env_group;
-    if (group_n <= 0) {
-        if (BR == 32) group_n = XT ? 2 : h->k * (8ll * BN) <= (9 << 19) ? 4 : 1;
-        else if (BR == 64) group_n = 1;
-        else group_n = !XT && one_round ? 2 : 4;
+    const int per_cu = env_wgs > 0 ? env_wgs : std::max(1, std::min(fit, 8 / (WM * WN)));
+    const int64_t resident = (int64_t)h->n_cus * per_cu;
+    RingWalk walk;
+    if (env_group > 0) {
+        walk.group_n = std::min(env_group, p.n_tiles);
+        walk.lists = ring_lists(BR, p.workgroups, resident, walk.group_n);
+    } else {
+        walk = env_wgs > 0 ? ring_walk(h->hb, h->k, BR, BN, XT, p.n_tiles, h->n_cus, per_cu) : kept_ring_walk(h, BN, XT, p.n_tiles, per_cu);
     }
-    if (group_n > p.n_tiles) group_n = p.n_tiles;
-    // the order whose lists are as many as the block-rows of a round (bcsr_build_schedule); 128-row blocks: 16, whose rounds
-    // start in nearer block columns (3584 x 18944, N = 4096, groups of 2: 77 us, with 32 lists 89)
-    const int64_t per_round = workers / 8 / group_n;
-    const int lists = BR == 128 || per_round < 24 ? 16 : per_round < 48 ? 32 : 64;
-    const int4 *rank_info = (const int4 *)(lists == 64 ? h->d_rank_info_64 : lists == 32 ? h->d_rank_info_32 : h->d_rank_info);
-    const XcdRuns runs = cut_runs(lists == 64 ? h->hb.weight_prefix_64 : lists == 32 ? h->hb.weight_prefix_32 : h->hb.sorted_weight_prefix,
-                                  h->n_brows, p.n_tiles, group_n);
-    // A workgroup for every tile of the longest run where the chip holds them: runs of equal weight differ in tiles, and with
-    // the mean number of workgroups one of them walked two (us, before / now: 3584 x 18944 at 90 %, 128-row, N = 3584 137 / 85,
-    // N = 3072 100 / 79; 3392 x 4864 at 50 %, N = 1464 75 / 54; 1664 x 3264 at 80 %, 32-row, K-contiguous, 1736 tokens 26.5 / 17.6).
-    for (int x = 0; x < 8; ++x) workers = std::max<int64_t>(workers, 8ll * (runs.start[x + 1] - runs.start[x]));
-    workers = std::min(workers, std::max<int64_t>(8, full / 8 * 8));
+    const int group_n = walk.group_n;
+    const int4 *rank_info = (const int4 *)(walk.lists == 64 ? h->d_rank_info_64 : walk.lists == 32 ? h->d_rank_info_32 : h->d_rank_info);
+    const XcdRuns runs = cut_runs(weight_prefix(h->hb, walk.lists), h->n_brows, p.n_tiles, group_n);
+    const int64_t workers = ring_workgroups(p.workgroups, runs, resident);
     dim3 grid((unsigned)workers), block(WM * WN * 64);
     // benchmarking switch: tiles pulled from per-XCD atomic counters (built for the 128 x 256 tiles of the ladder;
     // everything else keeps the static schedule)

@@ -94,6 +94,15 @@ inline int64_t longest_run(const XcdRuns &r) {
 // N-tiles, in the handle's order in even groups and backwards in odd ones, or always in order: turn = false) into 8 runs of
 // equal weight; pre[] are the prefix sums of the block-rows' tile weights in that order.
 XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t n_rows, int n_tiles, int group_n, bool turn = true);
+struct RingWalk {
+    int group_n, lists;
+};
+struct RingLoad {
+    int64_t workgroup;
+    double unit;
+};
+RingLoad ring_heaviest(const HostBcsr &b, const RingWalk &walk, int n_tiles, int64_t n_cus, int per_cu);
+RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int n_tiles, int64_t n_cus, int per_cu);
 int64_t wide_heaviest(const HostBcsr &b, const BcsrShares &s, int n_tiles, int t);
 int wide_shared_tiles(const HostBcsr &b, const BcsrShares &s, int64_t k, bool xt, int n_tiles, int64_t n_cus);
 bool register_staged_runs(const HostBcsr &b, int n_tiles, int64_t n_cus, int threads, XcdRuns &runs);

@@ -180,6 +180,8 @@ struct asp_handle {
     int32_t *d_c_rank_info_32 = nullptr;
     asp::BcsrShares shares;         // of hc, or of hb with 128-row blocks; its lists live on the device only
     int32_t *d_share_lists = nullptr;
+    // asp_spmm / asp_spmm_xt by the ring kernel in 64-, 128- and 256-wide tiles, 1 to 128 of them: group_n + lists, 0 before the first
+    mutable std::atomic<uint8_t> ring_walks[2][3][129] = {};
     // asp_spmm / asp_spmm_xt of 1 to 256 N-tiles: 1 + the number of shared ones, 0 before the first such call
     mutable std::atomic<uint8_t> n_shared[2][257] = {};
     int32_t *d_c_slice_rows = nullptr;     // [composite blocks][4]

@@ -105,6 +105,35 @@ def test_shared_tiles_by_what_is_walked(lists_of, n_tiles, k, lengths):  # noqa:
     assert lists_of("wide", n_tiles, k, 0, 128, *lengths)["shared"] == [[0]]   # the lists are for 256 workgroups
 
 
+# (column tiles, K, block, width, workgroups to a compute unit, block-row lengths): an XCD's runs that end inside the lists
+@pytest.mark.parametrize("n_tiles,k,b,width,per_cu,lengths", [
+    (5, 2560, 64, 256, 2, np.random.default_rng(1).binomial(40, 0.1, 160)), (12, 1536, 64, 128, 2, np.random.default_rng(2).binomial(24, 0.1, 44)),
+    (37, 18944, 64, 64, 4, np.random.default_rng(3).binomial(296, 0.1, 56)), (9, 2688, 128, 128, 2, np.random.default_rng(4).binomial(21, 0.1, 54)),
+    (3, 600, 32, 256, 2, np.r_[np.zeros(7, int), np.random.default_rng(5).geometric(0.1, 90)]), (1, 64, 128, 64, 2, [1]), (2, 64, 32, 64, 4, [0, 0, 3]),
+], ids=lambda v: len(v) if np.ndim(v) else v)
+def test_ring_walks_even_workgroups(lists_of, n_tiles, k, b, width, per_cu, lengths):  # noqa: F811
+    orders = lists_of("order", *lengths)
+    resident = 32 * per_cu                   # workgroups of an XCD
+    for xt in (0, 1):
+        got = lists_of("ring", n_tiles, k, b, width, xt, per_cu, *lengths)
+        most = {}
+        for group, lists, heaviest, *start in got["walk"]:
+            assert start[0] == 0 and start[8] == n_tiles * len(lengths)
+            rows = orders[str(lists)]
+            wgs = min(resident, max(max(np.diff(start)), 1, n_tiles * len(lengths) // 8))
+            load = np.zeros((8, wgs), int)
+            for x in range(8):
+                for tile in range(start[x], start[x + 1]):
+                    g, rest = divmod(tile, group * len(rows))
+                    place = rest // min(group, n_tiles - g * group)
+                    load[x, (tile - start[x]) % wgs] += rows[len(rows) - 1 - place if g % 2 else place][2] + 1
+            assert load.sum() == n_tiles * (sum(lengths) + len(lengths)) and load.max() == heaviest
+            most[group, lists] = heaviest
+        taken = tuple(got["taken"][0])
+        assert most[taken] <= 1.35 * min(most.values())   # (the price of slabs and of A may ask for a little)
+        assert b < 128 or taken[1] < 64                   # these handles have no such order
+
+
 def _partly_empty(rows, empty, seed):
     rng = np.random.default_rng(seed)
     return np.where(rng.random(rows) < empty, 0, rng.binomial(64, 0.3, rows))

@@ -3,6 +3,8 @@
 //   shares L..       the lists for shared N-tiles, and what they weigh
 //   wide N K X C L.. a launch of N 128x512 tiles to a block-row, K columns (X = 1: K-contiguous), C compute units: how many are
 //                    shared, the runs of the pairs, and what the heaviest workgroup walks with 0, 1, ... shared ones
+//   ring N K B W X P L..  a launch of the ring kernel: N column tiles W wide, blocks of B, P workgroups to a compute unit: the group
+//                    and order taken, and for each what the heaviest workgroup walks and the starts of the XCDs' runs
 //   staged T C L..   the register-staged kernel's launch of T column tiles on C compute units: 1 (longest block-row first) or 0
 //                    (as stored), the starts of the XCDs' runs, the order longest first
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -100,6 +102,24 @@ static int wide(int n_tiles, int64_t k, bool xt, int64_t n_cus, const std::vecto
     return 0;
 }
 
+static int ring(int n_tiles, int64_t k, int b_row, int bn, bool xt, int per_cu, const std::vector<int32_t> &lengths) {
+    asp::HostBcsr b;
+    schedule(lengths, b);
+    const asp::RingWalk taken = asp::ring_walk(b, k, b_row, bn, xt, n_tiles, 256, per_cu);
+    std::printf("taken %d %d\n", taken.group_n, taken.lists);
+    for (int group = 1; group <= 4; group *= 2)
+        for (int lists = 16; lists <= 64; lists *= 2) {
+            const int group_n = std::min(group, n_tiles);
+            const auto &prefix = lists == 64 ? b.weight_prefix_64 : lists == 32 ? b.weight_prefix_32 : b.sorted_weight_prefix;
+            const asp::XcdRuns runs = asp::cut_runs(prefix, lengths.size(), n_tiles, group_n);
+            const asp::RingLoad most = asp::ring_heaviest(b, asp::RingWalk{group_n, lists}, n_tiles, 256, per_cu);
+            std::printf("walk %d %d %lld", group_n, lists, (long long)most.workgroup);
+            for (int x = 0; x <= 8; ++x) std::printf(" %d", runs.start[x]);
+            std::printf("\n");
+        }
+    return 0;
+}
+
 static int staged(int n_tiles, int64_t n_cus, const std::vector<int32_t> &lengths) {
     asp::HostBcsr b;
     schedule(lengths, b);
@@ -121,6 +141,9 @@ int main(int argc, char **argv) {
     if (is("order", 2)) return order(lengths(2));
     if (is("shares", 2)) return shares(lengths(2));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
+    if (is("ring", 8))
+        return ring(std::atoi(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6]) != 0,
+                    std::atoi(argv[7]), lengths(8));
     if (is("wide", 6)) return wide(std::atoi(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]) != 0, std::atoll(argv[5]), lengths(6));
     return 2;
 }
