@@ -762,12 +762,14 @@ template <bool XT>
 static void launch_wide(const asp_handle *h, const void *B, void *C, int64_t N, int n_tiles, hipStream_t stream) {
     const int env_group = switches().bcsr_group_n;  // benchmarking switch
     // N-tiles walked together.  One: an XCD has half the slab of B (K x 512) in its 4 MB of L2; two: an A block is fetched once
-    // per pair.  One with 8 N-tiles (else an XCD gets a share of a pair), and where the slabs of two are more than L2 and the
-    // block-rows are enough for even lists of them; but two again where rows of B are a multiple of 32 KB apart: the slab of
-    // one tile then falls into a part of L2's sets (18944 x 3584, 128-row blocks, us per N-tile and XCD: N = 12288 61, 16384
-    // 68, 20480 60, 24576 60, 32768 68).  us, one / two, at 90 %, 128 / 32-row blocks: 18944 x 3584 N = 4096 64 / 79, 121 / 130,
-    // N = 8192 124 / 132, 235 / 250, N = 16384 273 / 257, 522 / 508; 8192 x 8192 N = 8192 118 / 129, 228 / 239, K-contiguous
-    // 121 / 137, 272 / 360; 4096 x 4096 36 / 33, 64 / 61; 8192 x 2048 38.6 / 37.7, 66 / 65.
+    // per pair.  One with 8 N-tiles (else an XCD gets a share of a pair), and from K = 3072 and 64 rows of tiles on, where both
+    // sides cross (us, one / two, N = 8192, at 90 %, 128 / 32-row blocks: 8192 x 2048 40.3 / 38.4, 70.7 / 68.0; x 2560 47.5 / 45.2,
+    // 87.8 / 81.0; x 3072 50.5 / 51.2, 94.9 / 96.0; x 8192 118 / 129, 228 / 239; with 32 to 48 rows of tiles 4096 x 3584 36.6 / 30.2,
+    // 62.9 / 58.3, 5120 x 3584 42.1 / 37.1, 77.1 / 75.3, 6144 x 3584 47.9 / 43.8, 87.7 / 83.9; 18944 x 3584 124 / 132, 235 / 250).
+    // Two again where rows of B are a multiple of 32 KB apart (18944 x 3584, us per N-tile and XCD with one: N = 12288 61, 16384
+    // 68, 20480 60, 24576 60, 32768 68; one / two, N = 16384 273 / 257, 522 / 508).  Below the lines one is faster for some rows of
+    // X (32-row, 18944 x 2560, 8192 tokens 197 / 220) and with an odd number of N-tiles to an XCD (5120 x 3584, 12288 tokens
+    // 117 / 142).
     WideOperand op = wide_operand(h);
     const int64_t n_rows = op.n_rows;
     const bool one = n_tiles == 8 || (n_rows >= 64 && h->k >= 3072 && (XT || N % 16384 != 0));

@@ -124,16 +124,16 @@ def test_shared_column_tiles(b, m, k, N, xt):
     test_groups_of_column_tiles(b, m, k, N, xt)
 
 
-# register-staged tiles with rows of C that are not aligned: fewer tiles than the chip holds at once, more (longest block-rows
-# first), and one dense block-row above empty ones (which would be most of a run of equal weight)
-@pytest.mark.parametrize("b,m,k,N,dense", [
-    (64, 1000, 700, 65, False), (32, 4001, 300, 1021, False), (64, 3000, 333, 2001, False), (128, 5000, 400, 4097, False),
-    (32, 38400, 200000, 33, True),
+# register-staged tiles (operands without 16-byte rows, block-rows short for the work: no strips): as many tiles as the chip holds, as
+# stored; more, longest block-rows first; empty block-rows at the end, as stored where one XCD would get half of all tiles,
+# longest first where that is less
+@pytest.mark.parametrize("b,m,k,N,sparsity,empty", [
+    (32, 4000, 1000, 1021, 0.5, 0), (64, 3900, 320, 1021, 0.1, 0), (64, 3000, 333, 2001, 0.75, 0), (128, 5000, 400, 4097, 0.75, 0),
+    (32, 40000, 512, 127, 0.5, 0), (32, 30720, 1280, 127, 0.0, 46080), (32, 32000, 512, 255, 0.5, 96000),
 ])
-def test_register_staged_tile_order(b, m, k, N, dense):
-    a = synth.block_sparse_bernoulli(b if dense else m, k, b, b, 0.0 if dense else 0.75, seed=9, dtype="bf16")
-    if dense:
-        a = dataclasses.replace(a, m=m, row_ptr=np.r_[a.row_ptr, np.full(m - b, a.row_ptr[-1], a.row_ptr.dtype)])
+def test_register_staged_tile_order(b, m, k, N, sparsity, empty):
+    a = synth.block_sparse_bernoulli(m, k, b, b, sparsity, seed=9, dtype="bf16")
+    a = dataclasses.replace(a, m=m + empty, row_ptr=np.r_[a.row_ptr, np.full(empty, a.row_ptr[-1], a.row_ptr.dtype)])
     B = synth.dense_normal(k, N, "bf16", seed=N)
     C = gpu_spmm(a, "bcsr", b, b, B)
     assert not C[np.diff(a.row_ptr) == 0].any() and not ((C & 0x7F80) == 0x7F80).any()
