@@ -553,9 +553,9 @@ static int64_t ring_workgroups(int64_t tiles, const XcdRuns &runs, int64_t resid
 }
 
 // as many lists as block-rows in a round
-static int ring_lists(int b_row, int64_t tiles, int64_t resident, int group_n) {
+static int ring_lists(int64_t tiles, int64_t resident, int group_n) {
     const int64_t per_round = std::max<int64_t>(1, std::min(tiles, resident) / 8) / group_n;
-    return b_row == 128 || per_round < 24 ? 16 : per_round < 48 ? 32 : 64;
+    return per_round < 24 ? 16 : per_round < 48 ? 32 : 64;
 }
 
 // What the heaviest workgroup walks, in stored blocks and 1 for every tile, and the heaviest compute unit (every 32nd workgroup
@@ -566,16 +566,16 @@ RingLoad ring_heaviest(const HostBcsr &b, const RingWalk &walk, int n_tiles, int
     const XcdRuns runs = cut_runs(weight_prefix(b, walk.lists), nbr, n_tiles, walk.group_n);
     const int64_t wgs = ring_workgroups(nbr * n_tiles, runs, n_cus * per_cu) / 8;
     RingLoad most = {0, 0};
+    std::vector<int64_t> load(wgs), unit(cus);
     for (int x = 0; x < 8; ++x) {
-        std::vector<int64_t> load(wgs, 0), unit(cus, 0);
+        std::fill(load.begin(), load.end(), 0);
+        std::fill(unit.begin(), unit.end(), 0);
         int64_t w = 0;
-        for (int i = runs.start[x]; i < runs.start[x + 1]; ++i) {
-            const int64_t grp = i / (walk.group_n * nbr), gw = std::min<int64_t>(walk.group_n, n_tiles - grp * walk.group_n);
-            const int64_t pos = (i - grp * walk.group_n * nbr) / gw;
-            load[w] += info[4 * ((grp & 1) ? nbr - 1 - pos : pos) + 2] + 1;
+        for_tiles(runs.start[x], runs.start[x + 1], nbr, n_tiles, walk.group_n, [&](int64_t rank) {
+            load[w] += info[4 * rank + 2] + 1;
             if (++w == wgs) w = 0;
-        }
-        for (w = 0; w < wgs; ++w) unit[w % cus] += load[w];
+        });
+        for (int64_t u = 0, v = 0; v < wgs; ++v, u = u + 1 < cus ? u + 1 : 0) unit[u] += load[v];
         most.workgroup = std::max(most.workgroup, *std::max_element(load.begin(), load.end()));
         most.unit = std::max(most.unit, (double)*std::max_element(unit.begin(), unit.end()) / per_cu);
     }
@@ -592,11 +592,12 @@ RingLoad ring_heaviest(const HostBcsr &b, const RingWalk &walk, int n_tiles, int
 // The order: with as many lists as block-rows in a round the heaviest workgroup is even; 128-row blocks 16, whose rounds start
 // in nearer block columns (3584 x 18944, N = 4096, groups of 2: 77 us, with 32 lists 89).
 // That is the rule where there are many tiles.  With few rounds of them more depends on where the XCDs' runs end in the lists,
-// so another group or order is taken where what the heaviest workgroup and compute unit walk, and the price of slabs of B
-// that pass 1.8 MB and of fetching A for every group, is 4.5 % less.  (Us, rule / taken, at 90 %: 64-row, 10240 x 2560, N = 1144
+// so another group, in the order that is even for it, is taken where what the heaviest workgroup and compute unit walk, and the
+// price of slabs of B that pass 1.8 MB and of fetching A for every group, is 4.5 % less.  (Us, rule / taken, at 90 %: 64-row, 10240 x 2560, N = 1144
 // 25 / 19; 2816 x 1536, N = 1472 11.3 / 9.0; 3584 x 18944 K-contiguous, 2344 tokens 100 / 77; 128-row, 6912 x 2688, N = 1104
 // 17.0 / 14.6.  Fitted to 192 launches, of which the rule is in the mean 1.07 and up to 1.34 times slower than the best of
-// the nine, what is taken 1.04 and 1.21.)
+// nine groups and orders, what is taken 1.05 and 1.27; all nine as candidates, 1.04 and 1.21, take three times as long to walk
+// on the first call: 10 to 60 us.)
 RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int n_tiles, int64_t n_cus, int per_cu) {
     const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1, tiles = nbr * n_tiles;
     RingWalk rule;
@@ -604,23 +605,26 @@ RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int
     else if (b_row == 64) rule.group_n = 1;
     else rule.group_n = !xt && tiles <= n_cus * per_cu ? 2 : 4;
     rule.group_n = std::min(rule.group_n, n_tiles);
-    rule.lists = ring_lists(b_row, tiles, n_cus * per_cu, rule.group_n);
-    if (n_tiles > 128 || tiles > 32768) return rule;
+    rule.lists = b_row == 128 ? 16 : ring_lists(tiles, n_cus * per_cu, rule.group_n);
+    if (n_tiles > 128 || tiles > 8192) return rule;
     const double mean = (double)(b.block_col_idx.size() + nbr) * n_tiles / (double)(n_cus * per_cu);
+    auto price = [&](int group_n) {
+        const double slabs = std::log2(std::max(1.0, (double)k * bn * 2 * group_n / 1.8e6));
+        return mean * (0.23 * (xt ? 1.45 : 1.0) * std::min(3.0, slabs) + 1.5 * b_row / bn / group_n);
+    };
     auto cost = [&](const RingWalk &w) {
         const RingLoad most = ring_heaviest(b, w, n_tiles, n_cus, per_cu);
-        const double slabs = std::log2(std::max(1.0, (double)k * bn * 2 * w.group_n / 1.8e6));
-        return (double)most.workgroup + 0.8 * most.unit +
-               mean * (0.23 * (xt ? 1.45 : 1.0) * std::min(3.0, slabs) + 1.5 * b_row / bn / w.group_n);
+        return (double)most.workgroup + 0.8 * most.unit + price(w.group_n);
     };
     double best = cost(rule) / 1.045;
+    const double least = std::max(mean, (double)(b.max_blocks + 1)) + 0.8 * mean;  // nothing walks less
     RingWalk taken = rule;
-    for (int group_n = 1; group_n <= 4 && group_n <= n_tiles; group_n *= 2)
-        for (int lists = 16; lists <= (b_row == 128 ? 32 : 64); lists *= 2) {
-            const RingWalk w = {group_n, lists};
-            const double c = cost(w);
-            if (c < best) best = c, taken = w;
-        }
+    for (int group_n = 1; group_n <= 4 && group_n <= n_tiles; group_n *= 2) {
+        const RingWalk w = {group_n, std::min(b_row == 128 ? 32 : 64, ring_lists(tiles, n_cus * per_cu, group_n))};
+        if ((w.group_n == rule.group_n && w.lists == rule.lists) || least + price(group_n) >= best) continue;
+        const double c = cost(w);
+        if (c < best) best = c, taken = w;
+    }
     return taken;
 }
 
@@ -647,7 +651,7 @@ static void launch_dma(const asp_handle *h, const void *B, void *C, int64_t N, c
     RingWalk walk;
     if (env_group > 0) {
         walk.group_n = std::min(env_group, p.n_tiles);
-        walk.lists = ring_lists(BR, p.workgroups, resident, walk.group_n);
+        walk.lists = BR == 128 ? 16 : ring_lists(p.workgroups, resident, walk.group_n);
     } else {
         walk = env_wgs > 0 ? ring_walk(h->hb, h->k, BR, BN, XT, p.n_tiles, h->n_cus, per_cu) : kept_ring_walk(h, BN, XT, p.n_tiles, per_cu);
     }

@@ -94,6 +94,22 @@ inline int64_t longest_run(const XcdRuns &r) {
 // N-tiles, in the handle's order in even groups and backwards in odd ones, or always in order: turn = false) into 8 runs of
 // equal weight; pre[] are the prefix sums of the block-rows' tile weights in that order.
 XcdRuns cut_runs(const std::vector<int64_t> &pre, int64_t n_rows, int n_tiles, int group_n, bool turn = true);
+// Calls tile(r) with the rank in the order of every tile first .. last - 1 of it.
+template <class F>
+inline void for_tiles(int64_t first, int64_t last, int64_t n_rows, int n_tiles, int group_n, F tile) {
+    int64_t grp = first / (group_n * n_rows), in = first - grp * group_n * n_rows;
+    int64_t gw = std::min<int64_t>(group_n, n_tiles - grp * group_n), pos = in / std::max<int64_t>(1, gw), j = in - pos * gw;
+    for (int64_t i = first; i < last; ++i) {
+        tile((grp & 1) ? n_rows - 1 - pos : pos);
+        if (++j < gw) continue;
+        j = 0;
+        if (++pos < n_rows) continue;
+        pos = 0;
+        ++grp;
+        gw = std::min<int64_t>(group_n, n_tiles - grp * group_n);
+    }
+}
+
 struct RingWalk {
     int group_n, lists;
 };

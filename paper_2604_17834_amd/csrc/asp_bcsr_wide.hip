@@ -702,11 +702,11 @@ int64_t wide_heaviest(const HostBcsr &b, const BcsrShares &s, int n_tiles, int t
             const int g = x * WGS + w, per_tile = BcsrShares::WORKERS / t;
             if (g < t * per_tile) load[w] = s.load[BcsrShares::slot(t) * BcsrShares::WORKERS + g % per_tile];
         }
-        for (int i = runs.start[x]; i < runs.start[x + 1]; ++i) {
-            const int64_t grp = i / (group_n * n), gw = std::min<int64_t>(group_n, n_tiles - grp * group_n);
-            const int64_t pos = (i - grp * group_n * n) / gw;
-            load[(i - runs.start[x]) % WGS] += info[4 * ((grp & 1) ? n - 1 - pos : pos) + 2] + 2;
-        }
+        int w = 0;
+        for_tiles(runs.start[x], runs.start[x + 1], n, n_tiles, group_n, [&](int64_t rank) {
+            load[w] += info[4 * rank + 2] + 2;
+            if (++w == WGS) w = 0;
+        });
         heaviest = std::max(heaviest, *std::max_element(load, load + WGS));
     }
     return heaviest;
@@ -734,12 +734,15 @@ int wide_shared_tiles(const HostBcsr &b, const BcsrShares &s, int64_t k, bool xt
     while (i < 3 && depth[i + 1] < (double)k) ++i;
     const double f = std::min(1.0, std::max(0.0, std::log((double)k / depth[i]) / std::log(depth[i + 1] / depth[i])));
     // one N-tile, in the mean over the workgroups
-    const double mean = (double)(b.block_col_idx.size() + 2 * b.n_nonempty) / BcsrShares::WORKERS * (xt ? 1.5 : 1.0);
+    const double tile = (double)(b.block_col_idx.size() + 2 * b.n_nonempty) / BcsrShares::WORKERS, mean = tile * (xt ? 1.5 : 1.0);
+    const double least = std::max(tile * n_tiles, (double)(b.max_blocks + 2));  // nothing walks less
     const double pair_price = mean * (pair[i] + f * (pair[i + 1] - pair[i])), slab_price = mean * (slab[i] + f * (slab[i + 1] - slab[i]));
     double best = (double)wide_heaviest(b, s, n_tiles, 0) + pair_price * n_tiles;
     int best_t = 0;
     for (int t = n_tiles % 8; t <= std::min(n_tiles, BcsrShares::MAX_TILES); t += 8) {
-        const double cost = (double)wide_heaviest(b, s, n_tiles, t) + slab_price * t * ((t - 1) / 8);
+        const double slabs = slab_price * t * ((t - 1) / 8);
+        if (least + slabs >= best) continue;
+        const double cost = (double)wide_heaviest(b, s, n_tiles, t) + slabs;
         if (cost < best) best = cost, best_t = t;
     }
     return best_t;
