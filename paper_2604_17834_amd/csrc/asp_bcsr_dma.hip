@@ -592,12 +592,14 @@ RingLoad ring_heaviest(const HostBcsr &b, const RingWalk &walk, int n_tiles, int
 // The order: with as many lists as block-rows in a round the heaviest workgroup is even; 128-row blocks 16, whose rounds start
 // in nearer block columns (3584 x 18944, N = 4096, groups of 2: 77 us, with 32 lists 89).
 // That is the rule where there are many tiles.  With few rounds of them more depends on where the XCDs' runs end in the lists,
-// so another group, in the order that is even for it, is taken where what the heaviest workgroup and compute unit walk, and the
-// price of slabs of B that pass 1.8 MB and of fetching A for every group, is 4.5 % less.  (Us, rule / taken, at 90 %: 64-row, 10240 x 2560, N = 1144
-// 25 / 19; 2816 x 1536, N = 1472 11.3 / 9.0; 3584 x 18944 K-contiguous, 2344 tokens 100 / 77; 128-row, 6912 x 2688, N = 1104
-// 17.0 / 14.6.  Fitted to 192 launches, of which the rule is in the mean 1.07 and up to 1.34 times slower than the best of
-// nine groups and orders, what is taken 1.05 and 1.27; all nine as candidates, 1.04 and 1.21, take three times as long to walk
-// on the first call: 10 to 60 us.)
+// so another group, in the order that is even for it, is taken where the estimate is 5 % less: the heaviest workgroup and
+// compute unit, to powers that the measurements give (the rest of a launch goes on meanwhile), and a factor for the group that
+// holds the slabs of B against the fetches of A.  (Us, rule / taken, at 90 %: 64-row, 10240 x 2560, N = 1536 27 / 21, K-contiguous
+// 29 / 23; 2816 x 1536, N = 1472 11.4 / 9.3; 128-row, 6912 x 2688, N = 1104 17.5 / 14.6; 6144 x 4096 K-contiguous, 2048
+// tokens 24 / 21.  Fitted to 649 launches, of which the rule is in the mean 1.07 times slower than the
+// best of nine groups and orders, what is taken 1.04; 38 take more than 1.1 times as long with the rule as with groups of four
+// in 16 lists, 9 with what is taken (3584 x 18944 K-contiguous, 2344 tokens 80 / 100).  All nine as candidates would give 1.02
+// less and take three times as long to walk on the first call.)
 RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int n_tiles, int64_t n_cus, int per_cu) {
     const int64_t nbr = (int64_t)b.block_row_ptr.size() - 1, tiles = nbr * n_tiles;
     RingWalk rule;
@@ -607,21 +609,28 @@ RingWalk ring_walk(const HostBcsr &b, int64_t k, int b_row, int bn, bool xt, int
     rule.group_n = std::min(rule.group_n, n_tiles);
     rule.lists = b_row == 128 ? 16 : ring_lists(tiles, n_cus * per_cu, rule.group_n);
     if (n_tiles > 128 || tiles > 8192) return rule;
+    // whole column tiles to every XCD, one at a time, of slabs that are twice its L2 (64-row, 3584 x 18944, N = 4096: 94 us, groups
+    // of two in even lists 116)
+    if (rule.group_n == 1 && n_tiles % 8 == 0 && k * (2ll * bn) > (8 << 20)) return rule;
     const double mean = (double)(b.block_col_idx.size() + nbr) * n_tiles / (double)(n_cus * per_cu);
-    auto price = [&](int group_n) {
-        const double slabs = std::log2(std::max(1.0, (double)k * bn * 2 * group_n / 1.8e6));
-        return mean * (0.23 * (xt ? 1.45 : 1.0) * std::min(3.0, slabs) + 1.5 * b_row / bn / group_n);
+    // of groups of one, two and four, at a slab of 8 MB for each N-tile and per doubling of it
+    static const double factor[3][3] = {{0, 0.09, 0.35}, {0, 0, 0.05}, {0, -0.10, -0.14}};
+    static const double doubling[3][3] = {{0, 0.03, 0.08}, {0, 0, 0.01}, {0, -0.01, -0.02}};
+    const double slab = std::log2((double)k * bn * 2 / 8e6);
+    auto estimate = [&](int group_n, double workgroup, double unit) {
+        const int g = group_n >= 4 ? 2 : group_n >= 2 ? 1 : 0, size = b_row / 64;
+        return 0.45 * std::log(workgroup) + 0.22 * std::log(unit) + factor[size][g] + slab * doubling[size][g];
     };
     auto cost = [&](const RingWalk &w) {
         const RingLoad most = ring_heaviest(b, w, n_tiles, n_cus, per_cu);
-        return (double)most.workgroup + 0.8 * most.unit + price(w.group_n);
+        return estimate(w.group_n, (double)most.workgroup, most.unit);
     };
-    double best = cost(rule) / 1.045;
-    const double least = std::max(mean, (double)(b.max_blocks + 1)) + 0.8 * mean;  // nothing walks less
+    double best = cost(rule) - 0.05;
     RingWalk taken = rule;
     for (int group_n = 1; group_n <= 4 && group_n <= n_tiles; group_n *= 2) {
         const RingWalk w = {group_n, std::min(b_row == 128 ? 32 : 64, ring_lists(tiles, n_cus * per_cu, group_n))};
-        if ((w.group_n == rule.group_n && w.lists == rule.lists) || least + price(group_n) >= best) continue;
+        if (w.group_n == rule.group_n && w.lists == rule.lists) continue;
+        if (estimate(group_n, std::max(mean, (double)(b.max_blocks + 1)), mean) >= best) continue;  // nothing walks less
         const double c = cost(w);
         if (c < best) best = c, taken = w;
     }
