@@ -10,8 +10,8 @@
 // ahead.  The waves' partial tiles meet in LDS once, are added in wave order (bitwise reproducible), rounded once, stored.
 // us a call, before -> now: 1024 x 1024, 64 x 64 blocks, 256 columns 6.2 -> 3.7; 3584 x 18944 at 64 / 256 / 1024 columns
 // 58 -> 6.6 / 58 -> 13 / 47 -> 34; 5003 x 3331 (80 %), 64 x 64 blocks, 1024 columns 42 -> 23.
-// With more columns a strip's reads (B once per strip, A once per column tile) run into the L1s' miss rate and the tile
-// kernels win.
+// With more columns a strip's reads (B once per strip, A once per column tile) are so many more than the tile kernels' that
+// these win.
 #include <algorithm>
 
 #include "asp_bcsr_pipe.h"
@@ -226,8 +226,10 @@ static bool launch_strips(const asp_handle *h, const void *B, void *C, int64_t N
 
 // Whether strips are the faster choice: estimates in us, linear in the longest block-row (K slices of 32) and in the
 // work, fitted to 3584 x 18944, 18944 x 3584, 4096 x 4096 (80 %), 1024 x 1024 and 5003 x 3331 (80 %) at 64 to 4096 columns.
-// The crossing is near 500 columns for 18944 x 3584 and 1500 to 2000 for the others; the other kernel would have been up to
-// 1.27 times faster (32-row blocks, 18944 x 3584 at 512 columns, 23.5 against 29.8 us, left to the ring kernel).
+// The crossing is near 500 columns for 18944 x 3584 and 1500 to 2000 for the others.  The ring kernel's costs are those of groups of
+// four column tiles, and it is faster now: of 240 products (ten matrices, 128 to 3072 columns) the choice is in the mean 1.005
+// (128-row), 1.02 (64) and 1.03 (32) times slower than the better kernel, at worst 1.43 (32-row, 2048 x 8192 at 80 %, 2048
+// columns, strips 53, tiles 37 us).
 static bool strips_win(const asp_handle *h, int64_t N, const BcsrPlan &p) {
     const double cus = h->n_cus > 0 ? h->n_cus : 256, b = h->b_row;
     const double work = (double)h->n_units * b * b * (double)N * 256 / cus;  // stored elements x columns

@@ -12,8 +12,9 @@
 // us a call at 16 tokens, before (128 x 512 tiles) -> now: gate 26 -> 5.6, down 78 -> 6.4, down in 64 x 64 / 32 x 32
 // blocks 122 -> 6.7 / 196 -> 5.8; down at 256 tokens 87.6 -> 18.5.  (The host takes 4.0 us to enqueue a call, 6.9 through
 // SparseLinear; the gate and down kernels alone 6.5 and 7.5 in a trace: the chain block-row -> columns -> X of a wave.)
-// With more tokens each strip's reads (A once per token tile, X once per strip) run into the L1s' miss rate, and the ring
-// kernel's larger tiles take over (bcsr_spmm_xt_launch).
+// With more tokens each strip's reads (A once per token tile, X once per strip) take longer at the latency of few loads in
+// flight (3584 x 18944, 1024 tokens: 38 requests for a compute unit, 328 cycles each, 14.7 B/clk), and the ring kernel's
+// larger tiles take over (bcsr_spmm_xt_launch).
 //
 // Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; elements past K count
 // as zeros.
@@ -276,8 +277,10 @@ __global__ __launch_bounds__(256) void bcsr_fill_zero_kernel(uint16_t *__restric
 
 // Which kernel: the one with the shortest estimate, in us on 256 compute units.  A ring kernel's launch takes as long as
 // its longest block-row at the pace of a lone tile plus all its work at the pace of the full chip; the strip kernel,
-// which splits the K loop, takes about 4 us plus its work.  Costs per K slice of 32 (fitted to 18944 x 3584, 3584 x 18944
-// and 4096 x 4096 at 90 %, 1 to 8192 tokens, 4 % from the best choice on average, 1.2 times at worst):
+// which splits the K loop, takes about 4 us plus its work.  Costs per K slice of 32, fitted to 18944 x 3584, 3584 x 18944
+// and 4096 x 4096 at 90 %, 1 to 8192 tokens, when the ring kernel walked groups of four (128, 64) or two (32) column tiles.  Of
+// 240 products of ten matrices, 128 to 3072 tokens, the choice is now in the mean 1.01 (128-row), 1.02 (64) and 1.06 (32)
+// times slower than the better kernel, at worst 1.3, 1.2 and 1.9 (32-row, 1024 x 1024 at 80 %, 768 tokens, ring 8.2, strips 4.3 us):
 struct XtCost {
     double slice_alone[3], slice[3];  // tiles 64, 128, 256 tokens wide
     double strip;                     // per stored element and token
