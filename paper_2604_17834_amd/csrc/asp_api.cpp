@@ -64,6 +64,12 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_e_row_ptr);
     (void)hipFree(h->d_e_col);
     (void)hipFree(h->d_e_val);
+    (void)hipFree(h->d_group_entries);
+    (void)hipFree(h->d_group_tasks);
+    (void)hipFree(h->d_group_slots);
+    (void)hipFree(h->d_g_row_tasks);
+    (void)hipFree(h->d_g_chunks);
+    (void)hipFree(h->d_g_split_rows);
     (void)hipFree(h->d_c_rank_info);
     (void)hipFree(h->d_c_rank_info_32);
     (void)hipFree(h->d_rank_info_32);
@@ -228,7 +234,8 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     if ((s = upload(&h->d_zero_windows, h->hw.zero_windows.data(), h->hw.zero_windows.size() * 4, stream))) return s;
     if ((s = upload(&h->d_ws_slot, h->hw.ws_slot.data(), h->hw.ws_slot.size() * 4, stream))) return s;
     if ((s = wcsr_build_tasks_device(h, stream))) return s;  // wavefront-scan partition on the GPU
-    HostRows rows;  // alive until the stream is synchronised below
+    HostRows rows;  // these are alive until the stream is synchronised below
+    HostGroups groups;
     std::vector<uint8_t> gathered;
     wcsr_build_rows(m, row_ptr, col_idx, es, h->b_row, h->task_cols, h->hw, rows);
     h->n_row_tasks = (int64_t)rows.tasks.size() / 4;
@@ -246,6 +253,21 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload(&h->d_e_row_ptr, rows.row_ptr.data(), rows.row_ptr.size() * 4, stream))) return s;
         if ((s = upload_runs((void **)&h->d_e_col, col_idx, 4, rows, gathered, stream))) return s;
         if ((s = upload_runs(&h->d_e_val, values, es, rows, gathered, stream))) return s;
+    }
+    wcsr_build_groups(m, row_ptr, col_idx, values, es, h->b_row, h->task_cols, h->hw, rows, groups);
+    if (groups.n_groups > 0) {
+        h->n_groups = groups.n_groups;
+        h->group_span = groups.span;
+        h->group_scratch_rows = groups.scratch_rows;
+        h->n_g_row_tasks = (int64_t)groups.row_tasks.size() / 4;
+        h->n_g_chunks = (int64_t)groups.chunks.size() / 4;
+        h->n_g_split_rows = (int64_t)groups.split.size() / 4;
+        if ((s = upload(&h->d_group_entries, groups.entries.data(), groups.entries.size(), stream))) return s;
+        if ((s = upload(&h->d_group_tasks, groups.tasks.data(), groups.tasks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_group_slots, groups.slots.data(), groups.slots.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_g_row_tasks, groups.row_tasks.data(), groups.row_tasks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_g_chunks, groups.chunks.data(), groups.chunks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_g_split_rows, groups.split.data(), groups.split.size() * 4, stream))) return s;
     }
     if (h->n_split_tasks > 0) {
         // set-up for asp_spmm_static_scratch: the device address of the static scratch array, once per device

@@ -698,6 +698,35 @@ bool deal_to_xcds(std::vector<int32_t> &tasks, const std::vector<int64_t> &weigh
 
 }  // namespace
 
+namespace {
+
+// Collects tasks of consecutive whole rows, up to 63 of them and `target` entries each (a longer row is its own task).
+struct RowRuns {
+    const std::vector<int32_t> &row_ptr;
+    int64_t target;
+    std::vector<int32_t> tasks;
+    std::vector<int64_t> weight;
+    int64_t first = -1, last = -1;  // open task: rows [first, last)
+
+    RowRuns(const std::vector<int32_t> &rp, int64_t t) : row_ptr(rp), target(t) {}
+    void close() {
+        if (first < 0) return;
+        tasks.insert(tasks.end(), {(int32_t)first, (int32_t)(last - first), row_ptr[first], row_ptr[last]});
+        weight.push_back(row_ptr[last] - row_ptr[first] + 2 * (last - first));
+        first = -1;
+    }
+    void add(int64_t r, int64_t len) {
+        if (first >= 0 && (last - first >= 63 || row_ptr[last] - row_ptr[first] + len > target)) close();
+        if (first < 0) first = r;
+        last = r + 1;
+    }
+};
+
+// Enough tasks for four rounds of the chip's 8192 waves, 32 to 256 entries each.
+int64_t run_target(int64_t entries) { return std::max<int64_t>(32, std::min<int64_t>(256, entries / 32768)); }
+
+}  // namespace
+
 void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, size_t esize, int32_t b_row,
                      int32_t task_cols, const HostWcsr &in, HostRows &out) {
     const auto &wrp = in.window_row_ptr;
@@ -756,23 +785,14 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         if (longest[i] * W >= MIN_CHUNK * (int64_t)k_used && sum >= 2 * (int64_t)k_used) dense_len = longest[i], dense_width = W;
     }
 
-    // Runs of whole rows: enough tasks for four rounds of the chip's 8192 waves, 32 to 256 entries each.
     int64_t in_long_rows = 0;
     for (int64_t len : longest) in_long_rows += len;
-    const int64_t target = std::max<int64_t>(32, std::min<int64_t>(256, (entries - in_long_rows) / 32768));
-    std::vector<int32_t> chunks, rows;
+    RowRuns runs(out.row_ptr, run_target(entries - in_long_rows));
+    std::vector<int32_t> chunks;
     std::vector<std::pair<int32_t, int64_t>> chunk_key;  // (first column, index)
-    std::vector<int64_t> rows_weight;
-    int64_t first = -1, last = -1;  // open task: rows [first, last)
-    auto close = [&]() {
-        if (first < 0) return;
-        rows.insert(rows.end(), {(int32_t)first, (int32_t)(last - first), out.row_ptr[first], out.row_ptr[last]});
-        rows_weight.push_back(out.row_ptr[last] - out.row_ptr[first] + 2 * (last - first));
-        first = -1;
-    };
     for (int64_t w = 0; w < nw; ++w) {
         if (!sparse[w]) {
-            close();
+            runs.close();
             continue;
         }
         const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
@@ -780,7 +800,7 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         for (int64_t r = r0; r < r1; ++r) {
             const int64_t len = row_ptr[r + 1] - row_ptr[r];
             if (len > task_cols) {  // (then the window is split and owns at least this many rows of scratch)
-                close();
+                runs.close();
                 int64_t step = task_cols;
                 if (len >= dense_len) {  // (no more chunks than the row's share of its window's scratch rows)
                     const int64_t rows_left = (int64_t)ceil_div(wrp[w + 1] - wrp[w], task_cols) * b_row;
@@ -800,12 +820,10 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
                 }
                 continue;
             }
-            if (first >= 0 && (last - first >= 63 || out.row_ptr[last] - out.row_ptr[first] + len > target)) close();
-            if (first < 0) first = r;
-            last = r + 1;
+            runs.add(r, len);
         }
     }
-    close();
+    runs.close();
     std::sort(chunk_key.begin(), chunk_key.end());
     std::vector<int64_t> chunk_weight;
     for (auto &c : chunk_key) {
@@ -814,8 +832,8 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         chunk_weight.push_back(t[3] - t[2]);
     }
     deal_to_xcds(out.chunks, chunk_weight);
-    deal_to_xcds(rows, rows_weight);
-    out.tasks.swap(rows);
+    deal_to_xcds(runs.tasks, runs.weight);
+    out.tasks.swap(runs.tasks);
 
     // the windows that stay with the tile kernels
     std::vector<int64_t> tile_weight;
@@ -833,6 +851,211 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
     // band of 27, N = 256, height 16: bf16 19.3 against 16.8 us, fp32 34.9 / 34.6; 20 000 rows, band of 9, fp32 9.5 / 8.5).  Longer ones
     // round-robin: they sweep the band anyway, and ranges are up to 3 % slower (1 000 000 rows, band of 13 and 24 long rows).
     if (tile_weight.size() <= 4096) out.tiles_dealt = deal_to_xcds(out.tile_tasks, tile_weight);
+}
+
+// Which rows walk in groups (asp_wcsr_groups.hip), and how.
+//
+// A range of columns and a row meet in a partial sum that is written and read once more, so rows take part from 8 entries
+// a range on, the longest as many as 256 groups hold: with more, an XCD's waves would walk the columns a second time (rows
+// that cannot go by whole rows because they are longer than task_cols do so all the same).  Rows longer than half of a
+// group's share are dealt to several groups, entry by entry, and so that a sum has at most about 128 terms: fp32 sums of one
+// row in one piece a range were twice as far from the 64-bit ones as chunks of task_cols = 512.
+// Not done for a few nearly dense rows (the chunks of asp_wcsr_rows.hip find their rows of B in L2 already: 2 000 000
+// rows with 64 of 200 000 entries, N = 64 216 us in chunks and 219 here), where the rows share few columns (two entries a column
+// on average), for less than 64 entries a task (16 915 rows with 118 000 entries, N = 200 36 us by rows, 39 here), where scratch memory, whose
+// size is that of the tiles' partial sums, does not hold the rows' sums, and where a range would pass 2^24 columns.
+void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
+                       int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out) {
+    constexpr int64_t S = HostGroups::RANGES, MIN_PART = 8, GROUPS = 256, MIN_ROWS = 128, MIN_TASK = 64, MAX_PART = 128;
+    const int64_t R = HostGroups::rows(esize);
+    out = HostGroups();
+    const auto &wrp = in.window_row_ptr;
+    const int64_t nw = (int64_t)wrp.size() - 1;
+    auto walked = [&](int64_t r) { return rows.row_ptr[r + 1] > rows.row_ptr[r]; };
+    auto length = [&](int64_t r) { return (int64_t)row_ptr[r + 1] - row_ptr[r]; };
+    std::vector<int32_t> longest;  // rows, longest first
+    for (int64_t r = 0; r < m; ++r)
+        if (walked(r) && length(r) >= S * MIN_PART) longest.push_back((int32_t)r);
+    if ((int64_t)longest.size() < MIN_ROWS) return;
+    std::sort(longest.begin(), longest.end(), [&](int32_t a, int32_t b) {
+        return length(a) != length(b) ? length(a) > length(b) : a < b;
+    });
+    int64_t n = std::min<int64_t>(longest.size(), GROUPS * R);
+    while (n < (int64_t)longest.size() && length(longest[n]) > task_cols) ++n;
+    int64_t G = std::max(GROUPS, ceil_div(n, R));
+    longest.resize((size_t)n);
+
+    int64_t total = 0;
+    int32_t k_used = 1;
+    for (int32_t r : longest) total += length(r), k_used = std::max(k_used, col_idx[row_ptr[r + 1] - 1] + 1);
+    if (total < 2 * (int64_t)k_used || total < MIN_TASK * GROUPS * S) return;
+
+    // rows, in parts where they are long, to groups: longest part first to the group with the least so far
+    struct Part {
+        int32_t row, part, parts;
+        int64_t slot;
+    };
+    const int64_t most = std::max(S * MIN_PART, std::min(S * MAX_PART, total / (2 * G)));
+    std::vector<Part> parts;
+    for (int32_t r : longest) {
+        const int32_t np = (int32_t)ceil_div(length(r), most);
+        for (int32_t p = 0; p < np; ++p) parts.push_back({r, p, np, -1});
+    }
+    while ((int64_t)parts.size() > G * R && length(longest.back()) <= std::min<int64_t>(task_cols, most)) {
+        total -= length(longest.back());
+        longest.pop_back();
+        parts.pop_back();
+    }
+    n = (int64_t)longest.size();
+    G = std::max(G, ceil_div((int64_t)parts.size(), R));
+    G = std::min(G, (int64_t)parts.size());
+    if (G * S > (1 << 24)) return;  // (one launch takes fewer than 2^32 threads)
+    std::stable_sort(parts.begin(), parts.end(), [&](const Part &a, const Part &b) { return length(a.row) / a.parts > length(b.row) / b.parts; });
+
+    // scratch rows: S for every part, those of a row one after the other, in the windows whose own split rows are all here
+    std::vector<uint8_t> grouped((size_t)m, 0);
+    for (int32_t r : longest) grouped[r] = 1;
+    std::vector<std::pair<int64_t, int64_t>> room;
+    for (int64_t w = 0; w < nw; ++w) {
+        if (in.ws_slot[w] < 0) continue;
+        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
+        bool is_free = rows.row_ptr[r1] > rows.row_ptr[r0];
+        for (int64_t r = r0; r < r1 && is_free; ++r) is_free = length(r) <= task_cols || grouped[r];
+        if (!is_free) continue;
+        const int64_t lo = (int64_t)in.ws_slot[w] * b_row, hi = lo + ceil_div(wrp[w + 1] - wrp[w], task_cols) * b_row;
+        if (!room.empty() && room.back().second == lo) room.back().second = hi;
+        else room.push_back({lo, hi});
+    }
+    std::vector<int64_t> row_slot((size_t)n);
+    size_t at = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const int64_t need = ceil_div(length(longest[i]), most) * S;
+        while (at < room.size() && room[at].second - room[at].first < need) ++at;
+        if (at == room.size()) return;
+        row_slot[i] = room[at].first;
+        room[at].first += need;
+        out.split.insert(out.split.end(), {longest[i], (int32_t)row_slot[i], (int32_t)need, 0});
+        out.scratch_rows += need;
+    }
+    {
+        std::vector<std::pair<int32_t, int64_t>> by_row((size_t)n);
+        for (int64_t i = 0; i < n; ++i) by_row[i] = {longest[i], row_slot[i]};
+        std::sort(by_row.begin(), by_row.end());
+        for (Part &p : parts)
+            p.slot = std::lower_bound(by_row.begin(), by_row.end(), std::make_pair(p.row, INT64_MIN))->second + p.part * S;
+    }
+    std::vector<std::vector<Part>> group((size_t)G);
+    {
+        std::vector<std::pair<int64_t, int64_t>> heap;  // (entries, group), least first
+        for (int64_t g = 0; g < G; ++g) heap.push_back({0, g});
+        const std::greater<std::pair<int64_t, int64_t>> more;
+        for (const Part &p : parts) {
+            std::pop_heap(heap.begin(), heap.end(), more);
+            group[heap.back().second].push_back(p);
+            heap.back().first += length(p.row) / p.parts;
+            if ((int64_t)group[heap.back().second].size() == R) heap.pop_back();
+            else std::push_heap(heap.begin(), heap.end(), more);
+        }
+    }
+
+    // ranges of columns with as many entries each, to 1 / 65536 of the columns
+    int shift = 0;
+    while ((k_used >> shift) >= 65536) ++shift;
+    std::vector<int64_t> count(65537, 0);
+    int64_t counted = 0;
+    for (int32_t r : longest)  // (every eighth entry tells)
+        for (int64_t p = row_ptr[r]; p < row_ptr[r + 1]; p += 8, ++counted) ++count[col_idx[p] >> shift];
+    std::vector<int32_t> start((size_t)S + 1, k_used);
+    start[0] = 0;
+    int64_t sum = 0, s = 1;
+    for (int64_t b = 0; b < 65537 && s < S; ++b) {
+        while (s < S && sum >= counted * s / S) start[s++] = (int32_t)std::min<int64_t>(b << shift, k_used);
+        sum += count[b];
+    }
+    for (s = 0; s < S; ++s) out.span = std::max<int64_t>(out.span, start[s + 1] - start[s]);
+    if (out.span > (1 << 24)) return;
+
+    // range s of group g is task s G + g
+    std::vector<int64_t> n_entries((size_t)(S * G) + 1, 0);
+    std::vector<std::vector<int32_t>> cuts((size_t)G);  // per part of a group, S + 1 positions in its row
+    parallel_chunks(G, 1, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t g = b; g < e; ++g) {
+            auto &cut = cuts[g];
+            cut.resize(group[g].size() * (S + 1));
+            for (size_t i = 0; i < group[g].size(); ++i) {
+                const Part &p = group[g][i];
+                const int32_t *lo = col_idx + row_ptr[p.row], *hi = col_idx + row_ptr[p.row + 1], *it = lo;
+                for (int64_t j = 0; j <= S; ++j) {
+                    it = j == S ? hi : std::lower_bound(it, hi, start[j]);
+                    cut[i * (S + 1) + j] = (int32_t)(it - lo);
+                }
+                for (int64_t j = 0; j < S; ++j) {  // positions = part modulo parts
+                    const int64_t c0 = cut[i * (S + 1) + j], c1 = cut[i * (S + 1) + j + 1];
+                    n_entries[j * G + g] += ceil_div(c1 - p.part, p.parts) - ceil_div(c0 - p.part, p.parts);
+                }
+            }
+        }
+    }, G * 64);
+    std::vector<int64_t> first((size_t)(S * G) + 1, 0);
+    for (int64_t t = 0; t < S * G; ++t) first[t + 1] = first[t] + ceil_div(n_entries[t], 16) * 16;
+    if (first[S * G] / 16 > INT32_MAX) return;
+    out.entries.reset((size_t)first[S * G] * 8);
+    uint64_t *const entries = (uint64_t *)out.entries.data();
+    out.tasks.resize((size_t)(S * G) * 4);
+    out.slots.assign((size_t)(G * R), -1);
+    parallel_chunks(G, 1, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t g = b; g < e; ++g) {
+            for (size_t i = 0; i < group[g].size(); ++i) out.slots[g * R + i] = (int32_t)group[g][i].slot;
+            for (int64_t j = 0; j < S; ++j) {
+                uint64_t *const dst = entries + first[j * G + g], *const end = entries + first[j * G + g + 1], *to = dst;
+                for (size_t i = 0; i < group[g].size(); ++i) {
+                    const Part &p = group[g][i];
+                    const int64_t c0 = cuts[g][i * (S + 1) + j], c1 = cuts[g][i * (S + 1) + j + 1];
+                    for (int64_t c = c0 + ((p.part - c0) % p.parts + p.parts) % p.parts; c < c1; c += p.parts) {
+                        const int64_t q = (int64_t)row_ptr[p.row] + c;
+                        uint32_t v = esize == 2 ? (uint32_t)((const uint16_t *)values)[q] << 16 : ((const uint32_t *)values)[q];
+                        *to++ = ((uint64_t)((uint32_t)(col_idx[q] - start[j]) << 8 | (uint32_t)i) << 32) | v;
+                    }
+                }
+                std::sort(dst, to);
+                const uint64_t fill = to > dst ? (to[-1] >> 40 << 40) | (uint64_t)R << 32 : 0;
+                for (; to < end; ++to) *to = fill;
+                for (to = dst; to < end; ++to) *to = *to >> 32 | *to << 32;  // the key is the first word
+                const int32_t t[4] = {(int32_t)(first[j * G + g] / 16), (int32_t)((end - dst) / 16), start[j], 0};
+                std::copy(t, t + 4, out.tasks.begin() + 4 * (j * G + g));
+            }
+        }
+    }, G * 64);
+
+    // the rest: chunks of other rows stay where they are dealt to, runs of whole rows without the grouped ones
+    bool any = false;
+    out.chunks = rows.chunks;
+    for (size_t c = 0; c < out.chunks.size(); c += 4) {
+        if (out.chunks[c + 2] < out.chunks[c + 3] && !grouped[out.chunks[c]]) any = true;
+        else std::fill(out.chunks.begin() + c, out.chunks.begin() + c + 4, 0);
+    }
+    if (!any) out.chunks.clear();
+    int64_t left = rows.n_entries - total;
+    for (size_t i = 0; i < rows.split.size(); i += 4)
+        if (!grouped[rows.split[i]]) {
+            out.split.insert(out.split.end(), rows.split.begin() + i, rows.split.begin() + i + 4);
+            left -= length(rows.split[i]);
+        }
+    RowRuns runs(rows.row_ptr, run_target(left));
+    for (int64_t w = 0; w < nw; ++w) {
+        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
+        if (rows.row_ptr[r1] == rows.row_ptr[r0] && row_ptr[r1] > row_ptr[r0]) {  // by tiles
+            runs.close();
+            continue;
+        }
+        for (int64_t r = r0; r < r1; ++r)
+            if (grouped[r] || length(r) > task_cols) runs.close();
+            else runs.add(r, length(r));
+    }
+    runs.close();
+    deal_to_xcds(runs.tasks, runs.weight);
+    out.row_tasks.swap(runs.tasks);
+    out.n_groups = G;
 }
 
 void wcsr_zero_windows(const std::vector<int32_t> &wrp, int32_t task_cols, std::vector<int32_t> &zw) {

@@ -138,6 +138,19 @@ struct HostRows {
     std::vector<int32_t> tile_split;  // the split windows among those
 };
 
+// Long rows of scattered entries that walk the columns of B together (wcsr_build_groups, asp_wcsr_groups.hip), and the
+// lists of HostRows without them.
+struct HostGroups {
+    static constexpr int rows(size_t esize) { return esize == 2 ? 31 : 63; }  // of a group
+    static constexpr int64_t RANGES = 8; // of columns, one to an XCD
+    int64_t n_groups = 0;                // 0: the rest is not used
+    int64_t span = 0;                    // columns of the widest range
+    int64_t scratch_rows = 0;
+    ZeroedBytes entries;                 // 8 bytes each, see wcsr_groups_kernel, as are:
+    std::vector<int32_t> tasks, slots;
+    std::vector<int32_t> row_tasks, chunks, split;  // as in HostRows
+};
+
 // converters (asp_convert.cpp); values are only bit-copied
 void csr_to_bcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                  size_t esize, int32_t b_row, int32_t b_col, HostBcsr &out);
@@ -152,6 +165,8 @@ bool csr_to_wcsr(int64_t m, int64_t k, const int32_t *row_ptr, const int32_t *co
 void wcsr_tasks_host(const std::vector<int32_t> &window_row_ptr, int32_t task_cols, std::vector<int32_t> &tasks);
 void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, size_t esize, int32_t b_row,
                      int32_t task_cols, const HostWcsr &in, HostRows &out);
+void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
+                       int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out);
 void wcsr_zero_windows(const std::vector<int32_t> &window_row_ptr, int32_t task_cols,
                        std::vector<int32_t> &zero_windows);
 // returns empty string when the CSR arrays are valid, else a description of the first problem
@@ -208,6 +223,11 @@ struct asp_handle {
     int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;
+    // WCSR: long rows in groups, and the lists of what is left beside them, for calls with scratch (HostGroups)
+    int64_t n_groups = 0, group_span = 0, group_scratch_rows = 0;
+    int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0;
+    uint64_t *d_group_entries = nullptr;
+    int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;
     float *d_ws = nullptr;          // fp32 scratch, one [b_row][N] tile per slot (asp_reserve)
     int64_t ws_floats = 0;          // its capacity
 };
@@ -252,6 +272,9 @@ int64_t wcsr_scratch_floats(const asp_handle *h, int64_t N);  // fp32 scratch el
 // windows that are walked entry by entry (empty ones among them), and the sums of their split rows
 void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream);
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
+// the groups of long rows: whether calls of this width (with scratch) use them, and their kernel
+bool wcsr_groups_apply(const asp_handle *h, int64_t N);
+void wcsr_groups_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream);
 // rows of split windows = sum of their tasks' partial tiles, in task order
 void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
 // GPU task partition: fills h->d_tasks / h->n_tasks from h->d_row_ptr (wavefront scans)

@@ -22,27 +22,12 @@
 // computes some of its neighbour's columns a second time (the same bits), so that no access leaves the row.
 #include <algorithm>
 
-#include "asp_internal.h"
+#include "asp_wcsr_rows.h"
 
 namespace asp {
 
 namespace {
 
-typedef __attribute__((address_space(1))) char global_char;
-
-template <typename T, int E>
-struct RowVec;
-template <int E>
-struct RowVec<float, E> {
-    typedef float type __attribute__((ext_vector_type(E), aligned(4)));
-};
-template <int E>
-struct RowVec<uint16_t, E> {
-    typedef uint16_t type __attribute__((ext_vector_type(E), aligned(2)));
-};
-
-__device__ __forceinline__ float widen(float v) { return v; }
-__device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 __device__ __forceinline__ void narrow(float v, float &out) { out = v; }
 __device__ __forceinline__ void narrow(float v, uint16_t &out) { out = __builtin_bit_cast(uint16_t, (__bf16)v); }  // to nearest even
 
@@ -359,16 +344,20 @@ __global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__re
 // ---- host side ------------------------------------------------------------------------------------
 template <typename T>
 static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
+    const bool groups = ws && wcsr_groups_apply(h, N);  // long rows run there: the lists without them
+    const int32_t *d_chunks = groups ? h->d_g_chunks : h->d_chunks, *d_row_tasks = groups ? h->d_g_row_tasks : h->d_row_tasks;
+    const int64_t n_chunks = groups ? h->n_g_chunks : h->n_chunks, n_row_tasks = groups ? h->n_g_row_tasks : h->n_row_tasks;
+    if (groups) wcsr_groups_launch(h, B, N, ws, stream);
     // a launch takes fewer than 2^32 threads
-    const int64_t waves = h->n_chunks + h->n_row_tasks, step = (1 << 26) - 32;
+    const int64_t waves = n_chunks + n_row_tasks, step = (1 << 26) - 32;
     for (int64_t first = 0; first < waves; first += step) {
         const int64_t end = std::min(waves, first + step);
-        const int64_t c0 = std::min(first, h->n_chunks), c1 = std::min(end, h->n_chunks), t0 = first - c0, t1 = end - c1;
+        const int64_t c0 = std::min(first, n_chunks), c1 = std::min(end, n_chunks), t0 = first - c0, t1 = end - c1;
         // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
 #define ASP_ROWS(E, CE, CL)                                                                                          \
     hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                             \
                        dim3((unsigned)ceil_div(end - first, 4), (unsigned)ceil_div(N, 64 * (E))), dim3(256), 0, stream, \
-                       (const int4 *)h->d_chunks + c0, (int)(c1 - c0), (const int4 *)h->d_row_tasks + t0, (int)(t1 - t0), \
+                       (const int4 *)d_chunks + c0, (int)(c1 - c0), (const int4 *)d_row_tasks + t0, (int)(t1 - t0), \
                        h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
         if (N <= 16) ASP_ROWS(1, 1, 16);
         else if (N <= 32) ASP_ROWS(1, 2, 16);
@@ -386,12 +375,15 @@ void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, fl
 }
 
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream) {
-    if (h->n_split_rows == 0) return;
-    const bool many = h->n_chunks > 32 * h->n_split_rows;
+    const bool groups = wcsr_groups_apply(h, N);
+    const int32_t *d_split = groups ? h->d_g_split_rows : h->d_split_rows;
+    const int64_t n_split = groups ? h->n_g_split_rows : h->n_split_rows;
+    if (n_split == 0) return;
+    const bool many = (groups ? h->group_scratch_rows + h->n_g_chunks : h->n_chunks) > 32 * n_split;
 #define ASP_ROWS_SUM(T, COLS, J)                                                                                          \
     hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>),                                                                \
-                       dim3((unsigned)std::min<int64_t>(h->n_split_rows, 1 << 21), (unsigned)ceil_div(N, COLS)),          \
-                       dim3((COLS) * (J)), 0, stream, (const int4 *)h->d_split_rows, (int)h->n_split_rows, ws, (T *)C, N)
+                       dim3((unsigned)std::min<int64_t>(n_split, 1 << 21), (unsigned)ceil_div(N, COLS)),          \
+                       dim3((COLS) * (J)), 0, stream, (const int4 *)d_split, (int)n_split, ws, (T *)C, N)
     if (h->dtype == ASP_DT_BF16) {
         if (many && N <= 65535 * 16) ASP_ROWS_SUM(uint16_t, 16, 64);
         else ASP_ROWS_SUM(uint16_t, 64, 4);

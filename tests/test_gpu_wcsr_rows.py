@@ -121,3 +121,31 @@ def test_several_column_tiles_of_a_task(dtype, b_row, N, windows):
     bits = (lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)) if dtype == "bf16" else \
         (lambda t: t.contiguous().cpu().numpy())
     check_against_oracle(a, bits(Bd[:, ct]), bits(Cd[:, ct]))
+
+
+@pytest.mark.parametrize("dtype,N", [("f32", n) for n in (33, 63, 64, 65, 127, 129, 257)] + [("bf16", n) for n in (65, 127, 128, 129, 257)])
+def test_long_rows_in_groups(dtype, N):
+    # rows from one to 4000 entries, members of groups from 64 on, some of them dealt to several groups; Inf and NaN in some
+    # rows of B reach the rows that store those columns only; the handle without scratch walks the same rows one by one
+    rng = np.random.default_rng(N)
+    lengths = np.concatenate([rng.integers(64, 4000, 300), rng.integers(0, 70, 3001)])
+    rng.shuffle(lengths)
+    a = _rows_of_lengths(list(lengths), 60000, dtype, seed=N)
+    B = synth.dense_normal(a.k, N, dtype, seed=8)
+    h = asp.asp_create_from_csr("wcsr", dtype, 16, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values, task_cols=64)
+    try:
+        if dtype == "f32":
+            check_against_oracle(a, B, gpu_spmm(a, "wcsr", 16, 8, B, handle=h, reserve=False))
+        C = gpu_spmm(a, "wcsr", 16, 8, B, handle=h)
+        check_against_oracle(a, B, C)
+        assert np.array_equal(C.view(np.uint8), gpu_spmm(a, "wcsr", 16, 8, B, handle=h).view(np.uint8))
+        assert not C[np.diff(a.row_ptr) == 0].any()
+        bad = rng.integers(0, a.k, 3)
+        B[bad[:2]] = 0x7F80 if dtype == "bf16" else np.inf
+        B[bad[2]] = 0x7FC1 if dtype == "bf16" else np.nan
+        C = synth.to_f64(gpu_spmm(a, "wcsr", 16, 8, B, handle=h), dtype)
+    finally:
+        asp.asp_destroy(h)
+    row = np.repeat(np.arange(a.m), np.diff(a.row_ptr))
+    touched = np.bincount(row[np.isin(a.col_idx, bad)], minlength=a.m) > 0
+    assert touched.sum() > 20 and not np.isfinite(C[touched]).any() and np.isfinite(C[~touched]).all()

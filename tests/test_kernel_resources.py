@@ -22,6 +22,7 @@ HOT = {
     "asp_bcsr_f32.hip": ["bcsr_f32_spmm_kernel"],
     "asp_wcsr.hip": ["wcsr16_spmm_kernel", "wcsr32_spmm_kernel"],
     "asp_wcsr_rows.hip": ["wcsr_rows_kernel"],
+    "asp_wcsr_groups.hip": ["wcsr_groups_kernel"],
     "asp_wcsr_bf16.hip": ["wcsr_bf16_spmm_kernel"],
 }
 

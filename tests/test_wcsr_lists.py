@@ -42,3 +42,29 @@ def test_scratch_rows_that_pass_int32_stay_with_the_tiles(lists_of):
     assert got["tile_split"] == [[1]] and all(t[0] == 1 for t in got["tile"])
     got = lists_of("slots", 2**27 - 1)
     assert "split" not in got and "chunk" not in got and got["tile_split"] == [[0], [1]]
+
+
+@pytest.mark.parametrize("esize", [4, 2])
+@pytest.mark.parametrize("m,k,task_cols,lengths", [
+    (2000, 60000, 512, [0, 1, 63, 64, 65, 300, 511, 512, 513, 2000]),          # either side of the shortest grouped row and of a task
+    (9000, 40000, 48, [900, 64, 70, 5] * 4 + [49, 63, 20, 3] * 4),             # rows longer than a task that are no members
+    (20000, 30000, 512, [520, 70, 3]),                                         # more rows than 256 groups hold
+    (400, 100000, 512, [40000] + [2000] * 99),                                 # rows dealt to several groups
+])
+def test_rows_in_groups_are_the_rows(lists_of, esize, m, k, task_cols, lengths):
+    got = lists_of("groups", m, k, task_cols, esize, *lengths)
+    assert got["groups"][0][0] >= 256 and got["largest"][0][0] > 0
+    assert got["scratch"][0][1] <= got["scratch"][0][0]
+    tiles = got.get("tile", [])
+    assert len(got["row"]) + len(tiles) == m and len(got["row"]) > m // 2
+    assert all(diff == 0 and times == 1 for _, diff, times in got["row"]) and not any(times for _, times in tiles)
+
+
+@pytest.mark.parametrize("m,k,lengths", [
+    (100, 20000, [2000]),                 # few rows
+    (4000, 1000000, [300, 600]),          # that share no columns
+    (400, 20000, [100, 300, 600]),        # less than 64 entries a task
+    (4000, 3000, [63, 20]),               # no row long enough
+])
+def test_no_groups_where_they_do_not_pay(lists_of, m, k, lengths):
+    assert lists_of("groups", m, k, 512, 4, *lengths)["groups"] == [[0]]
