@@ -12,9 +12,8 @@
 // us a call at 16 tokens, before (128 x 512 tiles) -> now: gate 26 -> 5.6, down 78 -> 6.4, down in 64 x 64 / 32 x 32
 // blocks 122 -> 6.7 / 196 -> 5.8; down at 256 tokens 87.6 -> 18.5.  (The host takes 4.0 us to enqueue a call, 6.9 through
 // SparseLinear; the gate and down kernels alone 6.5 and 7.5 in a trace: the chain block-row -> columns -> X of a wave.)
-// With more tokens each strip's reads (A once per token tile, X once per strip) take longer at the latency of few loads in
-// flight (3584 x 18944, 1024 tokens: 38 requests for a compute unit, 328 cycles each, 14.7 B/clk), and the ring kernel's
-// larger tiles take over (bcsr_spmm_xt_launch).
+// With more tokens X goes through LDS (bcsr_xt_staged_kernel), and with many the ring kernel's larger tiles take over
+// (bcsr_spmm_xt_launch).
 //
 // Any K, M, N and alignment (VEC = false): 16-byte loads of X at element alignment; elements past K count
 // as zeros.
@@ -172,6 +171,163 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int4 *__res
     }
 }
 
+// Strips of 64 or 128 outputs x 64 tokens for short prompts.  X goes through LDS here: an MFMA step wants 16 bytes of each of 32
+// tokens, and a load with as many cache lines as lanes takes the L1 four times as long as one that reads whole lines.  So a
+// wave reads 64 k of 8 tokens with an instruction, eight adjacent lanes to a token's 128 bytes, and leaves them in 8 KB of
+// its own LDS, chunk c of token t at place c ^ (t % 8), which both the writes and the fragment reads meet without
+// bank conflicts.  X is one unit of 64 k ahead in registers, A half a unit; a wave's LDS operations execute in order, so
+// the loop has no barrier.  LDS and registers are for two workgroups on a compute unit (MT = 2: three): each fills the waits
+// of the others.  us a call, straight to registers -> here: 3584 x 18944 at 90 %, 128-row blocks, 256 / 1024 / 2048 tokens 18.7 /
+// 37.3 / 60.5 -> 12.9 / 28.6 / 54.7, 64-row blocks, 1024 tokens 46 -> 37; 18944 x 3584, 512 tokens 30 -> 22.  What bounds it: L2 misses on X
+// (123 MB at 1024 tokens, the columns of different block-rows hardly meet) with one unit a wave ahead.
+template <int BR, int MT>
+__global__ __launch_bounds__(256, MT == 4 ? 2 : 3) void bcsr_xt_staged_kernel(const int4 *__restrict__ rank_info,
+                                                                             const int32_t *__restrict__ col_idx,
+                                                                             const uint16_t *__restrict__ a_packed,
+                                                                             const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
+                                                                             int M, int K, int64_t N, int units_m) {
+    constexpr int STRIPS = BR / (32 * MT), UPB = BR / 64;
+    __shared__ __attribute__((aligned(16))) union {
+        u32x4 x[4][64][8];             // [wave][token][chunk of 8 k]
+        f32x4 part[4][MT * 4][64];     // [wave][register / 4][lane]
+    } lds;
+    __shared__ __attribute__((aligned(16))) uint16_t out[64][16 * MT + 8];
+
+    typedef __attribute__((address_space(1))) char global_char;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // as above: an XCD takes a run of strips with all their column tiles
+    const int units_n = gridDim.x / units_m, xcd = blockIdx.x & 7, q = gridDim.x >> 3, r = gridDim.x & 7;
+    const int id = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
+    const int un = id % units_n, um = id / units_n;
+    const int n_brows = units_m / STRIPS, per = n_brows >> 3, more = n_brows & 7, at = um / STRIPS, strip = um % STRIPS;
+    const int list = at < more * (per + 1) ? at / (per + 1) : more + (at - more * (per + 1)) / per;
+    const int4 ri = rank_info[list + 8 * (at - list * per - (list < more ? list : more))];
+    const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
+    const int64_t n0 = (int64_t)un * 64;
+    const int u0 = n_units * wave / 4, u1 = n_units * (wave + 1) / 4;
+
+    f32x16 acc[MT][2];
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)  // 0 x 0 + 0 (copies of zeros would take a tile's registers more)
+            asm volatile("s_nop 3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[i][j]) : "v"(zero));
+
+    if (u0 < u1) {
+        const int chunk = lane & 7, row = lane >> 3, half = lane >> 5;
+        // offsets of tokens; those past N feed columns that are never stored
+        const uint32_t row_bytes = (uint32_t)K * 2, last_token = (N - n0 < 64 ? (uint32_t)(N - n0) - 1 : 63) * row_bytes;
+        const uint32_t first_token = row * row_bytes < last_token ? row * row_bytes : last_token;
+        const char *x0 = (const char *)(X + n0 * K);
+        const char *a_base = (const char *)(a_packed + (int64_t)blk0 * (BR * BR) + strip * (MT * 512));
+        const int last = u1 - 1;
+        // (a block column is a vector load of one address, a unit ahead of the loads of X that need it: it is waited for in
+        // order with them)
+        auto column = [&](int u) __attribute__((always_inline)) {
+            uint32_t zero = 0;
+            asm("" : "+v"(zero));
+            return col_idx[blk0 + (u < last ? u : last) / UPB + zero];
+        };
+        u32x4 xr[8], a0[MT][2], a1[MT][2];
+        int k0;  // first k of the unit in xr
+        auto load_x = [&](int u, int col) __attribute__((always_inline)) {
+            k0 = __builtin_amdgcn_readfirstlane(col) * BR + (u % UPB) * 64;
+            const uint32_t at = (uint32_t)(k0 + chunk * 8 < K ? k0 + chunk * 8 : K - 8) * 2;
+            uint32_t token = first_token;
+            asm("" : "+v"(token));  // (eight offsets kept through the loop are eight registers too many)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                xr[i] = *(const u32x4 *)(x0 + (token + at));
+                token = token + 8 * row_bytes < last_token ? token + 8 * row_bytes : last_token;
+            }
+        };
+        auto load_a = [&](int u, int h, u32x4 (&a)[MT][2]) __attribute__((always_inline)) {
+            uint32_t at = lane * 16;
+            asm("" : "+v"(at));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const global_char *src = (const global_char *)a_base + (int64_t)u * (128 * BR) + h * (64 * BR) + i * (32 * BR);
+                asm("" : "+s"(src));
+#pragma unroll
+                for (int g = 0; g < MT; ++g) a[g][i] = *(const __attribute__((address_space(1))) u32x4 *)(src + at + g * 1024);
+            }
+        };
+        auto multiply = [&](int h, const u32x4 (&a)[MT][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                u32x4 x[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) x[j] = lds.x[wave][j * 32 + (lane & 31)][(4 * h + 2 * i + half) ^ (lane & 7)];
+#pragma unroll
+                for (int g = 0; g < MT; ++g)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        // (in place, accumulation registers: the compiler's own moves them around the loop)
+                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc[g][j]) : "v"(a[g][i]), "v"(x[j]));
+            }
+        };
+        load_x(u0, column(u0));
+        int col = column(u0 + 1);
+        load_a(u0, 0, a0);
+        for (int u = u0; u < u1; ++u) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds.x[wave][i * 8 + row][chunk ^ (row & 7)] = xr[i];
+            if (k0 + 64 > K && k0 + chunk * 8 >= K)  // K % 8 == 0
+#pragma unroll
+                for (int i = 0; i < 8; ++i) lds.x[wave][i * 8 + row][chunk ^ (row & 7)] = u32x4{0u, 0u, 0u, 0u};
+            load_a(u, 1, a1);
+            const int next = u < last ? u + 1 : u;  // (the last unit once more, instead of a loop body without loads)
+            load_x(next, col);
+            col = column(u + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(0, a0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_a(next, 0, a0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(1, a1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last products, before anything reads them
+
+    // Half of the row tiles at a time: every wave leaves its products, [(g 2 + j) 4 + e] the registers 4 e .. of row tile g and
+    // tokens j, adds a quarter of all in wave order and rounds.  D of the MFMA: lane l holds token l % 32, rows
+    // 8 e + 4 (l / 32) + 0..3.
+    const int m0 = br * BR + strip * (32 * MT);
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < MT / 2; ++g)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f32x16 &v = acc[part * (MT / 2) + g][j];
+                    lds.part[wave][(g * 2 + j) * 4 + e][lane] = f32x4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
+                }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int at = wave * MT + i;
+            f32x4 v = lds.part[0][at][lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) v += lds.part[w][at][lane];
+            uint32_t o[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                o[c] = __builtin_bit_cast(uint16_t, (__bf16)v[2 * c]) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * c + 1]) << 16;
+            *(uint2 *)&out[at / 4 % 2 * 32 + (lane & 31)][at / 8 * 32 + at % 4 * 8 + 4 * (lane >> 5)] = uint2{o[0], o[1]};
+        }
+        __syncthreads();
+        for (int i = tid; i < 64 * 2 * MT; i += 256) {  // eight adjacent outputs of a token
+            const int t = i / (2 * MT), r = i % (2 * MT) * 8, m = m0 + part * (16 * MT) + r;
+            if (n0 + t < N && m < M) *(u32x4 *)(Y + (n0 + t) * M + m) = *(const u32x4 *)&out[t][r];
+        }
+    }
+}
+
 // ---- host side ------------------------------------------------------------------------------------
 // false: too many rows for a launch
 template <int BR, int MT, int NT, int W, int UK>
@@ -195,7 +351,31 @@ static bool launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N,
     return true;
 }
 
-// Shape of the wave tiles: the largest that still gives the chip enough of them, since a larger one reads fewer bytes
+template <int BR, int MT>
+static bool launch_staged(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream) {
+    const int64_t units_m = h->n_brows * (BR / 32 / MT), n64 = ceil_div(N, 64);
+    if (!launch_fits(units_m * n64, 256) || h->k >= (1ll << 25)) return false;  // (offsets of 64 tokens are 32-bit)
+    hipLaunchKernelGGL((bcsr_xt_staged_kernel<BR, MT>), dim3((unsigned)(units_m * n64)), dim3(256), 0, stream,
+                       (const int4 *)h->d_rank_info, h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)X,
+                       (uint16_t *)Y, (int)h->m, (int)h->k, N, (int)units_m);
+    return true;
+}
+
+// Whether 16-byte aligned operands go through the staged strips, and how high these are: 0, or 2 or 4 row tiles.  From three
+// 64-row strips to four compute units on; below, 32-token strips with eight waves are the better ones (3584 x 18944, 90 %, 128-row
+// blocks, 64 / 128 / 256 tokens 9.5 / 11.8 / 18.7 us, staged 11.4 / 11.6 / 12.9; 1664 x 3904, 80 %, 287 tokens 9.4 / 10.6).  With less than three
+// units of 64 k a block-row the ends of the strips are all there is (2944 x 1280, 90 %, 64-row blocks, 4185 tokens 18.8 / 21.5).
+// Three 64-row strips fit a compute unit, two of 128 rows, which read X once instead of twice: better where rows are long
+// enough (6 blocks) to be bound by that and there are more 64-row strips than places (256 / 768 / 1024 / 2048 tokens of the
+// former, 64 and 128 rows 12.9 / 17.0, 28.9 / 30.8, 35.4 / 30.9, 67 / 55 us; 18944 x 3584, three blocks a row, 512 / 1024 tokens
+// 22.3 / 22.8, 39.2 / 39.8).
+static int staged_strips(const asp_handle *h, int64_t N) {
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, strips = h->n_brows * (h->b_row / 64) * ceil_div(N, 64);
+    if (h->b_row < 64 || N <= 32 || 4 * strips < 3 * cus || h->n_units * (h->b_row / 64) < 3 * h->n_brows) return 0;
+    return h->b_row == 128 && strips > 3 * cus && h->n_units >= 6 * h->n_brows ? 4 : 2;
+}
+
+// Shape of the wave tiles of the other strips: the largest that still gives the chip enough of them, since a larger one reads fewer bytes
 // per MFMA.  18944 x 3584 (gate) and 3584 x 18944 (down), 90 % sparse, us a call, tiles of 32 x 32 / 64 x 32 / 64 x 64 /
 // 128 x 64: gate at 64 tokens 8.3 / 7.7 / 8.6 / 10.3, at 256 22 / 19 / 18 / 20; down at 64 tokens 9.3 / 10.9 / 17 / 21,
 // at 256 22 / 18 / 19 / 23, at 768 52 / 39 / 43 / 33.  128 x 64 needs block-rows long enough that every wave of the
@@ -204,9 +384,15 @@ template <int BR>
 static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64);
     if constexpr (BR == 128) {
+        if (vec && staged_strips(h, N) != 0 &&
+            (staged_strips(h, N) == 4 ? launch_staged<BR, 4>(h, X, Y, N, stream) : launch_staged<BR, 2>(h, X, Y, N, stream)))
+            return true;
         // (or too many rows for a launch of 64-row strips)
         if ((h->n_units >= 8 * h->n_brows && h->n_brows * n64 >= cus * 3 / 4) || h->n_brows >= (1 << 23))
             return launch_strip<BR, 4, 2, 4, 32>(h, X, Y, N, vec, stream);
+    }
+    if constexpr (BR == 64) {
+        if (vec && staged_strips(h, N) != 0 && launch_staged<BR, 2>(h, X, Y, N, stream)) return true;
     }
     if constexpr (BR >= 64) {
         const int64_t strips = h->n_brows * (BR / 64);
@@ -315,12 +501,19 @@ asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, in
         } else {
             const XtCost c = xt_cost(h->b_row);
             const double slices = (double)h->n_units * (h->b_row / 32), longest = (double)h->hb.max_blocks * (h->b_row / 32);
-            double best = 4.0 + c.strip * (double)h->n_units * h->b_row * h->b_row * (double)N * 256 / cus;
+            const double work = (double)h->n_units * h->b_row * h->b_row * (double)N * 256 / cus;
+            double best = 4.0 + c.strip * work, ring_at_least = 0.0;
             int bn = 0;
             for (int i = 0; i < (h->b_row == 32 ? 2 : 3) && tiles_ok; ++i) {  // (256 wide never pays with 32 rows)
-                const double t = c.slice_alone[i] * longest + c.slice[i] * slices * (double)ceil_div(N, 64 << i) / cus;
-                if (t < best) best = t, bn = 64 << i;
+                const double alone = c.slice_alone[i] * longest, all = c.slice[i] * slices * (double)ceil_div(N, 64 << i) / cus;
+                if (alone + all < best) best = alone + all, bn = 64 << i, ring_at_least = std::max(alone, all);
             }
+            // The staged strips are up to 1.8 times faster than those that the estimate was fitted to.  Where the ring kernel
+            // is said to be faster than those, it takes between the longer of its two terms and their sum, and stays where the
+            // staged strips are not below the former (2688 x 4352, 80 %, geometric rows, 5994 tokens ring 54, staged 66 us).
+            const int staged = vec ? staged_strips(h, N) : 0;
+            const double per_strip = h->b_row == 64 ? 5.2e-9 : staged == 4 ? 4.0e-9 : 4.4e-9;
+            if (staged && 4.0 + 4e-10 * (double)h->m * (double)N * 256 / cus + per_strip * work < ring_at_least) bn = 0;
             BcsrPlan p = {bn, bn ? (int32_t)ceil_div(N, bn) : 0, 1, 0};
             p.workgroups = h->n_brows * p.n_tiles;
             if (bn != 0 && p.workgroups * 8 < (1ll << 31)) bcsr_dma_xt_launch(h, X, Y, N, p, stream);

@@ -57,3 +57,17 @@ def test_tokens_do_not_reach_each_other(b, k, N):
     Xn = X.copy()
     Xn[1::2] = 0x7FC1
     assert np.array_equal(gpu_spmm_xt(a, b, Xn)[::2], gpu_spmm_xt(a, b, X)[::2])
+
+
+@pytest.mark.parametrize("b", [64, 128])
+@pytest.mark.parametrize("m,k,N,sparsity", [
+    (12808, 1032, 33, 0.5), (12808, 1032, 64, 0.5), (8200, 1992, 65, 0.5),   # edges of a token tile; a last unit of 8 k
+    (8200, 1992, 700, 0.5), (8200, 200, 500, 0.0), (8200, 384, 300, 0.0),    # 128-row strips; few units, the last of 8 k; whole ones
+])
+def test_staged_strips(b, m, k, N, sparsity):
+    a = synth.block_sparse_bernoulli(m, k, b, b, sparsity, seed=b + m + N, dtype="bf16")
+    X = synth.dense_normal(N, k, "bf16", seed=N)
+    Y = gpu_spmm_xt(a, b, X)
+    _check(a, X, Y, np.r_[0:24, N - 24:N])
+    X[1::2] = 0x7FC1   # NaN in every other token stays there, also where a block passes the last k
+    assert np.array_equal(gpu_spmm_xt(a, b, X)[::2], Y[::2])

@@ -18,7 +18,7 @@ HOT = {
     "asp_bcsr.hip": ["bcsr_spmm_kernel"],
     "asp_bcsr_dma.hip": ["bcsr_spmm_dma_kernel"],
     "asp_bcsr_strip.hip": ["bcsr_strip_kernel"],
-    "asp_bcsr_xt.hip": ["bcsr_xt_strip_kernel"],
+    "asp_bcsr_xt.hip": ["bcsr_xt_strip_kernel", "bcsr_xt_staged_kernel"],
     "asp_bcsr_f32.hip": ["bcsr_f32_spmm_kernel"],
     "asp_wcsr.hip": ["wcsr16_spmm_kernel", "wcsr32_spmm_kernel"],
     "asp_wcsr_rows.hip": ["wcsr_rows_kernel"],
