@@ -8,9 +8,9 @@
 // and all with as many entries: what one fetched the others find in L2.  The products stay one fp32 fused multiply-add
 // each, in the order of the columns.
 //
-// 2^20-row Zipf graph, fp32, N = 128, 11.1 of 16.7 million entries in groups: these took 680 us by rows and take 380 (and 18
-// for the larger sums), 14.5 TB/s of rows of B, 85 % of the lines from L2; the product 1194 -> 930 us.  200 003 rows, bf16,
-// N = 100: 126 -> 113.  What bounds it: the latency of L2 with the number of lines that an L1 keeps in flight, and the waves
+// 2^20-row Zipf graph, fp32, N = 128, 10.3 of 16.7 million entries in groups: these took 630 us by rows and take 367 (and 11 for
+// the larger sums), 14.5 TB/s of rows of B, 85 % of the lines from L2; the product 1198 -> 946 us.  200 003 rows, bf16,
+// N = 100: 121 -> 110.  What bounds it: the latency of L2 with the number of lines that an L1 keeps in flight, and the waves
 // that run ahead or behind their XCD's others, whose lines L2 no longer holds.  So fewer and longer tasks are better: 4096
 // tasks of up to 31 rows and 128 columns a wave 511 us with 48 % from L2, 4096 of 31 rows and 64 columns 416, 2048 of 63 rows 374.
 //
