@@ -855,18 +855,22 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
 
 // Which rows walk in groups (asp_wcsr_groups.hip), and how.
 //
-// A range of columns and a row meet in a partial sum that is written and read once more, so rows take part from 8 entries
-// a range on, the longest as many as 256 groups hold: with more, an XCD's waves would walk the columns a second time (rows
-// that cannot go by whole rows because they are longer than task_cols do so all the same).  Rows longer than half of a
-// group's share are dealt to several groups, entry by entry, and so that a sum has at most about 128 terms: fp32 sums of one
-// row in one piece a range were twice as far from the 64-bit ones as chunks of task_cols = 512.
+// The columns are cut into 8 ranges of equal work.  A row leaves one or several pieces in each range that it has entries in,
+// and the pieces of a range are dealt to that range's tasks by themselves, the longest to the task with the least so far: a
+// task holds as many entries as its neighbours whatever columns the rows store, all of them or those of a community.  A piece
+// is a partial sum that is written and read once more, so rows take part from 8 entries a range on, the longest as many as 256
+// tasks a range hold: with more, an XCD's waves would walk the columns a second time (rows that cannot go by whole rows
+// because they are longer than task_cols do so all the same).  Rows with more than half of a task's share in a range leave
+// several pieces there, entry by entry, and so that a sum has at most 160 terms and no more than task_cols: fp32 sums in one piece a
+// range were twice as far from the 64-bit ones as chunks of task_cols = 512.
 // Not done for a few nearly dense rows (the chunks of asp_wcsr_rows.hip find their rows of B in L2 already: 2 000 000
 // rows with 64 of 200 000 entries, N = 64 216 us in chunks and 219 here), where the rows share few columns (two entries a column
 // on average), for less than 64 entries a task (16 915 rows with 118 000 entries, N = 200 36 us by rows, 39 here), where scratch memory, whose
-// size is that of the tiles' partial sums, does not hold the rows' sums, and where a range would pass 2^24 columns.
+// size is that of the tiles' partial sums, does not hold the sums of all pieces, where a range would pass 2^24 columns, and where
+// one range has a quarter more to walk than the mean.
 void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
                        int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out) {
-    constexpr int64_t S = HostGroups::RANGES, MIN_PART = 8, GROUPS = 256, MIN_ROWS = 128, MIN_TASK = 64, MAX_PART = 128;
+    constexpr int64_t S = HostGroups::RANGES, MIN_PIECE = 8, GROUPS = 256, MIN_ROWS = 128, MIN_TASK = 64, MAX_TERMS = 128;
     const int64_t R = HostGroups::rows(esize);
     out = HostGroups();
     const auto &wrp = in.window_row_ptr;
@@ -875,88 +879,19 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     auto length = [&](int64_t r) { return (int64_t)row_ptr[r + 1] - row_ptr[r]; };
     std::vector<int32_t> longest;  // rows, longest first
     for (int64_t r = 0; r < m; ++r)
-        if (walked(r) && length(r) >= S * MIN_PART) longest.push_back((int32_t)r);
+        if (walked(r) && length(r) >= S * MIN_PIECE) longest.push_back((int32_t)r);
     if ((int64_t)longest.size() < MIN_ROWS) return;
     std::sort(longest.begin(), longest.end(), [&](int32_t a, int32_t b) {
         return length(a) != length(b) ? length(a) > length(b) : a < b;
     });
     int64_t n = std::min<int64_t>(longest.size(), GROUPS * R);
     while (n < (int64_t)longest.size() && length(longest[n]) > task_cols) ++n;
-    int64_t G = std::max(GROUPS, ceil_div(n, R));
     longest.resize((size_t)n);
 
     int64_t total = 0;
     int32_t k_used = 1;
     for (int32_t r : longest) total += length(r), k_used = std::max(k_used, col_idx[row_ptr[r + 1] - 1] + 1);
     if (total < 2 * (int64_t)k_used || total < MIN_TASK * GROUPS * S) return;
-
-    // rows, in parts where they are long, to groups: longest part first to the group with the least so far
-    struct Part {
-        int32_t row, part, parts;
-        int64_t slot;
-    };
-    const int64_t most = std::max(S * MIN_PART, std::min(S * MAX_PART, total / (2 * G)));
-    std::vector<Part> parts;
-    for (int32_t r : longest) {
-        const int32_t np = (int32_t)ceil_div(length(r), most);
-        for (int32_t p = 0; p < np; ++p) parts.push_back({r, p, np, -1});
-    }
-    while ((int64_t)parts.size() > G * R && length(longest.back()) <= std::min<int64_t>(task_cols, most)) {
-        total -= length(longest.back());
-        longest.pop_back();
-        parts.pop_back();
-    }
-    n = (int64_t)longest.size();
-    G = std::max(G, ceil_div((int64_t)parts.size(), R));
-    G = std::min(G, (int64_t)parts.size());
-    if (G * S > (1 << 24)) return;  // (one launch takes fewer than 2^32 threads)
-    std::stable_sort(parts.begin(), parts.end(), [&](const Part &a, const Part &b) { return length(a.row) / a.parts > length(b.row) / b.parts; });
-
-    // scratch rows: S for every part, those of a row one after the other, in the windows whose own split rows are all here
-    std::vector<uint8_t> grouped((size_t)m, 0);
-    for (int32_t r : longest) grouped[r] = 1;
-    std::vector<std::pair<int64_t, int64_t>> room;
-    for (int64_t w = 0; w < nw; ++w) {
-        if (in.ws_slot[w] < 0) continue;
-        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
-        bool is_free = rows.row_ptr[r1] > rows.row_ptr[r0];
-        for (int64_t r = r0; r < r1 && is_free; ++r) is_free = length(r) <= task_cols || grouped[r];
-        if (!is_free) continue;
-        const int64_t lo = (int64_t)in.ws_slot[w] * b_row, hi = lo + ceil_div(wrp[w + 1] - wrp[w], task_cols) * b_row;
-        if (!room.empty() && room.back().second == lo) room.back().second = hi;
-        else room.push_back({lo, hi});
-    }
-    std::vector<int64_t> row_slot((size_t)n);
-    size_t at = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        const int64_t need = ceil_div(length(longest[i]), most) * S;
-        while (at < room.size() && room[at].second - room[at].first < need) ++at;
-        if (at == room.size()) return;
-        row_slot[i] = room[at].first;
-        room[at].first += need;
-        out.split.insert(out.split.end(), {longest[i], (int32_t)row_slot[i], (int32_t)need, 0});
-        out.scratch_rows += need;
-    }
-    {
-        std::vector<std::pair<int32_t, int64_t>> by_row((size_t)n);
-        for (int64_t i = 0; i < n; ++i) by_row[i] = {longest[i], row_slot[i]};
-        std::sort(by_row.begin(), by_row.end());
-        for (Part &p : parts)
-            p.slot = std::lower_bound(by_row.begin(), by_row.end(), std::make_pair(p.row, INT64_MIN))->second + p.part * S;
-    }
-    std::vector<std::vector<Part>> group((size_t)G);
-    {
-        std::vector<std::pair<int64_t, int64_t>> heap;  // (entries, group), least first
-        for (int64_t g = 0; g < G; ++g) heap.push_back({0, g});
-        const std::greater<std::pair<int64_t, int64_t>> more;
-        for (const Part &p : parts) {
-            std::pop_heap(heap.begin(), heap.end(), more);
-            group[heap.back().second].push_back(p);
-            heap.back().first += length(p.row) / p.parts;
-            if ((int64_t)group[heap.back().second].size() == R) heap.pop_back();
-            else std::push_heap(heap.begin(), heap.end(), more);
-        }
-    }
 
     // ranges of columns with as many entries each, to 1 / 65536 of the columns
     int shift = 0;
@@ -975,57 +910,134 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     for (s = 0; s < S; ++s) out.span = std::max<int64_t>(out.span, start[s + 1] - start[s]);
     if (out.span > (1 << 24)) return;
 
-    // range s of group g is task s G + g
-    std::vector<int64_t> n_entries((size_t)(S * G) + 1, 0);
-    std::vector<std::vector<int32_t>> cuts((size_t)G);  // per part of a group, S + 1 positions in its row
-    parallel_chunks(G, 1, [&](unsigned, int64_t b, int64_t e) {
-        for (int64_t g = b; g < e; ++g) {
-            auto &cut = cuts[g];
-            cut.resize(group[g].size() * (S + 1));
-            for (size_t i = 0; i < group[g].size(); ++i) {
-                const Part &p = group[g][i];
-                const int32_t *lo = col_idx + row_ptr[p.row], *hi = col_idx + row_ptr[p.row + 1], *it = lo;
-                for (int64_t j = 0; j <= S; ++j) {
-                    it = j == S ? hi : std::lower_bound(it, hi, start[j]);
-                    cut[i * (S + 1) + j] = (int32_t)(it - lo);
-                }
-                for (int64_t j = 0; j < S; ++j) {  // positions = part modulo parts
-                    const int64_t c0 = cut[i * (S + 1) + j], c1 = cut[i * (S + 1) + j + 1];
-                    n_entries[j * G + g] += ceil_div(c1 - p.part, p.parts) - ceil_div(c0 - p.part, p.parts);
-                }
+    // where each row crosses from one range to the next, and how many pieces it leaves in each
+    std::vector<int32_t> cuts((size_t)(n * (S + 1)));
+    parallel_chunks(n, 256, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t i = b; i < e; ++i) {
+            const int32_t *lo = col_idx + row_ptr[longest[i]], *hi = col_idx + row_ptr[longest[i] + 1], *it = lo;
+            for (int64_t j = 0; j <= S; ++j) {
+                it = j == S ? hi : std::lower_bound(it, hi, start[j]);
+                cuts[i * (S + 1) + j] = (int32_t)(it - lo);
             }
         }
-    }, G * 64);
+    });
+    const int64_t share = std::max(MIN_PIECE, total / (2 * GROUPS * S));
+    const int64_t cut_at = std::min<int64_t>({MAX_TERMS, share, task_cols}), most = std::min<int64_t>(cut_at * 5 / 4, task_cols);
+    auto in_range = [&](int64_t i, int64_t j) { return (int64_t)cuts[i * (S + 1) + j + 1] - cuts[i * (S + 1) + j]; };
+    auto pieces = [&](int64_t i, int64_t j) {
+        const int64_t c = in_range(i, j);
+        return c <= most ? (int64_t)(c > 0) : ceil_div(c, cut_at);
+    };
+    int64_t n_pieces[S] = {0};
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t j = 0; j < S; ++j) n_pieces[j] += pieces(i, j);
+    std::vector<int64_t> kept;  // the rows that take part, as places in `longest`
+    for (int64_t i = n - 1; i >= 0; --i) {
+        bool full = false;
+        for (int64_t j = 0; j < S; ++j) full |= n_pieces[j] > GROUPS * R && in_range(i, j) > 0;
+        if (full && length(longest[i]) <= task_cols) {
+            total -= length(longest[i]);
+            for (int64_t j = 0; j < S; ++j) n_pieces[j] -= pieces(i, j);
+        } else {
+            kept.push_back(i);
+        }
+    }
+    std::reverse(kept.begin(), kept.end());
+    const int64_t widest = *std::max_element(n_pieces, n_pieces + S);
+    const int64_t G = std::min(std::max(GROUPS, ceil_div(widest, R)), widest);
+    if (G * S > (1 << 24)) return;  // (one launch takes fewer than 2^32 threads)
+
+    // scratch rows: one for every piece, those of a row one after the other, in the windows whose own split rows are all here
+    std::vector<uint8_t> grouped((size_t)m, 0);
+    for (int64_t i : kept) grouped[longest[i]] = 1;
+    std::vector<std::pair<int64_t, int64_t>> room;
+    for (int64_t w = 0; w < nw; ++w) {
+        if (in.ws_slot[w] < 0) continue;
+        const int64_t r0 = w * b_row, r1 = std::min<int64_t>(m, r0 + b_row);
+        bool is_free = rows.row_ptr[r1] > rows.row_ptr[r0];
+        for (int64_t r = r0; r < r1 && is_free; ++r) is_free = length(r) <= task_cols || grouped[r];
+        if (!is_free) continue;
+        const int64_t lo = (int64_t)in.ws_slot[w] * b_row, hi = lo + ceil_div(wrp[w + 1] - wrp[w], task_cols) * b_row;
+        if (!room.empty() && room.back().second == lo) room.back().second = hi;
+        else room.push_back({lo, hi});
+    }
+    struct Piece {
+        int32_t row, part, parts, size;  // row: its place in `longest`; entries c with c % parts == part of the row's range
+        int32_t slot;
+    };
+    std::vector<Piece> in_ranges[S];
+    size_t at = 0;
+    for (int64_t i : kept) {
+        int64_t need = 0;
+        for (int64_t j = 0; j < S; ++j) need += pieces(i, j);
+        while (at < room.size() && room[at].second - room[at].first < need) ++at;
+        if (at == room.size()) return;
+        out.split.insert(out.split.end(), {longest[i], (int32_t)room[at].first, (int32_t)need, 0});
+        for (int64_t j = 0; j < S; ++j) {
+            const int64_t c = in_range(i, j), np = pieces(i, j);
+            for (int64_t p = 0; p < np; ++p)
+                in_ranges[j].push_back({(int32_t)i, (int32_t)p, (int32_t)np, (int32_t)ceil_div(c - p, np), (int32_t)room[at].first++});
+        }
+        out.scratch_rows += need;
+    }
+
+    // range j of group g is task j G + g: pieces to tasks, the longest first to the task with the fewest entries so far
+    std::vector<std::vector<Piece>> task((size_t)(S * G));
+    std::vector<int64_t> n_entries((size_t)(S * G), 0);
+    parallel_chunks(S, 1, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t j = b; j < e; ++j) {
+            auto &all = in_ranges[j];
+            std::stable_sort(all.begin(), all.end(), [](const Piece &x, const Piece &y) { return x.size > y.size; });
+            std::vector<std::pair<int64_t, int64_t>> heap;  // (entries, group), least first
+            for (int64_t g = 0; g < G; ++g) heap.push_back({0, g});
+            const std::greater<std::pair<int64_t, int64_t>> more;
+            for (const Piece &p : all) {
+                std::pop_heap(heap.begin(), heap.end(), more);
+                auto &least = heap.back();
+                task[j * G + least.second].push_back(p);
+                n_entries[j * G + least.second] = least.first += p.size;
+                if ((int64_t)task[j * G + least.second].size() == R) heap.pop_back();
+                else std::push_heap(heap.begin(), heap.end(), more);
+            }
+        }
+    }, total);
+    if (*std::max_element(n_entries.begin(), n_entries.end()) * (4 * S * G) > 5 * total + 64 * S * G) {
+        out = HostGroups();
+        return;
+    }
+
     std::vector<int64_t> first((size_t)(S * G) + 1, 0);
     for (int64_t t = 0; t < S * G; ++t) first[t + 1] = first[t] + ceil_div(n_entries[t], 16) * 16;
-    if (first[S * G] / 16 > INT32_MAX) return;
+    if (first[S * G] / 16 > INT32_MAX) {
+        out = HostGroups();
+        return;
+    }
     out.entries.reset((size_t)first[S * G] * 8);
     uint64_t *const entries = (uint64_t *)out.entries.data();
     out.tasks.resize((size_t)(S * G) * 4);
-    out.slots.assign((size_t)(G * R), -1);
-    parallel_chunks(G, 1, [&](unsigned, int64_t b, int64_t e) {
-        for (int64_t g = b; g < e; ++g) {
-            for (size_t i = 0; i < group[g].size(); ++i) out.slots[g * R + i] = (int32_t)group[g][i].slot;
-            for (int64_t j = 0; j < S; ++j) {
-                uint64_t *const dst = entries + first[j * G + g], *const end = entries + first[j * G + g + 1], *to = dst;
-                for (size_t i = 0; i < group[g].size(); ++i) {
-                    const Part &p = group[g][i];
-                    const int64_t c0 = cuts[g][i * (S + 1) + j], c1 = cuts[g][i * (S + 1) + j + 1];
-                    for (int64_t c = c0 + ((p.part - c0) % p.parts + p.parts) % p.parts; c < c1; c += p.parts) {
-                        const int64_t q = (int64_t)row_ptr[p.row] + c;
-                        uint32_t v = esize == 2 ? (uint32_t)((const uint16_t *)values)[q] << 16 : ((const uint32_t *)values)[q];
-                        *to++ = ((uint64_t)((uint32_t)(col_idx[q] - start[j]) << 8 | (uint32_t)i) << 32) | v;
-                    }
+    out.slots.assign((size_t)(S * G * R), -1);
+    parallel_chunks(S * G, 8, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t t = b; t < e; ++t) {
+            const int64_t j = t / G;
+            uint64_t *const dst = entries + first[t], *const end = entries + first[t + 1], *to = dst;
+            for (size_t i = 0; i < task[t].size(); ++i) {
+                const Piece &p = task[t][i];
+                out.slots[t * R + i] = p.slot;
+                const int64_t row = row_ptr[longest[p.row]], c1 = cuts[p.row * (S + 1) + j + 1];
+                for (int64_t c = cuts[p.row * (S + 1) + j] + p.part; c < c1; c += p.parts) {
+                    const int64_t q = row + c;
+                    uint32_t v = esize == 2 ? (uint32_t)((const uint16_t *)values)[q] << 16 : ((const uint32_t *)values)[q];
+                    *to++ = ((uint64_t)((uint32_t)(col_idx[q] - start[j]) << 8 | (uint32_t)i) << 32) | v;
                 }
-                std::sort(dst, to);
-                const uint64_t fill = to > dst ? (to[-1] >> 40 << 40) | (uint64_t)R << 32 : 0;
-                for (; to < end; ++to) *to = fill;
-                for (to = dst; to < end; ++to) *to = *to >> 32 | *to << 32;  // the key is the first word
-                const int32_t t[4] = {(int32_t)(first[j * G + g] / 16), (int32_t)((end - dst) / 16), start[j], 0};
-                std::copy(t, t + 4, out.tasks.begin() + 4 * (j * G + g));
             }
+            std::sort(dst, to);
+            const uint64_t fill = to > dst ? (to[-1] >> 40 << 40) | (uint64_t)R << 32 : 0;
+            for (; to < end; ++to) *to = fill;
+            for (to = dst; to < end; ++to) *to = *to >> 32 | *to << 32;  // the key is the first word
+            const int32_t td[4] = {(int32_t)(first[t] / 16), (int32_t)((end - dst) / 16), start[j], 0};
+            std::copy(td, td + 4, out.tasks.begin() + 4 * t);
         }
-    }, G * 64);
+    });
 
     // the rest: chunks of other rows stay where they are dealt to, runs of whole rows without the grouped ones
     bool any = false;

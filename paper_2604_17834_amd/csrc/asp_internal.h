@@ -141,9 +141,9 @@ struct HostRows {
 // Long rows of scattered entries that walk the columns of B together (wcsr_build_groups, asp_wcsr_groups.hip), and the
 // lists of HostRows without them.
 struct HostGroups {
-    static constexpr int rows(size_t esize) { return esize == 2 ? 31 : 63; }  // of a group
+    static constexpr int rows(size_t esize) { return esize == 2 ? 31 : 63; }  // pieces of rows to a task
     static constexpr int64_t RANGES = 8; // of columns, one to an XCD
-    int64_t n_groups = 0;                // 0: the rest is not used
+    int64_t n_groups = 0;                // tasks of a range; 0: the rest is not used
     int64_t span = 0;                    // columns of the widest range
     int64_t scratch_rows = 0;
     ZeroedBytes entries;                 // 8 bytes each, see wcsr_groups_kernel, as are:

@@ -19,17 +19,19 @@
 // the third source, bit 3 the destination).  LDS would hold 160 KB of sums per compute unit and make an add a read, a wait
 // and a write where this is the multiply-add itself.
 //
-// The column ranges divide the entries evenly, 8 of them, one to an XCD; a task is a (range, group) and leaves a partial
-// sum per row of its group in scratch memory, which wcsr_rows_sum_kernel adds up in order.
+// The column ranges divide the entries evenly, 8 of them, one to an XCD.  The pieces that the rows leave in a range are dealt
+// to its tasks by themselves, so that these are even whatever columns the rows store: a 2^20-row Zipf graph whose rows keep to
+// one of 32 blocks of columns 1075 -> 856 us against one deal of whole rows for all ranges (by rows 893), its longest sum 1024
+// terms -> 160.  A task leaves a partial sum per piece in scratch memory, and wcsr_rows_sum_kernel adds those of a row in order.
 #include "asp_wcsr_rows.h"
 
 namespace asp {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// tasks[x * per_xcd + i] = {first entry / 16, entries / 16, first column of the range, -}: group i in the range of XCD x.  entries = {(column - first column) << 8 | row of the group, fp32 bits of the value}; what fills
-// up the last 16 belongs to the row behind the group's last, which nobody reads (no row of A that does not store a column may see its
-// values).  slots[group][ROWS]: scratch row of each row's first range, -1: none.
+// tasks[x * per_xcd + i] = {first entry / 16, entries / 16, first column of the range, -}: task i in the range of XCD x.  entries = {(column - first column) << 8 | piece of the task, fp32 bits of the value}; what fills
+// up the last 16 belongs to the piece behind the task's last, which nobody reads (no row of A that does not store a column may see its
+// values).  slots[task][ROWS]: scratch row of each piece, -1: none.
 template <typename T, int E>
 __global__ __launch_bounds__(256, 2) void wcsr_groups_kernel(const int4 *__restrict__ tasks, int per_xcd,
                                                           const u32x2 *__restrict__ entries, const int32_t *__restrict__ slots,
@@ -127,12 +129,12 @@ __global__ __launch_bounds__(256, 2) void wcsr_groups_kernel(const int4 *__restr
     }
 #undef ASP_GATHER
 #undef ASP_GATHER8
-    const int32_t *slot = slots + (int64_t)i * ROWS;
+    const int32_t *slot = slots + (int64_t)(xcd * per_xcd + i) * ROWS;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const int s = slot[r];
         if (s >= 0 && n < N) {
-            float *dst = ws + (int64_t)(s + xcd) * N + nc;
+            float *dst = ws + (int64_t)s * N + nc;
             dst[0] = r < 32 ? s0[r & 31] : s1[r & 31];
             if constexpr (E == 2) dst[1] = s1[r];
         }

@@ -149,3 +149,20 @@ def test_long_rows_in_groups(dtype, N):
     row = np.repeat(np.arange(a.m), np.diff(a.row_ptr))
     touched = np.bincount(row[np.isin(a.col_idx, bad)], minlength=a.m) > 0
     assert touched.sum() > 20 and not np.isfinite(C[touched]).any() and np.isfinite(C[~touched]).all()
+
+
+@pytest.mark.parametrize("dtype,b_row,N", [("f32", 16, 64), ("f32", 32, 100), ("f32", 64, 129), ("bf16", 32, 100), ("bf16", 64, 129)])
+def test_long_rows_of_communities_in_groups(dtype, b_row, N):
+    # every row's columns in one of 20 blocks: it leaves pieces in one or two of the eight ranges of columns only
+    rng = np.random.default_rng(N)
+    lengths = np.concatenate([rng.integers(64, 1500, 300), rng.integers(0, 70, 3001)])
+    rng.shuffle(lengths)
+    home = rng.integers(0, 20, len(lengths)) * 6000
+    cols = [h + np.sort(rng.choice(6000, n, replace=False)) for h, n in zip(home, lengths)]
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    v = rng.uniform(-1, 1, rp[-1]).astype(np.float32)
+    a = synth.Csr(len(lengths), 120000, rp, np.concatenate(cols).astype(np.int32), synth.f32_to_bf16_bits(v) if dtype == "bf16" else v, dtype)
+    B = synth.dense_normal(a.k, N, dtype, seed=8)
+    C = gpu_spmm(a, "wcsr", b_row, 8, B, task_cols=64)
+    check_against_oracle(a, B, C)
+    assert not C[np.diff(a.row_ptr) == 0].any()

@@ -52,7 +52,7 @@ def test_scratch_rows_that_pass_int32_stay_with_the_tiles(lists_of):
     (400, 100000, 512, [40000] + [2000] * 99),                                 # rows dealt to several groups
 ])
 def test_rows_in_groups_are_the_rows(lists_of, esize, m, k, task_cols, lengths):
-    got = lists_of("groups", m, k, task_cols, esize, *lengths)
+    got = lists_of("groups", m, k, 0, task_cols, esize, *lengths)
     assert got["groups"][0][0] >= 256 and got["largest"][0][0] > 0
     assert got["scratch"][0][1] <= got["scratch"][0][0]
     tiles = got.get("tile", [])
@@ -67,4 +67,21 @@ def test_rows_in_groups_are_the_rows(lists_of, esize, m, k, task_cols, lengths):
     (4000, 3000, [63, 20]),               # no row long enough
 ])
 def test_no_groups_where_they_do_not_pay(lists_of, m, k, lengths):
-    assert lists_of("groups", m, k, 512, 4, *lengths)["groups"] == [[0]]
+    assert lists_of("groups", m, k, 0, 512, 4, *lengths)["groups"] == [[0]]
+
+
+@pytest.mark.parametrize("esize", [4, 2])
+@pytest.mark.parametrize("m,k,width,task_cols,lengths", [
+    (20000, 100000, 0, 512, [70, 64, 300, 6, 5, 900, 7, 3]),                    # all columns
+    (20000, 100000, 5000, 512, [70, 64, 300, 6, 5, 900, 7, 3]),                 # communities smaller than a range of columns
+    (20000, 100000, 20000, 512, [70, 64, 300, 6, 5, 900, 7, 3]),                # larger than one
+    (20000, 100000, 5000, 64, [70, 64, 300, 6, 5, 900, 7, 3]),                  # short tasks: sums no longer than those
+    (4000, 100000, 100000, 512, [20000, 70, 70, 70, 70, 70, 70, 70]),
+])
+def test_sums_are_short_and_tasks_even_whatever_the_columns(lists_of, esize, m, k, width, task_cols, lengths):
+    got = lists_of("groups", m, k, width, task_cols, esize, *lengths)
+    (largest, entries), (groups,) = got["largest"][0], got["groups"][0]
+    assert groups >= 256 and got["terms"][0][0] <= min(160, task_cols)
+    assert largest * 8 * groups <= 1.25 * entries + 16 * 8 * groups
+    assert got["scratch"][0][1] <= got["scratch"][0][0]
+    assert all(diff == 0 and times == 1 for _, diff, times in got["row"])

@@ -7,9 +7,11 @@
 //                    and order taken, and for each what the heaviest workgroup walks and the starts of the XCDs' runs
 //   staged T C L..   the register-staged kernel's launch of T column tiles on C compute units: 1 (longest block-row first) or 0
 //                    (as stored), the starts of the XCDs' runs, the order longest first
-//   groups M K T E L..  M rows of K columns with L.. entries in turn, tasks of T columns, values of E bytes: the products of the
-//                    rows' values (1, 2, 3) with (column % 13 + 1), by the lists of groups, chunks and runs: "row r difference times"
-//                    ("tile r times" for rows that go tile by tile); and how many groups there are, their largest task, and the scratch rows there are and that they use
+//   groups M K W T E L..  M rows of K columns with L.. entries in turn (in W adjacent columns, other ones for every row; 0: in
+//                    all), tasks of T columns, values of E bytes: the products of the rows' values (1, 2, 3) with (column % 13 + 1),
+//                    by the lists of groups, chunks and runs: "row r difference times" ("tile r times" for rows that go tile by
+//                    tile); and how many groups there are, the entries of their largest task and of all, the most terms of a
+//                    sum in a task, and the scratch rows there are and that they use
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
@@ -133,11 +135,12 @@ static int staged(int n_tiles, int64_t n_cus, const std::vector<int32_t> &length
     return 0;
 }
 
-static int groups(int64_t m, int64_t k, int32_t task_cols, size_t esize, const std::vector<int32_t> &lengths) {
+static int groups(int64_t m, int64_t k, int64_t w, int32_t task_cols, size_t esize, const std::vector<int32_t> &lengths) {
     std::vector<int32_t> rp(1, 0), ci;
+    const int64_t cols = w > 0 ? w : k;
     for (int64_t r = 0; r < m; ++r) {
-        const int64_t n = lengths[r % lengths.size()];
-        for (int64_t j = 0; j < n; ++j) ci.push_back((int32_t)(j * k / n + (r * 7919 + j) % std::max<int64_t>(1, k / n)));
+        const int64_t n = lengths[r % lengths.size()], c0 = r * 7919 % (k / cols) * cols;
+        for (int64_t j = 0; j < n; ++j) ci.push_back((int32_t)(c0 + j * cols / n + (r * 7919 + j) % std::max<int64_t>(1, cols / n)));
         rp.push_back((int32_t)ci.size());
     }
     std::vector<uint8_t> values(ci.size() * esize);
@@ -148,18 +151,18 @@ static int groups(int64_t m, int64_t k, int32_t task_cols, size_t esize, const s
         if (esize == 4) std::memcpy(&values[e * 4], &bits, 4);
         else values[2 * e] = (uint8_t)(bits >> 16), values[2 * e + 1] = (uint8_t)(bits >> 24);
     }
-    asp::HostWcsr w;
-    if (!asp::csr_to_wcsr(m, k, rp.data(), ci.data(), values.data(), esize, 16, 8, w)) return 1;
+    asp::HostWcsr hw;
+    if (!asp::csr_to_wcsr(m, k, rp.data(), ci.data(), values.data(), esize, 16, 8, hw)) return 1;
     int64_t slots = 0;
-    for (size_t i = 0; i + 1 < w.window_row_ptr.size(); ++i) {
-        const int64_t n = w.window_row_ptr[i + 1] - w.window_row_ptr[i];
-        w.ws_slot.push_back(n > task_cols ? (int32_t)slots : -1);
+    for (size_t i = 0; i + 1 < hw.window_row_ptr.size(); ++i) {
+        const int64_t n = hw.window_row_ptr[i + 1] - hw.window_row_ptr[i];
+        hw.ws_slot.push_back(n > task_cols ? (int32_t)slots : -1);
         if (n > task_cols) slots += asp::ceil_div(n, task_cols);
     }
     asp::HostRows rows;
-    asp::wcsr_build_rows(m, rp.data(), ci.data(), esize, 16, task_cols, w, rows);
+    asp::wcsr_build_rows(m, rp.data(), ci.data(), esize, 16, task_cols, hw, rows);
     asp::HostGroups g;
-    asp::wcsr_build_groups(m, rp.data(), ci.data(), values.data(), esize, 16, task_cols, w, rows, g);
+    asp::wcsr_build_groups(m, rp.data(), ci.data(), values.data(), esize, 16, task_cols, hw, rows, g);
     auto b = [](int64_t col) { return (double)(col % 13 + 1); };
     std::vector<int64_t> at;  // where the entries walked row by row are
     for (auto &r : rows.runs)
@@ -172,24 +175,25 @@ static int groups(int64_t m, int64_t k, int32_t task_cols, size_t esize, const s
     std::vector<double> ws(slots * 16, 0), c(m, 0);
     std::vector<int> ws_times(slots * 16, 0), times(m, 0);
     const int64_t R = asp::HostGroups::rows(esize), S = asp::HostGroups::RANGES;
-    int64_t largest = 0, used = 0;
+    int64_t largest = 0, all = 0, terms = 0, used = 0;
     const uint64_t *entries = (const uint64_t *)g.entries.data();
     if (g.n_groups == 0) return std::printf("groups 0\n"), 0;
     for (int64_t t = 0; t < S * g.n_groups; ++t) {
         const int32_t *td = &g.tasks[4 * t];
         double sum[64] = {0};
-        largest = std::max<int64_t>(largest, 16 * (int64_t)td[1]);
+        int64_t n[64] = {0}, in_task = 0;
         if (td[0] < 0 || 128 * ((int64_t)td[0] + td[1]) > (int64_t)g.entries.size()) return std::printf("task %lld\n", (long long)t), 1;
         for (int64_t e = 16 * (int64_t)td[0]; e < 16 * ((int64_t)td[0] + td[1]); ++e) {
             const uint32_t key = (uint32_t)entries[e], bits = (uint32_t)(entries[e] >> 32);
             float v;
             std::memcpy(&v, &bits, 4);
             if (td[2] + (int64_t)(key >> 8) >= k || (key & 255) > R) return std::printf("entry %lld of task %lld\n", (long long)e, (long long)t), 1;
-            if ((int64_t)(key & 255) < R) sum[key & 255] += v * b(td[2] + (key >> 8));
+            if ((int64_t)(key & 255) < R) sum[key & 255] += v * b(td[2] + (key >> 8)), terms = std::max(terms, ++n[key & 255]), ++in_task;
         }
+        largest = std::max(largest, in_task), all += in_task;
         for (int64_t r = 0; r < R; ++r) {
-            const int32_t slot = g.slots[(t % g.n_groups) * R + r];
-            if (slot >= 0) ws.at(slot + t / g.n_groups) = sum[r], ++ws_times[slot + t / g.n_groups], ++used;
+            const int32_t slot = g.slots[t * R + r];
+            if (slot >= 0) ws.at(slot) = sum[r], ++ws_times[slot], ++used;
         }
     }
     for (size_t i = 0; i < g.chunks.size(); i += 4)
@@ -204,7 +208,8 @@ static int groups(int64_t m, int64_t k, int32_t task_cols, size_t esize, const s
         }
         ++times[g.split[i]];
     }
-    std::printf("groups %lld\nlargest %lld\nscratch %lld %lld\n", (long long)g.n_groups, (long long)largest, (long long)slots * 16, (long long)used);
+    std::printf("groups %lld\nlargest %lld %lld\nterms %lld\nscratch %lld %lld\n", (long long)g.n_groups, (long long)largest, (long long)all, (long long)terms,
+                (long long)slots * 16, (long long)used);
     for (int64_t r = 0; r < m; ++r) {
         double want = 0;
         for (int64_t e = rp[r]; e < rp[r + 1]; ++e) want += (1 + e % 3) * b(ci[e]);
@@ -227,7 +232,8 @@ int main(int argc, char **argv) {
     };
     if (is("order", 2)) return order(lengths(2));
     if (is("shares", 2)) return shares(lengths(2));
-    if (is("groups", 6)) return groups(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoll(argv[5]), lengths(6));
+    if (is("groups", 7))
+        return groups(std::atoll(argv[2]), std::atoll(argv[3]), std::atoll(argv[4]), std::atoi(argv[5]), std::atoll(argv[6]), lengths(7));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
     if (is("ring", 8))
         return ring(std::atoi(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6]) != 0,
