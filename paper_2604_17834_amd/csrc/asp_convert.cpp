@@ -898,8 +898,8 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     while ((k_used >> shift) >= 65536) ++shift;
     std::vector<int64_t> count(65537, 0);
     int64_t counted = 0;
-    for (int32_t r : longest)  // (every eighth entry tells)
-        for (int64_t p = row_ptr[r]; p < row_ptr[r + 1]; p += 8, ++counted) ++count[col_idx[p] >> shift];
+    for (int32_t r : longest)  // (every eighth entry tells; from another one in every row, or the first columns would count for more)
+        for (int64_t p = (int64_t)row_ptr[r] + r % 8; p < row_ptr[r + 1]; p += 8, ++counted) ++count[col_idx[p] >> shift];
     std::vector<int32_t> start((size_t)S + 1, k_used);
     start[0] = 0;
     int64_t sum = 0, s = 1;

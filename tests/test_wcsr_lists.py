@@ -77,6 +77,7 @@ def test_no_groups_where_they_do_not_pay(lists_of, m, k, lengths):
     (20000, 100000, 20000, 512, [70, 64, 300, 6, 5, 900, 7, 3]),                # larger than one
     (20000, 100000, 5000, 64, [70, 64, 300, 6, 5, 900, 7, 3]),                  # short tasks: sums no longer than those
     (4000, 100000, 100000, 512, [20000, 70, 70, 70, 70, 70, 70, 70]),
+    (80000, 20000, 0, 512, [70, 66, 64]),                                       # eight or nine entries of every row in a range
 ])
 def test_sums_are_short_and_tasks_even_whatever_the_columns(lists_of, esize, m, k, width, task_cols, lengths):
     got = lists_of("groups", m, k, width, task_cols, esize, *lengths)
