@@ -289,7 +289,13 @@ __global__ __launch_bounds__(256, MT == 4 ? 2 : 3) void bcsr_xt_staged_kernel(co
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last products, before anything reads them
+    // The last products, before anything reads them: what does depends on this statement (the compiler does not see that the
+    // accumulators were written by MFMAs, and would not wait by itself)
+    if constexpr (MT == 2)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[1][0]), "+a"(acc[1][1]));
+    else
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[1][0]), "+a"(acc[1][1]),
+                                              "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[3][0]), "+a"(acc[3][1]));
 
     // Half of the row tiles at a time: every wave leaves its products, [(g 2 + j) 4 + e] the registers 4 e .. of row tile g and
     // tokens j, adds a quarter of all in wave order and rounds.  D of the MFMA: lane l holds token l % 32, rows

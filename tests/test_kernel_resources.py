@@ -27,17 +27,22 @@ HOT = {
 }
 
 
-@pytest.mark.parametrize("source", sorted(HOT))
-def test_hot_kernels_use_no_scratch(source):
-    if not os.path.exists(HIPCC):
-        pytest.skip("hipcc not found")
+def _compiled(source, *options):
+    """What the compiler makes of a source's device code, as text."""
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "k.s")
         subprocess.check_call([HIPCC, "-O3", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                                "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                               "-S", "--cuda-device-only", "-o", out, os.path.join(CSRC, source)],
+                               "-S", "--cuda-device-only", *options, "-o", out, os.path.join(CSRC, source)],
                               stderr=subprocess.DEVNULL)
-        text = open(out).read()
+        return open(out).read()
+
+
+@pytest.mark.parametrize("source", sorted(HOT))
+def test_hot_kernels_use_no_scratch(source):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    text = _compiled(source)
     seen = 0
     for m in re.finditer(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", text):
         name, scratch = m.group(1), int(m.group(2))
@@ -45,3 +50,35 @@ def test_hot_kernels_use_no_scratch(source):
             seen += 1
             assert scratch == 0, "%s uses %d bytes of scratch per lane" % (name, scratch)
     assert seen >= len(HOT[source])
+
+
+def _registers(kind, operands):
+    found = set()
+    for first, last in re.findall(r"\b%s\[?(\d+)(?::(\d+))?" % kind, operands):
+        found |= set(range(int(first), int(last or first) + 1))
+    return found
+
+
+def test_staged_strips_wait_for_their_last_products():
+    """bcsr_xt_staged_kernel multiplies in inline assembly, which the compiler's waits do not cover: its own wait has to hold all
+    accumulators, so that nothing reads them before it, and no VALU result may be an operand in the next two instructions."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    ir = _compiled("asp_bcsr_xt.hip", "-emit-llvm")
+    waits = re.findall(r'asm sideeffect "s_nop 15[^"]*", "([^"]*)"', ir)
+    assert sorted(w.count("=a") for w in waits) == [4, 4, 8]     # 64-row strips of both block sizes, 128-row strips
+    kernels = [k for k in re.split(r"(?m)^(?=_ZN\S+:)", _compiled("asp_bcsr_xt.hip")) if k.startswith("_ZN3asp21bcsr_xt_staged_kernel")]
+    assert len(kernels) == 3
+    for k in kernels:
+        code = [l.split(";")[0].split() for l in k[:k.index("s_endpgm")].splitlines()]
+        code = [l for l in code if l and re.match(r"[a-z]+_", l[0])]
+        last = max(i for i, l in enumerate(code) if l[0].startswith("v_mfma"))
+        wait = next(i for i in range(last, len(code)) if code[i] == ["s_nop", "15"])
+        sums = set().union(*(_registers("a", l[1]) for l in code if l[0].startswith("v_mfma")))
+        assert len(sums) in (64, 128) and not any(sums & _registers("a", " ".join(l[1:])) for l in code[last + 1:wait])
+        for i, l in enumerate(code):
+            if l[0].startswith("v_mfma") and code[i - 1][0] != "s_nop":
+                read = _registers("v", " ".join(l[1:]))
+                for w in code[i - 2:i]:
+                    if w[0].startswith("v_") and not w[0].startswith("v_mfma"):
+                        assert not read & _registers("v", w[1]), (w, l)
