@@ -145,10 +145,17 @@ __global__ __launch_bounds__(256, 2) void wcsr_groups_kernel(const int4 *__restr
 // Narrow operands stay with the walk by rows, whose waves take several entries at once there: 831 834 rows, bf16, N = 19
 // 192 us by rows and 274 in groups, 417 427 rows, N = 64 114 / 121 (but N = 72, 139 866 rows 82 / 72); 225 543 rows, fp32, N = 23
 // 84 / 87, N = 34, 129 753 rows 64 / 55.  So does a B that an XCD's 4 MB of L2 hold.  (A range of B is addressed with 32 bits.)
+// And so do large graphs in whose rows, as they follow each other, the same columns come again soon (near_cols,
+// wcsr_build_groups), where these take few bytes of B: by rows most of them are found in L2 too, and the sums in pieces are extra
+// work.  1.5 million rows, fp32, N = 128, columns within 1000 of the diagonal (7 MB) 999 by rows and 1118 in groups, within 10 000
+// and 0.8 million rows (19 MB) 878 / 808; bf16, N = 128, communities of 16384 (6 MB) 548 / 608, of 65536 (16 MB) 356 / 346.
+// fp32 in whole tiles of 64 columns gains earlier: 15 MB there, 20 MB else.  Of 348 graphs, most with communities or bands, 30 000
+// to 2 000 000 rows, those in groups by this rule take at most 1.06 times as long as by rows (without it 1.27), 0.69 at best.
 bool wcsr_groups_apply(const asp_handle *h, int64_t N) {
     const int64_t row_bytes = N * (int64_t)dtype_size(h->dtype);
+    const int64_t least = h->dtype == ASP_DT_F32 && N % 64 == 0 ? 15000000 : 20000000;
     return h->n_groups > 0 && N > (h->dtype == ASP_DT_BF16 ? 64 : 32) && h->group_span * row_bytes < (1ll << 32) &&
-           h->k * row_bytes >= (4 << 20);
+           h->k * row_bytes >= (4 << 20) && (h->group_near_cols == 0 || h->group_near_cols * row_bytes >= least);
 }
 
 void wcsr_groups_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream) {

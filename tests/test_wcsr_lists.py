@@ -86,3 +86,15 @@ def test_sums_are_short_and_tasks_even_whatever_the_columns(lists_of, esize, m, 
     assert largest * 8 * groups <= 1.25 * entries + 16 * 8 * groups
     assert got["scratch"][0][1] <= got["scratch"][0][0]
     assert all(diff == 0 and times == 1 for _, diff, times in got["row"])
+
+
+@pytest.mark.parametrize("m,k,width,near", [
+    (40000, 20000, 0, True),         # 131 072 consecutive ones of 5.1 million entries meet in 20 000 columns
+    (40000, 1000000, 0, False),
+    (40000, 1000000, 5000, False),   # communities, but neighbours are in different ones
+    (35000, 20000, 0, False),        # not as many entries
+])
+def test_columns_that_near_rows_meet_in(lists_of, m, k, width, near):
+    got = lists_of("groups", m, k, width, 512, 4, 300, 64, 20)
+    assert got["groups"][0][0] >= 256
+    assert 10000 < got["near"][0][0] <= k if near else got["near"] == [[0]]
