@@ -260,6 +260,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         h->group_span = groups.span;
         h->group_scratch_rows = groups.scratch_rows;
         h->group_near_cols = groups.near_cols;
+        h->group_many = groups.n_many;
         h->n_g_row_tasks = (int64_t)groups.row_tasks.size() / 4;
         h->n_g_chunks = (int64_t)groups.chunks.size() / 4;
         h->n_g_split_rows = (int64_t)groups.split.size() / 4;

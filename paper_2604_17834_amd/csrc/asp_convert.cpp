@@ -1055,6 +1055,15 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
             out.split.insert(out.split.end(), rows.split.begin() + i, rows.split.begin() + i + 4);
             left -= length(rows.split[i]);
         }
+    // rows of many pieces first, which are added by more threads (wcsr_rows_sum_launch)
+    std::vector<int32_t> by_count[2];
+    for (size_t i = 0; i < out.split.size(); i += 4) {
+        auto &to = by_count[out.split[i + 2] > HostGroups::MANY_PIECES ? 0 : 1];
+        to.insert(to.end(), out.split.begin() + i, out.split.begin() + i + 4);
+    }
+    out.n_many = (int64_t)by_count[0].size() / 4;
+    out.split = std::move(by_count[0]);
+    out.split.insert(out.split.end(), by_count[1].begin(), by_count[1].end());
     // How many columns the long rows store where the walk by rows is at one time: the different ones in the rows of 2^17
     // consecutive entries, the mean of 16 places, where a quarter of those entries or more store a column again.  Asked where there
     // are many entries: with fewer, chunks of 512 are the last that the walk by rows ends with, and groups are the better ones on

@@ -146,6 +146,8 @@ struct HostGroups {
     int64_t n_groups = 0;                // tasks of a range; 0: the rest is not used
     int64_t span = 0;                    // columns of the widest range
     int64_t scratch_rows = 0;
+    static constexpr int32_t MANY_PIECES = 512;
+    int64_t n_many = 0;                  // rows with more scratch rows than that: the first ones of `split`
     int64_t near_cols = 0;               // many entries whose rows meet in few columns at a time: that many, 0: they do not
     ZeroedBytes entries;                 // 8 bytes each, see wcsr_groups_kernel, as are:
     std::vector<int32_t> tasks, slots;
@@ -225,7 +227,7 @@ struct asp_handle {
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;
     // WCSR: long rows in groups, and the lists of what is left beside them, for calls with scratch (HostGroups)
-    int64_t n_groups = 0, group_span = 0, group_scratch_rows = 0, group_near_cols = 0;
+    int64_t n_groups = 0, group_span = 0, group_scratch_rows = 0, group_near_cols = 0, group_many = 0;
     int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0;
     uint64_t *d_group_entries = nullptr;
     int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;

@@ -379,17 +379,22 @@ void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *
     const int32_t *d_split = groups ? h->d_g_split_rows : h->d_split_rows;
     const int64_t n_split = groups ? h->n_g_split_rows : h->n_split_rows;
     if (n_split == 0) return;
+    // Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
+    // 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
+    // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  Lists of up to 512 take as long either way.
     const bool many = (groups ? h->group_scratch_rows + h->n_g_chunks : h->n_chunks) > 32 * n_split;
-#define ASP_ROWS_SUM(T, COLS, J)                                                                                          \
-    hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>),                                                                \
-                       dim3((unsigned)std::min<int64_t>(n_split, 1 << 21), (unsigned)ceil_div(N, COLS)),          \
-                       dim3((COLS) * (J)), 0, stream, (const int4 *)d_split, (int)n_split, ws, (T *)C, N)
+    const int64_t n_many = N > 65535 * 16 ? 0 : many ? n_split : groups ? h->group_many : 0;
+#define ASP_ROWS_SUM(T, COLS, J, FIRST, COUNT)                                                                            \
+    if ((COUNT) > 0)                                                                                                      \
+        hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>),                                                            \
+                           dim3((unsigned)std::min<int64_t>(COUNT, 1 << 21), (unsigned)ceil_div(N, COLS)),                \
+                           dim3((COLS) * (J)), 0, stream, (const int4 *)d_split + (FIRST), (int)(COUNT), ws, (T *)C, N)
     if (h->dtype == ASP_DT_BF16) {
-        if (many && N <= 65535 * 16) ASP_ROWS_SUM(uint16_t, 16, 64);
-        else ASP_ROWS_SUM(uint16_t, 64, 4);
+        ASP_ROWS_SUM(uint16_t, 16, 64, 0, n_many);
+        ASP_ROWS_SUM(uint16_t, 64, 4, n_many, n_split - n_many);
     } else {
-        if (many && N <= 65535 * 16) ASP_ROWS_SUM(float, 16, 64);
-        else ASP_ROWS_SUM(float, 64, 4);
+        ASP_ROWS_SUM(float, 16, 64, 0, n_many);
+        ASP_ROWS_SUM(float, 64, 4, n_many, n_split - n_many);
     }
 #undef ASP_ROWS_SUM
 }

@@ -166,3 +166,12 @@ def test_long_rows_of_communities_in_groups(dtype, b_row, N):
     C = gpu_spmm(a, "wcsr", b_row, 8, B, task_cols=64)
     check_against_oracle(a, B, C)
     assert not C[np.diff(a.row_ptr) == 0].any()
+
+
+@pytest.mark.parametrize("dtype,N", [("f32", 40), ("f32", 65), ("bf16", 100)])
+def test_a_row_of_many_pieces_among_short_ones(dtype, N):
+    lengths = np.full(1500, 200)
+    lengths[[77, 901]] = 79000, 30000
+    a = _rows_of_lengths(list(lengths), 80000, dtype, seed=N)
+    B = synth.dense_normal(a.k, N, dtype, seed=9)
+    check_against_oracle(a, B, gpu_spmm(a, "wcsr", 16, 8, B, task_cols=64))

@@ -98,3 +98,16 @@ def test_columns_that_near_rows_meet_in(lists_of, m, k, width, near):
     got = lists_of("groups", m, k, width, 512, 4, 300, 64, 20)
     assert got["groups"][0][0] >= 256
     assert 10000 < got["near"][0][0] <= k if near else got["near"] == [[0]]
+
+
+@pytest.mark.parametrize("task_cols,hubs,many", [
+    (512, [90000, 20000, 400], 1),   # a row of more than 512 pieces among short ones
+    (512, [8000, 7000, 400], 0),
+    (64, [60000, 20000, 40000], 2),
+])
+def test_rows_of_many_pieces_come_first(lists_of, task_cols, hubs, many):
+    lengths = [n for hub in hubs for n in [hub] + [300] * 999]
+    got = lists_of("groups", 3000, 100000, 0, task_cols, 4, *lengths)
+    n, fewest, most = got["many"][0]
+    assert got["groups"][0][0] >= 256 and n == many and fewest > 512 >= most
+    assert all(diff == 0 and times == 1 for _, diff, times in got["row"])

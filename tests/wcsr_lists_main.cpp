@@ -11,7 +11,8 @@
 //                    all), tasks of T columns, values of E bytes: the products of the rows' values (1, 2, 3) with (column % 13 + 1),
 //                    by the lists of groups, chunks and runs: "row r difference times" ("tile r times" for rows that go tile by
 //                    tile); and how many groups there are, the entries of their largest task and of all, the most terms of a
-//                    sum in a task, the scratch rows there are and that they use, and the columns that near rows meet in
+//                    sum in a task, the scratch rows there are and that they use, the columns that near rows meet in, and how many
+//                    rows have their scratch rows added by many threads, the fewest of one and the most of another
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
@@ -208,8 +209,12 @@ static int groups(int64_t m, int64_t k, int64_t w, int32_t task_cols, size_t esi
         }
         ++times[g.split[i]];
     }
-    std::printf("groups %lld\nlargest %lld %lld\nterms %lld\nscratch %lld %lld\nnear %lld\n", (long long)g.n_groups, (long long)largest, (long long)all, (long long)terms,
-                (long long)slots * 16, (long long)used, (long long)g.near_cols);
+    int64_t fewest = INT32_MAX, most = 0;
+    for (size_t i = 0; i < g.split.size(); i += 4)
+        if ((int64_t)i < 4 * g.n_many) fewest = std::min<int64_t>(fewest, g.split[i + 2]);
+        else most = std::max<int64_t>(most, g.split[i + 2]);
+    std::printf("groups %lld\nlargest %lld %lld\nterms %lld\nscratch %lld %lld\nnear %lld\nmany %lld %lld %lld\n", (long long)g.n_groups, (long long)largest, (long long)all, (long long)terms,
+                (long long)slots * 16, (long long)used, (long long)g.near_cols, (long long)g.n_many, (long long)fewest, (long long)most);
     for (int64_t r = 0; r < m; ++r) {
         double want = 0;
         for (int64_t e = rp[r]; e < rp[r + 1]; ++e) want += (1 + e % 3) * b(ci[e]);
