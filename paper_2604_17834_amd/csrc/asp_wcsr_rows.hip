@@ -322,8 +322,7 @@ __global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__re
                 float t[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) t[e] = src[(int64_t)(j + J * e) * N];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sum += t[e];
+                sum += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
             }
             for (; j < s.z; j += J) sum += src[(int64_t)j * N];
         }
@@ -331,9 +330,9 @@ __global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__re
         part[first][c] = sum;
         __syncthreads();
         if (first == 0 && n < N) {
-            float t = part[0][c];
+            float t = 0.f;
 #pragma unroll
-            for (int e = 1; e < J; ++e) t += part[e][c];
+            for (int e = 0; e < J; e += 4) t += (part[e][c] + part[e + 1][c]) + (part[e + 2][c] + part[e + 3][c]);
             T o;
             narrow(t, o);
             C[(int64_t)s.x * N + n] = o;
@@ -381,7 +380,7 @@ void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *
     if (n_split == 0) return;
     // Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
     // 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
-    // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  Lists of up to 512 take as long either way.
+    // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  From lists of 128 on, the graph without that row 950 -> 959: another launch.
     const bool many = (groups ? h->group_scratch_rows + h->n_g_chunks : h->n_chunks) > 32 * n_split;
     const int64_t n_many = N > 65535 * 16 ? 0 : many ? n_split : groups ? h->group_many : 0;
 #define ASP_ROWS_SUM(T, COLS, J, FIRST, COUNT)                                                                            \
