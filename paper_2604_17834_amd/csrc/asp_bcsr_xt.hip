@@ -367,17 +367,28 @@ static bool launch_staged(const asp_handle *h, const void *X, void *Y, int64_t N
     return true;
 }
 
-// Whether 16-byte aligned operands go through the staged strips, and how high these are: 0, or 2 or 4 row tiles.  From three
-// 64-row strips to four compute units on; below, 32-token strips with eight waves are the better ones (3584 x 18944, 90 %, 128-row
-// blocks, 64 / 128 / 256 tokens 9.5 / 11.8 / 18.7 us, staged 11.4 / 11.6 / 12.9; 1664 x 3904, 80 %, 287 tokens 9.4 / 10.6).  With less than three
-// units of 64 k a block-row the ends of the strips are all there is (2944 x 1280, 90 %, 64-row blocks, 4185 tokens 18.8 / 21.5).
+// Whether 16-byte aligned operands go through the staged strips, and how high these are: 0, or 2 or 4 row tiles.  Their start and
+// end take 0.6 us more than those of the other strips, which wins from 7 pieces of 64 outputs x 64 k x 64 tokens to a compute unit on
+// (counted in 32 tokens, what the other strips pad to): of 466 products of 64- and 128-row blocks at 80 to 95 %, 33 to 6000 tokens,
+// timed in a captured graph, the 105 with less took 1.04 times as long in the mean, up to 1.21 (6656 x 2816, 71 tokens 5.4 / 6.5 us),
+// the others 0.85.  Not below three 64-row strips to four compute units, where eight waves to a strip are the better ones
+// (3584 x 18944, 90 %, 128-row blocks, 64 / 128 / 256 tokens 9.5 / 11.8 / 18.7 us, staged 11.4 / 11.6 / 12.9; 1664 x 3904, 80 %, 287
+// tokens 9.4 / 10.6), and with less than three units of 64 k a block-row, where the ends of the strips are all there is (2944 x 1280,
+// 90 %, 64-row blocks, 4185 tokens 18.8 / 21.5).  Nor where block-rows are about as long as each other and some compute units would
+// take a second strip while the 32-token strips are no more than two to each: the launch is as long as those few (3520 x 6208,
+// 80 %, 263 tokens, 280 strips 13.7 / 15.0 us, 90 % 9.5 / 10.3; 6336 x 10560, 143 tokens, 297 strips 17.9 / 18.6).  Of 600 products
+// drawn after these lines were, 350 take these strips: 0.84 of the others' time in the mean, 1.10 at worst (4288 x 7424, 90 %,
+// geometric rows, 150 tokens 9.0 / 9.9).
 // Three 64-row strips fit a compute unit, two of 128 rows, which read X once instead of twice: better where rows are long
-// enough (6 blocks) to be bound by that and there are more 64-row strips than places (256 / 768 / 1024 / 2048 tokens of the
-// former, 64 and 128 rows 12.9 / 17.0, 28.9 / 30.8, 35.4 / 30.9, 67 / 55 us; 18944 x 3584, three blocks a row, 512 / 1024 tokens
+// enough (6 blocks) to be bound by that and there are more 64-row strips than places (3584 x 18944, 256 / 768 / 1024 / 2048 tokens,
+// 64 and 128 rows 12.9 / 17.0, 28.9 / 30.8, 35.4 / 30.9, 67 / 55 us; 18944 x 3584, three blocks a row, 512 / 1024 tokens
 // 22.3 / 22.8, 39.2 / 39.8).
-static int staged_strips(const asp_handle *h, int64_t N) {
-    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, strips = h->n_brows * (h->b_row / 64) * ceil_div(N, 64);
+int bcsr_xt_staged_strips(const asp_handle *h, int64_t N) {
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, rows = h->n_brows * (h->b_row / 64);
+    const int64_t strips = rows * ceil_div(N, 64), strips_32 = rows * ceil_div(N, 32);
     if (h->b_row < 64 || N <= 32 || 4 * strips < 3 * cus || h->n_units * (h->b_row / 64) < 3 * h->n_brows) return 0;
+    if (h->n_units * (h->b_row / 64) * (h->b_row / 64) * ceil_div(N, 32) < 14 * cus) return 0;
+    if (strips > cus && strips_32 <= 2 * cus && h->hb.max_blocks * h->n_brows <= 3 * h->n_units) return 0;
     return h->b_row == 128 && strips > 3 * cus && h->n_units >= 6 * h->n_brows ? 4 : 2;
 }
 
@@ -390,15 +401,15 @@ template <int BR>
 static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64);
     if constexpr (BR == 128) {
-        if (vec && staged_strips(h, N) != 0 &&
-            (staged_strips(h, N) == 4 ? launch_staged<BR, 4>(h, X, Y, N, stream) : launch_staged<BR, 2>(h, X, Y, N, stream)))
+        const int staged = vec ? bcsr_xt_staged_strips(h, N) : 0;
+        if (staged != 0 && (staged == 4 ? launch_staged<BR, 4>(h, X, Y, N, stream) : launch_staged<BR, 2>(h, X, Y, N, stream)))
             return true;
         // (or too many rows for a launch of 64-row strips)
         if ((h->n_units >= 8 * h->n_brows && h->n_brows * n64 >= cus * 3 / 4) || h->n_brows >= (1 << 23))
             return launch_strip<BR, 4, 2, 4, 32>(h, X, Y, N, vec, stream);
     }
     if constexpr (BR == 64) {
-        if (vec && staged_strips(h, N) != 0 && launch_staged<BR, 2>(h, X, Y, N, stream)) return true;
+        if (vec && bcsr_xt_staged_strips(h, N) != 0 && launch_staged<BR, 2>(h, X, Y, N, stream)) return true;
     }
     if constexpr (BR >= 64) {
         const int64_t strips = h->n_brows * (BR / 64);
@@ -517,7 +528,7 @@ asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, in
             // The staged strips are up to 1.8 times faster than those that the estimate was fitted to.  Where the ring kernel
             // is said to be faster than those, it takes between the longer of its two terms and their sum, and stays where the
             // staged strips are not below the former (2688 x 4352, 80 %, geometric rows, 5994 tokens ring 54, staged 66 us).
-            const int staged = vec ? staged_strips(h, N) : 0;
+            const int staged = vec ? bcsr_xt_staged_strips(h, N) : 0;
             const double per_strip = h->b_row == 64 ? 5.2e-9 : staged == 4 ? 4.0e-9 : 4.4e-9;
             if (staged && 4.0 + 4e-10 * (double)h->m * (double)N * 256 / cus + per_strip * work < ring_at_least) bn = 0;
             BcsrPlan p = {bn, bn ? (int32_t)ceil_div(N, bn) : 0, 1, 0};

@@ -248,6 +248,8 @@ BcsrPlan bcsr_plan(const asp_handle *h, int64_t N, bool aligned);
 inline bool bcsr_wide_capable(const asp_handle *h) { return h->has_comp || (h->b_row == 128 && h->k % 128 == 0); }
 bool bcsr_dma_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 bool bcsr_dma_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, const BcsrPlan &p, hipStream_t stream);
+// the staged strips of asp_spmm_xt: 0, or their row tiles of 32 (asp_bcsr_xt.hip)
+int bcsr_xt_staged_strips(const asp_handle *h, int64_t N);
 void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);

@@ -161,3 +161,14 @@ def test_register_staged_runs_weigh_the_same(lists_of, n_tiles, lengths):  # noq
     eighth = -(-rows * n_tiles // 8)
     even = [int(c.sum()) for c in np.split(np.tile(lengths + tile, n_tiles), range(eighth, rows * n_tiles, eighth))]
     assert max(runs) <= (weight.sum() / 8 + max(lengths) + tile if by_length else max(even))
+
+
+@pytest.mark.parametrize("block,brows,units,longest,tokens,row_tiles", [
+    (128, 28, 414, 22, 256, 2), (128, 28, 414, 22, 1024, 4),     # 3584 x 18944 at 90 %
+    (128, 28, 414, 22, 32, 0), (32, 500, 9000, 30, 500, 0),      # no more than 32 tokens; 32-row blocks
+    (128, 52, 104, 8, 71, 0), (128, 48, 72, 6, 80, 0),           # 6656 x 2816, 6144 x 1024: little work, most of it start and end
+    (64, 178, 552, 9, 82, 0), (64, 178, 552, 9, 300, 2),         # 11392 x 1920
+    (128, 28, 281, 14, 263, 0), (128, 28, 281, 40, 263, 2),      # 3520 x 6208: 280 strips of about a length; of very different ones
+])
+def test_products_that_take_staged_strips(lists_of, block, brows, units, longest, tokens, row_tiles):  # noqa: F811
+    assert lists_of("xt", block, brows, units, longest, tokens)["staged"] == [[row_tiles]]

@@ -63,6 +63,7 @@ def test_tokens_do_not_reach_each_other(b, k, N):
 @pytest.mark.parametrize("m,k,N,sparsity", [
     (12808, 1032, 33, 0.5), (12808, 1032, 64, 0.5), (8200, 1992, 65, 0.5),   # edges of a token tile; a last unit of 8 k
     (8200, 1992, 700, 0.5), (8200, 200, 500, 0.0), (8200, 384, 300, 0.0),    # 128-row strips; few units, the last of 8 k; whole ones
+    (12808, 2056, 33, 0.5), (12808, 2056, 64, 0.5), (8200, 1992, 129, 0.5),  # edges of a token tile again, with work for these strips
 ])
 def test_staged_strips(b, m, k, N, sparsity):
     a = synth.block_sparse_bernoulli(m, k, b, b, sparsity, seed=b + m + N, dtype="bf16")

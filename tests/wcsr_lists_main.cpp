@@ -13,6 +13,8 @@
 //                    tile); and how many groups there are, the entries of their largest task and of all, the most terms of a
 //                    sum in a task, the scratch rows there are and that they use, the columns that near rows meet in, and how many
 //                    rows have their scratch rows added by many threads, the fewest of one and the most of another
+//   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
+//                    tokens on 256 compute units take in asp_spmm_xt, 0: none
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
 #include <cstdio>
 #include <cstdlib>
@@ -227,7 +229,16 @@ static int groups(int64_t m, int64_t k, int64_t w, int32_t task_cols, size_t esi
     return 0;
 }
 
+static int xt(char **argv) {
+    asp_handle h;
+    h.b_row = std::atoi(argv[0]), h.n_brows = std::atoll(argv[1]), h.n_units = std::atoll(argv[2]), h.hb.max_blocks = std::atoll(argv[3]);
+    h.n_cus = 256;
+    std::printf("staged %d\n", asp::bcsr_xt_staged_strips(&h, std::atoll(argv[4])));
+    return 0;
+}
+
 int main(int argc, char **argv) {
+    if (argc == 7 && std::strcmp(argv[1], "xt") == 0) return xt(argv + 2);
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
     auto is = [&](const char *what, int first) { return argc > first && std::strcmp(argv[1], what) == 0; };
     auto lengths = [&](int first) {
