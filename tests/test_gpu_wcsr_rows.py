@@ -175,3 +175,46 @@ def test_a_row_of_many_pieces_among_short_ones(dtype, N):
     a = _rows_of_lengths(list(lengths), 80000, dtype, seed=N)
     B = synth.dense_normal(a.k, N, dtype, seed=9)
     check_against_oracle(a, B, gpu_spmm(a, "wcsr", 16, 8, B, task_cols=64))
+
+
+@pytest.mark.parametrize("dtype,b_row", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
+def test_groups_under_capture_and_with_static_scratch(dtype, b_row):
+    # a B beyond 4 MB and rows enough for groups: both entry points give the same bits, eagerly and replayed with eager work
+    # between the replays
+    rng = np.random.default_rng(b_row)
+    lengths = np.concatenate([rng.integers(64, 900, 600), rng.integers(0, 20, 2000)])
+    rng.shuffle(lengths)
+    a = _rows_of_lengths(list(lengths), 24000, dtype, seed=b_row)
+    N = 96
+    tdt = torch.int16 if dtype == "bf16" else torch.float32
+    Bs = [synth.dense_normal(a.k, N, dtype, seed=20 + r) for r in range(3)]
+    dev = [torch.from_numpy(B.view(np.int16) if dtype == "bf16" else B).cuda() for B in Bs]
+    Bd, Cd = dev[0].clone(), torch.empty((a.m, N), dtype=tdt, device="cuda")
+    h = asp.asp_create_from_csr("wcsr", dtype, b_row, 8, a.m, a.k, a.row_ptr, a.col_idx, a.values, task_cols=256)
+    try:
+        asp.asp_reserve(h, N)
+        calls = [lambda f=f: f(h, Bd.data_ptr(), Cd.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+                 for f in (asp.asp_spmm, asp.asp_spmm_static_scratch)]
+
+        def result(go):
+            Cd.fill_(0x7FC1 if dtype == "bf16" else float("nan"))
+            go()
+            torch.cuda.synchronize()
+            return Cd.cpu().numpy().view(np.uint16 if dtype == "bf16" else np.float32).copy()
+
+        graphs = []
+        for call in calls:
+            call()
+            torch.cuda.synchronize()
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[-1]):
+                call()
+        for r in (1, 2, 0):
+            Bd.copy_(dev[r])
+            want = result(calls[0])
+            check_against_oracle(a, Bs[r], want)
+            for go in (graphs[0].replay, calls[1], graphs[1].replay, graphs[0].replay):
+                assert np.array_equal(result(go).view(np.uint8), want.view(np.uint8))
+    finally:
+        torch.cuda.synchronize()
+        asp.asp_destroy(h)
