@@ -52,6 +52,15 @@ def test_hot_kernels_use_no_scratch(source):
     assert seen >= len(HOT[source])
 
 
+def test_groups_leave_room_for_three_workgroups():
+    """wcsr_groups_kernel: the waves of an XCD's column tile have to be resident at once, and half of a second tile's: three
+    workgroups of four waves to a compute unit, so at most 512 / 3 registers a lane."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    found = re.findall(r"\.name:\s+(\S*wcsr_groups_kernel\S*)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)", _compiled("asp_wcsr_groups.hip"))
+    assert len(found) == 2 and all(int(n) <= 168 for _, n in found), found
+
+
 def _registers(kind, operands):
     found = set()
     for first, last in re.findall(r"\b%s\[?(\d+)(?::(\d+))?" % kind, operands):
