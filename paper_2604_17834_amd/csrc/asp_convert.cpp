@@ -867,13 +867,16 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
 // Not done for a few nearly dense rows (the chunks of asp_wcsr_rows.hip find their rows of B in L2 already: 2 000 000
 // rows with 64 of 200 000 entries, N = 64 216 us in chunks and 219 here), where the rows share few columns (two entries a column
 // on average), for less than 64 entries a task (16 915 rows with 118 000 entries, N = 200 36 us by rows, 39 here), where scratch memory, whose
-// size is that of the tiles' partial sums, does not hold the sums of all pieces, where a range would pass 2^24 columns, and where
-// one range has a quarter more to walk than the mean.
+// size is that of the tiles' partial sums, does not hold the sums of all pieces, where a range would pass 2^24 columns, where one
+// range has a quarter more to walk than the mean, and where short tasks would make short pieces (524 288 rows of Zipf lengths, fp32, N
+// = 128, task_cols = 16 / 32 / 64 / 128: 692 / 568 / 538 / 555 us by rows, 732 / 608 / 488 / 460 here; 200 003 rows, bf16, 253 / 149 /
+// 112 / 108 and 219 / 154 / 116 / 110).
 void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
                        int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out) {
-    constexpr int64_t S = HostGroups::RANGES, MIN_PIECE = 8, GROUPS = 256, MIN_ROWS = 128, MIN_TASK = 64, MAX_TERMS = 128, NEAR_ENTRIES = 4500000;
+    constexpr int64_t S = HostGroups::RANGES, MIN_PIECE = 8, GROUPS = 256, MIN_ROWS = 128, MIN_TASK = 64, MAX_TERMS = 128, NEAR_ENTRIES = 4500000, MIN_TASK_COLS = 48;
     const int64_t R = HostGroups::rows(esize);
     out = HostGroups();
+    if (task_cols < MIN_TASK_COLS) return;
     const auto &wrp = in.window_row_ptr;
     const int64_t nw = (int64_t)wrp.size() - 1;
     auto walked = [&](int64_t r) { return rows.row_ptr[r + 1] > rows.row_ptr[r]; };

@@ -111,3 +111,9 @@ def test_rows_of_many_pieces_come_first(lists_of, task_cols, hubs, many):
     n, fewest, most = got["many"][0]
     assert got["groups"][0][0] >= 256 and n == many and fewest > 512 >= most
     assert all(diff == 0 and times == 1 for _, diff, times in got["row"])
+
+
+def test_no_groups_of_short_pieces(lists_of):
+    for task_cols, groups in ((32, False), (40, False), (48, True)):
+        got = lists_of("groups", 9000, 40000, 0, task_cols, 4, 900, 64, 70, 5)
+        assert (got["groups"][0][0] > 0) == groups
