@@ -72,7 +72,11 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     if (u >= runs.start[xcd + 1]) return;
     const int nt = __builtin_amdgcn_readfirstlane(u / n_brows), pos = u - nt * n_brows;
     const int br = __builtin_amdgcn_readfirstlane(order ? order[pos] : pos);
-    const int n0 = nt * BN;
+    // Rows that are not 16-byte aligned: the last column tile moves left so that it ends at N, and its loads have no case of a
+    // row's end.  (18944 x 3584 at 90 %, N = 4093, 128 / 64 / 32-row blocks 134 / 148 / 199 -> 113 / 125 / 173 us with plain loads
+    // in every slice that does not reach past K; two slices ahead instead of one: 126 / 141 / 192.)
+    const int n_own = nt * BN, n0 = !VEC && N >= BN && n_own > N - BN ? N - BN : n_own;
+    const bool inner = n0 + BN <= N;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -88,17 +92,30 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    u32x4 ra[Cfg::A_LD], rb[Cfg::B_LD];
-
-    auto load_stage = [&](int t) {
+    struct Stage {
+        u32x4 a[Cfg::A_LD], b[Cfg::B_LD];
+    };
+    auto load_stage = [&](int t, Stage &f) __attribute__((always_inline)) {
         const int p = blk0 + t / Cfg::SPB, s = t % Cfg::SPB;
         const u32x4 *asrc = (const u32x4 *)(a_packed + (int64_t)p * (BR * BC) + (int64_t)s * (BR * KS));
 #pragma unroll
         for (int i = 0; i < Cfg::A_LD; ++i) {
             int c = i * NT + tid;
-            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) ra[i] = asrc[c];
+            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) f.a[i] = asrc[c];
         }
         const int krow0 = block_col_idx[p] * BC + s * KS;
+        if (inner && krow0 + KS <= K) {
+            const uint16_t *src = B + (int64_t)krow0 * N + n0;
+#pragma unroll
+            for (int i = 0; i < Cfg::B_LD; ++i) {
+                const int c = i * NT + tid;
+                if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) {
+                    const uint16_t *at = src + (int64_t)(c / Cfg::B_CPR) * N + c % Cfg::B_CPR * 8;
+                    f.b[i] = VEC ? *(const u32x4 *)at : *(const u32x4_a2 *)at;
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < Cfg::B_LD; ++i) {
             int c = i * NT + tid;
@@ -107,28 +124,26 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
                 int krow = krow0 + r, col = n0 + cc * 8;
                 u32x4 v = {0u, 0u, 0u, 0u};
                 if (krow < K && col < N) {  // rows past K belong to the zero padding of the last block column
-                    if (VEC)
-                        v = *(const u32x4 *)(B + (int64_t)krow * N + col);
-                    else
-                        v = load_tail8(B + (int64_t)krow * N, col, N);
+                    const uint16_t *row = B + (int64_t)krow * N;
+                    v = VEC ? *(const u32x4 *)(row + col) : load_tail8(row, col, N);
                 }
-                rb[i] = v;
+                f.b[i] = v;
             }
         }
     };
-    auto store_stage = [&](int buf) {
+    auto store_stage = [&](int buf, const Stage &f) __attribute__((always_inline)) {
         uint8_t *sa = lds + buf * Cfg::STAGE, *sb = sa + Cfg::A_STAGE;
 #pragma unroll
         for (int i = 0; i < Cfg::A_LD; ++i) {
             int c = i * NT + tid;
-            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) *(u32x4 *)(sa + c * 16) = ra[i];
+            if (Cfg::A_CHUNKS % NT == 0 || c < Cfg::A_CHUNKS) *(u32x4 *)(sa + c * 16) = f.a[i];
         }
 #pragma unroll
         for (int i = 0; i < Cfg::B_LD; ++i) {
             int c = i * NT + tid;
             if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) {
                 int r = c / Cfg::B_CPR, cc = c % Cfg::B_CPR;
-                *(u32x4 *)(sb + r * Cfg::PB + cc * 16) = rb[i];
+                *(u32x4 *)(sb + r * Cfg::PB + cc * 16) = f.b[i];
             }
         }
     };
@@ -166,14 +181,15 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     };
 
     if (T > 0) {
-        load_stage(0);
-        store_stage(0);
+        Stage f;
+        load_stage(0, f);
+        store_stage(0, f);
         __syncthreads();
         for (int t = 0; t < T; ++t) {
             const int buf = t & 1;
-            if (t + 1 < T) load_stage(t + 1);  // global loads fly while this stage is multiplied
+            if (t + 1 < T) load_stage(t + 1, f);  // global loads fly while this stage is multiplied
             compute_stage(buf);
-            if (t + 1 < T) store_stage(buf ^ 1);
+            if (t + 1 < T) store_stage(buf ^ 1, f);
             __syncthreads();
         }
     }
@@ -201,7 +217,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
         uint4 v = *(const uint4 *)(sc + row * Cfg::C_PITCH + cc * 16);
         int grow = br * BR + wm * Cfg::TM + row;
         int gcol = n0 + wn * Cfg::TN + cc * 8;
-        if (grow < M && gcol < N) {
+        if (grow < M && gcol < N && gcol + 8 > n_own) {  // (a column of two tiles gets the same bits from both)
             uint16_t *dst = C + (int64_t)grow * N + gcol;
             if (VEC) {
                 *(uint4 *)dst = v;

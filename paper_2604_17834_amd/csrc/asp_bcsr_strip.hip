@@ -10,6 +10,8 @@
 // ahead.  The waves' partial tiles meet in LDS once, are added in wave order (bitwise reproducible), rounded once, stored.
 // us a call, before -> now: 1024 x 1024, 64 x 64 blocks, 256 columns 6.2 -> 3.7; 3584 x 18944 at 64 / 256 / 1024 columns
 // 58 -> 6.6 / 58 -> 13 / 47 -> 34; 5003 x 3331 (80 %), 64 x 64 blocks, 1024 columns 42 -> 23.
+// Rows at other alignments: 5003 x 3331 (80 %), 64 x 64 blocks, 1021 columns 31.2 -> 22.7 since the last column tile moves left
+// instead of putting its lanes' loads together from a row's end (that tile alone had set the time of the launch).
 // With more columns a strip's reads (B once per strip, A once per column tile) are so many more than the tile kernels' that
 // these win.
 #include <algorithm>
@@ -45,7 +47,9 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
     const int list = at < more * (per + 1) ? at / (per + 1) : more + (at - more * (per + 1)) / per;
     const int4 ri = rank_info[list + 8 * (at - list * per - (list < more ? list : more))];
     const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
-    const int n0 = un * (32 * NT);
+    // rows that are not 16-byte aligned: the last column tile moves left so that it ends at N, and the loop has no case of a row's end
+    const bool inner = VEC || N >= 32 * NT;
+    const int n_own = un * (32 * NT), n0 = !VEC && inner && n_own > N - 32 * NT ? N - 32 * NT : n_own;
     const int u0 = (int)((int64_t)n_units * wave / W), u1 = (int)((int64_t)n_units * (wave + 1) / W);
 
     f32x16 acc[MT][NT];
@@ -63,7 +67,6 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
         // (chunks past N only feed columns that are never stored)
         const int col = VEC ? (col_l < N ? col_l : N - 8) : col_l;
         uint8_t *st = sb + row_l * PB + (lane % LPR) * 16;
-        const bool inner = VEC || n0 + 32 * NT <= N;
         // lane i holds the block column of the wave's i-th block, 64 at a time
         int col_base = u0 / UPB, cols;
         auto load_cols = [&]() __attribute__((always_inline)) {
@@ -94,9 +97,8 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
                 for (int i = 0; i < BL; ++i) {
                     const int k = k0 + row_l + i * RPI;
                     const uint16_t *row = B + (int64_t)(k < K ? k : K - 1) * N;
-                    u32x4 v = {0u, 0u, 0u, 0u};
-                    if (k < K) v = VEC ? *(const u32x4 *)(row + col) : load_tail8(row, col, N);
-                    f.b[i] = v;
+                    u32x4 v = VEC ? *(const u32x4 *)(row + col) : inner ? *(const u32x4_a2 *)(row + col) : load_tail8(row, col, N);
+                    f.b[i] = k < K ? v : u32x4{0u, 0u, 0u, 0u};
                 }
             }
 #pragma unroll
@@ -168,7 +170,7 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
             s0 += *(const f32x4 *)&part[(w * (MT * 32) + row) * PITCH + c];
             s1 += *(const f32x4 *)&part[(w * (MT * 32) + row) * PITCH + c + 4];
         }
-        if (m0 + row >= M || n0 + c >= N) continue;
+        if (m0 + row >= M || n0 + c >= N || n0 + c + 8 <= n_own) continue;  // (a column of two tiles gets the same bits from both)
         const bf16x4 lo = __builtin_convertvector(s0, bf16x4), hi = __builtin_convertvector(s1, bf16x4);  // to nearest even
         const bf16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         uint16_t *dst = C + (int64_t)(m0 + row) * N + n0 + c;
@@ -234,9 +236,14 @@ static bool strips_win(const asp_handle *h, int64_t N, const BcsrPlan &p) {
     const double cus = h->n_cus > 0 ? h->n_cus : 256, b = h->b_row;
     const double work = (double)h->n_units * b * b * (double)N * 256 / cus;  // stored elements x columns
     const double longest = (double)h->hb.max_blocks * (b / 32), slices = (double)h->n_units * (b / 32);
-    if (!p.vectorized)  // against the register-staged kernel
-        return 4 + (b == 32 ? 10e-9 : 8e-9) * work <
-               3 + std::max(0.75 * longest, (b == 32 ? 9.3e-9 : 6.4e-9) * work);
+    if (!p.vectorized) {
+        // Against the register-staged kernel: of 90 products (1000 to 9000 rows, 64 to 9000 columns, half with
+        // geometric block-row lengths) the choice is 1.007 times slower than the better one in the mean, 1.24 at most.  A block-row's strips run on
+        // one XCD, so one that outweighs an eighth of the rest sets the time (1280 x 2112, geometric, 6183 columns 61 / 32).
+        const double of_xcd = std::max(work, 8.0 * (double)h->hb.max_blocks * b * b * (double)N * 256 / cus);
+        return 4 + (b == 32 ? 8e-9 : 6e-9) * of_xcd <
+               3 + (b == 32 ? 0.3 : 0.33) * longest + (b == 32 ? 5.2e-9 : 2.5e-9) * work;
+    }
     // with more of B than this in flight between the XCDs strips fall behind (1024 x 8192, 12 000 columns: 184 / 244 us)
     if ((double)h->k * (double)N * 2 > 64e6) return false;
     const double strips = 1.1 * (3 + (b == 32 ? 6.5e-9 : 4.6e-9) * work + 4e-7 * (double)h->m * (double)N * 256 / cus);  // (5 TB/s of C)
