@@ -359,17 +359,26 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         if (!bcsr_wide_launch(h, B, C, N, p, stream) && !bcsr_dma_launch(h, B, C, N, p, stream))
             return fail(ASP_ERR_UNSUPPORTED, "no kernel for this block size / tile width");
     } else if (!p.vectorized) {  // 16-byte accesses at element alignment
-        // 128-wide tiles where that leaves enough of them: with the workgroups that a compute unit holds it reads A half as
-        // often, with fewer tiles the longest block-rows set the time.  us, 64 / 128 wide: 18944 x 3584 at 90 %, N = 8001,
-        // 128 / 64 / 32-row blocks 346 / 271, 356 / 316, 502 / 403; 5003 x 3331 at 80 %, N = 3001 58.7 / 53.7, 67 / 67, 100 / 86;
-        // 1500 x 8001 at 75 %, N = 8001, 64-row (1512 tiles) 148 / 180.  (256 wide: slower than both.)
-        // (64-wide ones again where a single column tile of 2^29 rows would pass the threads of a launch)
+        // Wide tiles where that leaves enough of them: A is read less often, but with few tiles the longest block-rows set the time.
+        // us, 64 / 128 / 256 wide, 128-row blocks: 18944 x 3584 at 90 %, N = 8001 338 / 257 / 199, 8000 x 2000 at 95 %, N = 6001 (1512
+        // tiles of 256) 42.6 / 40.0 / 37.3, 3940 x 1488 at 90 %, N = 5271 (651) - / 24.0 / 27.7, 5000 x 5000 at 90 %, N = 2001 (640 of 128) 32.4 /
+        // 34.0 / 43.0; 64-row: 359 / 272 / 232, 40.9 / 37.2 / 34.6 (3000), 3200 x 1920, geometric lengths, N = 6811 (1350) - / 52 / 58, 34.1 /
+        // 27.7 / 31.3; 32-row: 450 / 361 / 314, 50 / 46 / 40 (6000), 3057 x 2421, geometric lengths, N = 6099 (2304) - / 24.1 / 27.7, 41 / 34 / 33.
+        // (narrower again where a single column tile of 2^29 rows would pass the threads of a launch)
         bool done = false;
-        if (h->n_brows * ceil_div(N, 128) >= (h->b_row == 128 ? 3 : h->b_row == 64 ? 8 : 4) * (int64_t)h->n_cus) {
-            BcsrPlan w = p;
-            w.bn = 128;
-            w.n_tiles = (int32_t)ceil_div(N, 128);
+        BcsrPlan w = p;
+        auto enough = [&](int bn, int64_t quarters) {  // tiles of that width, in quarters of the compute units
+            w.bn = bn;
+            w.n_tiles = (int32_t)ceil_div(N, bn);
             w.workgroups = h->n_brows * w.n_tiles;
+            return 4 * w.workgroups >= quarters * (int64_t)h->n_cus;
+        };
+        if (enough(256, h->b_row == 128 ? 20 : h->b_row == 64 ? 32 : 48)) {
+            if (h->b_row == 128) done = launch<128, 256, 2, 2, false>(h, B, C, N, w, stream);
+            else if (h->b_row == 64) done = launch<64, 256, 1, 4, false>(h, B, C, N, w, stream);
+            else done = launch<32, 256, 1, 4, false>(h, B, C, N, w, stream);
+        }
+        if (!done && enough(128, h->b_row == 128 ? 11 : 16)) {
             if (h->b_row == 128) done = launch<128, 128, 2, 2, false>(h, B, C, N, w, stream);
             else if (h->b_row == 64) done = launch<64, 128, 2, 2, false>(h, B, C, N, w, stream);
             else done = launch<32, 128, 1, 4, false>(h, B, C, N, w, stream);
