@@ -69,6 +69,8 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_group_slots);
     (void)hipFree(h->d_g_row_tasks);
     (void)hipFree(h->d_g_chunks);
+    (void)hipFree(h->d_teams);
+    (void)hipFree(h->d_g_teams);
     (void)hipFree(h->d_g_split_rows);
     (void)hipFree(h->d_c_rank_info);
     (void)hipFree(h->d_c_rank_info_32);
@@ -238,6 +240,11 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     HostGroups groups;
     std::vector<uint8_t> gathered;
     wcsr_build_rows(m, row_ptr, col_idx, es, h->b_row, h->task_cols, h->hw, rows);
+    wcsr_build_groups(m, row_ptr, col_idx, values, es, h->b_row, h->task_cols, h->hw, rows, groups);
+    std::vector<int32_t> teams, g_teams;
+    h->chunk_rows = (int64_t)rows.chunks.size() / 4;
+    wcsr_build_teams(rows.n_entries, rows.chunks, rows.tasks, teams);
+    h->n_teams = (int64_t)teams.size() / 4;
     h->n_row_tasks = (int64_t)rows.tasks.size() / 4;
     h->n_chunks = (int64_t)rows.chunks.size() / 4;
     h->n_split_rows = (int64_t)rows.split.size() / 4;
@@ -246,7 +253,8 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     h->tiles_dealt = rows.tiles_dealt;
     if ((s = upload(&h->d_tile_tasks, rows.tile_tasks.data(), rows.tile_tasks.size() * 4, stream))) return s;
     if ((s = upload(&h->d_tile_split, rows.tile_split.data(), rows.tile_split.size() * 4, stream))) return s;
-    if (h->n_row_tasks > 0 || h->n_chunks > 0) {
+    if (h->n_row_tasks > 0 || h->n_chunks > 0 || h->n_teams > 0) {
+        if ((s = upload(&h->d_teams, teams.data(), teams.size() * 4, stream))) return s;
         if ((s = upload(&h->d_row_tasks, rows.tasks.data(), rows.tasks.size() * 4, stream))) return s;
         if ((s = upload(&h->d_chunks, rows.chunks.data(), rows.chunks.size() * 4, stream))) return s;
         if ((s = upload(&h->d_split_rows, rows.split.data(), rows.split.size() * 4, stream))) return s;
@@ -254,8 +262,12 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload_runs((void **)&h->d_e_col, col_idx, 4, rows, gathered, stream))) return s;
         if ((s = upload_runs(&h->d_e_val, values, es, rows, gathered, stream))) return s;
     }
-    wcsr_build_groups(m, row_ptr, col_idx, values, es, h->b_row, h->task_cols, h->hw, rows, groups);
     if (groups.n_groups > 0) {
+        int64_t left = rows.n_entries;
+        for (size_t i = 1; i < groups.tasks.size(); i += 4) left -= 16 * (int64_t)groups.tasks[i];
+        wcsr_build_teams(std::max<int64_t>(0, left), groups.chunks, groups.row_tasks, g_teams);
+        h->n_g_teams = (int64_t)g_teams.size() / 4;
+        if ((s = upload(&h->d_g_teams, g_teams.data(), g_teams.size() * 4, stream))) return s;
         h->n_groups = groups.n_groups;
         h->group_span = groups.span;
         h->group_scratch_rows = groups.scratch_rows;

@@ -170,6 +170,7 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
                      int32_t task_cols, const HostWcsr &in, HostRows &out);
 void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
                        int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out);
+void wcsr_build_teams(int64_t n_entries, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks, std::vector<int32_t> &teams);
 void wcsr_zero_windows(const std::vector<int32_t> &window_row_ptr, int32_t task_cols,
                        std::vector<int32_t> &zero_windows);
 // returns empty string when the CSR arrays are valid, else a description of the first problem
@@ -223,12 +224,15 @@ struct asp_handle {
     // WCSR: the kernels' work lists (HostRows) and the entries of the windows that are walked entry by entry
     int64_t n_row_tasks = 0, n_chunks = 0, n_split_rows = 0, n_tile_tasks = 0, n_tile_split = 0;
     bool tiles_dealt = false;
+    int64_t n_teams = 0, chunk_rows = 0;  // (chunk_rows: scratch rows of all chunks, those of teams among them)
+    int32_t *d_teams = nullptr;           // those that a workgroup takes instead of a wave (wcsr_build_teams)
     int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;
     // WCSR: long rows in groups, and the lists of what is left beside them, for calls with scratch (HostGroups)
     int64_t n_groups = 0, group_span = 0, group_scratch_rows = 0, group_near_cols = 0, group_many = 0;
-    int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0;
+    int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0, n_g_teams = 0;
+    int32_t *d_g_teams = nullptr;
     uint64_t *d_group_entries = nullptr;
     int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;
     float *d_ws = nullptr;          // fp32 scratch, one [b_row][N] tile per slot (asp_reserve)

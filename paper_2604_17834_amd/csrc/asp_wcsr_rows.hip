@@ -57,26 +57,32 @@ __device__ __forceinline__ void put_chunk(int4 td, const float (&acc)[E], int64_
     }
 }
 
+// The sum of a whole row at columns nc .. nc + E - 1.
+template <typename T, int E>
+__device__ __forceinline__ void put_row(int row, const float (&acc)[E], int64_t nc, int64_t N, T *C) {
+    T *dst = C + (int64_t)row * N + nc;
+#pragma unroll
+    for (int i = 0; i < E; ++i) narrow(acc[i], dst[i]);
+}
+
 }  // namespace
 
 // tasks[t] = {first row, rows (1..63), first entry, end entry}: consecutive whole rows.  row_ptr / col / val: the entries
 // of the rows handled here; col and val are readable up to the next multiple of 8 entries plus 8.
-// CHUNK: the task is a chunk of a long row, {row, scratch row, first entry, end entry}.
-// One wave: task `task`, columns from blockIdx.y * 64 E.
+// CHUNK: the task is (part of) a chunk of a long row, {row, scratch row, first entry, end entry}; its sum stays in `acc`.
+// One wave: task td, columns from blockIdx.y * 64 E.
 template <typename T, int E, bool CHUNK>
-__device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int task, const int32_t *__restrict__ row_ptr,
+__device__ __forceinline__ void walk_rows(const int4 td, const int32_t *__restrict__ row_ptr,
                                           const int32_t *__restrict__ col, const T *__restrict__ val,
-                                          const T *__restrict__ B, T *__restrict__ C, int64_t N, float *__restrict__ ws) {
+                                          const T *__restrict__ B, T *__restrict__ C, int64_t N, float (&acc)[E]) {
     typedef typename RowVec<T, E>::type vec_t;
     const int lane = threadIdx.x & 63;
-    const int4 td = tasks[task];
     const int64_t n = (int64_t)blockIdx.y * (64 * E) + lane * E;
     const int64_t nc = n < N - E ? n : N - E;  // N >= E
     const bool owner = n < N;
     const uint32_t voff = (uint32_t)(nc * (int64_t)sizeof(T)), row_bytes = (uint32_t)(N * (int64_t)sizeof(T));
     const int e0 = td.z, e1 = td.w;
 
-    float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.f;
 
@@ -168,7 +174,6 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
                 for (int j = 0; j < 8; ++j) fma_entry(t, bv, j);
             }
         });
-        if (owner && e0 < e1) put_chunk<T, E>(td, acc, n, nc, N, C, ws);
         return;
     }
 
@@ -211,22 +216,18 @@ __device__ __forceinline__ void walk_rows(const int4 *__restrict__ tasks, int ta
 // within the 16 lanes (row_newbcast) as they are used; the groups' sums are added at the end in a fixed order.
 // (64 rows of 200 000 entries, N = 64, fp32: 0.236 -> 0.211 ms; 3.2e6 Zipf entries, N = 100, bf16: 0.146 -> 0.133 ms.
 // At 8 bytes per lane walk_rows is the better one: 16.7e6 Zipf entries, N = 128, fp32: 1.255 against 1.208 ms.)
+// (e0 < e1; every lane group ends with the whole sum in `acc`)
 template <typename T, int E, int L>
-__device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int task, const int32_t *__restrict__ col,
-                                           const T *__restrict__ val, const T *__restrict__ B, T *__restrict__ C, int64_t N,
-                                           float *__restrict__ ws) {
+__device__ __forceinline__ void walk_chunk(int e0, int e1, const int32_t *__restrict__ col,
+                                           const T *__restrict__ val, const T *__restrict__ B, int64_t N, float (&acc)[E]) {
     typedef typename RowVec<T, E>::type vec_t;
     constexpr int G = 64 / L;
-    const int4 td = tasks[task];
-    const int e0 = td.z, e1 = td.w;
-    if (e0 >= e1) return;  // fills up a list
     const int lane = threadIdx.x & 63, g = lane / L, i16 = lane & 15;
     const int64_t n = (int64_t)blockIdx.y * (L * E) + (lane % L) * E;
     const int64_t nc = n < N - E ? n : N - E;  // N >= E
     const char *base = (const char *)B + nc * (int64_t)sizeof(T);
     const uint32_t row_bytes = (uint32_t)(N * (int64_t)sizeof(T));
 
-    float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.f;
     // batch b: entries (b G + g) * 16 .. + 15 of the chunk for this group; past the end: the last entry, and nothing is added
@@ -280,24 +281,70 @@ __device__ __forceinline__ void walk_chunk(const int4 *__restrict__ tasks, int t
         if (G >= 2) acc[i] += __shfl_xor(acc[i], 32);
         if (G >= 4) acc[i] += __shfl_xor(acc[i], 16);
     }
-    if (g == 0 && n < N) put_chunk<T, E>(td, acc, n, nc, N, C, ws);
 }
 
 // One wave per chunk or task, the chunks first (they are the longest).  A wave covers 64 * E = CL * CE columns
 // (CL = 64: walk_rows for the chunks too); grid.y = column tiles.
+// Before those: teams[t] = {row, scratch row or -1: the row is here whole, first entry, end entry}, n_teams of them, a workgroup to
+// each, whose waves take a quarter of the entries and add their sums in LDS, in order.  Where a launch is so small that its longest
+// chunk or row sets its time (wcsr_build_teams): a wave takes 0.4 us for every 8 entries, 25 us for 512, however few others there are.
+// (Whole rows are walked in the same order at every width: a slice of B's columns gives a slice of C, bit for bit.)
 template <typename T, int E, int CE, int CL>
-__global__ __launch_bounds__(256) void wcsr_rows_kernel(const int4 *__restrict__ chunks, int n_chunks,
+__global__ __launch_bounds__(256) void wcsr_rows_kernel(const int4 *__restrict__ teams, int n_teams,
+                                                        const int4 *__restrict__ chunks, int n_chunks,
                                                         const int4 *__restrict__ tasks, int n_tasks,
                                                         const int32_t *__restrict__ row_ptr,
                                                         const int32_t *__restrict__ col, const T *__restrict__ val,
                                                         const T *__restrict__ B, T *__restrict__ C, int64_t N,
                                                         float *__restrict__ ws) {
-    const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wave < n_chunks) {
-        if constexpr (CL < 64) walk_chunk<T, CE, CL>(chunks, wave, col, val, B, C, N, ws);
-        else walk_rows<T, E, true>(chunks, wave, row_ptr, col, val, B, C, N, ws);
+    constexpr int SUMS = E > CE ? E : CE;
+    __shared__ float part[4][SUMS][64];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool team = (int)blockIdx.x < n_teams;
+    const int wave = ((int)blockIdx.x - n_teams) * 4 + w;
+    // the waves' sums, in wave 0 (false elsewhere)
+    auto gather_sums = [&](auto &acc) __attribute__((always_inline)) {
+        constexpr int n = sizeof(acc) / 4;
+#pragma unroll
+        for (int i = 0; i < n; ++i) part[w][i][lane] = acc[i];
+        __syncthreads();
+        if (w != 0) return false;
+#pragma unroll
+        for (int i = 0; i < n; ++i) acc[i] = (acc[i] + part[1][i][lane]) + (part[2][i][lane] + part[3][i][lane]);
+        return true;
+    };
+    if (team || wave < n_chunks) {
+        int4 td = team ? teams[blockIdx.x] : chunks[wave];
+        if (td.z >= td.w) return;  // fills up a list
+        if (team) {
+            const int quarter = ((td.w - td.z + 3) / 4 + 15) & ~15;
+            const int lo = min(td.w - td.z, w * quarter), hi = min(td.w - td.z, (w + 1) * quarter);
+            td.w = td.z + hi;
+            td.z += lo;
+        }
+        if (team && td.y < 0) {
+            float acc[E];
+            walk_rows<T, E, true>(td, row_ptr, col, val, B, C, N, acc);
+            if (!gather_sums(acc)) return;
+            const int64_t n = (int64_t)blockIdx.y * (64 * E) + lane * E;
+            if (n < N) put_row<T, E>(td.x, acc, n < N - E ? n : N - E, N, C);
+            return;
+        }
+        float acc[CE];
+        if (CL == 64) {
+            walk_rows<T, CE, true>(td, row_ptr, col, val, B, C, N, acc);
+        } else if (td.z < td.w) {
+            walk_chunk<T, CE, CL>(td.z, td.w, col, val, B, N, acc);
+        } else {
+#pragma unroll
+            for (int i = 0; i < CE; ++i) acc[i] = 0.f;
+        }
+        if (team && !gather_sums(acc)) return;
+        const int64_t n = (int64_t)blockIdx.y * (CL * CE) + (lane % CL) * CE;
+        if (lane < CL && n < N) put_chunk<T, CE>(td, acc, n, n < N - CE ? n : N - CE, N, C, ws);  // N >= CE
     } else if (wave - n_chunks < n_tasks) {
-        walk_rows<T, E, false>(tasks, wave - n_chunks, row_ptr, col, val, B, C, N, ws);
+        float acc[E];
+        walk_rows<T, E, false>(tasks[wave - n_chunks], row_ptr, col, val, B, C, N, acc);
     }
 }
 
@@ -346,17 +393,19 @@ static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, 
     const bool groups = ws && wcsr_groups_apply(h, N);  // long rows run there: the lists without them
     const int32_t *d_chunks = groups ? h->d_g_chunks : h->d_chunks, *d_row_tasks = groups ? h->d_g_row_tasks : h->d_row_tasks;
     const int64_t n_chunks = groups ? h->n_g_chunks : h->n_chunks, n_row_tasks = groups ? h->n_g_row_tasks : h->n_row_tasks;
+    const int32_t *d_teams = groups ? h->d_g_teams : h->d_teams;
     if (groups) wcsr_groups_launch(h, B, N, ws, stream);
     // a launch takes fewer than 2^32 threads
     const int64_t waves = n_chunks + n_row_tasks, step = (1 << 26) - 32;
-    for (int64_t first = 0; first < waves; first += step) {
+    int64_t n_teams = groups ? h->n_g_teams : h->n_teams;  // (a few thousand)
+    for (int64_t first = 0; first < waves || n_teams > 0; first += step, n_teams = 0) {
         const int64_t end = std::min(waves, first + step);
         const int64_t c0 = std::min(first, n_chunks), c1 = std::min(end, n_chunks), t0 = first - c0, t1 = end - c1;
         // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
 #define ASP_ROWS(E, CE, CL)                                                                                          \
     hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                             \
-                       dim3((unsigned)ceil_div(end - first, 4), (unsigned)ceil_div(N, 64 * (E))), dim3(256), 0, stream, \
-                       (const int4 *)d_chunks + c0, (int)(c1 - c0), (const int4 *)d_row_tasks + t0, (int)(t1 - t0), \
+                       dim3((unsigned)(n_teams + ceil_div(end - first, 4)), (unsigned)ceil_div(N, 64 * (E))), dim3(256), 0, \
+                       stream, (const int4 *)d_teams, (int)n_teams, (const int4 *)d_chunks + c0, (int)(c1 - c0), (const int4 *)d_row_tasks + t0, (int)(t1 - t0), \
                        h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
         if (N <= 16) ASP_ROWS(1, 1, 16);
         else if (N <= 32) ASP_ROWS(1, 2, 16);
@@ -381,7 +430,7 @@ void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *
     // Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
     // 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
     // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  From lists of 128 on, the graph without that row 950 -> 959: another launch.
-    const bool many = (groups ? h->group_scratch_rows + h->n_g_chunks : h->n_chunks) > 32 * n_split;
+    const bool many = (groups ? h->group_scratch_rows + h->chunk_rows : h->chunk_rows) > 32 * n_split;
     const int64_t n_many = N > 65535 * 16 ? 0 : many ? n_split : groups ? h->group_many : 0;
 #define ASP_ROWS_SUM(T, COLS, J, FIRST, COUNT)                                                                            \
     if ((COUNT) > 0)                                                                                                      \
