@@ -138,7 +138,7 @@ def asp_create_from_csr(fmt, dtype, b_row, b_col, m, k, row_ptr, col_idx, values
 
 def asp_spmm(handle, B_ptr, C_ptr, N, stream=None, check=True):
     """B_ptr / C_ptr are device addresses (e.g. torch tensor .data_ptr()), stream a hipStream_t value."""
-    st = lib().asp_spmm(handle, B_ptr, C_ptr, N, stream)
+    st = (_lib or lib()).asp_spmm(handle, B_ptr, C_ptr, N, stream)
     if check and st != ASP_OK:
         raise AspError(st, "asp_spmm")
     return st
@@ -222,7 +222,7 @@ def asp_mtx_read(path, check=True):
 
 def asp_spmm_xt(handle, X_ptr, Y_ptr, N, stream=None, check=True):
     """Y[N x m] = X[N x k] x A^T; X_ptr / Y_ptr are device addresses, stream a hipStream_t value."""
-    st = lib().asp_spmm_xt(handle, X_ptr, Y_ptr, N, stream)
+    st = (_lib or lib()).asp_spmm_xt(handle, X_ptr, Y_ptr, N, stream)
     if check and st != ASP_OK:
         raise AspError(st, "asp_spmm_xt")
     return st
