@@ -334,6 +334,117 @@ __global__ __launch_bounds__(256, MT == 4 ? 2 : 3) void bcsr_xt_staged_kernel(co
     }
 }
 
+// Up to 16 NT tokens, 16-byte aligned operands: strips of 16 rows on v_mfma_f32_16x16x32_bf16, otherwise as above.  What bounds a
+// decoded batch is that a compute unit keeps some 115 lines in flight: 15 KB, in 0.6 us or more from the memory side.  Strips of
+// 32 rows give each compute unit at most one of the 112 of a projection with 28 block-rows, and twice the bytes of its longest one.
+template <int BR, int NT, int W>
+__global__ __launch_bounds__(W * 64) void bcsr_xt_decode_kernel(const int4 *__restrict__ rank_info,
+                                                                const int32_t *__restrict__ col_idx,
+                                                                const uint16_t *__restrict__ a_packed,
+                                                                const uint16_t *__restrict__ X, uint16_t *__restrict__ Y,
+                                                                int M, int K, int N, int units_m) {
+    constexpr int STRIPS = BR / 16, UK = BR < 64 ? BR : 64, KK = UK / 32, UPB = BR / UK;
+    constexpr int PITCH = 20;  // floats per token of a partial tile
+    __shared__ __attribute__((aligned(16))) float part[W][NT * 16][PITCH];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (XCDs and lists as in the strips above)
+    const int xcd = blockIdx.x & 7, q = gridDim.x >> 3, r = gridDim.x & 7;
+    const int um = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
+    const int n_brows = units_m / STRIPS, per = n_brows >> 3, more = n_brows & 7, at = um / STRIPS, strip = um % STRIPS;
+    const int list = at < more * (per + 1) ? at / (per + 1) : more + (at - more * (per + 1)) / per;
+    const int4 ri = rank_info[list + 8 * (at - list * per - (list < more ? list : more))];
+    const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
+    const int u0 = n_units * wave / W, u1 = n_units * (wave + 1) / W;
+
+    f32x4 acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    if (u0 < u1) {
+        const int k_l = 8 * (lane >> 4);  // this lane's 8 k of 32
+        const uint16_t *x[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int t = j * 16 + (lane & 15);
+            x[j] = X + (int64_t)(t < N ? t : N - 1) * K;  // tokens past N feed columns that are never stored
+        }
+        // row 16 strip + lane % 16, k 8 (lane / 16) of 32: groups of 32 rows, 16 k at a time
+        const uint16_t *a_lane = a_packed + (int64_t)blk0 * (BR * BR) + (lane >> 5) * (BR * 16) + (strip >> 1) * 512 +
+                                 ((lane & 15) + 16 * (strip & 1) + 32 * ((lane >> 4) & 1)) * 8;
+        // lane i holds the block column of the wave's i-th block, 64 at a time
+        int col_base = u0 / UPB, cols;
+        auto load_cols = [&]() __attribute__((always_inline)) {
+            const int last = n_units / UPB - 1, p = col_base + lane;
+            cols = col_idx[blk0 + (p < last ? p : last)];
+        };
+        load_cols();
+        struct Unit {
+            u32x4 a[KK], x[NT][KK];
+        };
+        auto load = [&](int u, Unit &f) __attribute__((always_inline)) {
+            const int p = u / UPB, s = u % UPB;
+            if (p - col_base >= 64) {
+                col_base = p;
+                load_cols();
+            }
+            const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));
+#pragma unroll
+            for (int i = 0; i < KK; ++i) f.a[i] = a[i * (BR * 4)];
+            const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * UK + k_l;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int i = 0; i < KK; ++i) {
+                    const int k = k0 + i * 32;  // K % 8 == 0; k past K count as zeros
+                    const u32x4 v = *(const u32x4 *)(x[j] + (k < K ? k : 0));
+                    f.x[j][i] = k < K ? v : u32x4{0u, 0u, 0u, 0u};
+                }
+        };
+        auto multiply = [&](const Unit &f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < KK; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.a[i]),
+                                                                     __builtin_bit_cast(bf16x8, f.x[j][i]), acc[j], 0, 0, 0);
+        };
+        Unit f0, f1;
+        load(u0, f0);
+        int u = u0;
+        for (; u + 2 < u1; u += 2) {
+            load(u + 1, f1);
+            multiply(f0);
+            load(u + 2, f0);
+            multiply(f1);
+        }
+        if (u + 1 < u1) {
+            load(u + 1, f1);
+            multiply(f0);
+            multiply(f1);
+        } else {
+            multiply(f0);
+        }
+    }
+
+    // D: lane l holds token l % 16, rows 4 (l / 16) + 0..3
+#pragma unroll
+    for (int j = 0; j < NT; ++j) *(f32x4 *)&part[wave][j * 16 + (lane & 15)][4 * (lane >> 4)] = acc[j];
+    __syncthreads();
+    const int m0 = br * BR + strip * 16;
+    for (int i = tid; i < NT * 16 * 8; i += W * 64) {  // two adjacent outputs of a token
+        const int t = i / 8, c = i % 8 * 2;
+        float s0 = part[0][t][c], s1 = part[0][t][c + 1];
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            s0 += part[w][t][c];
+            s1 += part[w][t][c + 1];
+        }
+        const uint32_t lo = __builtin_bit_cast(uint16_t, (__bf16)s0), hi = __builtin_bit_cast(uint16_t, (__bf16)s1);
+        if (t < N && m0 + c < M) *(uint32_t *)(Y + (int64_t)t * M + m0 + c) = lo | (hi << 16);  // M % 8 == 0
+    }
+}
+
 // ---- host side ------------------------------------------------------------------------------------
 // false: too many rows for a launch
 template <int BR, int MT, int NT, int W, int UK>
@@ -354,6 +465,16 @@ static bool launch_strip(const asp_handle *h, const void *X, void *Y, int64_t N,
         else ASP_STRIP(false);
 #undef ASP_STRIP
     }
+    return true;
+}
+
+template <int BR, int NT, int W>
+static bool launch_decode(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream) {
+    const int64_t units_m = h->n_brows * (BR / 16);
+    if (!launch_fits(units_m, W * 64)) return false;
+    hipLaunchKernelGGL((bcsr_xt_decode_kernel<BR, NT, W>), dim3((unsigned)units_m), dim3(W * 64), 0, stream,
+                       (const int4 *)h->d_rank_info, h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)X,
+                       (uint16_t *)Y, (int)h->m, (int)h->k, (int)N, (int)units_m);
     return true;
 }
 
@@ -392,6 +513,24 @@ int bcsr_xt_staged_strips(const asp_handle *h, int64_t N) {
     return h->b_row == 128 && strips > 3 * cus && h->n_units >= 6 * h->n_brows ? 4 : 2;
 }
 
+// Whether up to 32 tokens go through the strips of 16 rows, and by how many waves each: 0, 4 or 8.  us in a captured graph, the other
+// strips / 4 / 8 waves: 18944 x 3584, 90 %, 128-row blocks, 16 tokens 5.28 / 4.79 / 4.76, 1 token 4.79 / 3.53 / 4.02; 3584 x 18944,
+// 16 tokens 6.9 / 5.5 / 5.35; geometric rows, 18944 x 9472, 16 tokens 14.1 / 12.0 / 10.4; of 77 products of 64- and 128-row blocks up to
+// 16 tokens 0.84 in the mean.
+// Eight waves where a block-row has 24 units of 64 k (80 %, 18944 x 3584, up to 20: 6.7 / 7.0) or strips are few.  Not with 32-row
+// blocks and more than two strips to a compute unit: a 32-row block has a strip of its own already, and 16-row ones read X twice
+// (18944 x 3584, 16 tokens 4.62 / 4.73).  Nor where block-rows are long and alike and some compute units have a strip more than the
+// others (8960 x 18944, 80 %, 64-row, 560 strips on 256 units 14.4 / 15.9).  Above 16 tokens only where the others leave compute units
+// idle (3584 x 18944, 32 tokens 8.8 / 8.0; 18944 x 3584 5.8 / 6.9).
+static int decode_waves(const asp_handle *h, int64_t N) {
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, strips = h->n_brows * (h->b_row / 16);
+    if (N > 16) return h->b_row >= 64 && strips <= cus ? 8 : 0;
+    if (h->b_row == 32) return strips <= 2 * cus ? 8 : 0;
+    const bool alike = h->hb.max_blocks * h->n_brows <= 2 * h->n_units, long_rows = h->n_units * (h->b_row / 64) >= 24 * h->n_brows;
+    if (strips > cus && alike && long_rows && 4 * ceil_div(strips, cus) * cus > 5 * strips) return 0;
+    return h->hb.max_blocks * (h->b_row / 64) >= 24 || 4 * strips <= 5 * cus ? 8 : 4;
+}
+
 // Shape of the wave tiles of the other strips: the largest that still gives the chip enough of them, since a larger one reads fewer bytes
 // per MFMA.  18944 x 3584 (gate) and 3584 x 18944 (down), 90 % sparse, us a call, tiles of 32 x 32 / 64 x 32 / 64 x 64 /
 // 128 x 64: gate at 64 tokens 8.3 / 7.7 / 8.6 / 10.3, at 256 22 / 19 / 18 / 20; down at 64 tokens 9.3 / 10.9 / 17 / 21,
@@ -400,6 +539,12 @@ int bcsr_xt_staged_strips(const asp_handle *h, int64_t N) {
 template <int BR>
 static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N, bool vec, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64);
+    if (vec && N <= 32) {
+        const int waves = decode_waves(h, N);
+        if (waves == 8 && N <= 16 && launch_decode<BR, 1, 8>(h, X, Y, N, stream)) return true;
+        if (waves == 4 && N <= 16 && launch_decode<BR, 1, 4>(h, X, Y, N, stream)) return true;
+        if (waves == 8 && N > 16 && launch_decode<BR, 2, 8>(h, X, Y, N, stream)) return true;
+    }
     if constexpr (BR == 128) {
         const int staged = vec ? bcsr_xt_staged_strips(h, N) : 0;
         if (staged != 0 && (staged == 4 ? launch_staged<BR, 4>(h, X, Y, N, stream) : launch_staged<BR, 2>(h, X, Y, N, stream)))
