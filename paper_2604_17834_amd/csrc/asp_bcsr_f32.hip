@@ -7,6 +7,9 @@
 // a barrier every 1024 MFMA cycles that all waves of the workgroup had to reach).  The waves that share a strip of A or a
 // slab of B meet in the L1.  Block-rows are walked longest first, so that the launch ends with short ones: in the order of
 // the bf16 schedule the last heavy tiles were a fifth of it.
+// A load has no branch: with a case for rows past K in it the compiler left the loads of A to where they are multiplied, and every
+// look-up of a block column waited for all loads in flight.  Of 60 products (1000 to 9000 rows, 64 to 2048 columns) 0.89 of the
+// time in the mean, 0.80 at best; 9000 x 4000, 50 %, 64 x 64 blocks, 1024 columns 380 -> 327 us.
 // 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, before -> now: N = 8192 999 / 958 / 1141 -> 923 / 919 / 1000 us (121 TFLOP/s;
 // the same MFMAs on registers reach 149), N = 2048 301 / 276 / 306 -> 253 / 253 / 260, N = 64 140 / 83 / 63 -> 17 / 16 / 15
 // (both builds in turn in one process; clocks move all of them by 5 % together).
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32
     const int64_t n0 = ((int64_t)nt * WN + wn) * (32 * V);
     if (WK == 1 && n0 >= N) return;
     const int64_t n = n0 + jl * V, nc = n < N - V ? n : N - V;
-    const uint32_t row_bytes = (uint32_t)N * 4, voff = (uint32_t)(kq * N + nc) * 4;  // N <= ASP_MAX_N
+    const uint32_t row_bytes = (uint32_t)N * 4, coff = (uint32_t)nc * 4;  // N <= ASP_MAX_N: 8 rows take less than 2^32 bytes
     const int u0 = (int)((int64_t)n_units * wk / WK), u1 = (int)((int64_t)n_units * (wk + 1) / WK);
 
     f32x16 acc[MT][V];
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32
             for (int e = 0; e < 16; ++e) acc[i][v][e] = 0.f;
 
     if (u0 < u1) {
-        const float *a_lane = a_packed + (int64_t)blk0 * (BR * BR) + row0 * 512 + lane * 4;
+        const float *a_tile = a_packed + (int64_t)blk0 * (BR * BR) + row0 * 512;
         // lane i holds the block column of the wave's i-th block, 64 at a time
         int col_base = u0 / UPB, cols;
         auto load_cols = [&]() __attribute__((always_inline)) {
@@ -91,40 +94,40 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32
         struct Unit {
             f32x4 a[MT];
             cols_t b[4];
+            int left;  // rows of B from the unit's first one on, or less than 1
         };
         auto load = [&](int u, Unit &f) __attribute__((always_inline)) {
             const int p = u / UPB, s = u % UPB;
+            // (before the look-up: a wave's first columns are still on their way)  Blocks are [16 k][32-row tile][8 k][lane][4]
+            global_char *a = (global_char *)(a_tile + (int64_t)p * (BR * BR) + (s >> 1) * (BR * 16) + (s & 1) * 256);
+            uint32_t aoff = lane * 16;
+            asm("" : "+s"(a), "+v"(aoff));
+#pragma unroll
+            for (int i = 0; i < MT; ++i) f.a[i] = *(const __attribute__((address_space(1))) f32x4 *)(a + i * 2048 + aoff);
             if (p - col_base >= 64) {
                 col_base = p;
                 load_cols();
+                asm volatile("" : "+v"(cols));  // waited for here, or every look-up would wait for all loads in flight
             }
             const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * 8;
-            global_char *row = (global_char *)B + (uint64_t)(uint32_t)k0 * row_bytes;
-            if (k0 + 8 <= K) {
+            f.left = K - k0;
+            // past K, where a unit may also start: its last row, dropped when the unit is multiplied
+            global_char *row = (global_char *)B + (uint64_t)(uint32_t)min(k0, K - 1) * row_bytes;
+            const int last = max(f.left - 1, 0);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    uint32_t off = voff;
-                    asm("" : "+s"(row), "+v"(off));  // scalar base + 32-bit offset, instead of a 64-bit vector address per row
-                    f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + off);
-                    row += 2 * (uint64_t)row_bytes;
-                }
-            } else {  // rows past K count as zeros
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    cols_t z;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) z[v] = 0.f;
-                    f.b[t] = z;
-                    if (k0 + 2 * t + kq < K)
-                        f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + voff + 2 * t * (uint64_t)row_bytes);
-                }
+            for (int t = 0; t < 4; ++t) {
+                uint32_t off = (uint32_t)min(2 * t + kq, last) * row_bytes + coff;
+                asm("" : "+s"(row), "+v"(off));  // scalar base + 32-bit offset, instead of a 64-bit vector address per row
+                f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + off);
             }
-            // blocks are [16 k][32-row tile][8 k][lane][4]
-            const f32x4 *a = (const f32x4 *)(a_lane + (int64_t)p * (BR * BR) + (s >> 1) * (BR * 16) + (s & 1) * 256);
-#pragma unroll
-            for (int i = 0; i < MT; ++i) f.a[i] = a[i * 128];
+            asm volatile("" ::: "memory");  // (the loads are issued here, not where the next unit is multiplied)
         };
-        auto multiply = [&](const Unit &f) __attribute__((always_inline)) {
+        auto multiply = [&](Unit &f) __attribute__((always_inline)) {
+            if (f.left < 8)  // rows past K count as zeros
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) f.b[t][v] = 2 * t + kq < f.left ? f.b[t][v] : 0.f;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -221,6 +224,9 @@ static bool launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, h
     return true;
 }
 
+// 64 x 128 tiles by two waves that divide the blocks, rather than by one for twice the columns, where the tiles are many: long
+// block-rows end sooner (18944 x 3584 at 90 %, 2048 columns, 128 / 64 / 32-row blocks 244 / 253 / 241 -> 244 / 242 / 235, geometric
+// lengths 374 / 372 / 276 -> 238 / 231 / 215; 4096 columns 471 / 467 / 467 -> 463 / 466 / 474).
 // The largest wave tile that still gives the chip enough of them, and the narrower one where N would fill the wider one
 // badly.  us at 90 %, 64 x 64 blocks, tiles of 64 x 128 / 64 x 128 by four waves / 32 x 64 by four / 32 x 32 by eight:
 // 18944 x 3584 at 2048 columns 239 / 258 / 267 / -, at 1024 151 / 133 / 140 / 160, at 64 - / - / 19.5 / 16.2;
@@ -231,7 +237,7 @@ static bool launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64), n128 = ceil_div(N, 128);
     const int64_t tall = h->n_brows * BR / 64 * n128;  // tiles of 64 x 128 elements
     if (N >= 4 && 4 * n128 * 8 <= 2 * n64 * 9) {
-        if (tall >= 16 * cus) return launch_f32<BR, MT, 4, BR / (32 * MT), 2, 1>(h, B, C, N, stream);
+        if (tall >= 16 * cus) return launch_f32<BR, MT, 4, 1, 1, 2>(h, B, C, N, stream);
         if (tall >= 3 * cus) return launch_f32<BR, MT, 4, 1, 1, 4>(h, B, C, N, stream);
     }
     if (N >= 2 && 2 * n64 * 8 <= n32 * 9 && 2 * h->n_brows * (BR / 32) * n64 >= 5 * cus)

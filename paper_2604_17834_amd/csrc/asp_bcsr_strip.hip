@@ -82,6 +82,7 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
             if (p - col_base >= 64) {
                 col_base = p;
                 load_cols();
+                asm volatile("" : "+v"(cols));  // waited for here, or every look-up would wait for all loads in flight
             }
             const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * UK;
             const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));

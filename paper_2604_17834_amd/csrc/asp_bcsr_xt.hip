@@ -82,6 +82,7 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_strip_kernel(const int4 *__res
             if (p - col_base >= 64) {
                 col_base = p;
                 load_cols();
+                asm volatile("" : "+v"(cols));  // waited for here, or every look-up would wait for all loads in flight
             }
             const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));
 #pragma unroll
@@ -387,6 +388,7 @@ __global__ __launch_bounds__(W * 64) void bcsr_xt_decode_kernel(const int4 *__re
             if (p - col_base >= 64) {
                 col_base = p;
                 load_cols();
+                asm volatile("" : "+v"(cols));  // waited for here, or every look-up would wait for all loads in flight
             }
             const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));
 #pragma unroll
