@@ -20,7 +20,7 @@ LIB = os.path.join(PKG, "libasyncsparse.so")
 MEASURE_LIB = os.path.join(PKG, "libasyncsparse_measure.so")   # the benchmark's probe kernels: not part of the product
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["asp_api.cpp", "asp_convert.cpp", "asp_reorder.cpp", "asp_bcsr.hip", "asp_bcsr_dma.hip", "asp_bcsr_wide.hip", "asp_bcsr_strip.hip", "asp_bcsr_xt.hip", "asp_bcsr_f32.hip", "asp_wcsr.hip", "asp_wcsr_rows.hip", "asp_wcsr_groups.hip", "asp_wcsr_bf16.hip"]
+SOURCES = ["asp_api.cpp", "asp_convert.cpp", "asp_reorder.cpp", "asp_bcsr.hip", "asp_bcsr_dma.hip", "asp_bcsr_wide.hip", "asp_bcsr_strip.hip", "asp_bcsr_xt.hip", "asp_bcsr_f32.hip", "asp_wcsr.hip", "asp_wcsr_rows.hip", "asp_wcsr_groups.hip", "asp_wcsr_dense.hip", "asp_wcsr_bf16.hip"]
 EXTRA = os.environ.get("ASP_EXTRA_FLAGS", "").split()
 # host-side sanitizers: every -fsanitize= goes to the host compilation only
 HOSTSAN = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host",

@@ -70,6 +70,12 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_g_row_tasks);
     (void)hipFree(h->d_g_chunks);
     (void)hipFree(h->d_teams);
+    (void)hipFree(h->d_dense_rows);
+    (void)hipFree(h->d_dense_ptr);
+    (void)hipFree(h->d_d_row_tasks);
+    (void)hipFree(h->d_d_chunks);
+    (void)hipFree(h->d_d_split_rows);
+    (void)hipFree(h->d_d_teams);
     (void)hipFree(h->d_g_teams);
     (void)hipFree(h->d_g_split_rows);
     (void)hipFree(h->d_c_rank_info);
@@ -241,7 +247,9 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     std::vector<uint8_t> gathered;
     wcsr_build_rows(m, row_ptr, col_idx, es, h->b_row, h->task_cols, h->hw, rows);
     wcsr_build_groups(m, row_ptr, col_idx, values, es, h->b_row, h->task_cols, h->hw, rows, groups);
-    std::vector<int32_t> teams, g_teams;
+    HostDense dense;
+    if (groups.n_groups == 0 && h->dtype == ASP_DT_F32) wcsr_build_dense(m, row_ptr, col_idx, h->b_row, h->task_cols, h->hw, rows, dense);
+    std::vector<int32_t> teams, g_teams, d_teams;
     h->chunk_rows = (int64_t)rows.chunks.size() / 4;
     wcsr_build_teams(rows.n_entries, rows.chunks, rows.tasks, teams);
     h->n_teams = (int64_t)teams.size() / 4;
@@ -261,6 +269,25 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload(&h->d_e_row_ptr, rows.row_ptr.data(), rows.row_ptr.size() * 4, stream))) return s;
         if ((s = upload_runs((void **)&h->d_e_col, col_idx, 4, rows, gathered, stream))) return s;
         if ((s = upload_runs(&h->d_e_val, values, es, rows, gathered, stream))) return s;
+    }
+    if (dense.ranges > 0) {
+        h->n_dense = (int64_t)dense.rows.size() / 4;
+        int64_t left = rows.n_entries;
+        for (size_t i = 0; i < dense.rows.size(); i += 4) left -= row_ptr[dense.rows[i] + 1] - row_ptr[dense.rows[i]];
+        wcsr_build_teams(left, dense.chunks, dense.tasks, d_teams);
+        h->dense_ranges = dense.ranges;
+        h->dense_blocks = dense.blocks;
+        h->n_d_row_tasks = (int64_t)dense.tasks.size() / 4;
+        h->n_d_chunks = (int64_t)dense.chunks.size() / 4;
+        h->n_d_split_rows = (int64_t)dense.split.size() / 4;
+        h->n_d_teams = (int64_t)d_teams.size() / 4;
+        for (size_t i = 2; i < dense.split.size(); i += 4) h->dense_scratch_rows += dense.split[i];
+        if ((s = upload(&h->d_dense_rows, dense.rows.data(), dense.rows.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_dense_ptr, dense.ptr.data(), dense.ptr.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_d_row_tasks, dense.tasks.data(), dense.tasks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_d_chunks, dense.chunks.data(), dense.chunks.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_d_split_rows, dense.split.data(), dense.split.size() * 4, stream))) return s;
+        if ((s = upload(&h->d_d_teams, d_teams.data(), d_teams.size() * 4, stream))) return s;
     }
     if (groups.n_groups > 0) {
         int64_t left = rows.n_entries;

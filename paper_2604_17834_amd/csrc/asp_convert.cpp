@@ -786,6 +786,7 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
         if (longest[i] * W >= MIN_CHUNK * (int64_t)k_used && sum >= 2 * (int64_t)k_used) dense_len = longest[i], dense_width = W;
     }
 
+    out.dense_len = dense_len;
     int64_t in_long_rows = 0;
     for (int64_t len : longest) in_long_rows += len;
     RowRuns runs(out.row_ptr, run_target(entries - in_long_rows));
@@ -1105,6 +1106,72 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     deal_to_xcds(runs.tasks, runs.weight);
     out.row_tasks.swap(runs.tasks);
     out.n_groups = G;
+}
+
+// Nearly dense rows that walk their entries over columns of B in LDS (asp_wcsr_dense.hip): those whose chunks would be cut at the
+// same columns, when a column holds 4.5 of their entries in the mean (2 000 000 rows, band of 27, N = 64, long rows with a tenth
+// of the columns, chunks / so: 32 of them 412 / 420 us, 48 452 / 424, 64 488 / 427) and each has scratch rows for 64 ranges of columns.
+// The rest keeps its lists.
+void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
+                      const HostRows &rows, HostDense &out) {
+    constexpr int64_t MIN_MEET_TENTHS = 45, MIN_RANGES = 64;
+    out = HostDense();
+    int64_t entries = 0, fewest = HostDense::RANGES;
+    int32_t k_used = 1;
+    std::vector<uint8_t> dense((size_t)m, 0);
+    for (size_t i = 0; i < rows.split.size();) {  // (rows are in order: those of a window are together)
+        const int64_t w = rows.split[i] / b_row;
+        int64_t in_window = 0;
+        bool all = true;
+        size_t end = i;
+        for (; end < rows.split.size() && rows.split[end] / b_row == w; end += 4) {
+            const int32_t r = rows.split[end];
+            if (row_ptr[r + 1] - row_ptr[r] < rows.dense_len) {
+                all = false;
+                continue;
+            }
+            entries += row_ptr[r + 1] - row_ptr[r];
+            k_used = std::max(k_used, col_idx[row_ptr[r + 1] - 1] + 1);
+            dense[r] = 1;
+            ++in_window;
+        }
+        // a row's scratch rows: an even share of its window's, or what its chunks had beside rows that stay with theirs
+        const int64_t share = in_window > 0 ? ceil_div(in.window_row_ptr[w + 1] - in.window_row_ptr[w], task_cols) * b_row / in_window : 0;
+        int64_t slot = (int64_t)in.ws_slot[w] * b_row;
+        for (; i < end; i += 4) {
+            if (!dense[rows.split[i]]) continue;
+            fewest = std::min<int64_t>(fewest, all ? share : rows.split[i + 2]);
+            out.rows.insert(out.rows.end(), {rows.split[i], (int32_t)(all ? slot : rows.split[i + 1]), 0, 0});
+            slot += share;
+        }
+    }
+    const int64_t n = (int64_t)out.rows.size() / 4, blocks = ceil_div(k_used, HostDense::COLS);
+    if (n == 0 || 10 * entries < MIN_MEET_TENTHS * k_used || n > 65535 * HostDense::ROWS || std::min(fewest, blocks) < MIN_RANGES) return;
+    out.blocks = blocks;
+    out.ranges = std::min(fewest, blocks);
+    out.ptr.resize((size_t)((blocks + 1) * n));
+    parallel_chunks(n, 1, [&](unsigned, int64_t b, int64_t e) {
+        for (int64_t i = b; i < e; ++i) {
+            const int32_t r = out.rows[4 * i];
+            const int32_t *const lo = col_idx + row_ptr[r], *const hi = col_idx + row_ptr[r + 1], *it = lo;
+            for (int64_t j = 0; j <= blocks; ++j) {
+                it = j == blocks ? hi : std::lower_bound(it, hi, (int32_t)(j * HostDense::COLS));
+                out.ptr[i * (blocks + 1) + j] = (int32_t)(rows.row_ptr[r] + (it - lo));
+            }
+        }
+    }, entries);
+    for (int64_t i = 0; i < n; ++i)
+        out.split.insert(out.split.end(), {out.rows[4 * i], out.rows[4 * i + 1], (int32_t)out.ranges, 0});
+    for (size_t i = 0; i < rows.split.size(); i += 4)
+        if (!dense[rows.split[i]]) out.split.insert(out.split.end(), rows.split.begin() + i, rows.split.begin() + i + 4);
+    out.tasks = rows.tasks;
+    out.chunks = rows.chunks;
+    bool any = false;
+    for (size_t c = 0; c < out.chunks.size(); c += 4) {
+        if (out.chunks[c + 2] < out.chunks[c + 3] && !dense[out.chunks[c]]) any = true;
+        else std::fill(out.chunks.begin() + c, out.chunks.begin() + c + 4, 0);
+    }
+    if (!any) out.chunks.clear();
 }
 
 // Chunks and single rows that a workgroup takes instead of a wave: those with more entries than half of what each of the chip's 8192

@@ -133,9 +133,20 @@ struct HostRows {
     std::vector<int32_t> tasks;       // [..][4] whole rows, see walk_rows (asp_wcsr_rows.hip); empty tasks fill up
     std::vector<int32_t> chunks;      // [..][4] a chunk of a long row each, see walk_rows; empty tasks fill up
     std::vector<int32_t> split;       // [..][4] = {row, first scratch row, scratch rows, 0} of rows longer than task_cols
+    int64_t dense_len = INT64_MAX;    // rows of that many entries and more are nearly dense: cut at the same columns
     std::vector<int32_t> tile_tasks;  // [..][4] as the canonical tasks, of the other windows only; empty tasks fill up
     bool tiles_dealt = false;         // tile_tasks holds one range for each XCD (deal_to_xcds)
     std::vector<int32_t> tile_split;  // the split windows among those
+};
+
+// Nearly dense rows that meet in LDS (wcsr_build_dense, asp_wcsr_dense.hip), and the lists of HostRows without them.
+struct HostDense {
+    static constexpr int COLS = 256, ROWS = 64;  // columns of B at a time; rows to a workgroup
+    static constexpr int64_t RANGES = 256;       // of columns, at most
+    int64_t ranges = 0, blocks = 0;              // ranges 0: the rest is not used
+    std::vector<int32_t> rows;                   // [..][4] = {row, first scratch row, 0, 0}
+    std::vector<int32_t> ptr;                    // [rows][blocks + 1] first entry of each row from a block's first column on
+    std::vector<int32_t> tasks, chunks, split;   // as in HostRows; split: the dense rows first
 };
 
 // Long rows of scattered entries that walk the columns of B together (wcsr_build_groups, asp_wcsr_groups.hip), and the
@@ -170,6 +181,8 @@ void wcsr_build_rows(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, 
                      int32_t task_cols, const HostWcsr &in, HostRows &out);
 void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, const void *values, size_t esize,
                        int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out);
+void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
+                      const HostRows &rows, HostDense &out);
 void wcsr_build_teams(int64_t n_entries, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks, std::vector<int32_t> &teams);
 void wcsr_zero_windows(const std::vector<int32_t> &window_row_ptr, int32_t task_cols,
                        std::vector<int32_t> &zero_windows);
@@ -235,6 +248,11 @@ struct asp_handle {
     int32_t *d_g_teams = nullptr;
     uint64_t *d_group_entries = nullptr;
     int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;
+    // WCSR: nearly dense rows over columns in LDS, and the lists of what is left beside them, for calls with scratch (HostDense)
+    int64_t n_dense = 0, dense_ranges = 0, dense_blocks = 0, dense_scratch_rows = 0;
+    int64_t n_d_row_tasks = 0, n_d_chunks = 0, n_d_split_rows = 0, n_d_teams = 0;
+    int32_t *d_dense_rows = nullptr, *d_dense_ptr = nullptr, *d_d_row_tasks = nullptr, *d_d_chunks = nullptr, *d_d_split_rows = nullptr,
+            *d_d_teams = nullptr;
     float *d_ws = nullptr;          // fp32 scratch, one [b_row][N] tile per slot (asp_reserve)
     int64_t ws_floats = 0;          // its capacity
 };
@@ -284,6 +302,9 @@ void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *
 // the groups of long rows: whether calls of this width (with scratch) use them, and their kernel
 bool wcsr_groups_apply(const asp_handle *h, int64_t N);
 void wcsr_groups_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream);
+// the nearly dense rows: whether calls of this width (with scratch) use them, and their kernel
+bool wcsr_dense_apply(const asp_handle *h, int64_t N);
+void wcsr_dense_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream);
 // rows of split windows = sum of their tasks' partial tiles, in task order
 void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
 // GPU task partition: fills h->d_tasks / h->n_tasks from h->d_row_ptr (wavefront scans)

@@ -391,13 +391,17 @@ __global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__re
 template <typename T>
 static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
     const bool groups = ws && wcsr_groups_apply(h, N);  // long rows run there: the lists without them
-    const int32_t *d_chunks = groups ? h->d_g_chunks : h->d_chunks, *d_row_tasks = groups ? h->d_g_row_tasks : h->d_row_tasks;
-    const int64_t n_chunks = groups ? h->n_g_chunks : h->n_chunks, n_row_tasks = groups ? h->n_g_row_tasks : h->n_row_tasks;
-    const int32_t *d_teams = groups ? h->d_g_teams : h->d_teams;
+    const bool dense = ws && !groups && wcsr_dense_apply(h, N);  // nearly dense rows run there
+    const int32_t *d_chunks = groups ? h->d_g_chunks : dense ? h->d_d_chunks : h->d_chunks;
+    const int32_t *d_row_tasks = groups ? h->d_g_row_tasks : dense ? h->d_d_row_tasks : h->d_row_tasks;
+    const int32_t *d_teams = groups ? h->d_g_teams : dense ? h->d_d_teams : h->d_teams;
+    const int64_t n_chunks = groups ? h->n_g_chunks : dense ? h->n_d_chunks : h->n_chunks;
+    const int64_t n_row_tasks = groups ? h->n_g_row_tasks : dense ? h->n_d_row_tasks : h->n_row_tasks;
     if (groups) wcsr_groups_launch(h, B, N, ws, stream);
+    if (dense) wcsr_dense_launch(h, B, N, ws, stream);
     // a launch takes fewer than 2^32 threads
     const int64_t waves = n_chunks + n_row_tasks, step = (1 << 26) - 32;
-    int64_t n_teams = groups ? h->n_g_teams : h->n_teams;  // (a few thousand)
+    int64_t n_teams = groups ? h->n_g_teams : dense ? h->n_d_teams : h->n_teams;  // (a few thousand)
     for (int64_t first = 0; first < waves || n_teams > 0; first += step, n_teams = 0) {
         const int64_t end = std::min(waves, first + step);
         const int64_t c0 = std::min(first, n_chunks), c1 = std::min(end, n_chunks), t0 = first - c0, t1 = end - c1;
@@ -424,13 +428,14 @@ void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, fl
 
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream) {
     const bool groups = wcsr_groups_apply(h, N);
-    const int32_t *d_split = groups ? h->d_g_split_rows : h->d_split_rows;
-    const int64_t n_split = groups ? h->n_g_split_rows : h->n_split_rows;
+    const bool dense = !groups && wcsr_dense_apply(h, N);
+    const int32_t *d_split = groups ? h->d_g_split_rows : dense ? h->d_d_split_rows : h->d_split_rows;
+    const int64_t n_split = groups ? h->n_g_split_rows : dense ? h->n_d_split_rows : h->n_split_rows;
     if (n_split == 0) return;
     // Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
     // 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
     // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  From lists of 128 on, the graph without that row 950 -> 959: another launch.
-    const bool many = (groups ? h->group_scratch_rows + h->chunk_rows : h->chunk_rows) > 32 * n_split;
+    const bool many = (groups ? h->group_scratch_rows + h->chunk_rows : dense ? h->dense_scratch_rows : h->chunk_rows) > 32 * n_split;
     const int64_t n_many = N > 65535 * 16 ? 0 : many ? n_split : groups ? h->group_many : 0;
 #define ASP_ROWS_SUM(T, COLS, J, FIRST, COUNT)                                                                            \
     if ((COUNT) > 0)                                                                                                      \
