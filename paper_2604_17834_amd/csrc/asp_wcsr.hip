@@ -126,6 +126,34 @@ __device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, 
     return v;
 }
 
+// V = 1 or 2 adjacent columns, N >= V, as with VEC above
+template <int V>
+struct Columns {
+    typedef float any __attribute__((ext_vector_type(V), aligned(4)));
+};
+template <int V>
+__device__ __forceinline__ typename Columns<V>::any gather_few(const float *__restrict__ B, int col, int64_t N, int64_t n) {
+    typename Columns<V>::any v;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = 0.f;
+    if (col >= 0) v = *(const typename Columns<V>::any *)(B + (int64_t)col * N + n);
+    return v;
+}
+template <int V>
+__device__ __forceinline__ void put_few(float *__restrict__ C, int64_t row, int64_t M, int64_t N, int64_t own_n,
+                                        typename Columns<V>::any v, bool split) {
+    if (row >= M || own_n >= N) return;
+    const int64_t n = own_n > N - V ? N - V : own_n;
+    float *p = C + row * N + n;
+    if (split) {
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (n + i >= own_n) unsafeAtomicAdd(p + i, v[i]);
+    } else {
+        __builtin_nontemporal_store(v, (typename Columns<V>::any *)p);
+    }
+}
+
 template <bool VEC, bool NONTEMPORAL = true>
 __device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int64_t M, int64_t N, int64_t own_n, float4 v,
                                      bool split) {
@@ -279,8 +307,11 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 
 // ---- window heights 32 and 64: v_mfma_f32_32x32x2_f32 --------------------------------------------
 // lane l: kq = l / 32 picks one of 2 packed columns of a k step, jl = l % 32 is the MFMA N index;
-// the wave covers 128 columns.  MTW = window height / 32 MFMA row tiles share every gathered B value.
-template <int MTW, bool VEC>
+// the wave covers 32 V columns.  MTW = window height / 32 MFMA row tiles share every gathered B value.
+// N >= V; V = 4, or 2 and 1 where N <= 64 and 32 and most of 128 columns would be multiplied for nothing (and with the registers that
+// they take another wave or two fit a SIMD): 978 077 rows, band of 13, height 64, N = 64 257 -> 171 us, N = 16 245 -> 86; height 32
+// 189 -> 139, 156 -> 61; 30 000 rows, height 64, N = 64 16.6 -> 11.9.
+template <int MTW, int V>
 __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
@@ -294,19 +325,20 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
     const int lane = threadIdx.x & 63, kq = lane >> 5, jl = lane & 31;
     const int4 td = tasks[task];
     if (td.y >= td.z) return;
-    const int64_t own_n0 = (int64_t)nt * 128 + 4 * jl, n0 = lane_column<VEC>(own_n0, N);
+    typedef float cols_t __attribute__((ext_vector_type(V)));
+    const int64_t own_n0 = (int64_t)nt * (32 * V) + V * jl, n0 = own_n0 > N - V ? N - V : own_n0;  // N >= V
 
-    f32x16 acc[MTW][4];
+    f32x16 acc[MTW][V];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < V; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
 
     struct Stage {
         float a[4][MTW];
-        float4 b[4];
+        cols_t b[4];
     };
     // lane group kq takes packed columns 4 kq .. 4 kq + 3 of a tile (k steps h = 0..3; any assignment works as long
     // as A and B agree): its four indices and its four values of a row are one 16-byte load each, and the 32 x 2
@@ -323,17 +355,23 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
             s.a[3][i] = a4.w;
         }
 #pragma unroll
-        for (int h = 0; h < 4; ++h) s.b[h] = gather4<VEC>(B, col[h], N, n0);
+        for (int h = 0; h < 4; ++h) {
+            if constexpr (V == 4) {
+                const float4 v = gather4<true>(B, col[h], N, n0);
+                s.b[h] = cols_t{v.x, v.y, v.z, v.w};
+            } else {
+                s.b[h] = gather_few<V>(B, col[h], N, n0);
+            }
+        }
     };
     auto multiply = [&](const Stage &s) {
 #pragma unroll
         for (int h = 0; h < 4; ++h)
 #pragma unroll
             for (int i = 0; i < MTW; ++i) {
-                acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[h][i], s.b[h].x, acc[i][0], 0, 0, 0);
-                acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[h][i], s.b[h].y, acc[i][1], 0, 0, 0);
-                acc[i][2] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[h][i], s.b[h].z, acc[i][2], 0, 0, 0);
-                acc[i][3] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[h][i], s.b[h].w, acc[i][3], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < V; ++t)
+                    acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[h][i], s.b[h][t], acc[i][t], 0, 0, 0);
             }
     };
 
@@ -358,9 +396,16 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            float4 v = make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
             int row = i * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
-            put4<VEC>(out.base, out.row0 + row, out.rows, N, own_n0, v, out.atomic);
+            if constexpr (V == 4)
+                put4<true>(out.base, out.row0 + row, out.rows, N, own_n0,
+                           make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]), out.atomic);
+            else {
+                typename Columns<V>::any v;
+#pragma unroll
+                for (int t = 0; t < V; ++t) v[t] = acc[i][t][r];
+                put_few<V>(out.base, out.row0 + row, out.rows, N, own_n0, v, out.atomic);
+            }
         }
 }
 
@@ -554,8 +599,18 @@ void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float
 asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws_buf, int64_t ws_floats,
                               hipStream_t stream) {
     if (h->dtype == ASP_DT_BF16) return wcsr_bf16_spmm_launch(h, B, C, N, ws_buf, ws_floats, stream);
-    const WcsrPlan p = wcsr_plan(h, N, true);
+    WcsrPlan p = wcsr_plan(h, N, true);
     const bool vec = N >= 4;
+    // Heights 32 and 64: 32 or 64 columns to a wave where that covers N; 64 also where two such tiles do at height 64, whose 128-column
+    // ones leave a wave to a SIMD (30 000 rows, band of 13, N = 128 16.6 -> 12.3 us, 300 000 rows 99.9 / 97.6; at height 32 8.3 / 9.4,
+    // 72.6 / 75.1), and where three do instead of two of 128 and there are enough of them (N = 160, 300 000 rows, heights 32 / 64 108 / 158
+    // -> 102 / 143; 30 000 rows 13.6 -> 12.6, but at height 64, 469 windows, 17.3 / 20.6).
+    int columns = 4;  // of a lane
+    if (h->b_row > 16) {
+        if (N <= 64) columns = N <= 32 ? 1 : 2;
+        else if (N <= 128 ? h->b_row == 64 : N <= 192 && h->n_tile_tasks >= 900) columns = 2;
+        if (columns < 4) p.n_tiles = (int32_t)ceil_div(N, 32 * columns);
+    }
     // split windows: partial tiles in the scratch buffer when it is large enough, else atomic adds into C
     const bool partial = h->n_split_tasks > 0 && ws_buf && ws_floats >= wcsr_scratch_floats(h, N);
     float *ws = partial ? ws_buf : nullptr;
@@ -574,15 +629,9 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
 #define ASP_W16(NG, VEC, RAGGED, UNIFORM)                                                                           \
     hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, VEC, RAGGED, UNIFORM>), grid, block, 0, stream, tasks, nt, h->d_col_idx, \
                        vals, Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
-#define ASP_W32(MTW)                                                                                                   \
-    do {                                                                                                               \
-        if (vec)                                                                                                       \
-            hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, true>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, \
-                               Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
-        else                                                                                                           \
-            hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, false>), grid, block, 0, stream, tasks, nt, h->d_col_idx,      \
-                               vals, Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols);        \
-    } while (0)
+#define ASP_W32(MTW, V)                                                                                          \
+    hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, V>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bf, Cf, M, N, \
+                       p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
         if (h->b_row == 16) {
             // 256-wide tiles in 168 registers, 3 waves per SIMD, where B and C are well past the 256 MB behind the L2s; in
             // 176, 2 waves, where they are not: the waves of one moment then reach over less of them.  us, N = 256, 3 / 2 waves:
@@ -596,9 +645,13 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
             else if (p.bn == 128) ASP_W16(2, true, false, false);
             else ASP_W16(1, true, false, false);
         } else if (h->b_row == 32) {
-            ASP_W32(1);
+            if (columns == 1) ASP_W32(1, 1);
+            else if (columns == 2) ASP_W32(1, 2);
+            else ASP_W32(1, 4);
         } else {
-            ASP_W32(2);
+            if (columns == 1) ASP_W32(2, 1);
+            else if (columns == 2) ASP_W32(2, 2);
+            else ASP_W32(2, 4);
         }
 #undef ASP_W16
 #undef ASP_W32
