@@ -98,35 +98,24 @@ __global__ __launch_bounds__(256) void wcsr_sum_partials_kernel(const int32_t *_
     }
 }
 
-// 4 adjacent columns n..n+3 of a row, at any alignment.  VEC (N >= 4): n was moved left so that n + 3 < N (own_n, the
-// column it was moved from, tells which columns belong to this lane alone); else one column at a time.
+// 4 adjacent columns n..n+3 of a row, at any alignment, N >= 4: n was moved left so that n + 3 < N (own_n, the column it was
+// moved from, tells which columns belong to this lane alone).
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool VEC>
-__device__ __forceinline__ int64_t lane_column(int64_t own_n, int64_t N) {
-    return VEC && own_n > N - 4 ? N - 4 : own_n;
-}
+__device__ __forceinline__ int64_t lane_column(int64_t own_n, int64_t N) { return own_n > N - 4 ? N - 4 : own_n; }
 
-// wanted: whether the lane has a column of its own (a lane without one may load or not)
-template <bool VEC>
+// wanted: whether the lane has a column of its own (a lane without one may load or not).  (As float4: with the four kept as one
+// vector the tiles of height 16 take 3 to 6 % longer.)
 __device__ __forceinline__ float4 gather4(const float *__restrict__ B, int col, int64_t N, int64_t n, bool wanted = true) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);  // zeros for a pad column (col < 0) or past the edge
-    if (VEC) {
-        if (col >= 0 && wanted) {
-            const f32x4_any u = *(const f32x4_any *)(B + (int64_t)col * N + n);
-            v = make_float4(u.x, u.y, u.z, u.w);
-        }
-    } else if (col >= 0 && n < N) {
-        const float *p = B + (int64_t)col * N + n;
-        v.x = p[0];
-        if (n + 1 < N) v.y = p[1];
-        if (n + 2 < N) v.z = p[2];
-        if (n + 3 < N) v.w = p[3];
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);  // zeros for a pad column (col < 0)
+    if (col >= 0 && wanted) {
+        const f32x4_any u = *(const f32x4_any *)(B + (int64_t)col * N + n);
+        v = make_float4(u.x, u.y, u.z, u.w);
     }
     return v;
 }
 
-// V = 1 or 2 adjacent columns, N >= V, as with VEC above
+// V = 1 or 2 adjacent columns, N >= V, in the same way
 template <int V>
 struct Columns {
     typedef float any __attribute__((ext_vector_type(V), aligned(4)));
@@ -154,26 +143,21 @@ __device__ __forceinline__ void put_few(float *__restrict__ C, int64_t row, int6
     }
 }
 
-template <bool VEC, bool NONTEMPORAL = true>
+template <bool NONTEMPORAL = true>
 __device__ __forceinline__ void put4(float *__restrict__ C, int64_t row, int64_t M, int64_t N, int64_t own_n, float4 v,
                                      bool split) {
     if (row >= M || own_n >= N) return;
-    const int64_t n = lane_column<VEC>(own_n, N);
+    const int64_t n = lane_column(own_n, N);
     float *p = C + row * N + n;
     if (split) {  // (columns shared with another lane are added by that one)
         if (n >= own_n) unsafeAtomicAdd(p, v.x);
-        if (n + 1 >= own_n && n + 1 < N) unsafeAtomicAdd(p + 1, v.y);
-        if (n + 2 >= own_n && n + 2 < N) unsafeAtomicAdd(p + 2, v.z);
-        if (n + 3 >= own_n && n + 3 < N) unsafeAtomicAdd(p + 3, v.w);
-    } else if (VEC && NONTEMPORAL) {
+        if (n + 1 >= own_n) unsafeAtomicAdd(p + 1, v.y);
+        if (n + 2 >= own_n) unsafeAtomicAdd(p + 2, v.z);
+        unsafeAtomicAdd(p + 3, v.w);  // (own_n < N: the lane's own column, moved left or not)
+    } else if (NONTEMPORAL) {
         __builtin_nontemporal_store(f32x4_any{v.x, v.y, v.z, v.w}, (f32x4_any *)p);
-    } else if (VEC) {
-        *(f32x4_any *)p = f32x4_any{v.x, v.y, v.z, v.w};
     } else {
-        p[0] = v.x;
-        if (n + 1 < N) p[1] = v.y;
-        if (n + 2 < N) p[2] = v.z;
-        if (n + 3 < N) p[3] = v.w;
+        *(f32x4_any *)p = f32x4_any{v.x, v.y, v.z, v.w};
     }
 }
 
@@ -202,7 +186,9 @@ __device__ __forceinline__ SplitTarget split_target(int4 td, int b_row, float *C
 // RAGGED, for 256-wide tiles whose rows end inside a cache line: lanes past N load nothing, and stores are ordinary ones, so
 // that L2 completes the lines that two rows share (band of 27, 500 000 rows, N = 200: 262 -> 254 us; narrower tiles
 // gain nothing from either, and lose up to 20 % with ordinary stores).
-template <int NG, bool VEC, bool RAGGED, bool UNIFORM>
+// N >= V; V = 4 columns to a lane, 2 and 1 (with NG = 1) where N <= 32 and 16: 1 000 000 rows, band of 23, N = 29 114 -> 87 us, N = 16
+// 90 -> 49; 30 000 rows 5.8 -> 5.1, 5.3 -> 4.4.
+template <int NG, bool RAGGED, bool UNIFORM, int V>
 __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                           const int32_t *__restrict__ window_col_idx,
                                                           const float *__restrict__ values,
@@ -215,18 +201,20 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
     const int lane = threadIdx.x & 63, kq = lane >> 4, jl = lane & 15;
     const int4 td = tasks[task];  // window, first packed column, end packed column, split flag
     if (td.y >= td.z) return;     // fills up a list
-    int64_t n0[NG];  // first of the lane's 4 columns in each group
+    static_assert(V == 4 || (NG == 1 && !RAGGED), "narrow tiles");
+    typedef float cols_t __attribute__((ext_vector_type(V)));
+    int64_t n0[NG];  // first of the lane's columns in each group
 #pragma unroll
-    for (int g = 0; g < NG; ++g) n0[g] = lane_column<VEC>((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N);
+    for (int g = 0; g < NG; ++g) n0[g] = V == 4 ? lane_column((int64_t)nt * (64 * NG) + 64 * g + 4 * jl, N) : V * jl > N - V ? N - V : V * jl;
     bool wanted[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) wanted[g] = !RAGGED || (int64_t)nt * (64 * NG) + 64 * g + 4 * jl < N;
 
-    f32x4 acc[NG][4];
+    f32x4 acc[NG][V];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < V; ++t) acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Software pipeline over chunks of D tiles (D*8 packed columns): while chunk c is multiplied, the B
     // rows and A values of chunk c+1 are in flight and the column indices of chunk c+2 are being read,
@@ -234,7 +222,7 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
     constexpr int D = NG >= 2 ? 1 : 2;
     struct Chunk {
         float a[D][2];
-        float4 b[D][2][NG];
+        cols_t b[D][2][NG];
     };
     const int tile0 = td.y >> 3, tile1 = td.z >> 3;
     // Which packed column a lane multiplies in which k step is free as long as A and B agree: lane group kq takes
@@ -259,7 +247,14 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int g = 0; g < NG; ++g) c.b[d][h][g] = gather4<VEC>(B, idx[d][h], N, n0[g], wanted[g]);
+                for (int g = 0; g < NG; ++g) {
+                    if constexpr (V == 4) {
+                        const float4 v = gather4(B, idx[d][h], N, n0[g], wanted[g]);
+                        c.b[d][h][g] = cols_t{v.x, v.y, v.z, v.w};
+                    } else {
+                        c.b[d][h][g] = gather_few<V>(B, idx[d][h], N, n0[g]);
+                    }
+                }
         }
     };
     auto multiply = [&](int base, const Chunk &c) {
@@ -270,10 +265,9 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
-                    acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[d][h], c.b[d][h][g].x, acc[g][0], 0, 0, 0);
-                    acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[d][h], c.b[d][h][g].y, acc[g][1], 0, 0, 0);
-                    acc[g][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[d][h], c.b[d][h][g].z, acc[g][2], 0, 0, 0);
-                    acc[g][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[d][h], c.b[d][h][g].w, acc[g][3], 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < V; ++t)
+                        acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[d][h], c.b[d][h][g][t], acc[g][t], 0, 0, 0);
                 }
         }
     };
@@ -299,9 +293,15 @@ __global__ __launch_bounds__(256) void wcsr16_spmm_kernel(const int4 *__restrict
     for (int g = 0; g < NG; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float4 v = make_float4(acc[g][0][r], acc[g][1][r], acc[g][2][r], acc[g][3][r]);
-            put4<VEC, !RAGGED>(out.base, out.row0 + 4 * kq + r, out.rows, N, (int64_t)nt * (64 * NG) + 64 * g + 4 * jl, v,
-                               out.atomic);
+            if constexpr (V == 4) {
+                put4<!RAGGED>(out.base, out.row0 + 4 * kq + r, out.rows, N, (int64_t)nt * (64 * NG) + 64 * g + 4 * jl,
+                              make_float4(acc[g][0][r], acc[g][1][r], acc[g][2][r], acc[g][3][r]), out.atomic);
+            } else {
+                typename Columns<V>::any v;
+#pragma unroll
+                for (int t = 0; t < V; ++t) v[t] = acc[g][t][r];
+                put_few<V>(out.base, out.row0 + 4 * kq + r, out.rows, N, V * jl, v, out.atomic);
+            }
         }
 }
 
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
             if constexpr (V == 4) {
-                const float4 v = gather4<true>(B, col[h], N, n0);
+                const float4 v = gather4(B, col[h], N, n0);
                 s.b[h] = cols_t{v.x, v.y, v.z, v.w};
             } else {
                 s.b[h] = gather_few<V>(B, col[h], N, n0);
@@ -398,8 +398,8 @@ __global__ __launch_bounds__(256, 2) void wcsr32_spmm_kernel(const int4 *__restr
         for (int r = 0; r < 16; ++r) {
             int row = i * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
             if constexpr (V == 4)
-                put4<true>(out.base, out.row0 + row, out.rows, N, own_n0,
-                           make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]), out.atomic);
+                put4(out.base, out.row0 + row, out.rows, N, own_n0,
+                     make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]), out.atomic);
             else {
                 typename Columns<V>::any v;
 #pragma unroll
@@ -600,7 +600,6 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
                               hipStream_t stream) {
     if (h->dtype == ASP_DT_BF16) return wcsr_bf16_spmm_launch(h, B, C, N, ws_buf, ws_floats, stream);
     WcsrPlan p = wcsr_plan(h, N, true);
-    const bool vec = N >= 4;
     // Heights 32 and 64: 32 or 64 columns to a wave where that covers N; 64 also where two such tiles do at height 64, whose 128-column
     // ones leave a wave to a SIMD (30 000 rows, band of 13, N = 128 16.6 -> 12.3 us, 300 000 rows 99.9 / 97.6; at height 32 8.3 / 9.4,
     // 72.6 / 75.1), and where three do instead of two of 128 and there are enough of them (N = 160, 300 000 rows, heights 32 / 64 108 / 158
@@ -626,8 +625,8 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         const float *vals = (const float *)h->d_values;
         const float *Bf = (const float *)B;
         float *Cf = (float *)C;
-#define ASP_W16(NG, VEC, RAGGED, UNIFORM)                                                                           \
-    hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, VEC, RAGGED, UNIFORM>), grid, block, 0, stream, tasks, nt, h->d_col_idx, \
+#define ASP_W16(NG, RAGGED, UNIFORM, V)                                                                           \
+    hipLaunchKernelGGL((wcsr16_spmm_kernel<NG, RAGGED, UNIFORM, V>), grid, block, 0, stream, tasks, nt, h->d_col_idx, \
                        vals, Bf, Cf, M, N, p.n_tiles, h->tiles_dealt, ws, h->d_ws_slot, h->d_row_ptr, h->task_cols)
 #define ASP_W32(MTW, V)                                                                                          \
     hipLaunchKernelGGL((wcsr32_spmm_kernel<MTW, V>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bf, Cf, M, N, \
@@ -637,13 +636,14 @@ asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
             // 176, 2 waves, where they are not: the waves of one moment then reach over less of them.  us, N = 256, 3 / 2 waves:
             // 60 000 rows, band of 27 43 / 34, 500 000 rows 270 / 301; N = 200, 300 000 rows, band of 9 126 / 121.
             const bool far = (h->m + h->k) * N * 4 >= (512ll << 20);
-            if (!vec) ASP_W16(1, false, false, false);  // N < 4: one tile of any width
-            else if (p.bn == 256 && N % 32 != 0 && far) ASP_W16(4, true, true, true);
-            else if (p.bn == 256 && N % 32 != 0) ASP_W16(4, true, true, false);
-            else if (p.bn == 256 && far) ASP_W16(4, true, false, true);
-            else if (p.bn == 256) ASP_W16(4, true, false, false);
-            else if (p.bn == 128) ASP_W16(2, true, false, false);
-            else ASP_W16(1, true, false, false);
+            if (N <= 16) ASP_W16(1, false, false, 1);
+            else if (N <= 32) ASP_W16(1, false, false, 2);
+            else if (p.bn == 256 && N % 32 != 0 && far) ASP_W16(4, true, true, 4);
+            else if (p.bn == 256 && N % 32 != 0) ASP_W16(4, true, false, 4);
+            else if (p.bn == 256 && far) ASP_W16(4, false, true, 4);
+            else if (p.bn == 256) ASP_W16(4, false, false, 4);
+            else if (p.bn == 128) ASP_W16(2, false, false, 4);
+            else ASP_W16(1, false, false, 4);
         } else if (h->b_row == 32) {
             if (columns == 1) ASP_W32(1, 1);
             else if (columns == 2) ASP_W32(1, 2);

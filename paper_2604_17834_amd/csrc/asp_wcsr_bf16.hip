@@ -28,7 +28,9 @@ namespace asp {
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int MTW>
+// Tiles of 16 J columns: J = 8, 4 and 2 where N <= 64 and 32 (as much less to multiply and to keep): 1 000 000 rows, band of 23, N = 29,
+// heights 16 / 32 / 64 76 / 66 / 89 -> 64 / 47 / 64 us, N = 64 93 / 88 / 102 -> 92 / 80 / 100.
+template <int MTW, int J>
 __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restrict__ tasks, int n_tasks,
                                                              const int32_t *__restrict__ window_col_idx,
                                                              const uint16_t *__restrict__ values,
@@ -48,7 +50,7 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
     const int lane = threadIdx.x & 63, h = lane >> 4, p = lane & 15;
     // chunk c of the tile = 8 columns from chunk_col(c): chunks that would pass N end there instead and repeat columns of
     // their neighbour (the same bits), so that every access is 16 bytes at any N >= 8 and any alignment
-    const int64_t n0 = (int64_t)nt * 128;
+    const int64_t n0 = (int64_t)nt * (16 * J);
     auto chunk_col = [&](int c) { return n0 + 8 * c < N - 8 ? n0 + 8 * c : N - 8; };
     const int64_t n = chunk_col(p);
     const int tile0 = td.y >> 3, tile1 = td.z >> 3;
@@ -73,7 +75,7 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             v[q] = make_uint4(0, 0, 0, 0);  // pads (index -1) contribute zeros
-            if (ix.c[q] >= 0) v[q] = __builtin_bit_cast(uint4, *(const u32x4_any *)(B + (int64_t)ix.c[q] * N + n));
+            if (ix.c[q] >= 0 && (J == 8 || p < 2 * J)) v[q] = __builtin_bit_cast(uint4, *(const u32x4_any *)(B + (int64_t)ix.c[q] * N + n));
         }
     };
     auto load_a = [&](int st, bf16x8 (&af)[MTW]) {
@@ -92,11 +94,11 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
         for (int q = 0; q < 8; ++q) *(uint4 *)(sb + (q * 4 + h) * 256 + ((p ^ ((q & 3) << 2)) * 16)) = v[q];
     };
 
-    f32x4 acc[MTW][8];
+    f32x4 acc[MTW][J];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < J; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto compute = [&](const bf16x8 (&af)[MTW]) {
         // transposing read: lane i of a 16-lane group addresses row i/4 of its k group and the 4 columns of
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
         const int j4 = p >> 2, c = p & 3;
         const uint8_t *row = sb + (j4 * 4 + h) * 256;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < J; ++j) {
             const uint8_t *p0 = row + ((((j >> 1) * 4 + c) ^ (j4 << 2)) * 16) + (j & 1) * 8;
             short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3))) *)(p0));
             short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -143,7 +145,7 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
         for (int i = 0; i < MTW; ++i) {
             const int64_t grow = row0 + i * 16 + p;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < J / 2; ++t) {
                 const int64_t gcol = chunk_col(4 * t + h);
                 if (grow < M && n0 + t * 32 + h * 8 < N) {
                     bf16x4 a = __builtin_convertvector(acc[i][2 * t], bf16x4);      // round to nearest even
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(256) void wcsr_bf16_spmm_kernel(const int4 *__restr
         for (int i = 0; i < MTW; ++i) {
             float *wr = ws + (slot * BRW + i * 16 + p) * N;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < J / 2; ++t) {
                 const int64_t gcol = chunk_col(4 * t + h);
                 if (n0 + t * 32 + h * 8 < N) {
                     *(f32x4_any *)(wr + gcol) = acc[i][2 * t];
@@ -226,18 +228,27 @@ asp_status_t wcsr_bf16_spmm_launch(const asp_handle *h, const void *B, void *C, 
         }
     } else {
         wcsr_rows_launch(h, B, C, N, ws, stream);
-        const int n_tiles = (int)ceil_div(N, 128);
+        const int j = N <= 32 ? 2 : N <= 64 ? 4 : 8, n_tiles = (int)ceil_div(N, 16 * j);
         const int64_t step = tasks_per_launch(n_tiles);
         for (int64_t first = 0; first < h->n_tile_tasks; first += step) {
             const int nt = (int)std::min(step, h->n_tile_tasks - first);
             const dim3 grid = tile_grid(nt, n_tiles, h->tiles_dealt), block(256);
             const int4 *tasks = (const int4 *)h->d_tile_tasks + first;
-#define ASP_WB(MTW)                                                                                                 \
-    hipLaunchKernelGGL((wcsr_bf16_spmm_kernel<MTW>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bh, Ch, \
+#define ASP_WB(MTW, J)                                                                                                 \
+    hipLaunchKernelGGL((wcsr_bf16_spmm_kernel<MTW, J>), grid, block, 0, stream, tasks, nt, h->d_col_idx, vals, Bh, Ch, \
                        ws, h->d_ws_slot, h->d_row_ptr, h->task_cols, M, N, n_tiles, h->tiles_dealt)
-            if (h->b_row == 16) ASP_WB(1);
-            else if (h->b_row == 32) ASP_WB(2);
-            else ASP_WB(4);
+#define ASP_WB_ROWS(MTW)             \
+    if (j == 2) ASP_WB(MTW, 2);      \
+    else if (j == 4) ASP_WB(MTW, 4); \
+    else ASP_WB(MTW, 8)
+            if (h->b_row == 16) {
+                ASP_WB_ROWS(1);
+            } else if (h->b_row == 32) {
+                ASP_WB_ROWS(2);
+            } else {
+                ASP_WB_ROWS(4);
+            }
+#undef ASP_WB_ROWS
 #undef ASP_WB
         }
         wcsr_rows_sum_launch(h, C, N, ws, stream);
