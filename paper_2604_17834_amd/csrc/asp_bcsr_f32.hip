@@ -10,9 +10,8 @@
 // A load has no branch: with a case for rows past K in it the compiler left the loads of A to where they are multiplied, and every
 // look-up of a block column waited for all loads in flight.  Of 60 products (1000 to 9000 rows, 64 to 2048 columns) 0.89 of the
 // time in the mean, 0.80 at best; 9000 x 4000, 50 %, 64 x 64 blocks, 1024 columns 380 -> 327 us.
-// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, before -> now: N = 8192 999 / 958 / 1141 -> 923 / 919 / 1000 us (121 TFLOP/s;
-// the same MFMAs on registers reach 149), N = 2048 301 / 276 / 306 -> 253 / 253 / 260, N = 64 140 / 83 / 63 -> 17 / 16 / 15
-// (both builds in turn in one process; clocks move all of them by 5 % together).
+// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, through LDS -> so: N = 2048 301 / 276 / 306 -> 244 / 242 / 235 us (116 to 119 TFLOP/s;
+// the same MFMAs on registers reach 149), N = 64 140 / 83 / 63 -> 17 / 16 / 15 (clocks move all of them by 5 % together).
 //
 // Operand layouts
 //   A  blocks are pre-permuted on the host (bcsr_pack_fragments_f32): for every 32-row tile and group of
