@@ -1108,32 +1108,43 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     out.n_groups = G;
 }
 
-// Nearly dense rows that walk their entries over columns of B in LDS (asp_wcsr_dense.hip): those whose chunks would be cut at the
-// same columns, when a column holds 4.5 of their entries in the mean (2 000 000 rows, band of 27, N = 64, long rows with a tenth
-// of the columns, chunks / so: 32 of them 412 / 420 us, 48 452 / 424, 64 488 / 427) and each has scratch rows for 64 ranges of columns.
-// The rest keeps its lists.
+// Nearly dense rows that walk their entries over columns of B in LDS (asp_wcsr_dense.hip): of those whose chunks would be cut at the
+// same columns, in order and 64 at a time, as a workgroup takes them and reads all of B for them, the ones among which a column holds
+// 4.5 entries in the mean (2 000 000 rows, band of 27, N = 64, long rows with a tenth of the columns, chunks / so: 32 of them 412 / 420
+// us, 48 452 / 424, 64 488 / 427), when each of them has scratch rows for 64 ranges of columns.  (So a row has 18 entries in a block of
+// 256 columns in the mean, and the table of their first entries takes a 36th of the entries' bytes at most.)  The rest keeps its lists.
 void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
                       const HostRows &rows, HostDense &out) {
     constexpr int64_t MIN_MEET_TENTHS = 45, MIN_RANGES = 64;
     out = HostDense();
-    int64_t entries = 0, fewest = HostDense::RANGES;
+    auto length = [&](int32_t r) { return (int64_t)row_ptr[r + 1] - row_ptr[r]; };
     int32_t k_used = 1;
+    std::vector<int32_t> candidates;  // (rows are in order: those of a window are together)
+    for (size_t i = 0; i < rows.split.size(); i += 4)
+        if (length(rows.split[i]) >= rows.dense_len) {
+            candidates.push_back(rows.split[i]);
+            k_used = std::max(k_used, col_idx[row_ptr[rows.split[i] + 1] - 1] + 1);
+        }
+    int64_t entries = 0;
     std::vector<uint8_t> dense((size_t)m, 0);
-    for (size_t i = 0; i < rows.split.size();) {  // (rows are in order: those of a window are together)
+    for (size_t c = 0; c < candidates.size(); c += HostDense::ROWS) {
+        const size_t end = std::min(candidates.size(), c + HostDense::ROWS);
+        int64_t sum = 0;
+        for (size_t i = c; i < end; ++i) sum += length(candidates[i]);
+        if (10 * sum < MIN_MEET_TENTHS * k_used) continue;
+        for (size_t i = c; i < end; ++i) dense[candidates[i]] = 1;
+        entries += sum;
+    }
+    if (entries == 0) return;
+    int64_t fewest = HostDense::RANGES;
+    for (size_t i = 0; i < rows.split.size();) {
         const int64_t w = rows.split[i] / b_row;
         int64_t in_window = 0;
         bool all = true;
         size_t end = i;
         for (; end < rows.split.size() && rows.split[end] / b_row == w; end += 4) {
-            const int32_t r = rows.split[end];
-            if (row_ptr[r + 1] - row_ptr[r] < rows.dense_len) {
-                all = false;
-                continue;
-            }
-            entries += row_ptr[r + 1] - row_ptr[r];
-            k_used = std::max(k_used, col_idx[row_ptr[r + 1] - 1] + 1);
-            dense[r] = 1;
-            ++in_window;
+            if (dense[rows.split[end]]) ++in_window;
+            else all = false;
         }
         // a row's scratch rows: an even share of its window's, or what its chunks had beside rows that stay with theirs
         const int64_t share = in_window > 0 ? ceil_div(in.window_row_ptr[w + 1] - in.window_row_ptr[w], task_cols) * b_row / in_window : 0;
@@ -1146,7 +1157,7 @@ void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx,
         }
     }
     const int64_t n = (int64_t)out.rows.size() / 4, blocks = ceil_div(k_used, HostDense::COLS);
-    if (n == 0 || 10 * entries < MIN_MEET_TENTHS * k_used || n > 65535 * HostDense::ROWS || std::min(fewest, blocks) < MIN_RANGES) return;
+    if (n > 65535 * HostDense::ROWS || std::min(fewest, blocks) < MIN_RANGES) return;
     out.blocks = blocks;
     out.ranges = std::min(fewest, blocks);
     out.ptr.resize((size_t)((blocks + 1) * n));

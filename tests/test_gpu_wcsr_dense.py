@@ -1,5 +1,5 @@
-"""Nearly dense rows of a WCSR matrix in fp32 that are walked over columns of B in LDS: more than the 64 rows of one workgroup, an odd
-width, columns that no row stores, rows that are empty in whole blocks of columns or full in some, beside shorter rows.
+"""Nearly dense rows of a WCSR matrix in fp32 that are walked over columns of B in LDS: more than the 64 rows of one workgroup (a
+few, which stay with their chunks, and enough for a second one), an odd width, columns that no row stores, rows that are empty in whole blocks of columns or full in some, beside shorter rows.
 
 1e-5 * S, S = |A| x |B| from the oracle, as everywhere in fp32; and, from the 64-bit result, no further than by chunks."""
 import numpy as np
@@ -13,7 +13,7 @@ from paper_2604_17834_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_dense,k,N,height", [(64, 530_001, 64, 16), (70, 300_007, 131, 16), (48, 530_001, 65, 64)])
+@pytest.mark.parametrize("n_dense,k,N,height", [(64, 530_001, 64, 16), (70, 300_007, 131, 16), (112, 300_007, 131, 16), (48, 530_001, 65, 64)])
 def test_dense_rows(n_dense, k, N, height):
     rng = np.random.default_rng(n_dense + N)
     m, stored = 16 * (n_dense + 4), k - 100

@@ -117,3 +117,23 @@ def test_no_groups_of_short_pieces(lists_of):
     for task_cols, groups in ((32, False), (40, False), (48, True)):
         got = lists_of("groups", 9000, 40000, 0, task_cols, 4, 900, 64, 70, 5)
         assert (got["groups"][0][0] > 0) == groups
+
+
+@pytest.mark.parametrize("m,k,height,task_cols,lengths", [
+    (6000, 250000, 16, 40, [200]),                             # 94 times 64 rows, 0.05 entries of each 64 in a column
+    (6000, 100000, 16, 40, [200]),
+    (6400, 200000, 64, 32, [100, 400]),
+    (44 * 16, 100000, 16, 512, [10000] + [2] * 15),            # 4.4 entries a column
+    (64 * 16, 100000, 16, 512, [6000] + [2] * 15),
+])
+def test_no_dense_rows_where_64_of_them_do_not_meet(lists_of, m, k, height, task_cols, lengths):
+    assert lists_of("dense", m, k, height, task_cols, *lengths)["dense"][0][0] == 0
+
+
+@pytest.mark.parametrize("n,taken", [(46, 46), (64, 64), (65, 64), (108, 64), (109, 109), (127, 127), (130, 128)])
+def test_dense_rows_are_taken_64_at_a_time(lists_of, n, taken):
+    got = lists_of("dense", 16 * n, 100000, 16, 512, 10000, 300, *[2] * 14)
+    ranges, blocks, rows, table = got["dense"][0]
+    assert rows == taken and 64 <= ranges <= min(256, blocks) and blocks == 391
+    assert 10 * got["fewest"][0][0] >= 45 * 99900 and 36 * 4 * table <= 8 * 10000 * rows
+    assert len(got["row"]) == 16 * n and all(diff == 0 and times == 1 for _, diff, times in got["row"])

@@ -13,6 +13,9 @@
 //                    tile); and how many groups there are, the entries of their largest task and of all, the most terms of a
 //                    sum in a task, the scratch rows there are and that they use, the columns that near rows meet in, and how many
 //                    rows have their scratch rows added by many threads, the fewest of one and the most of another
+//   dense M K H T L..  M rows of K columns with L.. entries in turn, spread over all, in windows of H rows, tasks of T columns: the
+//                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
+//                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
 //   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
 //                    tokens on 256 compute units take in asp_spmm_xt, 0: none
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -229,6 +232,87 @@ static int groups(int64_t m, int64_t k, int64_t w, int32_t task_cols, size_t esi
     return 0;
 }
 
+// Rows of L.. entries in turn over all k columns, in fp32 (1, 2, 3), and what is made of them.
+struct Spread {
+    std::vector<int32_t> rp{0}, ci;
+    std::vector<float> values;
+    asp::HostWcsr hw;
+    asp::HostRows rows;
+    std::vector<int64_t> at;  // where the entries walked row by row are
+    int64_t slots = 0;
+
+    bool make(int64_t m, int64_t k, int32_t height, int32_t task_cols, const std::vector<int32_t> &lengths) {
+        for (int64_t r = 0; r < m; ++r) {
+            const int64_t n = lengths[r % lengths.size()];
+            for (int64_t j = 0; j < n; ++j) ci.push_back((int32_t)(j * k / n + (r * 7919 + j) % std::max<int64_t>(1, k / n)));
+            rp.push_back((int32_t)ci.size());
+        }
+        for (size_t e = 0; e < ci.size(); ++e) values.push_back((float)(1 + e % 3));
+        if (!asp::csr_to_wcsr(m, k, rp.data(), ci.data(), values.data(), 4, height, 8, hw)) return false;
+        for (size_t i = 0; i + 1 < hw.window_row_ptr.size(); ++i) {
+            const int64_t n = hw.window_row_ptr[i + 1] - hw.window_row_ptr[i];
+            hw.ws_slot.push_back(n > task_cols ? (int32_t)slots : -1);
+            if (n > task_cols) slots += asp::ceil_div(n, task_cols);
+        }
+        asp::wcsr_build_rows(m, rp.data(), ci.data(), 4, height, task_cols, hw, rows);
+        for (auto &r : rows.runs)
+            for (int64_t p = r.first; p < r.second; ++p) at.push_back(p);
+        return true;
+    }
+    double walk(int64_t e0, int64_t e1) const {
+        double sum = 0;
+        for (int64_t e = e0; e < e1; ++e) sum += (1 + at[e] % 3) * (double)(ci[at[e]] % 13 + 1);
+        return sum;
+    }
+};
+
+static int dense(int64_t m, int64_t k, int32_t height, int32_t task_cols, const std::vector<int32_t> &lengths) {
+    Spread a;
+    if (!a.make(m, k, height, task_cols, lengths)) return 1;
+    asp::HostDense d;
+    asp::wcsr_build_dense(m, a.rp.data(), a.ci.data(), height, task_cols, a.hw, a.rows, d);
+    const int64_t n = d.ranges > 0 ? (int64_t)d.rows.size() / 4 : 0;
+    std::printf("dense %lld %lld %lld %lld\n", (long long)d.ranges, (long long)d.blocks, (long long)n, (long long)d.ptr.size());
+    if (n == 0) return 0;
+    std::vector<double> ws(a.slots * height, 0), c(m, 0);
+    std::vector<int> ws_times(a.slots * height, 0), times(m, 0);
+    int64_t fewest = INT64_MAX, entries = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t *ptr = &d.ptr[i * (d.blocks + 1)], row = d.rows[4 * i];
+        if (i % asp::HostDense::ROWS == 0 && i > 0) fewest = std::min(fewest, entries), entries = 0;
+        entries += ptr[d.blocks] - ptr[0];
+        if (ptr[0] != a.rows.row_ptr[row] || ptr[d.blocks] != a.rows.row_ptr[row + 1]) return std::printf("ends of row %d\n", row), 1;
+        for (int64_t x = 0; x < d.ranges; ++x) {
+            const int64_t slot = d.rows[4 * i + 1] + x;
+            for (int64_t b = d.blocks * x / d.ranges; b < d.blocks * (x + 1) / d.ranges; ++b) {
+                for (int64_t e = ptr[b]; e < ptr[b + 1]; ++e)
+                    if (a.ci[a.at[e]] / asp::HostDense::COLS != b) return std::printf("entry %lld in block %lld\n", (long long)e, (long long)b), 1;
+                ws.at(slot) += a.walk(ptr[b], ptr[b + 1]);
+            }
+            ++ws_times[slot];
+        }
+    }
+    std::printf("fewest %lld\n", (long long)std::min(fewest, entries));
+    for (size_t i = 0; i < d.chunks.size(); i += 4)
+        if (d.chunks[i + 2] < d.chunks[i + 3]) ws.at(d.chunks[i + 1]) = a.walk(d.chunks[i + 2], d.chunks[i + 3]), ++ws_times[d.chunks[i + 1]];
+    for (size_t i = 0; i < d.tasks.size(); i += 4)
+        for (int64_t r = d.tasks[i]; r < d.tasks[i] + d.tasks[i + 1]; ++r) c.at(r) = a.walk(a.rows.row_ptr[r], a.rows.row_ptr[r + 1]), ++times[r];
+    for (size_t i = 0; i < d.split.size(); i += 4) {
+        for (int64_t j = d.split[i + 1]; j < d.split[i + 1] + d.split[i + 2]; ++j) {
+            c.at(d.split[i]) += ws.at(j);
+            if (ws_times[j] != 1) return std::printf("scratch row %lld written %d times\n", (long long)j, ws_times[j]), 1;
+        }
+        ++times[d.split[i]];
+    }
+    for (int64_t r = 0; r < m; ++r) {
+        if (a.rows.row_ptr[r + 1] == a.rows.row_ptr[r] && a.rp[r + 1] > a.rp[r]) continue;  // by tiles
+        double want = 0;
+        for (int64_t e = a.rp[r]; e < a.rp[r + 1]; ++e) want += (1 + e % 3) * (double)(a.ci[e] % 13 + 1);
+        std::printf("row %lld %lld %d\n", (long long)r, (long long)(c[r] - want), times[r]);
+    }
+    return 0;
+}
+
 static int xt(char **argv) {
     asp_handle h;
     h.b_row = std::atoi(argv[0]), h.n_brows = std::atoll(argv[1]), h.n_units = std::atoll(argv[2]), h.hb.max_blocks = std::atoll(argv[3]);
@@ -250,6 +334,8 @@ int main(int argc, char **argv) {
     if (is("shares", 2)) return shares(lengths(2));
     if (is("groups", 7))
         return groups(std::atoll(argv[2]), std::atoll(argv[3]), std::atoll(argv[4]), std::atoi(argv[5]), std::atoll(argv[6]), lengths(7));
+    if (is("dense", 6))
+        return dense(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
     if (is("ring", 8))
         return ring(std::atoi(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6]) != 0,
