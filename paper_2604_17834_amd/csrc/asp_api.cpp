@@ -272,9 +272,8 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     }
     if (dense.ranges > 0) {
         h->n_dense = (int64_t)dense.rows.size() / 4;
-        int64_t left = rows.n_entries;
-        for (size_t i = 0; i < dense.rows.size(); i += 4) left -= row_ptr[dense.rows[i] + 1] - row_ptr[dense.rows[i]];
-        wcsr_build_teams(left, dense.chunks, dense.tasks, d_teams);
+        // (by the entries of all rows, as above: a whole row is summed alike by both lists)
+        wcsr_build_teams(rows.n_entries, dense.chunks, dense.tasks, d_teams);
         h->dense_ranges = dense.ranges;
         h->dense_blocks = dense.blocks;
         h->n_d_row_tasks = (int64_t)dense.tasks.size() / 4;

@@ -288,7 +288,8 @@ __device__ __forceinline__ void walk_chunk(int e0, int e1, const int32_t *__rest
 // Before those: teams[t] = {row, scratch row or -1: the row is here whole, first entry, end entry}, n_teams of them, a workgroup to
 // each, whose waves take a quarter of the entries and add their sums in LDS, in order.  Where a launch is so small that its longest
 // chunk or row sets its time (wcsr_build_teams): a wave takes 0.4 us for every 8 entries, 25 us for 512, however few others there are.
-// (Whole rows are walked in the same order at every width: a slice of B's columns gives a slice of C, bit for bit.)
+// (Whole rows are walked in the same order at every width unless the handle has groups, which the width decides on: a slice of B's
+// columns gives a slice of C there, bit for bit.)
 template <typename T, int E, int CE, int CL>
 __global__ __launch_bounds__(256) void wcsr_rows_kernel(const int4 *__restrict__ teams, int n_teams,
                                                         const int4 *__restrict__ chunks, int n_chunks,

@@ -50,3 +50,32 @@ def test_dense_rows(n_dense, k, N, height):
     assert np.isfinite(got).all() and (np.abs(got - ref) <= 1e-5 * S).all()
     dense = np.diff(row_ptr) > 10000
     assert np.linalg.norm((got - ref)[dense]) <= 3e-7 * np.linalg.norm(ref[dense])
+
+
+def test_whole_rows_do_not_depend_on_the_width():
+    """Whole rows beside dense ones, either side of the length from which a workgroup shares a row (172 entries: all entries / 16384): a
+    slice of B's columns gives a slice of C, bit for bit, at a width that walks the dense rows in chunks (63) and one that does not."""
+    rng = np.random.default_rng(3)
+    n_dense, k = 48, 530_001
+    whole = [64, 65, 66, 80, 100, 128, 150, 170, 171, 172, 173, 174, 200, 300, 400, 511, 512]
+    lengths = np.full(16 * n_dense, 2)
+    lengths[3::16] = k // 9
+    lengths[5::16] = (whole * 3)[:n_dense]
+    cols = [np.unique(rng.choice(k, n, replace=False)) for n in lengths]
+    row_ptr = np.r_[0, np.cumsum(lengths)].astype(np.int32)
+    values = rng.uniform(-1, 1, row_ptr[-1]).astype(np.float32)
+    m = len(lengths)
+    h = asp.asp_create_from_csr("wcsr", "f32", 16, 8, m, k, row_ptr, np.concatenate(cols).astype(np.int32), values)
+    asp.asp_reserve(h, 130)
+    B = torch.from_numpy(synth.dense_normal(k, 130, "f32", seed=4)).cuda()
+    got = {}
+    for N in (17, 63, 64, 130):
+        C = torch.full((m, N), float("nan"), device="cuda")
+        Bn = B[:, :N].contiguous()
+        asp.asp_spmm(h, Bn.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got[N] = C.cpu().numpy()[lengths <= 512]
+    asp.asp_destroy(h)
+    assert np.isfinite(got[130]).all()
+    for N in (17, 63, 64):
+        assert np.array_equal(got[N].view(np.uint32), np.ascontiguousarray(got[130][:, :N]).view(np.uint32)), N
