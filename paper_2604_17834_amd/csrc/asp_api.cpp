@@ -250,7 +250,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     HostDense dense;
     if (groups.n_groups == 0 && h->dtype == ASP_DT_F32) wcsr_build_dense(m, row_ptr, col_idx, h->b_row, h->task_cols, h->hw, rows, dense);
     std::vector<int32_t> teams, g_teams, d_teams;
-    h->chunk_rows = (int64_t)rows.chunks.size() / 4;
+    h->scratch_rows = split_scratch_rows(rows.split);
     wcsr_build_teams(rows.n_entries, rows.chunks, rows.tasks, teams);
     h->n_teams = (int64_t)teams.size() / 4;
     h->n_row_tasks = (int64_t)rows.tasks.size() / 4;
@@ -280,7 +280,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         h->n_d_chunks = (int64_t)dense.chunks.size() / 4;
         h->n_d_split_rows = (int64_t)dense.split.size() / 4;
         h->n_d_teams = (int64_t)d_teams.size() / 4;
-        for (size_t i = 2; i < dense.split.size(); i += 4) h->dense_scratch_rows += dense.split[i];
+        h->d_scratch_rows = split_scratch_rows(dense.split);
         if ((s = upload(&h->d_dense_rows, dense.rows.data(), dense.rows.size() * 4, stream))) return s;
         if ((s = upload(&h->d_dense_ptr, dense.ptr.data(), dense.ptr.size() * 4, stream))) return s;
         if ((s = upload(&h->d_d_row_tasks, dense.tasks.data(), dense.tasks.size() * 4, stream))) return s;
@@ -296,7 +296,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         if ((s = upload(&h->d_g_teams, g_teams.data(), g_teams.size() * 4, stream))) return s;
         h->n_groups = groups.n_groups;
         h->group_span = groups.span;
-        h->group_scratch_rows = groups.scratch_rows;
+        h->g_scratch_rows = split_scratch_rows(groups.split);
         h->group_near_cols = groups.near_cols;
         h->group_many = groups.n_many;
         h->n_g_row_tasks = (int64_t)groups.row_tasks.size() / 4;

@@ -984,7 +984,6 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
             for (int64_t p = 0; p < np; ++p)
                 in_ranges[j].push_back({(int32_t)i, (int32_t)p, (int32_t)np, (int32_t)ceil_div(c - p, np), (int32_t)room[at].first++});
         }
-        out.scratch_rows += need;
     }
 
     // range j of group g is task j G + g: pieces to tasks, the longest first to the task with the fewest entries so far

@@ -156,7 +156,6 @@ struct HostGroups {
     static constexpr int64_t RANGES = 8; // of columns, one to an XCD
     int64_t n_groups = 0;                // tasks of a range; 0: the rest is not used
     int64_t span = 0;                    // columns of the widest range
-    int64_t scratch_rows = 0;
     static constexpr int32_t MANY_PIECES = 512;
     int64_t n_many = 0;                  // rows with more scratch rows than that: the first ones of `split`
     int64_t near_cols = 0;               // many entries whose rows meet in few columns at a time: that many, 0: they do not
@@ -184,6 +183,11 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
 void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
                       const HostRows &rows, HostDense &out);
 void wcsr_build_teams(int64_t n_entries, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks, std::vector<int32_t> &teams);
+inline int64_t split_scratch_rows(const std::vector<int32_t> &split) {  // of a list of split rows, all together
+    int64_t rows = 0;
+    for (size_t i = 2; i < split.size(); i += 4) rows += split[i];
+    return rows;
+}
 void wcsr_zero_windows(const std::vector<int32_t> &window_row_ptr, int32_t task_cols,
                        std::vector<int32_t> &zero_windows);
 // returns empty string when the CSR arrays are valid, else a description of the first problem
@@ -237,20 +241,20 @@ struct asp_handle {
     // WCSR: the kernels' work lists (HostRows) and the entries of the windows that are walked entry by entry
     int64_t n_row_tasks = 0, n_chunks = 0, n_split_rows = 0, n_tile_tasks = 0, n_tile_split = 0;
     bool tiles_dealt = false;
-    int64_t n_teams = 0, chunk_rows = 0;  // (chunk_rows: scratch rows of all chunks, those of teams among them)
+    int64_t n_teams = 0, scratch_rows = 0;  // (scratch_rows: that the split rows of the list add, here and in the lists below)
     int32_t *d_teams = nullptr;           // those that a workgroup takes instead of a wave (wcsr_build_teams)
     int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;
     // WCSR: long rows in groups, and the lists of what is left beside them, for calls with scratch (HostGroups)
-    int64_t n_groups = 0, group_span = 0, group_scratch_rows = 0, group_near_cols = 0, group_many = 0;
-    int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0, n_g_teams = 0;
+    int64_t n_groups = 0, group_span = 0, group_near_cols = 0, group_many = 0;
+    int64_t n_g_row_tasks = 0, n_g_chunks = 0, n_g_split_rows = 0, n_g_teams = 0, g_scratch_rows = 0;
     int32_t *d_g_teams = nullptr;
     uint64_t *d_group_entries = nullptr;
     int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;
     // WCSR: nearly dense rows over columns in LDS, and the lists of what is left beside them, for calls with scratch (HostDense)
-    int64_t n_dense = 0, dense_ranges = 0, dense_blocks = 0, dense_scratch_rows = 0;
-    int64_t n_d_row_tasks = 0, n_d_chunks = 0, n_d_split_rows = 0, n_d_teams = 0;
+    int64_t n_dense = 0, dense_ranges = 0, dense_blocks = 0;
+    int64_t n_d_row_tasks = 0, n_d_chunks = 0, n_d_split_rows = 0, n_d_teams = 0, d_scratch_rows = 0;
     int32_t *d_dense_rows = nullptr, *d_dense_ptr = nullptr, *d_d_row_tasks = nullptr, *d_d_chunks = nullptr, *d_d_split_rows = nullptr,
             *d_d_teams = nullptr;
     float *d_ws = nullptr;          // fp32 scratch, one [b_row][N] tile per slot (asp_reserve)
@@ -299,6 +303,8 @@ int64_t wcsr_scratch_floats(const asp_handle *h, int64_t N);  // fp32 scratch el
 // windows that are walked entry by entry (empty ones among them), and the sums of their split rows
 void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream);
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
+// how many of the split rows (the first of the call's list) have their scratch rows added by many threads
+int64_t wcsr_rows_sum_many(const asp_handle *h, int64_t N);
 // the groups of long rows: whether calls of this width (with scratch) use them, and their kernel
 bool wcsr_groups_apply(const asp_handle *h, int64_t N);
 void wcsr_groups_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream);

@@ -427,17 +427,25 @@ void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, fl
     else launch_rows<float>(h, B, C, N, ws, stream);
 }
 
+// Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
+// 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
+// in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  From lists of 128 on, the graph without that row 950 -> 959: another launch.
+// Only the scratch rows of the call's own list count (with those of chunks whose rows are in groups counted too, 1 814 284 rows of Zipf
+// lengths, degree 15, N = 41 went over the line: the sums 11 -> 59 us).
+int64_t wcsr_rows_sum_many(const asp_handle *h, int64_t N) {
+    const bool groups = wcsr_groups_apply(h, N), dense = !groups && wcsr_dense_apply(h, N);
+    const int64_t n_split = groups ? h->n_g_split_rows : dense ? h->n_d_split_rows : h->n_split_rows;
+    const int64_t rows = groups ? h->g_scratch_rows : dense ? h->d_scratch_rows : h->scratch_rows;
+    return N > 65535 * 16 ? 0 : rows > 32 * n_split ? n_split : groups ? h->group_many : 0;
+}
+
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream) {
     const bool groups = wcsr_groups_apply(h, N);
     const bool dense = !groups && wcsr_dense_apply(h, N);
     const int32_t *d_split = groups ? h->d_g_split_rows : dense ? h->d_d_split_rows : h->d_split_rows;
     const int64_t n_split = groups ? h->n_g_split_rows : dense ? h->n_d_split_rows : h->n_split_rows;
     if (n_split == 0) return;
-    // Long lists, where they are so on average, or each that is (the groups leave thousands of short ones beside those of a hub):
-    // 2^20 rows of Zipf lengths and a row of 604 368 entries, fp32, N = 128 1041 -> 986 us, the row 6.4e-7 -> 2.6e-7 from its sum
-    // in 64 bits (by rows 1244, 4.9e-7); bf16 633 -> 575 (616).  From lists of 128 on, the graph without that row 950 -> 959: another launch.
-    const bool many = (groups ? h->group_scratch_rows + h->chunk_rows : dense ? h->dense_scratch_rows : h->chunk_rows) > 32 * n_split;
-    const int64_t n_many = N > 65535 * 16 ? 0 : many ? n_split : groups ? h->group_many : 0;
+    const int64_t n_many = wcsr_rows_sum_many(h, N);
 #define ASP_ROWS_SUM(T, COLS, J, FIRST, COUNT)                                                                            \
     if ((COUNT) > 0)                                                                                                      \
         hipLaunchKernelGGL((wcsr_rows_sum_kernel<T, COLS, J>),                                                            \

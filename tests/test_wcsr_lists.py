@@ -113,6 +113,12 @@ def test_rows_of_many_pieces_come_first(lists_of, task_cols, hubs, many):
     assert all(diff == 0 and times == 1 for _, diff, times in got["row"])
 
 
+@pytest.mark.parametrize("length,many", [(3300, False), (6000, True)])   # 32 and 48 pieces of a row; 7 and 12 chunks without groups
+def test_sums_count_the_pieces_that_they_add(lists_of, length, many):
+    got = lists_of("groups", 400, 100000, 0, 512, 4, length)
+    assert got["groups"][0][0] >= 256 and got["sums"] == [[400 if many else 0, 400]]
+
+
 def test_no_groups_of_short_pieces(lists_of):
     for task_cols, groups in ((32, False), (40, False), (48, True)):
         got = lists_of("groups", 9000, 40000, 0, task_cols, 4, 900, 64, 70, 5)

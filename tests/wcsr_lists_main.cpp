@@ -12,7 +12,8 @@
 //                    by the lists of groups, chunks and runs: "row r difference times" ("tile r times" for rows that go tile by
 //                    tile); and how many groups there are, the entries of their largest task and of all, the most terms of a
 //                    sum in a task, the scratch rows there are and that they use, the columns that near rows meet in, and how many
-//                    rows have their scratch rows added by many threads, the fewest of one and the most of another
+//                    rows have their scratch rows added by many threads, the fewest of one and the most of another; and how many of
+//                    how many split rows a product with 128 columns adds so
 //   dense M K H T L..  M rows of K columns with L.. entries in turn, spread over all, in windows of H rows, tasks of T columns: the
 //                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
 //                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
@@ -220,6 +221,11 @@ static int groups(int64_t m, int64_t k, int64_t w, int32_t task_cols, size_t esi
         else most = std::max<int64_t>(most, g.split[i + 2]);
     std::printf("groups %lld\nlargest %lld %lld\nterms %lld\nscratch %lld %lld\nnear %lld\nmany %lld %lld %lld\n", (long long)g.n_groups, (long long)largest, (long long)all, (long long)terms,
                 (long long)slots * 16, (long long)used, (long long)g.near_cols, (long long)g.n_many, (long long)fewest, (long long)most);
+    asp_handle h;
+    h.dtype = esize == 2 ? ASP_DT_BF16 : ASP_DT_F32, h.m = m, h.k = k, h.n_groups = g.n_groups, h.group_span = g.span, h.group_many = g.n_many;
+    h.n_split_rows = (int64_t)rows.split.size() / 4, h.scratch_rows = asp::split_scratch_rows(rows.split);
+    h.n_g_split_rows = (int64_t)g.split.size() / 4, h.g_scratch_rows = asp::split_scratch_rows(g.split);
+    std::printf("sums %lld %lld\n", (long long)asp::wcsr_rows_sum_many(&h, 128), (long long)h.n_g_split_rows);
     for (int64_t r = 0; r < m; ++r) {
         double want = 0;
         for (int64_t e = rp[r]; e < rp[r + 1]; ++e) want += (1 + e % 3) * b(ci[e]);
