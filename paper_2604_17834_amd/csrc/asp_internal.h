@@ -44,7 +44,7 @@ struct Switches {
 const Switches &switches();
 
 inline size_t dtype_size(int32_t dt) { return dt == ASP_DT_BF16 ? 2 : 4; }
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // HIP takes fewer than 2^32 threads along a dimension of a launch
 constexpr bool launch_fits(int64_t workgroups, int64_t threads) { return workgroups * threads < (1ll << 32); }
 
@@ -303,6 +303,12 @@ int64_t wcsr_scratch_floats(const asp_handle *h, int64_t N);  // fp32 scratch el
 // windows that are walked entry by entry (empty ones among them), and the sums of their split rows
 void wcsr_rows_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream);
 void wcsr_rows_sum_launch(const asp_handle *h, void *C, int64_t N, const float *ws, hipStream_t stream);
+// The walk by rows from wave `first` on, four to a workgroup, behind n_teams workgroups (a multiple of 8): where its launch ends.
+constexpr int64_t rows_launch_end(int64_t waves, int64_t first, int64_t n_teams) {
+    const int64_t most = first + (1 << 26) - 32 - 4 * n_teams;
+    return waves < most ? waves : most;
+}
+static_assert(launch_fits(131072 + ceil_div(rows_launch_end(1ll << 31, 0, 131072), 4), 256), "one launch");
 // how many of the split rows (the first of the call's list) have their scratch rows added by many threads
 int64_t wcsr_rows_sum_many(const asp_handle *h, int64_t N);
 // the groups of long rows: whether calls of this width (with scratch) use them, and their kernel

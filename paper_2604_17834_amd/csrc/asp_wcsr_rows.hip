@@ -400,11 +400,10 @@ static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, 
     const int64_t n_row_tasks = groups ? h->n_g_row_tasks : dense ? h->n_d_row_tasks : h->n_row_tasks;
     if (groups) wcsr_groups_launch(h, B, N, ws, stream);
     if (dense) wcsr_dense_launch(h, B, N, ws, stream);
-    // a launch takes fewer than 2^32 threads
-    const int64_t waves = n_chunks + n_row_tasks, step = (1 << 26) - 32;
-    int64_t n_teams = groups ? h->n_g_teams : dense ? h->n_d_teams : h->n_teams;  // (a few thousand)
-    for (int64_t first = 0; first < waves || n_teams > 0; first += step, n_teams = 0) {
-        const int64_t end = std::min(waves, first + step);
+    const int64_t waves = n_chunks + n_row_tasks;
+    int64_t n_teams = groups ? h->n_g_teams : dense ? h->n_d_teams : h->n_teams, end;  // (131 072 at most)
+    for (int64_t first = 0; first < waves || n_teams > 0; first = end, n_teams = 0) {
+        end = rows_launch_end(waves, first, n_teams);
         const int64_t c0 = std::min(first, n_chunks), c1 = std::min(end, n_chunks), t0 = first - c0, t1 = end - c1;
         // columns per lane: as few as cover N in one pass of the wave -- more lanes per row of B, fewer bytes per lane
 #define ASP_ROWS(E, CE, CL)                                                                                          \

@@ -143,3 +143,14 @@ def test_dense_rows_are_taken_64_at_a_time(lists_of, n, taken):
     assert rows == taken and 64 <= ranges <= min(256, blocks) and blocks == 391
     assert 10 * got["fewest"][0][0] >= 45 * 99900 and 36 * 4 * table <= 8 * 10000 * rows
     assert len(got["row"]) == 16 * n and all(diff == 0 and times == 1 for _, diff, times in got["row"])
+
+
+@pytest.mark.parametrize("waves", [0, 5, 2**26 - 33, 2**26 - 32, 2**26 - 31, 2**26, 3 * 2**26])
+@pytest.mark.parametrize("teams", [0, 8, 4096, 131072])
+def test_a_launch_of_the_walk_by_rows_takes_fewer_than_2_to_the_32_threads(lists_of, waves, teams):
+    got = lists_of("launches", waves, teams).get("launch", [])
+    assert all(workgroups * 256 < 2**32 for _, _, workgroups in got)
+    assert [first for first, _, _ in got] == [0, *(end for _, end, _ in got[:-1])][:len(got)]
+    assert not got or got[-1][1] == waves
+    assert len(got) == (1 if waves + teams else 0) if waves <= 2**26 - 32 - 4 * teams else len(got) >= 2
+    assert sum(workgroups for _, _, workgroups in got) == teams + -(-waves // 4)

@@ -17,6 +17,7 @@
 //   dense M K H T L..  M rows of K columns with L.. entries in turn, spread over all, in windows of H rows, tasks of T columns: the
 //                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
 //                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
+//   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
 //   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
 //                    tokens on 256 compute units take in asp_spmm_xt, 0: none
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -327,9 +328,19 @@ static int xt(char **argv) {
     return 0;
 }
 
+static int launches(int64_t waves, int64_t n_teams) {
+    for (int64_t first = 0, end; first < waves || n_teams > 0; first = end, n_teams = 0) {
+        end = asp::rows_launch_end(waves, first, n_teams);
+        std::printf("launch %lld %lld %lld\n", (long long)first, (long long)end, (long long)(n_teams + asp::ceil_div(end - first, 4)));
+        if (end <= first && waves > 0) return 1;
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc == 7 && std::strcmp(argv[1], "xt") == 0) return xt(argv + 2);
     if (argc == 3 && std::strcmp(argv[1], "slots") == 0) return slots((int32_t)std::atoll(argv[2]));
+    if (argc == 4 && std::strcmp(argv[1], "launches") == 0) return launches(std::atoll(argv[2]), std::atoll(argv[3]));
     auto is = [&](const char *what, int first) { return argc > first && std::strcmp(argv[1], what) == 0; };
     auto lengths = [&](int first) {
         std::vector<int32_t> v;
