@@ -72,11 +72,12 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     if (u >= runs.start[xcd + 1]) return;
     const int nt = __builtin_amdgcn_readfirstlane(u / n_brows), pos = u - nt * n_brows;
     const int br = __builtin_amdgcn_readfirstlane(order ? order[pos] : pos);
-    // Rows that are not 16-byte aligned: the last column tile moves left so that it ends at N, and its loads have no case of a
-    // row's end.  (18944 x 3584 at 90 %, N = 4093, 128 / 64 / 32-row blocks 134 / 148 / 199 -> 113 / 125 / 173 us with plain loads
-    // in every slice that does not reach past K; two slices ahead instead of one: 126 / 141 / 192.)
-    const int n_own = nt * BN, n0 = !VEC && N >= BN && n_own > N - BN ? N - BN : n_own;
-    const bool inner = n0 + BN <= N;
+    // Chunks of 8 columns that would pass N end there instead and repeat columns of their neighbour (the same bits), so no load of
+    // N >= 8 columns has a case of a row's end.  (18944 x 3584 at 90 %, N = 4093, 128 / 64 / 32-row blocks 134 / 148 / 199 -> 113 / 125 / 173 us
+    // with plain loads in every slice that does not reach past K; two slices ahead instead of one: 126 / 141 / 192.)
+    const int n0 = nt * BN;
+    const bool inner = N >= 8;
+    auto chunk_col = [&](int col) __attribute__((always_inline)) { return inner && col > N - 8 ? N - 8 : col; };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -105,12 +106,12 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
         }
         const int krow0 = block_col_idx[p] * BC + s * KS;
         if (inner && krow0 + KS <= K) {
-            const uint16_t *src = B + (int64_t)krow0 * N + n0;
+            const uint16_t *src = B + (int64_t)krow0 * N;
 #pragma unroll
             for (int i = 0; i < Cfg::B_LD; ++i) {
                 const int c = i * NT + tid;
                 if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) {
-                    const uint16_t *at = src + (int64_t)(c / Cfg::B_CPR) * N + c % Cfg::B_CPR * 8;
+                    const uint16_t *at = src + (int64_t)(c / Cfg::B_CPR) * N + chunk_col(n0 + c % Cfg::B_CPR * 8);
                     f.b[i] = VEC ? *(const u32x4 *)at : *(const u32x4_a2 *)at;
                 }
             }
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
             int c = i * NT + tid;
             if (Cfg::B_CHUNKS % NT == 0 || c < Cfg::B_CHUNKS) {
                 int r = c / Cfg::B_CPR, cc = c % Cfg::B_CPR;
-                int krow = krow0 + r, col = n0 + cc * 8;
+                int krow = krow0 + r, col = chunk_col(n0 + cc * 8);
                 u32x4 v = {0u, 0u, 0u, 0u};
                 if (krow < K && col < N) {  // rows past K belong to the zero padding of the last block column
                     const uint16_t *row = B + (int64_t)krow * N;
@@ -216,8 +217,8 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
         int row = it * RPI + lane / CPR, cc = lane % CPR;
         uint4 v = *(const uint4 *)(sc + row * Cfg::C_PITCH + cc * 16);
         int grow = br * BR + wm * Cfg::TM + row;
-        int gcol = n0 + wn * Cfg::TN + cc * 8;
-        if (grow < M && gcol < N && gcol + 8 > n_own) {  // (a column of two tiles gets the same bits from both)
+        const int own = n0 + wn * Cfg::TN + cc * 8, gcol = chunk_col(own);
+        if (grow < M && own < N) {
             uint16_t *dst = C + (int64_t)grow * N + gcol;
             if (VEC) {
                 *(uint4 *)dst = v;
@@ -341,6 +342,24 @@ static bool launch(const asp_handle *h, const void *B, void *C, int64_t N, const
     return true;
 }
 
+// Wide tiles where that leaves enough of them: A is read less often, but with few tiles the longest block-rows set the time.
+// us, 64 / 128 / 256 wide, 128-row blocks: 18944 x 3584 at 90 %, N = 8001 338 / 257 / 199, 8000 x 2000 at 95 %, N = 6001 (1512
+// tiles of 256) 42.6 / 40.0 / 37.3, 3940 x 1488 at 90 %, N = 5271 (651) - / 24.0 / 27.7, 5000 x 5000 at 90 %, N = 2001 (640 of 128) 32.4 /
+// 34.0 / 43.0; 64-row: 359 / 272 / 232, 40.9 / 37.2 / 34.6 (3000), 3200 x 1920, geometric lengths, N = 6811 (1350) - / 52 / 58, 34.1 /
+// 27.7 / 31.3; 32-row: 450 / 361 / 314, 50 / 46 / 40 (6000), 3057 x 2421, geometric lengths, N = 6099 (2304) - / 24.1 / 27.7, 41 / 34 / 33.
+// And where N fills them: a column of a 128- or 256-wide tile costs about 0.72 and 0.6 of one of a 64-wide tile.  150 001 x 512 at
+// 50 %, 64-row blocks, N = 70 32.5 / 22.1 / 32.8, 130 51 / 41 / 35, 257 83 / 67 / 74; 50 001 x 1024 at 80 %, 32-row, N = 513 51 / 47 / 49,
+// 641 62 / 56 / 51; of 66 such products of 70 to 2050 columns the choice is the fastest or within 3 %, but for those whose number of
+// 256-wide tiles is just short (128-row, N = 130, 1172 of them, 41 / 33).
+int bcsr_unaligned_bn(const asp_handle *h, int64_t N) {
+    const int64_t cost64 = 100 * 64 * ceil_div(N, 64), cost128 = 72 * 128 * ceil_div(N, 128), cost256 = 60 * 256 * ceil_div(N, 256);
+    auto enough = [&](int bn, int64_t quarters) {  // tiles of that width, in quarters of the compute units
+        return 4 * h->n_brows * ceil_div(N, bn) >= quarters * (int64_t)h->n_cus;
+    };
+    if (cost256 < cost128 && cost256 < cost64 && enough(256, h->b_row == 128 ? 20 : h->b_row == 64 ? 32 : 48)) return 256;
+    return cost128 < cost64 && enough(128, h->b_row == 128 ? 11 : 16) ? 128 : 64;
+}
+
 asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
     const bool aligned = (((uintptr_t)B | (uintptr_t)C) & 15) == 0;
     const BcsrPlan p = bcsr_plan(h, N, aligned);
@@ -359,34 +378,23 @@ asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64
         if (!bcsr_wide_launch(h, B, C, N, p, stream) && !bcsr_dma_launch(h, B, C, N, p, stream))
             return fail(ASP_ERR_UNSUPPORTED, "no kernel for this block size / tile width");
     } else if (!p.vectorized) {  // 16-byte accesses at element alignment
-        // Wide tiles where that leaves enough of them: A is read less often, but with few tiles the longest block-rows set the time.
-        // us, 64 / 128 / 256 wide, 128-row blocks: 18944 x 3584 at 90 %, N = 8001 338 / 257 / 199, 8000 x 2000 at 95 %, N = 6001 (1512
-        // tiles of 256) 42.6 / 40.0 / 37.3, 3940 x 1488 at 90 %, N = 5271 (651) - / 24.0 / 27.7, 5000 x 5000 at 90 %, N = 2001 (640 of 128) 32.4 /
-        // 34.0 / 43.0; 64-row: 359 / 272 / 232, 40.9 / 37.2 / 34.6 (3000), 3200 x 1920, geometric lengths, N = 6811 (1350) - / 52 / 58, 34.1 /
-        // 27.7 / 31.3; 32-row: 450 / 361 / 314, 50 / 46 / 40 (6000), 3057 x 2421, geometric lengths, N = 6099 (2304) - / 24.1 / 27.7, 41 / 34 / 33.
-        // (narrower again where a single column tile of 2^29 rows would pass the threads of a launch)
         bool done = false;
         BcsrPlan w = p;
-        auto enough = [&](int bn, int64_t quarters) {  // tiles of that width, in quarters of the compute units
-            w.bn = bn;
-            w.n_tiles = (int32_t)ceil_div(N, bn);
+        // (narrower again where a single column tile of 2^29 rows would pass the threads of a launch)
+        for (w.bn = bcsr_unaligned_bn(h, N); !done && w.bn >= 64; w.bn /= 2) {
+            w.n_tiles = (int32_t)ceil_div(N, w.bn);
             w.workgroups = h->n_brows * w.n_tiles;
-            return 4 * w.workgroups >= quarters * (int64_t)h->n_cus;
-        };
-        if (enough(256, h->b_row == 128 ? 20 : h->b_row == 64 ? 32 : 48)) {
-            if (h->b_row == 128) done = launch<128, 256, 2, 2, false>(h, B, C, N, w, stream);
-            else if (h->b_row == 64) done = launch<64, 256, 1, 4, false>(h, B, C, N, w, stream);
-            else done = launch<32, 256, 1, 4, false>(h, B, C, N, w, stream);
-        }
-        if (!done && enough(128, h->b_row == 128 ? 11 : 16)) {
-            if (h->b_row == 128) done = launch<128, 128, 2, 2, false>(h, B, C, N, w, stream);
-            else if (h->b_row == 64) done = launch<64, 128, 2, 2, false>(h, B, C, N, w, stream);
-            else done = launch<32, 128, 1, 4, false>(h, B, C, N, w, stream);
-        }
-        if (!done) {
-            if (h->b_row == 128) done = launch<128, 64, 2, 2, false>(h, B, C, N, p, stream);
-            else if (h->b_row == 64) done = launch<64, 64, 2, 2, false>(h, B, C, N, p, stream);
-            else done = launch<32, 64, 1, 2, false>(h, B, C, N, p, stream);
+            switch (h->b_row * 1000 + w.bn) {
+                case 128256: done = launch<128, 256, 2, 2, false>(h, B, C, N, w, stream); break;
+                case 128128: done = launch<128, 128, 2, 2, false>(h, B, C, N, w, stream); break;
+                case 128064: done = launch<128, 64, 2, 2, false>(h, B, C, N, w, stream); break;
+                case 64256: done = launch<64, 256, 1, 4, false>(h, B, C, N, w, stream); break;
+                case 64128: done = launch<64, 128, 2, 2, false>(h, B, C, N, w, stream); break;
+                case 64064: done = launch<64, 64, 2, 2, false>(h, B, C, N, w, stream); break;
+                case 32256: done = launch<32, 256, 1, 4, false>(h, B, C, N, w, stream); break;
+                case 32128: done = launch<32, 128, 1, 4, false>(h, B, C, N, w, stream); break;
+                case 32064: done = launch<32, 64, 1, 2, false>(h, B, C, N, w, stream); break;
+            }
         }
         if (!done) return fail(ASP_ERR_UNSUPPORTED, "too many output tiles");
     } else {

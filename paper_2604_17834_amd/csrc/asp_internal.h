@@ -280,6 +280,8 @@ void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N,
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
 bool bcsr_wide_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
+// the tile width of the register-staged kernel where rows are not 16-byte aligned (asp_bcsr.hip)
+int bcsr_unaligned_bn(const asp_handle *h, int64_t N);
 asp_status_t bcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
 asp_status_t bcsr_spmm_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
 

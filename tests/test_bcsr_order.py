@@ -172,3 +172,14 @@ def test_register_staged_runs_weigh_the_same(lists_of, n_tiles, lengths):  # noq
 ])
 def test_products_that_take_staged_strips(lists_of, block, brows, units, longest, tokens, row_tiles):  # noqa: F811
     assert lists_of("xt", block, brows, units, longest, tokens)["staged"] == [[row_tiles]]
+
+
+@pytest.mark.parametrize("block,brows,widths", [
+    (32, 6250, {1: 64, 64: 64, 65: 128, 70: 128, 127: 128, 130: 256, 257: 128, 300: 128, 385: 256, 513: 128, 641: 256, 2050: 256}),
+    (64, 3125, {33: 64, 70: 128, 129: 256, 201: 256, 257: 128, 390: 256, 600: 128, 770: 256}),
+    (128, 1563, {70: 128, 130: 256, 300: 128, 390: 256, 1290: 256}),
+    (128, 391, {70: 64, 127: 64, 257: 128, 450: 128, 513: 128, 641: 128, 1290: 256}),      # few tiles: narrower ones
+    (64, 20, {70: 64, 4000: 64, 8001: 128, 30000: 256}),
+])
+def test_unaligned_rows_take_tiles_that_they_fill(lists_of, block, brows, widths):  # noqa: F811
+    assert lists_of("unaligned", block, brows, *widths)["bn"] == [[bn] for bn in widths.values()]

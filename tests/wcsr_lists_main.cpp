@@ -18,6 +18,7 @@
 //                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
 //                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
 //   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
+//   unaligned B R N..  R block-rows of height B on 256 compute units: the tile width for N.. columns in rows that are not aligned
 //   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
 //                    tokens on 256 compute units take in asp_spmm_xt, 0: none
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -351,6 +352,12 @@ int main(int argc, char **argv) {
     if (is("shares", 2)) return shares(lengths(2));
     if (is("groups", 7))
         return groups(std::atoll(argv[2]), std::atoll(argv[3]), std::atoll(argv[4]), std::atoi(argv[5]), std::atoll(argv[6]), lengths(7));
+    if (is("unaligned", 4)) {
+        asp_handle h;
+        h.b_row = std::atoi(argv[2]), h.n_brows = std::atoll(argv[3]), h.n_cus = 256;
+        for (int32_t n : lengths(4)) std::printf("bn %d\n", asp::bcsr_unaligned_bn(&h, n));
+        return 0;
+    }
     if (is("dense", 6))
         return dense(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
