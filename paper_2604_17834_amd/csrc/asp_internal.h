@@ -292,6 +292,8 @@ struct WcsrPlan {
     int64_t workgroups;
 };
 WcsrPlan wcsr_plan(const asp_handle *h, int64_t N, bool aligned);
+// columns of a lane in the tiles of heights 32 and 64, fp32
+int wcsr_lane_columns(const asp_handle *h, int64_t N);
 // ws / ws_floats: the fp32 buffer that takes the partial tiles of split windows and its capacity (the handle's
 // reserved buffer, or the library's static one; nullptr / 0: none)
 asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, int64_t ws_floats,

@@ -596,20 +596,28 @@ void wcsr_sum_partial_tiles(const asp_handle *h, void *C, int64_t N, const float
 #undef ASP_SUM
 }
 
+// fp32, columns of a lane, 32 lanes to a wave's tile.  Heights 32 and 64: 32 or 64 columns to a wave where that covers N; 64 also
+// where two such tiles do at height 64, if that leaves every wave a SIMD of its own (30 000 rows, band of 13, N = 128 16.9 -> 12.4 us)
+// or brings few SIMDs to three of them instead of two twice as long ones, or five instead of three (80 000 rows 33.0 -> 32.0, 150 000 64.1 ->
+// 59.5; two instead of one, 50 000 rows, 19.5 / 21.4, on every SIMD, 98 000, N = 100, 34 / 38, four instead of two, 120 000, 36 / 56,
+// 600 000 rows 186 / 200, N = 80 166 / 192); and where three do instead of two of 128 and there are enough of them (N = 160, 300 000 rows,
+// heights 32 / 64 108 / 158 -> 102 / 143; 30 000 rows 13.6 -> 12.6, but at height 64, 469 windows, 17.3 / 20.6).  At height 32 two instead
+// of one are slower (30 000 rows, N = 128 8.3 / 9.4, 300 000 72.6 / 75.1).
+int wcsr_lane_columns(const asp_handle *h, int64_t N) {
+    constexpr int64_t SIMDS = 1024;
+    const int64_t n = h->n_tile_tasks;
+    if (h->b_row == 16) return 4;
+    if (N <= 64) return N <= 32 ? 1 : 2;
+    if (N > 128) return N <= 192 && n >= 900 ? 2 : 4;
+    return h->b_row == 64 && (2 * n <= SIMDS || (n > SIMDS && n <= 3 * SIMDS && (n - 1) % SIMDS < SIMDS / 3)) ? 2 : 4;
+}
+
 asp_status_t wcsr_spmm_launch(const asp_handle *h, const void *B, void *C, int64_t N, float *ws_buf, int64_t ws_floats,
                               hipStream_t stream) {
     if (h->dtype == ASP_DT_BF16) return wcsr_bf16_spmm_launch(h, B, C, N, ws_buf, ws_floats, stream);
     WcsrPlan p = wcsr_plan(h, N, true);
-    // Heights 32 and 64: 32 or 64 columns to a wave where that covers N; 64 also where two such tiles do at height 64, whose 128-column
-    // ones leave a wave to a SIMD (30 000 rows, band of 13, N = 128 16.6 -> 12.3 us, 300 000 rows 99.9 / 97.6; at height 32 8.3 / 9.4,
-    // 72.6 / 75.1), and where three do instead of two of 128 and there are enough of them (N = 160, 300 000 rows, heights 32 / 64 108 / 158
-    // -> 102 / 143; 30 000 rows 13.6 -> 12.6, but at height 64, 469 windows, 17.3 / 20.6).
-    int columns = 4;  // of a lane
-    if (h->b_row > 16) {
-        if (N <= 64) columns = N <= 32 ? 1 : 2;
-        else if (N <= 128 ? h->b_row == 64 : N <= 192 && h->n_tile_tasks >= 900) columns = 2;
-        if (columns < 4) p.n_tiles = (int32_t)ceil_div(N, 32 * columns);
-    }
+    const int columns = wcsr_lane_columns(h, N);
+    if (columns < 4) p.n_tiles = (int32_t)ceil_div(N, 32 * columns);
     // split windows: partial tiles in the scratch buffer when it is large enough, else atomic adds into C
     const bool partial = h->n_split_tasks > 0 && ws_buf && ws_floats >= wcsr_scratch_floats(h, N);
     float *ws = partial ? ws_buf : nullptr;

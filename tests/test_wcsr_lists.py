@@ -154,3 +154,14 @@ def test_a_launch_of_the_walk_by_rows_takes_fewer_than_2_to_the_32_threads(lists
     assert not got or got[-1][1] == waves
     assert len(got) == (1 if waves + teams else 0) if waves <= 2**26 - 32 - 4 * teams else len(got) >= 2
     assert sum(workgroups for _, _, workgroups in got) == teams + -(-waves // 4)
+
+
+@pytest.mark.parametrize("height,tasks,columns", [
+    (64, 469, {16: 1, 32: 1, 33: 2, 64: 2, 65: 2, 100: 2, 128: 2, 129: 4, 160: 4, 256: 4}),
+    (64, 512, {80: 2}), (64, 513, {80: 4, 128: 4}), (64, 1024, {128: 4, 160: 2, 193: 4}), (64, 1025, {128: 2}), (64, 1365, {72: 2, 128: 2}), (64, 1366, {128: 4}),
+    (64, 2389, {128: 2}), (64, 2390, {128: 4}), (64, 3200, {80: 4}),
+    (64, 1875, {72: 4, 128: 4}), (64, 9375, {64: 2, 66: 4, 80: 4, 128: 4, 160: 2}),     # two waves for one: more rounds of them
+    (32, 469, {32: 1, 64: 2, 80: 4, 128: 4}), (32, 20000, {80: 4, 160: 2, 200: 4}), (16, 20000, {16: 4, 160: 4}),
+])
+def test_columns_of_a_lane(lists_of, height, tasks, columns):
+    assert lists_of("columns", height, tasks, *columns)["columns"] == [[c] for c in columns.values()]

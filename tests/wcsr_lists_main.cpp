@@ -19,6 +19,7 @@
 //                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
 //   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
 //   unaligned B R N..  R block-rows of height B on 256 compute units: the tile width for N.. columns in rows that are not aligned
+//   columns H T N..  T tasks of windows of height H in fp32: the columns of a lane for N.. columns
 //   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
 //                    tokens on 256 compute units take in asp_spmm_xt, 0: none
 //   slots S          two windows of 16 rows with 20 scattered entries each, tasks of 8 columns, scratch slots from S on
@@ -356,6 +357,12 @@ int main(int argc, char **argv) {
         asp_handle h;
         h.b_row = std::atoi(argv[2]), h.n_brows = std::atoll(argv[3]), h.n_cus = 256;
         for (int32_t n : lengths(4)) std::printf("bn %d\n", asp::bcsr_unaligned_bn(&h, n));
+        return 0;
+    }
+    if (is("columns", 4)) {
+        asp_handle h;
+        h.b_row = std::atoi(argv[2]), h.n_tile_tasks = std::atoll(argv[3]);
+        for (int32_t n : lengths(4)) std::printf("columns %d\n", asp::wcsr_lane_columns(&h, n));
         return 0;
     }
     if (is("dense", 6))
