@@ -70,6 +70,8 @@ static void free_device(asp_handle *h) {
     (void)hipFree(h->d_g_row_tasks);
     (void)hipFree(h->d_g_chunks);
     (void)hipFree(h->d_teams);
+    (void)hipFree(h->wide.d_chunks);
+    (void)hipFree(h->d_wide.d_chunks);
     (void)hipFree(h->d_dense_rows);
     (void)hipFree(h->d_dense_ptr);
     (void)hipFree(h->d_d_row_tasks);
@@ -250,8 +252,17 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     HostDense dense;
     if (groups.n_groups == 0 && h->dtype == ASP_DT_F32) wcsr_build_dense(m, row_ptr, col_idx, h->b_row, h->task_cols, h->hw, rows, dense);
     std::vector<int32_t> teams, g_teams, d_teams;
+    HostWide wide, d_wide, g_wide;
+    auto set_wide = [&](asp_handle::Wide &to, const HostWide &w, std::vector<int32_t> &list) {
+        to.n_teams = (int64_t)w.teams.size() / 4;
+        to.n_chunks = (int64_t)w.chunks.size() / 4;
+        to.count = w.count;
+        to.len = w.len;
+        list.insert(list.begin(), w.teams.begin(), w.teams.end());
+        return upload(&to.d_chunks, w.chunks.data(), w.chunks.size() * 4, stream);
+    };
     h->scratch_rows = split_scratch_rows(rows.split);
-    wcsr_build_teams(rows.n_entries, rows.chunks, rows.tasks, teams);
+    wcsr_build_teams(rows.n_entries, rows, rows.chunks, rows.tasks, teams, wide);
     h->n_teams = (int64_t)teams.size() / 4;
     h->n_row_tasks = (int64_t)rows.tasks.size() / 4;
     h->n_chunks = (int64_t)rows.chunks.size() / 4;
@@ -262,6 +273,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     if ((s = upload(&h->d_tile_tasks, rows.tile_tasks.data(), rows.tile_tasks.size() * 4, stream))) return s;
     if ((s = upload(&h->d_tile_split, rows.tile_split.data(), rows.tile_split.size() * 4, stream))) return s;
     if (h->n_row_tasks > 0 || h->n_chunks > 0 || h->n_teams > 0) {
+        if ((s = set_wide(h->wide, wide, teams))) return s;
         if ((s = upload(&h->d_teams, teams.data(), teams.size() * 4, stream))) return s;
         if ((s = upload(&h->d_row_tasks, rows.tasks.data(), rows.tasks.size() * 4, stream))) return s;
         if ((s = upload(&h->d_chunks, rows.chunks.data(), rows.chunks.size() * 4, stream))) return s;
@@ -273,13 +285,14 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     if (dense.ranges > 0) {
         h->n_dense = (int64_t)dense.rows.size() / 4;
         // (by the entries of all rows, as above: a whole row is summed alike by both lists)
-        wcsr_build_teams(rows.n_entries, dense.chunks, dense.tasks, d_teams);
+        wcsr_build_teams(rows.n_entries, rows, dense.chunks, dense.tasks, d_teams, d_wide);
         h->dense_ranges = dense.ranges;
         h->dense_blocks = dense.blocks;
         h->n_d_row_tasks = (int64_t)dense.tasks.size() / 4;
         h->n_d_chunks = (int64_t)dense.chunks.size() / 4;
         h->n_d_split_rows = (int64_t)dense.split.size() / 4;
         h->n_d_teams = (int64_t)d_teams.size() / 4;
+        if ((s = set_wide(h->d_wide, d_wide, d_teams))) return s;
         h->d_scratch_rows = split_scratch_rows(dense.split);
         if ((s = upload(&h->d_dense_rows, dense.rows.data(), dense.rows.size() * 4, stream))) return s;
         if ((s = upload(&h->d_dense_ptr, dense.ptr.data(), dense.ptr.size() * 4, stream))) return s;
@@ -291,7 +304,7 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
     if (groups.n_groups > 0) {
         int64_t left = rows.n_entries;
         for (size_t i = 1; i < groups.tasks.size(); i += 4) left -= 16 * (int64_t)groups.tasks[i];
-        wcsr_build_teams(std::max<int64_t>(0, left), groups.chunks, groups.row_tasks, g_teams);
+        wcsr_build_teams(std::max<int64_t>(0, left), rows, groups.chunks, groups.row_tasks, g_teams, g_wide);
         h->n_g_teams = (int64_t)g_teams.size() / 4;
         if ((s = upload(&h->d_g_teams, g_teams.data(), g_teams.size() * 4, stream))) return s;
         h->n_groups = groups.n_groups;

@@ -1185,37 +1185,66 @@ void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx,
 }
 
 // Chunks and single rows that a workgroup takes instead of a wave: those with more entries than half of what each of the chip's 8192
-// waves would have, and more than 64 (the chunks of nearly dense rows come in multiples of 64, and short ones are as fast by a
-// wave each: 121 502 rows, band of 21 and 23 long rows, fp32, N = 88 56.2 us, 61.4 with workgroups).  They run on the XCD that the lists have
-// them on.  us, by waves / so: 19 732 rows of Zipf lengths, degree 17, fp32, N = 64 29.1 / 15.4; 57 008, degree 24, N = 19 53 / 40;
+// waves would have, and more than 64.  They run on the XCD that the lists have them on.
+// us, by waves / so: 19 732 rows of Zipf lengths, degree 17, fp32, N = 64 29.1 / 15.4; 57 008, degree 24, N = 19 53 / 40;
 // 182 898, degree 11, bf16, N = 32 68 / 56; 51 331, degree 9, fp32, N = 221 86 / 71; with more entries less (2^20 rows, N = 31 473 /
-// 466).  From 1 / 2 of such a wave's entries on rather than a half: up to 1.1 / 1.3 times as long; from a quarter on: the same.
-void wcsr_build_teams(int64_t n_entries, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks, std::vector<int32_t> &teams) {
+// 466).  From as many entries on as such a wave would have, rather than half: up to 1.1 / 1.3 times as long; from a quarter on: the same.
+// The chunks of nearly dense rows are not among them: they are many, and meet in L2 as they are dealt.  Where a wave walks an entry at a
+// time it can pay to share those of more than 100 entries too (wcsr_share_chunks): `wide` holds the lists for that.
+void wcsr_build_teams(int64_t n_entries, const HostRows &rows, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks,
+                      std::vector<int32_t> &teams, HostWide &wide) {
     const int64_t least = std::max<int64_t>(65, n_entries / (2 * 8192));
-    std::vector<int32_t> of_xcd[8];
-    auto take = [&](std::vector<int32_t> &list, bool rows) {
+    auto length = [&](int32_t r) { return (int64_t)rows.row_ptr[r + 1] - rows.row_ptr[r]; };
+    std::vector<int32_t> of_xcd[8];  // four to a workgroup, which the XCDs take round-robin
+    // takes tasks out of a list
+    auto take = [&](std::vector<int32_t> &list, bool whole, auto fits) {
         bool left = false;
         for (size_t i = 0; i < list.size(); i += 4) {
-            const bool empty = rows ? list[i + 1] == 0 : list[i + 2] >= list[i + 3];
-            if (empty) continue;
-            if (list[i + 3] - list[i + 2] < least || (rows && list[i + 1] != 1)) {
+            if (whole ? list[i + 1] == 0 : list[i + 2] >= list[i + 3]) continue;  // fills up
+            if (!fits(&list[i])) {
                 left = true;
                 continue;
             }
             auto &to = of_xcd[i / 16 % 8];
-            to.insert(to.end(), {list[i], rows ? -1 : list[i + 1], list[i + 2], list[i + 3]});
+            to.insert(to.end(), {list[i], whole ? -1 : list[i + 1], list[i + 2], list[i + 3]});
             std::fill(list.begin() + i, list.begin() + i + 4, 0);
         }
         if (!left) list.clear();
     };
-    take(chunks, false);
-    take(tasks, true);
-    size_t most = 0;
-    for (auto &v : of_xcd) most = std::max(most, v.size());
-    teams.assign(most * 8, 0);
-    for (size_t x = 0; x < 8; ++x)
-        for (size_t i = 0; i < of_xcd[x].size(); i += 4)
-            std::copy(of_xcd[x].begin() + i, of_xcd[x].begin() + i + 4, teams.begin() + i * 8 + x * 4);
+    // a list of them, `per` to a workgroup
+    auto deal = [&](std::vector<int32_t> &out, size_t per) {
+        size_t most = 0;
+        for (auto &v : of_xcd) most = std::max(most, ceil_div(v.size() / 4, per) * per);
+        out.assign(most * 8 * 4, 0);
+        for (size_t x = 0; x < 8; ++x) {
+            for (size_t i = 0; i < of_xcd[x].size() / 4; ++i)
+                std::copy(of_xcd[x].begin() + 4 * i, of_xcd[x].begin() + 4 * i + 4, out.begin() + 4 * ((i / per * 8 + x) * per + i % per));
+            of_xcd[x].clear();
+        }
+    };
+    take(chunks, false, [&](const int32_t *c) { return c[3] - c[2] >= least && length(c[0]) < rows.dense_len; });
+    take(tasks, true, [&](const int32_t *c) { return c[3] - c[2] >= least && c[1] == 1; });
+    deal(teams, 1);
+
+    wide = HostWide();
+    std::vector<uint8_t> shared;  // rows
+    for (size_t i = 0; i < rows.split.size(); i += 4)
+        if (const int32_t r = rows.split[i]; length(r) >= rows.dense_len && length(r) > std::max<int64_t>(least, 100) * rows.split[i + 2]) {
+            shared.resize(rows.row_ptr.size());
+            shared[r] = 1;
+        }
+    if (shared.empty()) return;
+    wide.chunks = chunks;
+    take(wide.chunks, false, [&](const int32_t *c) {
+        if (!shared[c[0]]) return false;
+        ++wide.count;
+        wide.len += c[3] - c[2];
+        return true;
+    });
+    deal(wide.teams, 1);
+    if (wide.count > 0) wide.len /= wide.count;
+    take(wide.chunks, false, [](const int32_t *) { return true; });
+    deal(wide.chunks, 4);
 }
 
 void wcsr_zero_windows(const std::vector<int32_t> &wrp, int32_t task_cols, std::vector<int32_t> &zw) {

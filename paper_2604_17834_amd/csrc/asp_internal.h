@@ -149,6 +149,12 @@ struct HostDense {
     std::vector<int32_t> tasks, chunks, split;   // as in HostRows; split: the dense rows first
 };
 
+// Chunks of nearly dense rows for workgroups instead of waves, and the list of chunks without them (wcsr_build_teams).
+struct HostWide {
+    std::vector<int32_t> teams, chunks;
+    int64_t count = 0, len = 0;  // of those chunks, and their entries in the mean
+};
+
 // Long rows of scattered entries that walk the columns of B together (wcsr_build_groups, asp_wcsr_groups.hip), and the
 // lists of HostRows without them.
 struct HostGroups {
@@ -182,7 +188,8 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
                        int32_t b_row, int32_t task_cols, const HostWcsr &in, const HostRows &rows, HostGroups &out);
 void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
                       const HostRows &rows, HostDense &out);
-void wcsr_build_teams(int64_t n_entries, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks, std::vector<int32_t> &teams);
+void wcsr_build_teams(int64_t n_entries, const HostRows &rows, std::vector<int32_t> &chunks, std::vector<int32_t> &tasks,
+                      std::vector<int32_t> &teams, HostWide &wide);
 inline int64_t split_scratch_rows(const std::vector<int32_t> &split) {  // of a list of split rows, all together
     int64_t rows = 0;
     for (size_t i = 2; i < split.size(); i += 4) rows += split[i];
@@ -243,6 +250,10 @@ struct asp_handle {
     bool tiles_dealt = false;
     int64_t n_teams = 0, scratch_rows = 0;  // (scratch_rows: that the split rows of the list add, here and in the lists below)
     int32_t *d_teams = nullptr;           // those that a workgroup takes instead of a wave (wcsr_build_teams)
+    struct Wide {                         // HostWide; its teams stand before the others
+        int64_t n_teams = 0, n_chunks = 0, count = 0, len = 0;
+        int32_t *d_chunks = nullptr;
+    } wide, d_wide;
     int32_t *d_row_tasks = nullptr, *d_chunks = nullptr, *d_split_rows = nullptr, *d_tile_tasks = nullptr, *d_tile_split = nullptr;
     int32_t *d_e_row_ptr = nullptr, *d_e_col = nullptr;
     void *d_e_val = nullptr;
@@ -312,7 +323,9 @@ constexpr int64_t rows_launch_end(int64_t waves, int64_t first, int64_t n_teams)
     const int64_t most = first + (1 << 26) - 32 - 4 * n_teams;
     return waves < most ? waves : most;
 }
-static_assert(launch_fits(131072 + ceil_div(rows_launch_end(1ll << 31, 0, 131072), 4), 256), "one launch");
+static_assert(launch_fits(262144 + ceil_div(rows_launch_end(1ll << 31, 0, 262144), 4), 256), "one launch");
+// whether workgroups share the chunks of nearly dense rows too: `count` of them, of `len` entries each
+bool wcsr_share_chunks(const asp_handle *h, int64_t N, int64_t count, int64_t len);
 // how many of the split rows (the first of the call's list) have their scratch rows added by many threads
 int64_t wcsr_rows_sum_many(const asp_handle *h, int64_t N);
 // the groups of long rows: whether calls of this width (with scratch) use them, and their kernel

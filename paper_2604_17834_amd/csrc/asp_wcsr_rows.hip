@@ -389,19 +389,42 @@ __global__ __launch_bounds__(COLS *J) void wcsr_rows_sum_kernel(const int4 *__re
 }
 
 // ---- host side ------------------------------------------------------------------------------------
+// Where a wave walks such a chunk an entry at a time (walk_rows), and not the 64 entries of the shortest: four waves are as much
+// more to start as they are less to walk; and where their number leaves the chip waiting for the last ones, or the rows of B are long.
+// us, band of 13 and long rows with a tenth of the columns, by a wave each / by four.  fp32, N = 128: 30 000 rows, 48 long ones, chunks of
+// 128 23.4 / 21.6, 60 000 33.5 / 32.8, 250 000 (8900 of them) 108 / 112; 56, of 192, 30 000 22.5 / 20.5, 250 000 102 / 100 (N = 66 88 / 90);
+// N = 256: 120 000 rows, 40, 96 / 84, 56 110 / 92; 100 000, 30, of 64 75 / 83.  bf16, N = 160: 30 000, 30, of 192 20.9 / 15.8, 250 000, 24, of 128
+// (4500) 61 / 62, 26 61 / 64, 56, of 320, 88 / 83.  With up to 16 lanes to a row of B (walk_chunk) never: fp32, N = 20, 298 434 rows, 33, 43 / 51;
+// bf16, N = 77, 198 717 rows, 53, of 320 55 / 64, N = 68, 736 246 rows, 48 133 / 150.
+bool wcsr_share_chunks(const asp_handle *h, int64_t N, int64_t count, int64_t len) {
+    const bool f32 = h->dtype == ASP_DT_F32;
+    if (count == 0 || N <= (f32 ? 64 : 128)) return false;
+    return count <= (len > 160 ? 5000 : 2500) || (f32 ? N > 128 : N > 160 || len > 160);
+}
+
 template <typename T>
 static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, float *ws, hipStream_t stream) {
     const bool groups = ws && wcsr_groups_apply(h, N);  // long rows run there: the lists without them
     const bool dense = ws && !groups && wcsr_dense_apply(h, N);  // nearly dense rows run there
     const int32_t *d_chunks = groups ? h->d_g_chunks : dense ? h->d_d_chunks : h->d_chunks;
     const int32_t *d_row_tasks = groups ? h->d_g_row_tasks : dense ? h->d_d_row_tasks : h->d_row_tasks;
-    const int32_t *d_teams = groups ? h->d_g_teams : dense ? h->d_d_teams : h->d_teams;
-    const int64_t n_chunks = groups ? h->n_g_chunks : dense ? h->n_d_chunks : h->n_chunks;
+    const int4 *d_teams = (const int4 *)(groups ? h->d_g_teams : dense ? h->d_d_teams : h->d_teams);
+    int64_t n_chunks = groups ? h->n_g_chunks : dense ? h->n_d_chunks : h->n_chunks;
     const int64_t n_row_tasks = groups ? h->n_g_row_tasks : dense ? h->n_d_row_tasks : h->n_row_tasks;
     if (groups) wcsr_groups_launch(h, B, N, ws, stream);
     if (dense) wcsr_dense_launch(h, B, N, ws, stream);
+    int64_t n_teams = groups ? h->n_g_teams : dense ? h->n_d_teams : h->n_teams, end;  // (131 072 at most, twice)
+    if (!groups) {
+        const asp_handle::Wide &wide = dense ? h->d_wide : h->wide;
+        if (wcsr_share_chunks(h, N, wide.count, wide.len)) {
+            n_teams += wide.n_teams;
+            d_chunks = wide.d_chunks;
+            n_chunks = wide.n_chunks;
+        } else {
+            d_teams += wide.n_teams;
+        }
+    }
     const int64_t waves = n_chunks + n_row_tasks;
-    int64_t n_teams = groups ? h->n_g_teams : dense ? h->n_d_teams : h->n_teams, end;  // (131 072 at most)
     for (int64_t first = 0; first < waves || n_teams > 0; first = end, n_teams = 0) {
         end = rows_launch_end(waves, first, n_teams);
         const int64_t c0 = std::min(first, n_chunks), c1 = std::min(end, n_chunks), t0 = first - c0, t1 = end - c1;
@@ -409,7 +432,7 @@ static void launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, 
 #define ASP_ROWS(E, CE, CL)                                                                                          \
     hipLaunchKernelGGL((wcsr_rows_kernel<T, E, CE, CL>),                                                             \
                        dim3((unsigned)(n_teams + ceil_div(end - first, 4)), (unsigned)ceil_div(N, 64 * (E))), dim3(256), 0, \
-                       stream, (const int4 *)d_teams, (int)n_teams, (const int4 *)d_chunks + c0, (int)(c1 - c0), (const int4 *)d_row_tasks + t0, (int)(t1 - t0), \
+                       stream, d_teams, (int)n_teams, (const int4 *)d_chunks + c0, (int)(c1 - c0), (const int4 *)d_row_tasks + t0, (int)(t1 - t0), \
                        h->d_e_row_ptr, h->d_e_col, (const T *)h->d_e_val, (const T *)B, (T *)C, N, ws)
         if (N <= 16) ASP_ROWS(1, 1, 16);
         else if (N <= 32) ASP_ROWS(1, 2, 16);

@@ -165,3 +165,28 @@ def test_a_launch_of_the_walk_by_rows_takes_fewer_than_2_to_the_32_threads(lists
 ])
 def test_columns_of_a_lane(lists_of, height, tasks, columns):
     assert lists_of("columns", height, tasks, *columns)["columns"] == [[c] for c in columns.values()]
+
+
+@pytest.mark.parametrize("m,k,height,task_cols,lengths,dense", [
+    (48 * 16, 100000, 16, 512, [10000, 300, 64, 65] + [2] * 12, True),      # nearly dense rows, and whole rows around the shortest
+    (30 * 16, 100000, 16, 512, [10000, 1500] + [2] * 14, True),             # long rows that are not, beside them
+    (20 * 16, 100000, 16, 512, [20000] + [2] * 15 + [9000] + [2] * 15, True),   # chunks of more and of less than 100 entries
+    (700, 300000, 16, 512, [2000, 513, 512, 65, 64, 63, 1, 0], False),
+    (700, 300000, 64, 100, [2000, 101, 100, 66, 65, 64, 1, 0], False),      # short tasks
+    (64, 50000, 16, 512, [40, 3], False),                                   # nothing to share
+])
+def test_rows_and_chunks_that_workgroups_share(lists_of, m, k, height, task_cols, lengths, dense):
+    got = lists_of("teams", m, k, height, task_cols, *lengths)
+    (teams, wide, count, length), (least, of_dense, as_long) = got["teams"][0], got["least"][0]
+    assert teams % 8 == 0 and wide % 8 == 0 and (count > 0) == dense and 0 <= count <= wide <= 2 * count and (length > 100) == dense
+    assert (least >= 65 or teams == 0) and of_dense == 0 and as_long == 0 and got["moved"] == [[0]]
+    assert len(got["row"]) == m and all(row[1:] == [0, 1, 0, 1] for row in got["row"])
+
+
+@pytest.mark.parametrize("bf16,N,chunks,length,shared", [
+    (0, 64, 100, 512, 0), (0, 65, 100, 128, 1), (0, 128, 0, 0, 0), (0, 128, 2500, 128, 1), (0, 128, 2501, 128, 0), (0, 128, 5000, 192, 1),
+    (0, 128, 5001, 192, 0), (0, 129, 60000, 128, 1), (1, 128, 100, 512, 0), (1, 129, 100, 128, 1), (1, 160, 4500, 128, 0),
+    (1, 160, 60000, 192, 1), (1, 161, 4500, 128, 1),
+])
+def test_chunks_of_nearly_dense_rows_that_workgroups_share(lists_of, bf16, N, chunks, length, shared):
+    assert lists_of("share", bf16, N, chunks, length)["share"] == [[shared]]

@@ -17,6 +17,10 @@
 //   dense M K H T L..  M rows of K columns with L.. entries in turn, spread over all, in windows of H rows, tasks of T columns: the
 //                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
 //                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
+//   teams M K H T L..  the same rows by waves and workgroups: how many workgroups, those for chunks of nearly dense rows, and how many
+//                    these are, of how many entries; the least entries of the others, how many of them nearly dense rows have, and of
+//                    what waves walk what is as long; chunks that change their XCD; and "row r difference times difference times" without and with the chunks shared
+//   share D N C L    whether workgroups share C chunks of L entries for N columns, D: fp32 (0) or bf16 (1)
 //   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
 //   unaligned B R N..  R block-rows of height B on 256 compute units: the tile width for N.. columns in rows that are not aligned
 //   columns H T N..  T tasks of windows of height H in fp32: the columns of a lane for N.. columns
@@ -322,6 +326,64 @@ static int dense(int64_t m, int64_t k, int32_t height, int32_t task_cols, const 
     return 0;
 }
 
+static int teams(int64_t m, int64_t k, int32_t height, int32_t task_cols, const std::vector<int32_t> &lengths) {
+    Spread a;
+    if (!a.make(m, k, height, task_cols, lengths)) return 1;
+    auto dense_row = [&](int64_t r) { return a.rows.row_ptr[r + 1] - a.rows.row_ptr[r] >= a.rows.dense_len; };
+    std::vector<int32_t> chunks = a.rows.chunks, tasks = a.rows.tasks, list;
+    asp::HostWide wide;
+    asp::wcsr_build_teams(a.rows.n_entries, a.rows, chunks, tasks, list, wide);
+    const auto &shared = wide.teams;
+    auto on_xcd = [&](const int32_t *c, size_t xcd) {
+        size_t t = 0;
+        while (t < chunks.size() && !std::equal(c, c + 4, chunks.begin() + t)) t += 4;
+        return t < chunks.size() && t / 16 % 8 == xcd;
+    };
+    std::printf("teams %zu %zu %lld %lld\n", list.size() / 4, shared.size() / 4, (long long)wide.count, (long long)wide.len);
+    int64_t least = INT64_MAX, of_dense = 0, as_long = 0, moved = 0;
+    for (size_t i = 0; i < list.size(); i += 4)
+        if (list[i + 2] < list[i + 3]) least = std::min<int64_t>(least, list[i + 3] - list[i + 2]), of_dense += dense_row(list[i]);
+    const int64_t line = std::max<int64_t>(65, a.rows.n_entries / 16384);
+    for (size_t i = 0; i < chunks.size(); i += 4) as_long += chunks[i + 3] - chunks[i + 2] >= line && !dense_row(chunks[i]);
+    for (size_t i = 0; i < tasks.size(); i += 4) as_long += tasks[i + 1] == 1 && tasks[i + 3] - tasks[i + 2] >= line;
+    for (size_t i = 0; i < shared.size(); i += 4) moved += shared[i + 2] < shared[i + 3] && !on_xcd(&shared[i], i / 4 % 8);
+    for (size_t i = 0; i < wide.chunks.size(); i += 4) moved += wide.chunks[i + 2] < wide.chunks[i + 3] && !on_xcd(&wide.chunks[i], i / 16 % 8);
+    std::printf("least %lld %lld %lld\nmoved %lld\n", (long long)least, (long long)of_dense, (long long)as_long, (long long)moved);
+    std::vector<double> c[2];
+    std::vector<int> times[2];
+    for (int mode = 0; mode < 2; ++mode) {
+        std::vector<double> ws(a.slots * height, 0);
+        std::vector<int> ws_times(a.slots * height, 0);
+        c[mode].assign(m, 0), times[mode].assign(m, 0);
+        auto all = [&](const std::vector<int32_t> &of) {
+            for (size_t i = 0; i < of.size(); i += 4) {
+                if (of[i + 2] >= of[i + 3]) continue;
+                if (of[i + 1] < 0) c[mode].at(of[i]) = a.walk(of[i + 2], of[i + 3]), ++times[mode][of[i]];
+                else ws.at(of[i + 1]) = a.walk(of[i + 2], of[i + 3]), ++ws_times[of[i + 1]];
+            }
+        };
+        all(list);
+        if (mode == 1 && wide.count > 0) all(shared), all(wide.chunks);
+        else all(chunks);
+        for (size_t i = 0; i < tasks.size(); i += 4)
+            for (int64_t r = tasks[i]; r < tasks[i] + tasks[i + 1]; ++r) c[mode].at(r) = a.walk(a.rows.row_ptr[r], a.rows.row_ptr[r + 1]), ++times[mode][r];
+        for (size_t i = 0; i < a.rows.split.size(); i += 4) {
+            for (int64_t j = a.rows.split[i + 1]; j < a.rows.split[i + 1] + a.rows.split[i + 2]; ++j) {
+                c[mode].at(a.rows.split[i]) += ws.at(j);
+                if (ws_times[j] != 1) return std::printf("scratch row %lld written %d times\n", (long long)j, ws_times[j]), 1;
+            }
+            ++times[mode][a.rows.split[i]];
+        }
+    }
+    for (int64_t r = 0; r < m; ++r) {
+        if (a.rows.row_ptr[r + 1] == a.rows.row_ptr[r] && a.rp[r + 1] > a.rp[r]) continue;  // by tiles
+        double want = 0;
+        for (int64_t e = a.rp[r]; e < a.rp[r + 1]; ++e) want += (1 + e % 3) * (double)(a.ci[e] % 13 + 1);
+        std::printf("row %lld %lld %d %lld %d\n", (long long)r, (long long)(c[0][r] - want), times[0][r], (long long)(c[1][r] - want), times[1][r]);
+    }
+    return 0;
+}
+
 static int xt(char **argv) {
     asp_handle h;
     h.b_row = std::atoi(argv[0]), h.n_brows = std::atoll(argv[1]), h.n_units = std::atoll(argv[2]), h.hb.max_blocks = std::atoll(argv[3]);
@@ -365,6 +427,14 @@ int main(int argc, char **argv) {
         for (int32_t n : lengths(4)) std::printf("columns %d\n", asp::wcsr_lane_columns(&h, n));
         return 0;
     }
+    if (argc == 6 && std::strcmp(argv[1], "share") == 0) {
+        asp_handle h;
+        h.dtype = std::atoi(argv[2]) ? ASP_DT_BF16 : ASP_DT_F32;
+        std::printf("share %d\n", (int)asp::wcsr_share_chunks(&h, std::atoll(argv[3]), std::atoll(argv[4]), std::atoll(argv[5])));
+        return 0;
+    }
+    if (is("teams", 6))
+        return teams(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
     if (is("dense", 6))
         return dense(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
