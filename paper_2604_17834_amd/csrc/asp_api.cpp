@@ -288,6 +288,8 @@ static asp_status_t create_impl(const asp_config_t *cfg, int64_t m, int64_t k, i
         wcsr_build_teams(rows.n_entries, rows, dense.chunks, dense.tasks, d_teams, d_wide);
         h->dense_ranges = dense.ranges;
         h->dense_blocks = dense.blocks;
+        h->dense_per_pass = dense.per_pass;
+        h->dense_meet_tenths = dense.meet_tenths;
         h->n_d_row_tasks = (int64_t)dense.tasks.size() / 4;
         h->n_d_chunks = (int64_t)dense.chunks.size() / 4;
         h->n_d_split_rows = (int64_t)dense.split.size() / 4;

@@ -1107,14 +1107,15 @@ void wcsr_build_groups(int64_t m, const int32_t *row_ptr, const int32_t *col_idx
     out.n_groups = G;
 }
 
-// Nearly dense rows that walk their entries over columns of B in LDS (asp_wcsr_dense.hip): of those whose chunks would be cut at the
-// same columns, in order and 64 at a time, as a workgroup takes them and reads all of B for them, the ones among which a column holds
-// 4.5 entries in the mean (2 000 000 rows, band of 27, N = 64, long rows with a tenth of the columns, chunks / so: 32 of them 412 / 420
-// us, 48 452 / 424, 64 488 / 427), when each of them has scratch rows for 64 ranges of columns.  (So a row has 18 entries in a block of
-// 256 columns in the mean, and the table of their first entries takes a 36th of the entries' bytes at most.)  The rest keeps its lists.
+// Nearly dense rows that walk their entries over columns of B in LDS (asp_wcsr_dense.hip): those whose chunks would be cut at the
+// same columns, in equal numbers to a pass over B, 64 at most, when a column holds 4.5 entries of every pass in the mean (2 000 000 rows, band of
+// 27, N = 64, long rows with a tenth of the columns, chunks / so: 32 of them 412 / 420 us, 48 452 / 424, 64 488 / 427), and each row has
+// scratch rows for 64 ranges of columns.  (So a row has 18 entries in a block of 256 columns in the mean, and the table of their first entries
+// takes a 36th of the entries' bytes at most.)  All of them or none: 36 rows left of 100 lose more as chunks, whose rows of B are met less
+// often then, than the others gain (600 000 rows, N = 64 139 by chunks, 171).  The rest keeps its lists.
 void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx, int32_t b_row, int32_t task_cols, const HostWcsr &in,
                       const HostRows &rows, HostDense &out) {
-    constexpr int64_t MIN_MEET_TENTHS = 45, MIN_RANGES = 64;
+    constexpr int64_t MIN_RANGES = 64;
     out = HostDense();
     auto length = [&](int32_t r) { return (int64_t)row_ptr[r + 1] - row_ptr[r]; };
     int32_t k_used = 1;
@@ -1124,17 +1125,18 @@ void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx,
             candidates.push_back(rows.split[i]);
             k_used = std::max(k_used, col_idx[row_ptr[rows.split[i] + 1] - 1] + 1);
         }
-    int64_t entries = 0;
+    if (candidates.empty()) return;
+    const size_t per_pass = ceil_div(candidates.size(), ceil_div(candidates.size(), HostDense::ROWS));
+    int64_t entries = 0, meet = INT64_MAX;
     std::vector<uint8_t> dense((size_t)m, 0);
-    for (size_t c = 0; c < candidates.size(); c += HostDense::ROWS) {
-        const size_t end = std::min(candidates.size(), c + HostDense::ROWS);
+    for (size_t c = 0; c < candidates.size(); c += per_pass) {
+        const size_t end = std::min(candidates.size(), c + per_pass);
         int64_t sum = 0;
-        for (size_t i = c; i < end; ++i) sum += length(candidates[i]);
-        if (10 * sum < MIN_MEET_TENTHS * k_used) continue;
-        for (size_t i = c; i < end; ++i) dense[candidates[i]] = 1;
+        for (size_t i = c; i < end; ++i) sum += length(candidates[i]), dense[candidates[i]] = 1;
+        meet = std::min(meet, 10 * sum / k_used);
         entries += sum;
     }
-    if (entries == 0) return;
+    if (meet < 45) return;
     int64_t fewest = HostDense::RANGES;
     for (size_t i = 0; i < rows.split.size();) {
         const int64_t w = rows.split[i] / b_row;
@@ -1157,6 +1159,8 @@ void wcsr_build_dense(int64_t m, const int32_t *row_ptr, const int32_t *col_idx,
     }
     const int64_t n = (int64_t)out.rows.size() / 4, blocks = ceil_div(k_used, HostDense::COLS);
     if (n > 65535 * HostDense::ROWS || std::min(fewest, blocks) < MIN_RANGES) return;
+    out.per_pass = (int64_t)per_pass;
+    out.meet_tenths = meet;
     out.blocks = blocks;
     out.ranges = std::min(fewest, blocks);
     out.ptr.resize((size_t)((blocks + 1) * n));

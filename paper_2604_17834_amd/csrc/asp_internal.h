@@ -141,9 +141,10 @@ struct HostRows {
 
 // Nearly dense rows that meet in LDS (wcsr_build_dense, asp_wcsr_dense.hip), and the lists of HostRows without them.
 struct HostDense {
-    static constexpr int COLS = 256, ROWS = 64;  // columns of B at a time; rows to a workgroup
+    static constexpr int COLS = 256, ROWS = 64;  // columns of B at a time; rows to a workgroup, at most
     static constexpr int64_t RANGES = 256;       // of columns, at most
-    int64_t ranges = 0, blocks = 0;              // ranges 0: the rest is not used
+    int64_t ranges = 0, blocks = 0, per_pass = 0;  // ranges 0: the rest is not used; per_pass: rows to a workgroup
+    int64_t meet_tenths = 0;                       // entries of a pass in a column in the mean, in tenths
     std::vector<int32_t> rows;                   // [..][4] = {row, first scratch row, 0, 0}
     std::vector<int32_t> ptr;                    // [rows][blocks + 1] first entry of each row from a block's first column on
     std::vector<int32_t> tasks, chunks, split;   // as in HostRows; split: the dense rows first
@@ -264,7 +265,7 @@ struct asp_handle {
     uint64_t *d_group_entries = nullptr;
     int32_t *d_group_tasks = nullptr, *d_group_slots = nullptr, *d_g_row_tasks = nullptr, *d_g_chunks = nullptr, *d_g_split_rows = nullptr;
     // WCSR: nearly dense rows over columns in LDS, and the lists of what is left beside them, for calls with scratch (HostDense)
-    int64_t n_dense = 0, dense_ranges = 0, dense_blocks = 0;
+    int64_t n_dense = 0, dense_ranges = 0, dense_blocks = 0, dense_per_pass = 0, dense_meet_tenths = 0;
     int64_t n_d_row_tasks = 0, n_d_chunks = 0, n_d_split_rows = 0, n_d_teams = 0, d_scratch_rows = 0;
     int32_t *d_dense_rows = nullptr, *d_dense_ptr = nullptr, *d_d_row_tasks = nullptr, *d_d_chunks = nullptr, *d_d_split_rows = nullptr,
             *d_d_teams = nullptr;

@@ -21,8 +21,8 @@ constexpr int DENSE_COLS = HostDense::COLS, DENSE_WAVES = 16, DENSE_RPW = HostDe
 }
 
 // rows[r] = {row, first scratch row, -, -}; block_ptr[r * (n_blocks + 1) + b]: first entry of row r (a position of col / val) in the
-// columns from b * 256 on, b = 0 .. n_blocks.  grid = (ranges, tiles of 64 columns of B, groups of 64 rows).  N >= 64.
-__global__ __launch_bounds__(DENSE_WAVES * 64) void wcsr_dense_kernel(const int4 *__restrict__ rows, int n_rows,
+// columns from b * 256 on, b = 0 .. n_blocks.  grid = (ranges, tiles of 64 columns of B, groups of per_pass <= 64 rows).  N >= 64.
+__global__ __launch_bounds__(DENSE_WAVES * 64) void wcsr_dense_kernel(const int4 *__restrict__ rows, int n_rows, int per_pass,
                                                                      const int32_t *__restrict__ block_ptr, int n_blocks, int K,
                                                                      const int32_t *__restrict__ col, const float *__restrict__ val,
                                                                      const float *__restrict__ B, int64_t N, float *__restrict__ ws) {
@@ -40,8 +40,8 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void wcsr_dense_kernel(const int4
     bool have[DENSE_RPW];
 #pragma unroll
     for (int r = 0; r < DENSE_RPW; ++r) {
-        const int x = blockIdx.z * HostDense::ROWS + r * DENSE_WAVES + wave;
-        have[r] = x < n_rows;
+        const int i = r * DENSE_WAVES + wave, x = blockIdx.z * per_pass + i;
+        have[r] = i < per_pass && x < n_rows;
         row_of[r] = have[r] ? x : n_rows - 1;
     }
 
@@ -178,15 +178,28 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void wcsr_dense_kernel(const int4
 }
 
 // ---- host side ------------------------------------------------------------------------------------
-// Where B passes 128 MB; from chunks its rows come faster where the memory-side cache holds it and the entries of a row are few.  us, band
-// of 15, N = 128 (100), 61 long rows, chunks / here: 300 000 rows (154 MB) 125 / 120, 600 000 (240 MB) 258 / 236, but 100 000, N = 64 (26 MB)
-// 29 / 37, N = 234 (94 MB) 83 / 113.  In bf16 chunks are always faster (600 000 rows 126 / 154).
-bool wcsr_dense_apply(const asp_handle *h, int64_t N) { return h->n_dense > 0 && N >= 64 && h->k * N * 4 >= (128ll << 20); }
+// Where the pass over B costs less than the chunks' rows of B, which come faster where the memory-side cache holds it, where a row is
+// walked by lane groups (N = 64) and where it is long and workgroups share the chunks (N > 128), and which have no columns to fill up.
+// us, band of 9, 54 long rows / 64, chunks / here: N = 64, 600 000 rows (154 MB) 105 / 115, 114 / 119, 1 500 000 (384 MB) 306 / 278, 324 / 280;
+// N = 72, 600 000 187 / 186, 206 / 186; N = 128, 300 000 (154 MB) 116 / 114, 122 / 114, 600 000 252 / 219, 269 / 221.  Shared, 54 of them: N = 130,
+// 300 000 143 / 174, 600 000 319 / 338; N = 160 (192 columns walked), 300 000 142 / 164, 600 000 (384 MB) 324 / 321; N = 256, 300 000 (307 MB) 231
+// / 238, 600 000 463 / 448; N = 200 (256 walked), 600 000 429 / 457.  Not shared, 64 of them, 600 000 rows: N = 130 333 / 342, N = 160 345 / 323, N =
+// 200 457 / 461: even or faster here, and 1.6e-7 from the 64-bit sums instead of 2.7e-7 (shared 1.6e-7, lane groups 1.6e-7), with 4 entries a
+// column walked and more; 54 of them, 1 500 000 rows, N = 130 770 / 796.  In two passes, 100 of them: 300 000 rows, N = 128 151 / 160, 600 000
+// (307 MB) 335 / 313; 122, 600 000, N = 160 455 / 466, N = 200 596 / 677; 115, N = 192 493 / 485.  In bf16 chunks are always faster (600 000 rows 126 / 154).
+bool wcsr_dense_apply(const asp_handle *h, int64_t N) {
+    const int64_t bytes = h->k * N * 4, walked = 64 * ceil_div(N, 64);
+    const bool one_pass = h->n_dense <= h->dense_per_pass;
+    if (h->n_dense == 0 || N < 64 || bytes < ((N == 64 ? 224ll : one_pass ? 128ll : 160ll) << 20)) return false;
+    if (N <= 128) return true;
+    if (wcsr_share_chunks(h, N, h->wide.count, h->wide.len)) return bytes >= 352ll << 20 && 5 * walked <= 6 * N;
+    return one_pass ? h->dense_meet_tenths * N >= 40 * walked : 20 * walked <= 21 * N;
+}
 
 void wcsr_dense_launch(const asp_handle *h, const void *B, int64_t N, float *ws, hipStream_t stream) {
-    const dim3 grid((unsigned)h->dense_ranges, (unsigned)ceil_div(N, 64), (unsigned)ceil_div(h->n_dense, HostDense::ROWS));
+    const dim3 grid((unsigned)h->dense_ranges, (unsigned)ceil_div(N, 64), (unsigned)ceil_div(h->n_dense, h->dense_per_pass));
     hipLaunchKernelGGL(wcsr_dense_kernel, grid, dim3(DENSE_WAVES * 64), 0, stream, (const int4 *)h->d_dense_rows, (int)h->n_dense,
-                       h->d_dense_ptr, (int)h->dense_blocks, (int)h->k, h->d_e_col, (const float *)h->d_e_val, (const float *)B, N, ws);
+                       (int)h->dense_per_pass, h->d_dense_ptr, (int)h->dense_blocks, (int)h->k, h->d_e_col, (const float *)h->d_e_val, (const float *)B, N, ws);
 }
 
 }  // namespace asp

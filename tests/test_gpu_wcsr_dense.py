@@ -1,5 +1,6 @@
-"""Nearly dense rows of a WCSR matrix in fp32 that are walked over columns of B in LDS: more than the 64 rows of one workgroup (a
-few, which stay with their chunks, and enough for a second one), an odd width, columns that no row stores, rows that are empty in whole blocks of columns or full in some, beside shorter rows.
+"""Nearly dense rows of a WCSR matrix in fp32, walked over columns of B in LDS or, where that is not faster, in chunks: the rows of one
+workgroup and of two, odd widths, columns that no row stores, rows that are empty in whole blocks of columns or full in some, beside
+shorter rows.
 
 1e-5 * S, S = |A| x |B| from the oracle, as everywhere in fp32; and, from the 64-bit result, no further than by chunks."""
 import numpy as np
@@ -13,7 +14,8 @@ from paper_2604_17834_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_dense,k,N,height", [(64, 530_001, 64, 16), (70, 300_007, 131, 16), (112, 300_007, 131, 16), (48, 530_001, 65, 64)])
+@pytest.mark.parametrize("n_dense,k,N,height", [(64, 530_001, 64, 16), (70, 300_007, 131, 16), (64, 920_001, 64, 16),
+                                                  (112, 331_001, 127, 16), (48, 500_001, 191, 16), (48, 530_001, 65, 64)])
 def test_dense_rows(n_dense, k, N, height):
     rng = np.random.default_rng(n_dense + N)
     m, stored = 16 * (n_dense + 4), k - 100
@@ -54,7 +56,7 @@ def test_dense_rows(n_dense, k, N, height):
 
 def test_whole_rows_do_not_depend_on_the_width():
     """Whole rows beside dense ones, either side of the length from which a workgroup shares a row (172 entries: all entries / 16384): a
-    slice of B's columns gives a slice of C, bit for bit, at a width that walks the dense rows in chunks (63) and one that does not."""
+    slice of B's columns gives a slice of C, bit for bit, at widths that walk the dense rows in chunks and at those that do not (65, 128)."""
     rng = np.random.default_rng(3)
     n_dense, k = 48, 530_001
     whole = [64, 65, 66, 80, 100, 128, 150, 170, 171, 172, 173, 174, 200, 300, 400, 511, 512]
@@ -69,7 +71,7 @@ def test_whole_rows_do_not_depend_on_the_width():
     asp.asp_reserve(h, 130)
     B = torch.from_numpy(synth.dense_normal(k, 130, "f32", seed=4)).cuda()
     got = {}
-    for N in (17, 63, 64, 130):
+    for N in (17, 63, 65, 128, 130):
         C = torch.full((m, N), float("nan"), device="cuda")
         Bn = B[:, :N].contiguous()
         asp.asp_spmm(h, Bn.data_ptr(), C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
@@ -77,5 +79,5 @@ def test_whole_rows_do_not_depend_on_the_width():
         got[N] = C.cpu().numpy()[lengths <= 512]
     asp.asp_destroy(h)
     assert np.isfinite(got[130]).all()
-    for N in (17, 63, 64):
+    for N in (17, 63, 65, 128):
         assert np.array_equal(got[N].view(np.uint32), np.ascontiguousarray(got[130][:, :N]).view(np.uint32)), N

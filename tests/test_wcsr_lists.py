@@ -136,13 +136,28 @@ def test_no_dense_rows_where_64_of_them_do_not_meet(lists_of, m, k, height, task
     assert lists_of("dense", m, k, height, task_cols, *lengths)["dense"][0][0] == 0
 
 
-@pytest.mark.parametrize("n,taken", [(46, 46), (64, 64), (65, 64), (108, 64), (109, 109), (127, 127), (130, 128)])
-def test_dense_rows_are_taken_64_at_a_time(lists_of, n, taken):
+@pytest.mark.parametrize("n,per_pass", [(46, 46), (64, 64), (65, 0), (89, 0), (92, 46), (127, 64), (130, 0), (141, 47), (150, 50)])
+def test_dense_rows_are_taken_in_equal_passes(lists_of, n, per_pass):
     got = lists_of("dense", 16 * n, 100000, 16, 512, 10000, 300, *[2] * 14)
-    ranges, blocks, rows, table = got["dense"][0]
-    assert rows == taken and 64 <= ranges <= min(256, blocks) and blocks == 391
+    if not per_pass:                                     # passes of 33 to 45 rows: 3.3 to 4.5 entries a column
+        assert got["dense"][0][0] == 0
+        return
+    ranges, blocks, rows, table, taken = got["dense"][0]
+    assert rows == n and taken == per_pass and 64 <= ranges <= min(256, blocks) and blocks == 391
     assert 10 * got["fewest"][0][0] >= 45 * 99900 and 36 * 4 * table <= 8 * 10000 * rows
     assert len(got["row"]) == 16 * n and all(diff == 0 and times == 1 for _, diff, times in got["row"])
+
+
+@pytest.mark.parametrize("k,rows,shared,tenths,widths", [
+    (300_000, 50, 9000, 60, {63: 0, 64: 0, 65: 0, 111: 0, 112: 1, 128: 1, 129: 0, 160: 0, 192: 0, 256: 0, 320: 1}),
+    (600_000, 50, 9000, 60, {64: 0, 65: 1, 128: 1, 130: 0, 159: 0, 160: 1, 192: 1, 200: 0, 214: 1, 256: 1, 257: 0, 1000: 1}),
+    (600_000, 50, 0, 60, {64: 0, 65: 1, 128: 1, 130: 1, 200: 1, 257: 1}),
+    (600_000, 50, 0, 47, {65: 1, 128: 1, 130: 0, 160: 0, 192: 1, 200: 0, 257: 0}),
+    (2_000_000, 50, 0, 60, {32: 0, 63: 0, 64: 1, 72: 1, 130: 1, 159: 1, 192: 1}),
+    (300_000, 100, 0, 60, {112: 0, 128: 0, 130: 0, 192: 1}), (600_000, 100, 0, 60, {64: 0, 72: 1, 128: 1, 130: 0, 160: 0, 200: 0, 256: 1}),
+])
+def test_products_that_take_dense_rows_through_lds(lists_of, k, rows, shared, tenths, widths):
+    assert lists_of("apply", k, rows, shared, tenths, *widths)["apply"] == [[taken] for taken in widths.values()]
 
 
 @pytest.mark.parametrize("waves", [0, 5, 2**26 - 33, 2**26 - 32, 2**26 - 31, 2**26, 3 * 2**26])

@@ -15,12 +15,14 @@
 //                    rows have their scratch rows added by many threads, the fewest of one and the most of another; and how many of
 //                    how many split rows a product with 128 columns adds so
 //   dense M K H T L..  M rows of K columns with L.. entries in turn, spread over all, in windows of H rows, tasks of T columns: the
-//                    ranges and blocks of columns, rows of the nearly dense ones and of the table of their first entries; the fewest
-//                    entries among 64 of those rows; and, by their lists, "row r difference times" as above
+//                    ranges and blocks of columns, the nearly dense rows, the size of the table of their first entries and the rows to a
+//                    pass over B; the fewest entries of a pass; and, by their lists, "row r difference times" as above
 //   teams M K H T L..  the same rows by waves and workgroups: how many workgroups, those for chunks of nearly dense rows, and how many
 //                    these are, of how many entries; the least entries of the others, how many of them nearly dense rows have, and of
 //                    what waves walk what is as long; chunks that change their XCD; and "row r difference times difference times" without and with the chunks shared
 //   share D N C L    whether workgroups share C chunks of L entries for N columns, D: fp32 (0) or bf16 (1)
+//   apply K R C T N..  whether R nearly dense rows over K columns, of whose chunks C can be shared, T tenths of an entry a column, go through
+//                    LDS for N.. columns of B, 50 to a pass
 //   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
 //   unaligned B R N..  R block-rows of height B on 256 compute units: the tile width for N.. columns in rows that are not aligned
 //   columns H T N..  T tasks of windows of height H in fp32: the columns of a lane for N.. columns
@@ -285,14 +287,15 @@ static int dense(int64_t m, int64_t k, int32_t height, int32_t task_cols, const 
     asp::HostDense d;
     asp::wcsr_build_dense(m, a.rp.data(), a.ci.data(), height, task_cols, a.hw, a.rows, d);
     const int64_t n = d.ranges > 0 ? (int64_t)d.rows.size() / 4 : 0;
-    std::printf("dense %lld %lld %lld %lld\n", (long long)d.ranges, (long long)d.blocks, (long long)n, (long long)d.ptr.size());
+    std::printf("dense %lld %lld %lld %lld %lld\n", (long long)d.ranges, (long long)d.blocks, (long long)n, (long long)d.ptr.size(),
+                (long long)d.per_pass);
     if (n == 0) return 0;
     std::vector<double> ws(a.slots * height, 0), c(m, 0);
     std::vector<int> ws_times(a.slots * height, 0), times(m, 0);
     int64_t fewest = INT64_MAX, entries = 0;
     for (int64_t i = 0; i < n; ++i) {
         const int32_t *ptr = &d.ptr[i * (d.blocks + 1)], row = d.rows[4 * i];
-        if (i % asp::HostDense::ROWS == 0 && i > 0) fewest = std::min(fewest, entries), entries = 0;
+        if (i % d.per_pass == 0 && i > 0) fewest = std::min(fewest, entries), entries = 0;
         entries += ptr[d.blocks] - ptr[0];
         if (ptr[0] != a.rows.row_ptr[row] || ptr[d.blocks] != a.rows.row_ptr[row + 1]) return std::printf("ends of row %d\n", row), 1;
         for (int64_t x = 0; x < d.ranges; ++x) {
@@ -435,6 +438,13 @@ int main(int argc, char **argv) {
     }
     if (is("teams", 6))
         return teams(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
+    if (is("apply", 6)) {
+        asp_handle h;
+        h.k = std::atoll(argv[2]), h.n_dense = std::atoll(argv[3]), h.dense_per_pass = 50, h.dtype = ASP_DT_F32;
+        h.wide.count = std::atoll(argv[4]), h.wide.len = 192, h.dense_meet_tenths = std::atoll(argv[5]);
+        for (int32_t n : lengths(6)) std::printf("apply %d\n", (int)asp::wcsr_dense_apply(&h, n));
+        return 0;
+    }
     if (is("dense", 6))
         return dense(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), lengths(6));
     if (is("staged", 4)) return staged(std::atoi(argv[2]), std::atoll(argv[3]), lengths(4));
