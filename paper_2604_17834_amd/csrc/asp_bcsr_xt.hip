@@ -544,8 +544,10 @@ static bool launch_strips(const asp_handle *h, const void *X, void *Y, int64_t N
     if (vec && N <= 32) {
         const int waves = decode_waves(h, N);
         if (waves == 8 && N <= 16 && launch_decode<BR, 1, 8>(h, X, Y, N, stream)) return true;
-        if (waves == 4 && N <= 16 && launch_decode<BR, 1, 4>(h, X, Y, N, stream)) return true;
-        if (waves == 8 && N > 16 && launch_decode<BR, 2, 8>(h, X, Y, N, stream)) return true;
+        if constexpr (BR >= 64) {  // (32-row blocks: eight waves, up to 16 tokens)
+            if (waves == 4 && launch_decode<BR, 1, 4>(h, X, Y, N, stream)) return true;
+            if (waves == 8 && N > 16 && launch_decode<BR, 2, 8>(h, X, Y, N, stream)) return true;
+        }
     }
     if constexpr (BR == 128) {
         const int staged = vec ? bcsr_xt_staged_strips(h, N) : 0;

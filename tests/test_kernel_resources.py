@@ -1,6 +1,7 @@
 """Build-time guard (no GPU): the hot kernels must not touch scratch memory.  A spill or a stack object in one of
 them costs more than any tuning gains (a lone wave per SIMD cannot hide scratch latency), and it happens silently
 when a change makes the register allocator give up."""
+import functools
 import os
 import re
 import shutil
@@ -27,6 +28,7 @@ HOT = {
 }
 
 
+@functools.lru_cache(maxsize=4)
 def _compiled(source, *options):
     """What the compiler makes of a source's device code, as text."""
     with tempfile.TemporaryDirectory() as tmp:
@@ -91,3 +93,12 @@ def test_staged_strips_wait_for_their_last_products():
                 for w in code[i - 2:i]:
                     if w[0].startswith("v_") and not w[0].startswith("v_mfma"):
                         assert not read & _registers("v", w[1]), (w, l)
+
+
+def test_decode_kernels_that_are_built_are_reached():
+    """bcsr_xt_decode_kernel: the waves and tokens that decode_waves gives each block size, and no others."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    found = re.findall(r"\.name:\s+\S*bcsr_xt_decode_kernelILi(\d+)ELi(\d+)ELi(\d+)E", _compiled("asp_bcsr_xt.hip"))
+    shapes = {(int(a), int(b), int(c)) for a, b, c in found}
+    assert shapes == {(32, 1, 8), (64, 1, 4), (64, 1, 8), (64, 2, 8), (128, 1, 4), (128, 1, 8), (128, 2, 8)}
