@@ -19,11 +19,12 @@ HOT = {
     "asp_bcsr.hip": ["bcsr_spmm_kernel"],
     "asp_bcsr_dma.hip": ["bcsr_spmm_dma_kernel"],
     "asp_bcsr_strip.hip": ["bcsr_strip_kernel"],
-    "asp_bcsr_xt.hip": ["bcsr_xt_strip_kernel", "bcsr_xt_staged_kernel"],
+    "asp_bcsr_xt.hip": ["bcsr_xt_strip_kernel", "bcsr_xt_staged_kernel", "bcsr_xt_decode_kernel"],
     "asp_bcsr_f32.hip": ["bcsr_f32_spmm_kernel"],
     "asp_wcsr.hip": ["wcsr16_spmm_kernel", "wcsr32_spmm_kernel"],
     "asp_wcsr_rows.hip": ["wcsr_rows_kernel"],
     "asp_wcsr_groups.hip": ["wcsr_groups_kernel"],
+    "asp_wcsr_dense.hip": ["wcsr_dense_kernel"],
     "asp_wcsr_bf16.hip": ["wcsr_bf16_spmm_kernel"],
 }
 
@@ -45,13 +46,14 @@ def test_hot_kernels_use_no_scratch(source):
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not found")
     text = _compiled(source)
-    seen = 0
+    seen = set()
     for m in re.finditer(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", text):
         name, scratch = m.group(1), int(m.group(2))
-        if any(k in name for k in HOT[source]):
-            seen += 1
+        kernels = [k for k in HOT[source] if k in name]
+        if kernels:
+            seen.update(kernels)
             assert scratch == 0, "%s uses %d bytes of scratch per lane" % (name, scratch)
-    assert seen >= len(HOT[source])
+    assert seen == set(HOT[source])
 
 
 def test_groups_leave_room_for_three_workgroups():
