@@ -223,9 +223,22 @@ static bool launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, h
     return true;
 }
 
-// 64 x 128 tiles by two waves that divide the blocks, rather than by one for twice the columns, where the tiles are many: long
-// block-rows end sooner (18944 x 3584 at 90 %, 2048 columns, 128 / 64 / 32-row blocks 244 / 253 / 241 -> 244 / 242 / 235, geometric
-// lengths 374 / 372 / 276 -> 238 / 231 / 215; 4096 columns 471 / 467 / 467 -> 463 / 466 / 474).
+// 64 x 128 tiles, where they are many: by two waves that divide the blocks (false), or by one, side by side for twice the columns.
+// Two end long block-rows sooner (18944 x 3584 at 90 %, 2048 columns, 18 tiles to a compute unit, 128 / 64 / 32-row blocks 244 / 253 / 241 ->
+// 244 / 242 / 235, geometric lengths 374 / 372 / 276 -> 238 / 231 / 215), one starts and adds up less: from some 30 tiles to a unit on, but not
+// where block-rows are long and alike (two / one: 15 260 x 3035 at 95 %, geometric, 64-row, 8192 columns 355 / 340, 13 202 x 2023 at 50 % 1698 /
+// 1781), from fewer where all are short (12 034 x 1955 at 90 %, 128-row, 4096 columns 208 / 199, 12 567 x 4176 at 98 %, 8192 columns 188 / 172);
+// with 32-row blocks, whose waves have half the sums, where they are alike too (10 094 x 3359 at 95 %, 8192 columns 281 / 274).  Of 230 products
+// of 512 to 8192 columns 1.01 times faster in the mean than two everywhere, 1.06 than one.
+bool bcsr_f32_one_wave(const asp_handle *h, int64_t N) {
+    const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, tall = h->n_brows * h->b_row / 64 * ceil_div(N, 128);
+    const int64_t k_stored = h->n_units * h->b_row / h->n_brows;  // of a block-row in the mean
+    auto longest_within = [&](int64_t times) { return h->hb.max_blocks * h->n_brows <= times * h->n_units; };
+    if (h->b_row == 32) return tall >= 31 * cus || (longest_within(2) && k_stored <= 800);
+    if (k_stored <= 256 && longest_within(5) && tall >= 23 * cus) return true;  // (geometric lengths: 5 to 7 times the mean)
+    return tall >= 31 * cus && !longest_within(2);
+}
+
 // The largest wave tile that still gives the chip enough of them, and the narrower one where N would fill the wider one
 // badly.  us at 90 %, 64 x 64 blocks, tiles of 64 x 128 / 64 x 128 by four waves / 32 x 64 by four / 32 x 32 by eight:
 // 18944 x 3584 at 2048 columns 239 / 258 / 267 / -, at 1024 151 / 133 / 140 / 160, at 64 - / - / 19.5 / 16.2;
@@ -236,6 +249,7 @@ static bool launch_f32_rows(const asp_handle *h, const void *B, void *C, int64_t
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n32 = ceil_div(N, 32), n64 = ceil_div(N, 64), n128 = ceil_div(N, 128);
     const int64_t tall = h->n_brows * BR / 64 * n128;  // tiles of 64 x 128 elements
     if (N >= 4 && 4 * n128 * 8 <= 2 * n64 * 9) {
+        if (tall >= 16 * cus && bcsr_f32_one_wave(h, N)) return launch_f32<BR, MT, 4, BR / (32 * MT), 2, 1>(h, B, C, N, stream);
         if (tall >= 16 * cus) return launch_f32<BR, MT, 4, 1, 1, 2>(h, B, C, N, stream);
         if (tall >= 3 * cus) return launch_f32<BR, MT, 4, 1, 1, 4>(h, B, C, N, stream);
     }

@@ -290,6 +290,8 @@ bool bcsr_dma_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, 
 int bcsr_xt_staged_strips(const asp_handle *h, int64_t N);
 void bcsr_wide_xt_launch(const asp_handle *h, const void *X, void *Y, int64_t N, hipStream_t stream);
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
+// fp32, many 64 x 128 tiles: whether one wave takes a whole one (asp_bcsr_f32.hip)
+bool bcsr_f32_one_wave(const asp_handle *h, int64_t N);
 bool bcsr_f32_launch(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream);
 bool bcsr_wide_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream);
 // the tile width of the register-staged kernel where rows are not 16-byte aligned (asp_bcsr.hip)

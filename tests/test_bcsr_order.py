@@ -183,3 +183,13 @@ def test_products_that_take_staged_strips(lists_of, block, brows, units, longest
 ])
 def test_unaligned_rows_take_tiles_that_they_fill(lists_of, block, brows, widths):  # noqa: F811
     assert lists_of("unaligned", block, brows, *widths)["bn"] == [[bn] for bn in widths.values()]
+
+
+@pytest.mark.parametrize("block,brows,units,longest,widths", [
+    (128, 148, 207, 6, {2048: 0, 3072: 1, 4096: 1}), (128, 100, 200, 10, {4096: 1, 3712: 0, 3840: 1}),    # short block-rows
+    (128, 100, 200, 11, {3840: 0, 4864: 0, 5120: 1}),
+    (64, 296, 1658, 14, {2048: 0, 3328: 0, 3456: 1, 8192: 1}), (64, 206, 3300, 26, {8192: 0}),            # unequal; long and alike
+    (32, 592, 6600, 22, {2048: 1, 8192: 1}), (32, 592, 30000, 80, {2048: 0, 4096: 1}), (32, 592, 6600, 60, {2048: 0, 4096: 1}),
+])
+def test_fp32_tiles_by_one_wave(lists_of, block, brows, units, longest, widths):  # noqa: F811
+    assert lists_of("f32", block, brows, units, longest, *widths)["one"] == [[one] for one in widths.values()]

@@ -24,6 +24,7 @@
 //   apply K R C T N..  whether R nearly dense rows over K columns, of whose chunks C can be shared, T tenths of an entry a column, go through
 //                    LDS for N.. columns of B, 50 to a pass
 //   launches W T     the walk by rows of W waves and T workgroups before them: first and end wave and workgroups of each launch
+//   f32 B R U L N..  R block-rows of height B in fp32, U blocks, the longest row L, on 256 compute units: whether one wave takes a tile
 //   unaligned B R N..  R block-rows of height B on 256 compute units: the tile width for N.. columns in rows that are not aligned
 //   columns H T N..  T tasks of windows of height H in fp32: the columns of a lane for N.. columns
 //   xt B R U L N     a BCSR handle of R block-rows, U blocks of B x B, the longest row L: the row tiles of the staged strips that N
@@ -418,6 +419,13 @@ int main(int argc, char **argv) {
     if (is("shares", 2)) return shares(lengths(2));
     if (is("groups", 7))
         return groups(std::atoll(argv[2]), std::atoll(argv[3]), std::atoll(argv[4]), std::atoi(argv[5]), std::atoll(argv[6]), lengths(7));
+    if (is("f32", 6)) {
+        asp_handle h;
+        h.b_row = std::atoi(argv[2]), h.n_brows = std::atoll(argv[3]), h.n_units = std::atoll(argv[4]), h.hb.max_blocks = std::atoll(argv[5]);
+        h.n_cus = 256;
+        for (int32_t n : lengths(6)) std::printf("one %d\n", (int)asp::bcsr_f32_one_wave(&h, n));
+        return 0;
+    }
     if (is("unaligned", 4)) {
         asp_handle h;
         h.b_row = std::atoi(argv[2]), h.n_brows = std::atoll(argv[3]), h.n_cus = 256;
