@@ -10,8 +10,10 @@
 // ahead.  The waves' partial tiles meet in LDS once, are added in wave order (bitwise reproducible), rounded once, stored.
 // us a call, before -> now: 1024 x 1024, 64 x 64 blocks, 256 columns 6.2 -> 3.7; 3584 x 18944 at 64 / 256 / 1024 columns
 // 58 -> 6.6 / 58 -> 13 / 47 -> 34; 5003 x 3331 (80 %), 64 x 64 blocks, 1024 columns 42 -> 23.
-// Rows at other alignments: 5003 x 3331 (80 %), 64 x 64 blocks, 1021 columns 31.2 -> 22.7 since the last column tile moves left
-// instead of putting its lanes' loads together from a row's end (that tile alone had set the time of the launch).
+// Rows at other alignments: 5003 x 3331 (80 %), 64 x 64 blocks, 1021 columns 26.8 -> 22.7 since the last column tile moves left
+// instead of putting its lanes' loads together from a row's end (that tile alone had set the time of the launch).  Narrower than a tile single
+// chunks move left: 26 713 x 852 (90 %), 128 x 128 blocks, 13 columns 11.9 -> 6.7, 68 784 x 862 (80 %), 64 x 64, 43 16.2 -> 11.1 (where a tile can
+// move as a whole its 64 contiguous bytes are faster: 2012 x 7811 (80 %), 32 x 32, 61 columns 13.1 / 17.4).
 // With more columns a strip's reads (B once per strip, A once per column tile) are so many more than the tile kernels' that
 // these win.
 #include <algorithm>
@@ -22,8 +24,10 @@ namespace asp {
 
 // grid = units_m strips of 32 MT rows x column tiles of 32 NT; rank_info: {block-row, first block, blocks, -} in
 // the schedule's order; col_idx / a_packed: the stored blocks,
-// fragment-ordered; UKT: k per unit; VEC: N % 8 == 0, B and C 16-byte aligned
-template <int BR, int MT, int NT, int W, int UKT, bool VEC>
+// fragment-ordered; UKT: k per unit
+enum StripRows { FEW, ANY, ALIGNED };  // N < 8; N >= 8; N % 8 == 0, B and C 16-byte aligned
+
+template <int BR, int MT, int NT, int W, int UKT, StripRows ROWS>
 __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restrict__ rank_info,
                                                             const int32_t *__restrict__ col_idx,
                                                             const uint16_t *__restrict__ a_packed,
@@ -47,9 +51,15 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
     const int list = at < more * (per + 1) ? at / (per + 1) : more + (at - more * (per + 1)) / per;
     const int4 ri = rank_info[list + 8 * (at - list * per - (list < more ? list : more))];
     const int br = ri.x, blk0 = ri.y, n_units = ri.z * UPB;
-    // rows that are not 16-byte aligned: the last column tile moves left so that it ends at N, and the loop has no case of a row's end
-    const bool inner = VEC || N >= 32 * NT;
-    const int n_own = un * (32 * NT), n0 = !VEC && inner && n_own > N - 32 * NT ? N - 32 * NT : n_own;
+    // Rows that are not 16-byte aligned: the last column tile moves left so that it ends at N.  Where N does not fill one tile, chunks of 8
+    // columns that would pass N end there instead (those that start past it only feed columns that are never stored).
+    const int n_own = un * (32 * NT), n0 = ROWS == ANY && N >= 32 * NT && n_own > N - 32 * NT ? N - 32 * NT : n_own;
+    auto chunk_col = [&](int col) __attribute__((always_inline)) { return ROWS != FEW && col > N - 8 ? N - 8 : col; };
+    auto chunk = [&](const uint16_t *row, int col) __attribute__((always_inline)) {
+        if constexpr (ROWS == ALIGNED) return *(const u32x4 *)(row + col);
+        else if constexpr (ROWS == ANY) return u32x4(*(const u32x4_a2 *)(row + col));
+        else return load_tail8(row, col, N);
+    };
     const int u0 = (int)((int64_t)n_units * wave / W), u1 = (int)((int64_t)n_units * (wave + 1) / W);
 
     f32x16 acc[MT][NT];
@@ -63,9 +73,7 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
     if (u0 < u1) {
         uint8_t *sb = lds + wave * STAGE;
         const uint16_t *a_lane = a_packed + (int64_t)blk0 * (BR * BR) + strip * (MT * 512) + lane * 8;
-        const int row_l = lane / LPR, col_l = n0 + (lane % LPR) * 8;
-        // (chunks past N only feed columns that are never stored)
-        const int col = VEC ? (col_l < N ? col_l : N - 8) : col_l;
+        const int row_l = lane / LPR, col = chunk_col(n0 + (lane % LPR) * 8);
         uint8_t *st = sb + row_l * PB + (lane % LPR) * 16;
         // lane i holds the block column of the wave's i-th block, 64 at a time
         int col_base = u0 / UPB, cols;
@@ -86,19 +94,16 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
             }
             const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * UK;
             const u32x4 *a = (const u32x4 *)(a_lane + (int64_t)p * (BR * BR) + s * (UK * BR));
-            if (k0 + UK <= K && inner) {
-                const uint16_t *src = B + (int64_t)(k0 + row_l) * N + col;
+            if (k0 + UK <= K) {
+                const uint16_t *src = B + (int64_t)(k0 + row_l) * N;
 #pragma unroll
-                for (int i = 0; i < BL; ++i) {
-                    const uint16_t *row = src + (int64_t)(i * RPI) * N;
-                    f.b[i] = VEC ? *(const u32x4 *)row : *(const u32x4_a2 *)row;
-                }
+                for (int i = 0; i < BL; ++i) f.b[i] = chunk(src + (int64_t)(i * RPI) * N, col);
             } else {
 #pragma unroll
                 for (int i = 0; i < BL; ++i) {
                     const int k = k0 + row_l + i * RPI;
                     const uint16_t *row = B + (int64_t)(k < K ? k : K - 1) * N;
-                    u32x4 v = VEC ? *(const u32x4 *)(row + col) : inner ? *(const u32x4_a2 *)(row + col) : load_tail8(row, col, N);
+                    const u32x4 v = chunk(row, col);
                     f.b[i] = k < K ? v : u32x4{0u, 0u, 0u, 0u};
                 }
             }
@@ -171,37 +176,34 @@ __global__ __launch_bounds__(W * 64) void bcsr_strip_kernel(const int4 *__restri
             s0 += *(const f32x4 *)&part[(w * (MT * 32) + row) * PITCH + c];
             s1 += *(const f32x4 *)&part[(w * (MT * 32) + row) * PITCH + c + 4];
         }
-        if (m0 + row >= M || n0 + c >= N || n0 + c + 8 <= n_own) continue;  // (a column of two tiles gets the same bits from both)
+        if (m0 + row >= M || n0 + c >= N || n0 + c + 8 <= n_own) continue;  // (a column of two tiles or chunks gets the same bits from both)
         const bf16x4 lo = __builtin_convertvector(s0, bf16x4), hi = __builtin_convertvector(s1, bf16x4);  // to nearest even
         const bf16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        uint16_t *dst = C + (int64_t)(m0 + row) * N + n0 + c;
+        const int col = chunk_col(n0 + c);
+        uint16_t *dst = C + (int64_t)(m0 + row) * N + col;
         const short8v bits = __builtin_bit_cast(short8v, v);
-        if (VEC) {
+        if constexpr (ROWS == ALIGNED) {
             *(u32x4 *)dst = __builtin_bit_cast(u32x4, v);
-        } else if (n0 + c + 8 <= N) {
+        } else if constexpr (ROWS == ANY) {
             *(u32x4_a2 *)dst = __builtin_bit_cast(u32x4, v);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                if (n0 + c + e < N) dst[e] = (uint16_t)bits[e];
+                if (col + e < N) dst[e] = (uint16_t)bits[e];
         }
     }
 }
 
 // ---- host side ------------------------------------------------------------------------------------
 // false: too many threads for a launch
-template <int BR, int MT, int NT, int W, int UK>
-static bool launch_strip(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
+template <int BR, int MT, int NT, int W, int UK, StripRows ROWS>
+static bool launch_strip(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
     const int units_m = (int)h->n_brows * (BR / 32 / MT);
     if (!launch_fits(units_m * ceil_div(N, 32 * NT), W * 64)) return false;
     dim3 grid((unsigned)(units_m * ceil_div(N, 32 * NT))), block(W * 64);
-#define ASP_STRIP(VEC)                                                                                             \
-    hipLaunchKernelGGL((bcsr_strip_kernel<BR, MT, NT, W, UK, VEC>), grid, block, 0, stream, (const int4 *)h->d_rank_info,          \
-                       h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m, \
-                       (int)h->k, (int)N, units_m)
-    if (vec) ASP_STRIP(true);
-    else ASP_STRIP(false);
-#undef ASP_STRIP
+    hipLaunchKernelGGL((bcsr_strip_kernel<BR, MT, NT, W, UK, ROWS>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
+                       h->d_col_idx, (const uint16_t *)h->d_values, (const uint16_t *)B, (uint16_t *)C, (int)h->m,
+                       (int)h->k, (int)N, units_m);
     return true;
 }
 
@@ -209,22 +211,30 @@ static bool launch_strip(const asp_handle *h, const void *B, void *C, int64_t N,
 // 64 x 64 x 8 / 64 x 64 x 4: 3584 x 18944 at 64 columns 6.6 / 10.5 / 11, at 256 17.8 / 13.0 / 17, at 512 - / 22.6 / 20.8;
 // 18944 x 3584, whose strips have too few units for 8 waves, at 64 columns 8.2 / 8.4 / 6.7, at 512 - / 45 / 25.6.
 // 32-row blocks, 32 x 64 / 32 x 128: 3584 x 18944 at 512 columns 34 / 29, 18944 x 3584 27 / 23.5 (aligned rows only).
-template <int BR>
-static bool launch_strips(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
+template <int BR, StripRows ROWS>
+static bool launch_strips(const asp_handle *h, const void *B, void *C, int64_t N, hipStream_t stream) {
     const int64_t cus = h->n_cus > 0 ? h->n_cus : 256, n64 = ceil_div(N, 64);
     const bool short_rows = h->n_units * (BR / 32) < 14 * h->n_brows;
-    if constexpr (BR >= 64) {
+    if constexpr (ROWS != FEW && BR >= 64) {
         const int64_t tiles = h->n_brows * (BR / 64) * n64;
         if (2 * tiles >= cus) {
-            if (2 * tiles >= 3 * cus || short_rows) return launch_strip<BR, 2, 2, 4, 32>(h, B, C, N, vec, stream);
-            return launch_strip<BR, 2, 2, 8, 32>(h, B, C, N, vec, stream);
+            if (2 * tiles >= 3 * cus || short_rows) return launch_strip<BR, 2, 2, 4, 32, ROWS>(h, B, C, N, stream);
+            return launch_strip<BR, 2, 2, 8, 32, ROWS>(h, B, C, N, stream);
         }
-    } else {
-        if (vec && 2 * h->n_brows * ceil_div(N, 128) >= 3 * cus) return launch_strip<BR, 1, 4, 2, 32>(h, B, C, N, vec, stream);
-        if (2 * h->n_brows * n64 >= 3 * cus) return launch_strip<BR, 1, 2, 4, 64>(h, B, C, N, vec, stream);
+    } else if constexpr (ROWS != FEW) {
+        if constexpr (ROWS == ALIGNED)
+            if (2 * h->n_brows * ceil_div(N, 128) >= 3 * cus) return launch_strip<BR, 1, 4, 2, 32, ROWS>(h, B, C, N, stream);
+        if (2 * h->n_brows * n64 >= 3 * cus) return launch_strip<BR, 1, 2, 4, 64, ROWS>(h, B, C, N, stream);
     }
-    if (short_rows) return launch_strip<BR, 1, 1, 4, 64>(h, B, C, N, vec, stream);
-    return launch_strip<BR, 1, 1, 8, 64>(h, B, C, N, vec, stream);
+    if (short_rows) return launch_strip<BR, 1, 1, 4, 64, ROWS>(h, B, C, N, stream);
+    return launch_strip<BR, 1, 1, 8, 64, ROWS>(h, B, C, N, stream);
+}
+
+template <int BR>
+static bool launch_rows(const asp_handle *h, const void *B, void *C, int64_t N, bool vec, hipStream_t stream) {
+    if (vec) return launch_strips<BR, ALIGNED>(h, B, C, N, stream);
+    if (N >= 8) return launch_strips<BR, ANY>(h, B, C, N, stream);
+    return launch_strips<BR, FEW>(h, B, C, N, stream);
 }
 
 // Whether strips are the faster choice: estimates in us, linear in the longest block-row (K slices of 32) and in the
@@ -264,9 +274,9 @@ static bool strips_win(const asp_handle *h, int64_t N, const BcsrPlan &p) {
 bool bcsr_strip_launch(const asp_handle *h, const void *B, void *C, int64_t N, const BcsrPlan &p, hipStream_t stream) {
     if (h->n_units == 0 || N >= (1ll << 25) || !strips_win(h, N, p)) return false;
     const bool vec = p.vectorized != 0;
-    if (h->b_row == 128) return launch_strips<128>(h, B, C, N, vec, stream);
-    if (h->b_row == 64) return launch_strips<64>(h, B, C, N, vec, stream);
-    return launch_strips<32>(h, B, C, N, vec, stream);
+    if (h->b_row == 128) return launch_rows<128>(h, B, C, N, vec, stream);
+    if (h->b_row == 64) return launch_rows<64>(h, B, C, N, vec, stream);
+    return launch_rows<32>(h, B, C, N, vec, stream);
 }
 
 }  // namespace asp

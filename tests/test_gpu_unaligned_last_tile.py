@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("b", [32, 64, 128])
 @pytest.mark.parametrize("m,k", [(300, 1000), (9000, 131)])   # strips; the register-staged kernel from some hundred columns on
-@pytest.mark.parametrize("N", [31, 33, 63, 65, 127, 129, 1021, 2049])
+@pytest.mark.parametrize("N", [1, 7, 9, 15, 17, 31, 33, 63, 65, 127, 129, 1021, 2049])
 def test_last_tile(b, m, k, N):
     product(b, m, k, N)
 
