@@ -72,12 +72,13 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     if (u >= runs.start[xcd + 1]) return;
     const int nt = __builtin_amdgcn_readfirstlane(u / n_brows), pos = u - nt * n_brows;
     const int br = __builtin_amdgcn_readfirstlane(order ? order[pos] : pos);
-    // Chunks of 8 columns that would pass N end there instead and repeat columns of their neighbour (the same bits), so no load of
-    // N >= 8 columns has a case of a row's end.  (18944 x 3584 at 90 %, N = 4093, 128 / 64 / 32-row blocks 134 / 148 / 199 -> 113 / 125 / 173 us
-    // with plain loads in every slice that does not reach past K; two slices ahead instead of one: 126 / 141 / 192.)
-    const int n0 = nt * BN;
+    // Rows that are not 16-byte aligned: the last column tile moves left so that it ends at N, and its loads have no case of a
+    // row's end.  (18944 x 3584 at 90 %, N = 4093, 128 / 64 / 32-row blocks 134 / 148 / 199 -> 113 / 125 / 173 us with plain loads
+    // in every slice that does not reach past K; two slices ahead instead of one: 126 / 141 / 192.)  Where N does not fill one tile, chunks
+    // of 8 columns that would pass N end there instead.
+    const int n_own = nt * BN, n0 = !VEC && N >= BN && n_own > N - BN ? N - BN : n_own;
     const bool inner = N >= 8;
-    auto chunk_col = [&](int col) __attribute__((always_inline)) { return inner && col > N - 8 ? N - 8 : col; };
+    auto chunk_col = [&](int col) __attribute__((always_inline)) { return !VEC && N >= 8 && col > N - 8 ? N - 8 : col; };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
         uint4 v = *(const uint4 *)(sc + row * Cfg::C_PITCH + cc * 16);
         int grow = br * BR + wm * Cfg::TM + row;
         const int own = n0 + wn * Cfg::TN + cc * 8, gcol = chunk_col(own);
-        if (grow < M && own < N) {
+        if (grow < M && own < N && own + 8 > n_own) {  // (a column of two tiles or chunks gets the same bits from both)
             uint16_t *dst = C + (int64_t)grow * N + gcol;
             if (VEC) {
                 *(uint4 *)dst = v;
