@@ -78,7 +78,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void bcsr_spmm_kernel(
     // of 8 columns that would pass N end there instead.
     const int n_own = nt * BN, n0 = !VEC && N >= BN && n_own > N - BN ? N - BN : n_own;
     const bool inner = N >= 8;
-    auto chunk_col = [&](int col) __attribute__((always_inline)) { return !VEC && N >= 8 && col > N - 8 ? N - 8 : col; };
+    auto chunk_col = [&](int col) __attribute__((always_inline)) { return inner && col > N - 8 ? N - 8 : col; };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
