@@ -181,7 +181,7 @@ asp_status_t asp_spmm_static_scratch(const asp_handle_t *h, const void *B, void 
  * overwritten; Y must not alias X.  1 <= N <= ASP_MAX_N.  BCSR handles (bf16) only; others return ASP_ERR_UNSUPPORTED.
  * Asynchronous, never synchronises, never allocates.  fp32 accumulation, round-to-nearest-even to bf16;
  * bitwise reproducible.  Every size and alignment runs on the matrix cores: few tokens, and operands that are not 16-byte
- * aligned with k % 8 == 0 and m % 8 == 0, in strips of 32 to 128 outputs x 32 or 64 tokens whose waves split the K loop; more
+ * aligned with k % 8 == 0 and m % 8 == 0, in strips of 16 to 128 outputs x 16 to 64 tokens whose waves split the K loop; more
  * tokens in tiles of a block-row x 64 to 256 tokens, and once these are 1.5 per compute unit in tiles of 128 outputs x 512
  * tokens (128x128 blocks, or smaller ones when k >= 32 and grouping their block-rows into 128-row tiles adds at most
  * 2.6x / 4.3x zero fill).

@@ -11,7 +11,8 @@
 // those in flight: one wavefront walks a run of consecutive rows, 64 to 256 entries; columns and values are uniform
 // for the wave and come through scalar loads (16 entries ahead), so an entry costs one vector load with a scalar base
 // and E multiply-adds with a scalar factor; two batches of 8 rows of B are in flight per wave, up to 8 waves per SIMD.
-// A row's entries are summed in order in fp32.  Rows longer than task_cols are cut into chunks (Section III-C) whose
+// A row's entries are summed in fp32, in order where one wave walks them, by quarters where a workgroup does (wcsr_rows_kernel).  Rows
+// longer than task_cols are cut into chunks (Section III-C) whose
 // sums go to rows of scratch memory, which wcsr_rows_sum_kernel adds up.
 //
 // Order of the work: chunks of long rows are sorted by column and dealt to the XCDs in contiguous ranges, so that the

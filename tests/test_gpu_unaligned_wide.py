@@ -1,4 +1,4 @@
-"""bf16 BCSR products whose rows are not 16-byte aligned, wide enough for the register-staged kernel (64- and 128-wide tiles):
+"""bf16 BCSR products whose rows are not 16-byte aligned, wide enough for the register-staged kernel (128- and 256-wide tiles):
 tiles' edges and the last columns.  Tolerance as everywhere in bf16: 1e-2 * S + 1e-5, S = |A| x |B| from the oracle."""
 import numpy as np
 import pytest

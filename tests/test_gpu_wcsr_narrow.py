@@ -26,12 +26,11 @@ def product(h, B, m, dtype):
     return got[:m * N].reshape(m, N)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,m,half,task_cols,reserve", [
+    (dtype, *shape) for dtype in ("f32", "bf16") for shape in ((1000, 13, 0, True), (1000, 60, 24, True), (1000, 60, 24, False), (58_000, 3, 0, True))
+    if dtype == "f32" or shape[-1]])                                        # (bf16 needs scratch for split windows)
 @pytest.mark.parametrize("height", [16, 32, 64])
-@pytest.mark.parametrize("m,half,task_cols,reserve", [(1000, 13, 0, True), (1000, 60, 24, True), (1000, 60, 24, False), (58_000, 3, 0, True)])
 def test_widths(dtype, height, m, half, task_cols, reserve):
-    if dtype == "bf16" and not reserve:
-        pytest.skip("bf16 handles with split windows need scratch")
     a = synth.banded_plus_dense_rows(m, seed=half, half_band=half, n_dense_rows=0)
     values = a.values if dtype == "f32" else synth.f32_to_bf16_bits(a.values)
     widths = [1, 2, 3, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 128, 129, 160, 192, 193] if m < 10000 else [33, 160]
