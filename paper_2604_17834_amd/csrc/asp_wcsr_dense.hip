@@ -4,7 +4,7 @@
 // pulls a row of B from L2, 15 TB/s.  Here a workgroup takes a range of the columns, 256 of them at a time: it reads these
 // rows of B once, into LDS, and its 16 waves walk the entries of up to 64 rows against them, four rows to a wave, whose sums stay in
 // registers for the whole range.  What bounds it is the one pass over B with the lines that the one workgroup on a compute unit
-// has in flight (53 in the mean, 791 cycles each; 4.1 TB/s with the entries); LDS is busy for a quarter of that time, without bank conflicts.
+// has in flight (56 in the mean, 791 cycles each; 4.1 TB/s with the entries); LDS is busy for a quarter of that time, without bank conflicts.
 // 64 rows of 200 000 entries over 2 000 000 columns, N = 64: 207 us in chunks, 150 here.
 //
 // A wave's 64 lanes are 4 groups of 16 that cover a row of B (64 columns, 4 to a lane) each and take every fourth entry: lane i of a
