@@ -10,8 +10,10 @@
 // A load has no branch: with a case for rows past K in it the compiler left the loads of A to where they are multiplied, and every
 // look-up of a block column waited for all loads in flight.  Of 60 products (1000 to 9000 rows, 64 to 2048 columns) 0.89 of the
 // time in the mean, 0.80 at best; 9000 x 4000, 50 %, 64 x 64 blocks, 1024 columns 380 -> 327 us.
-// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, through LDS -> so: N = 2048 301 / 276 / 306 -> 244 / 242 / 235 us (116 to 119 TFLOP/s;
-// the same MFMAs on registers reach 149), N = 64 140 / 83 / 63 -> 17 / 16 / 15 (clocks move all of them by 5 % together).
+// Where K is a multiple of the blocks no row has to be looked at twice (WHOLE): 18944 x 3584 at 90 %, N = 16384, 128 / 64 / 32-row blocks 1.910 /
+// 1.857 / 2.041 -> 1.750 / 1.760 / 1.905 ms (with that branch 1.829 / 1.825 / 2.022); of 110 products 0.965 of the time in the mean, 1.06 at most.
+// 18944 x 3584 at 90 %, blocks of 128 / 64 / 32, through LDS -> so: N = 2048 301 / 276 / 306 -> 243 / 238 / 229 us (116 to 121 TFLOP/s;
+// the same MFMAs on registers reach 149), N = 64 140 / 83 / 63 -> 15 / 14 / 13 (clocks move all of them by 5 % together).
 //
 // Operand layouts
 //   A  blocks are pre-permuted on the host (bcsr_pack_fragments_f32): for every 32-row tile and group of
@@ -43,8 +45,8 @@ struct Cols {
 }  // namespace
 
 // rank_info[r] = {block-row, first stored block, stored blocks, -}.  A workgroup is WM x WN x WK waves and computes 32 MT WM
-// rows of a block-row x 32 V WN columns.  N >= V.
-template <int BR, int MT, int V, int WM, int WN, int WK>
+// rows of a block-row x 32 V WN columns.  N >= V.  WHOLE: K % BR == 0, no unit has rows past K.
+template <int BR, int MT, int V, int WM, int WN, int WK, bool WHOLE>
 __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32_spmm_kernel(
     const int4 *__restrict__ rank_info, const int32_t *__restrict__ block_col_idx, const float *__restrict__ a_packed,
     const float *__restrict__ B, float *__restrict__ C, int M, int K, int64_t N, int n_brows, int n_tiles, int xcd_cols) {
@@ -109,20 +111,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MT *V > 4 ? 2 : 4) void bcsr_f32
                 asm volatile("" : "+v"(cols));  // waited for here, or every look-up would wait for all loads in flight
             }
             const int k0 = __builtin_amdgcn_readlane(cols, p - col_base) * BR + s * 8;
-            f.left = K - k0;
+            f.left = WHOLE ? 8 : K - k0;
             // past K, where a unit may also start: its last row, dropped when the unit is multiplied
-            global_char *row = (global_char *)B + (uint64_t)(uint32_t)min(k0, K - 1) * row_bytes;
+            global_char *row = (global_char *)B + (uint64_t)(uint32_t)(WHOLE ? k0 : min(k0, K - 1)) * row_bytes;
             const int last = max(f.left - 1, 0);
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                uint32_t off = (uint32_t)min(2 * t + kq, last) * row_bytes + coff;
+                uint32_t off = (uint32_t)(WHOLE ? 2 * t + kq : min(2 * t + kq, last)) * row_bytes + coff;
                 asm("" : "+s"(row), "+v"(off));  // scalar base + 32-bit offset, instead of a 64-bit vector address per row
                 f.b[t] = *(const __attribute__((address_space(1))) cols_t *)(row + off);
             }
             asm volatile("" ::: "memory");  // (the loads are issued here, not where the next unit is multiplied)
         };
         auto multiply = [&](Unit &f) __attribute__((always_inline)) {
-            if (f.left < 8)  // rows past K count as zeros
+            if (!WHOLE && f.left < 8)  // rows past K count as zeros
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -217,15 +219,19 @@ static bool launch_f32(const asp_handle *h, const void *B, void *C, int64_t N, h
     const int64_t per_xcd = ceil_div(h->n_brows * (BR / (32 * MT * WM)), 8 / xcd_cols) * ceil_div(n_tiles, xcd_cols);
     if (!launch_fits(8 * per_xcd, 64 * WM * WN * WK)) return false;
     dim3 grid((unsigned)(8 * per_xcd)), block(64 * WM * WN * WK);
-    hipLaunchKernelGGL((bcsr_f32_spmm_kernel<BR, MT, V, WM, WN, WK>), grid, block, 0, stream, (const int4 *)h->d_rank_info,
-                       h->d_col_idx, (const float *)h->d_values, (const float *)B, (float *)C, (int)h->m, (int)h->k, N,
-                       (int)h->n_brows, (int)n_tiles, xcd_cols);
+#define ASP_F32(WHOLE)                                                                                                              \
+    hipLaunchKernelGGL((bcsr_f32_spmm_kernel<BR, MT, V, WM, WN, WK, WHOLE>), grid, block, 0, stream, (const int4 *)h->d_rank_info, \
+                       h->d_col_idx, (const float *)h->d_values, (const float *)B, (float *)C, (int)h->m, (int)h->k, N,             \
+                       (int)h->n_brows, (int)n_tiles, xcd_cols)
+    if (h->k % BR == 0) ASP_F32(true);
+    else ASP_F32(false);
+#undef ASP_F32
     return true;
 }
 
 // 64 x 128 tiles, where they are many: by two waves that divide the blocks (false), or by one, side by side for twice the columns.
 // Two end long block-rows sooner (18944 x 3584 at 90 %, 2048 columns, 18 tiles to a compute unit, 128 / 64 / 32-row blocks 244 / 253 / 241 ->
-// 244 / 242 / 235, geometric lengths 374 / 372 / 276 -> 238 / 231 / 215), one starts and adds up less: from some 30 tiles to a unit on, but not
+// 244 / 242 / 235, geometric lengths 374 / 372 / 276 -> 238 / 231 / 215, before WHOLE), one starts and adds up less: from some 30 tiles to a unit on, but not
 // where block-rows are long and alike (two / one: 15 260 x 3035 at 95 %, geometric, 64-row, 8192 columns 355 / 340, 13 202 x 2023 at 50 % 1698 /
 // 1781), from fewer where all are short (12 034 x 1955 at 90 %, 128-row, 4096 columns 208 / 199, 12 567 x 4176 at 98 %, 8192 columns 188 / 172);
 // with 32-row blocks, whose waves have half the sums, where they are alike too (10 094 x 3359 at 95 %, 8192 columns 281 / 274).  Of 230 products

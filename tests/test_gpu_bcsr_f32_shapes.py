@@ -24,6 +24,7 @@ def test_narrow(b, m, k, misalign, N):
     (5003, 331, 1279, False), (5003, 331, 1280, True),    # 64 x 128 of four waves
     (9003, 270, 3967, False), (9003, 270, 3968, True),    # 64 x 128 of two waves (32-row blocks: of one); empty block-rows
     (9003, 270, 7935, False), (9003, 270, 7936, True),    # 64 x 128, one wave each
+    (520, 256, 161, True), (3000, 640, 513, False), (5003, 384, 1280, True), (9003, 256, 3967, False), (9003, 256, 7936, True),   # K % b == 0
 ])
 def test_wide(b, m, k, N, misalign):
     a = synth.block_sparse_bernoulli(m, k, b, b, 0.7, seed=b + N, dtype="f32", std=1.0)
